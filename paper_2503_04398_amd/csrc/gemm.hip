@@ -21,6 +21,7 @@ int tuning_value(int key) { return (key >= 0 && key < 8) ? g_tune[key].load(std:
 
 static int grid_for(long long tile_bound, long long cap) {
   if (tuning_value(SEMMOE_TUNE_GRID_CAP) > 0 && cap > tuning_value(SEMMOE_TUNE_GRID_CAP)) cap = tuning_value(SEMMOE_TUNE_GRID_CAP);
+  tile_bound = (tile_bound + 7) / 8 * 8;  // whole rounds over the XCDs: the kernels split their list among these
   return (int)(tile_bound < cap ? tile_bound : cap);
 }
 

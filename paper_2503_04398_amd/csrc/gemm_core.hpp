@@ -101,13 +101,33 @@ __device__ __forceinline__ int find_group(const int* pre, int nq, int t) {
   return lo;
 }
 
-// Workgroups are handed to the 8 XCDs round-robin by workgroup id, and each XCD has its own L2.  Worker
-// index = the position of this workgroup in an order where the workgroups of one XCD are consecutive, so
-// that at any time one XCD works on a contiguous run of the tile list.
-__device__ __forceinline__ int xcd_worker_index() {
+// A workgroup's share of a list of `total` items: item(0), item(1), ... item(count - 1).  Workgroups are handed to the 8
+// XCDs round-robin by workgroup id, and each XCD has its own L2 and its own path to memory.  In every full round of the
+// grid an XCD's workgroups take a contiguous run of the list (neighbouring items share weight or token panels, which
+// its L2 then holds) and all XCDs together one run as well, whose panels meet in the memory-side cache: with an eighth
+// of the whole list per XCD instead, 8 experts of d = F = 2880 took 511 us against 484.  The last, partly filled round
+// is dealt out evenly over the XCDs: left to the first ones alone, 384 weight tiles on 512 workgroups ran on six XCDs
+// and at six eighths of the memory rate.
+struct ItemWalk {
+  int count, first, step, last;  // last: the item of the partly filled round
+  __device__ __forceinline__ int item(int r) const { return r + 1 == count && last >= 0 ? last : first + r * step; }
+};
+__device__ __forceinline__ ItemWalk xcd_share(int total) {
   const int g = gridDim.x, b = blockIdx.x;
-  if (g % 8 != 0) return b;
-  return (b & 7) * (g >> 3) + (b >> 3);
+  const int full = total / g, rem = total - full * g;
+  ItemWalk w;
+  w.step = g;
+  if (g % 8 != 0) {
+    w.first = b;
+    w.last = b < rem ? full * g + b : -1;
+  } else {
+    const int x = b & 7, l = b >> 3;
+    const int lo = rem * x / 8, hi = rem * (x + 1) / 8;
+    w.first = x * (g >> 3) + l;
+    w.last = lo + l < hi ? full * g + lo + l : -1;
+  }
+  w.count = full + (w.last >= 0 ? 1 : 0);
+  return w;
 }
 
 // Inside a group the tile list walks blocks of kFeatBlock feature tiles x all token tiles of the group
@@ -280,7 +300,9 @@ __global__ __launch_bounds__(64 * NWF * NWT, MINW) void gemm_bf16_kernel(GemmArg
   const TileWalk walk = make_walk(a, pre, C::BT, C::FEAT);
   const int nk = (a.K + BK - 1) / BK;
 
-  for (int item = xcd_worker_index(); item < walk.total; item += gridDim.x) {
+  const ItemWalk my = xcd_share(walk.total);
+  for (int r = 0; r < my.count; ++r) {
+    const int item = my.item(r);
     TileAt at;
     if (!walk_tile(a, walk, pre, item, C::BT, C::FEAT, &at)) continue;  // uniform: no barrier is skipped
     const int q = at.q, row_lo = at.row_lo, n_tok = at.n_tok, f0 = at.f0;
@@ -496,7 +518,9 @@ __global__ __launch_bounds__(64 * NWF * NWT, MINW) void gemm_bf16_dma_kernel(Gem
   const int d_row = lane / C::CPR;
   const int d_pos = lane % C::CPR;
 
-  for (int item = xcd_worker_index(); item < walk.total; item += gridDim.x) {
+  const ItemWalk my = xcd_share(walk.total);
+  for (int r = 0; r < my.count; ++r) {
+    const int item = my.item(r);
     TileAt at;
     if (!walk_tile(a, walk, pre, item, C::BT, C::FEAT, &at)) continue;  // uniform: no barrier is skipped
     const int q = at.q, row_lo = at.row_lo, n_tok = at.n_tok, f0 = at.f0;

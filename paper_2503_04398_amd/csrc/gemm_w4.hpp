@@ -154,8 +154,8 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   const int listed = __builtin_amdgcn_readfirstlane(build_tile_prefix(a, n_ftiles, pre, C::BT));  // ends with a barrier
   const int total = a.sched_mode == 1 ? head_tiles(listed, G, a.sched_thr) : listed;  // head launch of a split
   const int nk = a.K / BK;
-  const int worker = xcd_worker_index();
-  if (worker >= total) return;  // whole workgroup: no barrier is pending
+  const ItemWalk my = xcd_share(total);
+  if (my.count == 0) return;  // whole workgroup: no barrier is pending
 
   // fragment-read geometry: lane reads row (lane & 31) of a 32-row MFMA tile, chunk 2*ks + lane/32
   const int frag_swz = ((lane & 31) / C::RPB) % C::CPR;
@@ -170,7 +170,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   const bool loads_w = wave < 2;
 
   // ---- load stream state (runs NSTAGE slices ahead of the MFMAs, across tiles)
-  int i_tile = worker;
+  int i_tile = 0;  // round of this workgroup
   int i_slice = 0;
   int i_stage = 0;
   bool i_done = false;
@@ -218,7 +218,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
     }
   };
   auto i_next_slice = [&]() __attribute__((always_inline)) {
-    if (i_slice + 1 == nk && i_tile + G >= total) {  // no further slice: stand still on the last one
+    if (i_slice + 1 == nk && i_tile + 1 >= my.count) {  // no further slice: stand still on the last one
       i_done = true;
       return;
     }
@@ -227,8 +227,8 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
     i_dst = lds_base + i_stage * C::kStageBytes + wave * C::IPW * 1024;
     if (++i_slice == nk) {
       i_slice = 0;
-      i_tile += G;
-      i_setup(i_tile);
+      ++i_tile;
+      i_setup(my.item(i_tile));
     }
   };
   // load number i of the current slice of the stream; after the last one the stream moves to the next slice
@@ -250,7 +250,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   };
 
   // ---- prologue: the first NSTAGE slices of the first tile
-  i_setup(i_tile);
+  i_setup(my.item(0));
   for (int s = 0; s < NSTAGE; ++s) {  // nk >= NSTAGE: these slices belong to the first tile
 #pragma unroll
     for (int i = 0; i < C::IPW; ++i)
@@ -270,7 +270,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   frag(0, 0, af[0], bfr[0]);
   int c_stage = 0;
 
-  for (int tile = worker; tile < total; tile += G) {
+  for (int round = 0; round < my.count; ++round) {
     // the stream is in this tile (K / BK >= NSTAGE: never further), so its tile is this one
     const TileRef t = s_tile;
     // MFMA columns of this wave that hold tokens (the others are computed on clamped rows and never stored:
@@ -478,7 +478,9 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
   // first LDS byte of this wave's rows inside a stage (an instruction fills 8 rows = 1 KB)
   const unsigned my_rows_lds = loads_w ? wave * kIpwW * 1024 : (C::BW / 8 + (wave - 2) * kIpwX) * 1024;
 
-  for (int item = xcd_worker_index(); item < walk.total; item += gridDim.x) {
+  const ItemWalk my = xcd_share(walk.total);
+  for (int r = 0; r < my.count; ++r) {
+    const int item = my.item(r);
     TileAt at;
     if (!walk_tile(a, walk, pre, item, C::BT, C::FEAT, &at)) continue;  // uniform: no barrier is skipped
     const int widx = a.group_to_weight ? a.group_to_weight[a.q_lo + at.q] : (a.q_lo + at.q);
