@@ -1,6 +1,7 @@
 // Kernel instantiations and the host launcher of the grouped GEMM core.
 #include "gemm_core.hpp"
 #include "gemm_w4.hpp"
+#include "gemm_stream.hpp"
 
 namespace semmoe {
 
@@ -233,17 +234,59 @@ static int big_tile_grid(const GemmArgs& a, int max_rows, int feat) {
   return grid_for(bound, num_cu());
 }
 
-template <int MODE>
-static int32_t launch_f32(const GemmArgs& a, int max_rows, hipStream_t stream) {
-  using C = F32Cfg;
-  constexpr int FEAT = (MODE == kModeSwiglu) ? C::BW / 2 : C::BW;
-  const int n_ftiles = cdiv(a.N, FEAT);
-  const long long bound = (long long)(max_rows / C::BT + a.nq) * n_ftiles;
+template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE>
+static int32_t launch_stream_as(const GemmArgs& a, int max_rows, int per_cu, hipStream_t stream) {
+  using C = StreamCfg<MODE, TW, TT, NW>;
+  const long long bound = (long long)(max_rows / C::BT + a.nq) * cdiv(a.N, C::FEAT);
   if (bound <= 0) return SEMMOE_OK;
-  const int grid = (int)(bound < (long long)num_cu() * 4 ? bound : (long long)num_cu() * 4);
-  hipLaunchKernelGGL((gemm_f32_kernel<MODE>), dim3(grid), dim3(C::kThreads), C::kLdsBytes, stream, a);
+  const size_t lds = C::lds_bytes(a.nq);
+  const int grid = grid_for(bound, (long long)num_cu() * per_cu);
+  auto kern = gemm_stream_kernel<MODE, F32, TW, TT, NW, KTAIL, WIDE>;
+  if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
+  if (lds > 48 * 1024) {
+    static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
+    const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
+    if (as != SEMMOE_OK) return as;
+  }
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), lds, stream, a);
   SEMMOE_LAUNCH_CHECK();
   return SEMMOE_OK;
+}
+
+// SEMMOE_EUNSUPPORTED where 32-bit offsets do not reach every row: fp32 then takes the wide form, bf16 another tile
+template <int MODE, bool F32, int TW, int TT, int NW>
+static int32_t launch_stream(const GemmArgs& a, int max_rows, int per_cu, hipStream_t stream) {
+  const unsigned long long es = F32 ? 4 : 2, row_bytes = a.K * es;
+  const unsigned long long w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N, x_rows = StreamCfg<MODE, TW, TT, NW>::BT;
+  if (w_rows * a.ldw * es >= (1ull << 31) || x_rows * a.ldx * es >= (1ull << 31)) return SEMMOE_EUNSUPPORTED;
+  if (row_bytes % 128 == 0 && row_bytes >= 128 * NW)
+    return launch_stream_as<MODE, F32, TW, TT, NW, false, false>(a, max_rows, per_cu, stream);
+  return launch_stream_as<MODE, F32, TW, TT, NW, true, false>(a, max_rows, per_cu, stream);
+}
+
+// fp32: 16 x 4 weight rows and 16 x 4 tokens a workgroup, halved along either while that leaves compute units idle
+template <int MODE>
+static int32_t launch_f32(const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
+  const int est = est_rows_per_group < 1 ? 1 : est_rows_per_group;
+  auto items = [&](int tw, int tt) {
+    return (long long)a.nq * cdiv(est, 16 * tt) * cdiv(a.N, (MODE == kModeSwiglu) ? 8 * tw : 16 * tw);
+  };
+  const int tt = est <= 16 ? 1 : (est <= 32 ? 2 : 4);
+  const long long fill = 2LL * num_cu();
+  int32_t st;
+  if (tt == 4 && items(4, 4) >= fill) st = launch_stream<MODE, true, 4, 4, 4>(a, max_rows, 2, stream);
+  else if (tt == 4 && items(2, 4) >= fill) st = launch_stream<MODE, true, 2, 4, 4>(a, max_rows, 2, stream);
+  else if (tt >= 2 && items(2, 2) >= fill) st = launch_stream<MODE, true, 2, 2, 4>(a, max_rows, 2, stream);
+  else st = launch_stream<MODE, true, 2, 1, 4>(a, max_rows, 2, stream);
+  if (st != SEMMOE_EUNSUPPORTED) return st;
+  if ((unsigned long long)a.K * 4 >= (1ull << 32) - 1024) return SEMMOE_EUNSUPPORTED;  // a row of 4 GB
+  return launch_stream_as<MODE, true, 2, 1, 4, true, true>(a, max_rows, 2, stream);
+}
+
+// left-over share of a round (in sixteenths) up to which the split happens
+static int split_threshold() {
+  const int t = tuning_value(SEMMOE_TUNE_HEAD_TAIL);
+  return (t >= 1 && t <= 16) ? t : 8;
 }
 
 // tile shapes: id -> (waves along weight rows, waves along tokens, MFMA tiles per wave, K slice)
@@ -265,6 +308,14 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
     case 25: return launch_dma<MODE, 4, 1, 2, 2, 64, 3>(a, max_rows, bpc > 0 ? bpc : 1, s);     // 256 x 64, ring of 3
     case 26: return launch_dma<MODE, 2, 2, 2, 1, 64, 3>(a, max_rows, bpc > 0 ? bpc : 2, s);     // 128 x 64, ring of 3, two per CU
     case 27: return launch_dma<MODE, 2, 2, 2, 1, 64, 4>(a, max_rows, bpc > 0 ? bpc : 1, s);     // 128 x 64, ring of 4
+    // weights streamed through registers: 16 x TW weight rows, 16 x TT tokens
+    case 30: case 31: case 32: {
+      const int32_t st = id == 30   ? launch_stream<MODE, false, 2, 2, 4>(a, max_rows, bpc > 0 ? bpc : 2, s)
+                         : id == 31 ? launch_stream<MODE, false, 2, 4, 4>(a, max_rows, bpc > 0 ? bpc : 2, s)
+                                    : launch_stream<MODE, false, 4, 4, 4>(a, max_rows, bpc > 0 ? bpc : 2, s);
+      if (st != SEMMOE_EUNSUPPORTED) return st;
+      return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);  // panels beyond 32-bit offsets
+    }
     case 28: {  // 128 x 128 pieces, loads between the MFMAs
       const int32_t st = launch_all_pieces<MODE>(a, max_rows, s);
       if (st != SEMMOE_EUNSUPPORTED) return st;
@@ -285,14 +336,32 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
   return SEMMOE_EINVAL;
 }
 
-// Default tile shape from the mean rows per group the caller expects (the true, ragged row counts live on
-// the device): big direct-to-LDS tiles when groups fill them, small register-staged tiles otherwise.
-static int default_tile(int est_rows_per_group, long long big_tiles_at_most) {
-  // big tiles only pay when they fill the chip: 512 rows of the shared expert give 48 of them for 256 compute units
-  // (measured, d 7168, F 2048: 171 us as 256 x 256 tiles, 84 us as 128 x 128 pieces; with 2048 rows 202 against 216)
-  if (est_rows_per_group >= 192) return big_tiles_at_most * 2 >= num_cu() ? 22 : 28;
-  if (est_rows_per_group >= 96) return 0;
-  return 26;  // few rows per group (decode): the weights stream through; narrow tiles, deep ring, two per CU
+// Default tile shape from the mean rows per group that the caller expects (the true, ragged row counts live on the
+// device).  Measured over rows per group, us of a whole FFN (gate/up + down, lognormal spread 0.3 of the group sizes):
+//   A: 128 experts, d 2048, F 768;  B: 16 experts, d 4096, F 1536;  C: 8 experts, d 7168, F 2048
+//   rows   streamed 32 rows x 32   streamed 64 x 64    128 x 64, ring of 3
+//   8      A 192 B 102 C 115       197 111 118         228 131 138
+//   16     A 215 B 107 C 124       213 110 129         241 128 138
+//   32     A 302 B 157 C 180       240 116 137         261 132 143
+//   48                             283 143 169         259 147 185
+// The streaming kernel loses as the token rows it drags past every weight tile grow.
+// One set of weights (the shared expert) with so few rows that big tiles would leave most compute units idle is bound by
+// the latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
+// 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).
+static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group, int n_ftiles256) {
+  const int est = est_rows_per_group;
+  const long long tiles128 = (long long)a.nq * cdiv(est < 1 ? 1 : est, 128) * n_ftiles256;
+  const bool narrow = a.offsets ? tiles128 * 4 < num_cu() : tiles128 * 4 < 3LL * num_cu();
+  if (narrow) {
+    if (est <= 160) return 30;
+    if (est <= 256) return 31;
+    return 28;
+  }
+  if (est < 20) return 30;
+  if (est < 40) return 32;
+  if (est < 96) return 26;
+  if (est < 192) return 0;
+  return (long long)(max_rows / 256 + a.nq) * n_ftiles256 * 2 >= num_cu() ? 22 : 28;
 }
 
 // Head/tail split: for the tile shapes of 256 x 256 with a persistent grid of one workgroup per compute unit.
@@ -300,12 +369,6 @@ static bool split_launch(int id) {
   const bool big = id == 16 || (id >= 20 && id <= 22);
   const int t = tuning_value(SEMMOE_TUNE_HEAD_TAIL);
   return big && t != 0;
-}
-
-// left-over share of a round (in sixteenths) up to which the split happens
-static int split_threshold() {
-  const int t = tuning_value(SEMMOE_TUNE_HEAD_TAIL);
-  return (t >= 1 && t <= 16) ? t : 8;
 }
 
 int32_t launch_ksplit_gemm(const void* X, const void* W, int T, int N, int d, int n_parts, float* partial,
@@ -334,7 +397,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       case kModeSwiglu: {
         const int id = tuning_value(SEMMOE_TUNE_GATEUP_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_GATEUP_TILE)
-                           : default_tile(est_rows_per_group, (long long)(max_rows / 256 + a.nq) * cdiv(a.N, 128));
+                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 128));
         if (!split_launch(id)) return launch_bf16_tile<kModeSwiglu>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;
@@ -350,7 +413,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       default: {
         const int id = tuning_value(SEMMOE_TUNE_DOWN_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_DOWN_TILE)
-                           : default_tile(est_rows_per_group, (long long)(max_rows / 256 + a.nq) * cdiv(a.N, 256));
+                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 256));
         if (!split_launch(id)) return launch_bf16_tile<kModeStore>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;
@@ -366,9 +429,9 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
     }
   }
   switch (mode) {
-    case kModeLogits: return launch_f32<kModeLogits>(a, max_rows, stream);
-    case kModeSwiglu: return launch_f32<kModeSwiglu>(a, max_rows, stream);
-    default: return launch_f32<kModeStore>(a, max_rows, stream);
+    case kModeLogits: return launch_f32<kModeLogits>(a, max_rows, est_rows_per_group, stream);
+    case kModeSwiglu: return launch_f32<kModeSwiglu>(a, max_rows, est_rows_per_group, stream);
+    default: return launch_f32<kModeStore>(a, max_rows, est_rows_per_group, stream);
   }
 }
 

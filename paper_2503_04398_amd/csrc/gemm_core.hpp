@@ -5,7 +5,7 @@
 //
 // bf16 path: v_mfma_f32_32x32x16_bf16, 256 threads = 4 waves, weights as the MFMA "A" operand so a
 // lane ends up with 4 consecutive output features of one row (8-byte stores).
-// fp32 path: plain FMA micro-tiles (the fp32 workload is tiny; it exists for exactness, not speed).
+// fp32 path, and bf16 with few rows per group: gemm_stream.hpp.
 #pragma once
 #include "common.hpp"
 
@@ -628,127 +628,6 @@ __global__ __launch_bounds__(64 * NWF * NWT, MINW) void gemm_bf16_dma_kernel(Gem
     static_assert(MODE != kModeLogits, "the router has its own kernel");
     store_tile_via_lds<MODE, NWF, NWT, TF, TT>(acc, lds_raw, a, row_lo, n_tok, f0, wf, wt);
     __syncthreads();  // the next tile's loads overwrite the staged tile
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// fp32 FMA kernel: 64 weight rows x 64 tokens per tile, 256 threads, 4x4 outputs per thread
-// ------------------------------------------------------------------------------------------------
-struct F32Cfg {
-  static constexpr int kThreads = 256, BW = 64, BT = 64, BK = 16, LD = 64 + 4;
-  static constexpr size_t kLdsBytes = size_t(2) * BK * LD * 4 + 520 * 4;
-};
-
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  using C = F32Cfg;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  float* Ws = reinterpret_cast<float*>(lds_raw);  // [BK][LD], k-major
-  float* Xs = Ws + C::BK * C::LD;
-  int* pre = reinterpret_cast<int*>(Xs + C::BK * C::LD);
-  constexpr int FEAT = (MODE == kModeSwiglu) ? C::BW / 2 : C::BW;
-
-  const int tid = threadIdx.x;
-  const int tx = tid & 15;  // tokens 4*tx .. 4*tx+3
-  const int ty = tid >> 4;  // weight rows 4*ty .. 4*ty+3
-  const int n_ftiles = (a.N + FEAT - 1) / FEAT;
-  const int total = build_tile_prefix(a, n_ftiles, pre, C::BT);
-
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    const int q = find_group(pre, a.nq, tile);
-    const int local = tile - pre[q];
-    const int ft = local % n_ftiles;
-    const int tt_idx = local / n_ftiles;
-    const int row_lo = (a.offsets ? a.offsets[a.q_lo + q] : 0) + tt_idx * C::BT;
-    const int row_hi = a.offsets ? a.offsets[a.q_lo + q + 1] : a.n_rows_single;
-    const int n_tok = min(C::BT, row_hi - row_lo);
-    const int f0 = ft * FEAT;
-    const int widx = a.group_to_weight ? a.group_to_weight[a.q_lo + q] : (a.q_lo + q);
-    const float* Wg = static_cast<const float*>(a.W) + size_t(widx) * a.w_group_stride;
-    const float* Xg = static_cast<const float*>(a.X) + size_t(row_lo) * a.ldx;
-
-    // loader: thread loads row lr = tid/4, 4 floats at k = (tid%4)*4
-    const int lr = tid >> 2, kc = (tid & 3) * 4;
-    int grow;
-    bool wok;
-    if constexpr (MODE == kModeSwiglu) {  // local row lr: (lr&1)=0 gate / 1 up of feature f0 + lr/2
-      const int feat = f0 + (lr >> 1);
-      wok = feat < a.N;
-      grow = (lr & 1) * a.N + feat;
-    } else {
-      grow = f0 + lr;
-      wok = grow < a.N;
-    }
-    const float* wsrc = wok ? Wg + size_t(grow) * a.ldw + kc : nullptr;
-    const float* xsrc = lr < n_tok ? Xg + size_t(lr) * a.ldx + kc : nullptr;
-
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
-
-    for (int k0 = 0; k0 < a.K; k0 += C::BK) {
-      const bool kin = (k0 + kc) < a.K;  // K % 4 == 0 is guaranteed by the K % 8 rule
-      float4 wv = (wsrc && kin) ? *reinterpret_cast<const float4*>(wsrc + k0) : make_float4(0, 0, 0, 0);
-      float4 xv = (xsrc && kin) ? *reinterpret_cast<const float4*>(xsrc + k0) : make_float4(0, 0, 0, 0);
-      __syncthreads();
-      Ws[(kc + 0) * C::LD + lr] = wv.x; Ws[(kc + 1) * C::LD + lr] = wv.y;
-      Ws[(kc + 2) * C::LD + lr] = wv.z; Ws[(kc + 3) * C::LD + lr] = wv.w;
-      Xs[(kc + 0) * C::LD + lr] = xv.x; Xs[(kc + 1) * C::LD + lr] = xv.y;
-      Xs[(kc + 2) * C::LD + lr] = xv.z; Xs[(kc + 3) * C::LD + lr] = xv.w;
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < C::BK; ++kk) {
-        const float4 w4 = *reinterpret_cast<const float4*>(Ws + kk * C::LD + 4 * ty);
-        const float4 x4 = *reinterpret_cast<const float4*>(Xs + kk * C::LD + 4 * tx);
-        const float wr[4] = {w4.x, w4.y, w4.z, w4.w};
-        const float xr[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(wr[i], xr[j], acc[i][j]);
-      }
-    }
-
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int tl = 4 * tx + j;
-      if (tl >= n_tok) continue;
-      const size_t row = size_t(row_lo) + tl;
-      if constexpr (MODE == kModeSwiglu) {
-        float* o = static_cast<float*>(a.out) + row * a.ldo;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const int feat = f0 + 2 * ty + p;
-          if (feat < a.N) {
-            const float g = acc[2 * p][j], u = acc[2 * p + 1][j];
-            o[feat] = g / (1.0f + expf(-g)) * u;
-          }
-        }
-      } else if constexpr (MODE == kModeStore) {
-        float* o = static_cast<float*>(a.out) + row * a.ldo;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int feat = f0 + 4 * ty + i;
-          if (feat < a.N) o[feat] = acc[i][j];
-        }
-      } else {
-        float* o = static_cast<float*>(a.out) + row * size_t(a.N);
-        const int cls = a.token_class ? a.token_class[row] : -1;
-        const float* cb = (cls >= 0 && cls < a.n_classes && a.class_bias) ? a.class_bias + size_t(cls) * a.N : nullptr;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int feat = f0 + 4 * ty + i;
-          if (feat < a.N) {
-            float v = acc[i][j];
-            if (a.b_g) v += a.b_g[feat];
-            if (cb) v += cb[feat];
-            o[feat] = v;
-          }
-        }
-      }
-    }
   }
 }
 

@@ -1,0 +1,95 @@
+"""Grouped FFN kernels for few and for middling rows per expert, on group sizes at the edges of their tiles.
+
+The expert FFN is called with offsets written by hand and compared row by row with a float64 product on the CPU.  Bounds:
+fp32 1e-5, bf16 2e-2 of the largest value (the hidden activation and the result are rounded to the activation type)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_04398_amd as S
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _ffn(rows, d, F, dtype, D=1, rank=-1, knobs=(), seed=0):
+    """(Y, its float64 reference, rows of the rank, poison) of one expert_ffn call with `rows` rows per expert"""
+    r = np.random.default_rng(seed)
+    E, P = len(rows), int(sum(rows))
+    act = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X = torch.from_numpy(r.standard_normal((P, d), dtype=np.float32)).to(act)
+    W_gu = torch.from_numpy(0.05 * r.standard_normal((E, 2 * F, d), dtype=np.float32)).to(act)
+    W_dn = torch.from_numpy(0.05 * r.standard_normal((E, d, F), dtype=np.float32)).to(act)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    of_phys = r.permutation(E).astype(np.int32)
+    m = S.SemMoE(S.Config(T=P, d=d, E=E, k=1, F=F, D=D, dtype=dtype, cap=P))
+    Y = torch.full((P, d), 512.0, dtype=act, device=H.DEV)
+    try:
+        for key, value in knobs:
+            m.set_tuning(key, value)
+        m.expert_ffn(rank, X.to(H.DEV), torch.from_numpy(off).to(H.DEV), torch.from_numpy(of_phys).to(H.DEV), W_gu.to(H.DEV),
+                     W_dn.to(H.DEV), Y)
+        torch.cuda.synchronize()
+    finally:
+        for key, _ in knobs:
+            m.set_tuning(key, -1)
+    lo, hi = (0, E) if rank < 0 else (rank * (E // D), (rank + 1) * (E // D))
+    want = np.full((P, d), 512.0)
+    for q in range(lo, hi):
+        x = X[off[q]:off[q + 1]].double().numpy()
+        gu, dn = W_gu[of_phys[q]].double().numpy(), W_dn[of_phys[q]].double().numpy()
+        gate, up = x @ gu[:F].T, x @ gu[F:].T
+        want[off[q]:off[q + 1]] = (gate / (1.0 + np.exp(-gate)) * up) @ dn.T
+    return H.to_np(Y), want, slice(int(off[lo]), int(off[hi]))
+
+
+def _check(got, want, mine, dtype):
+    H.assert_close(got[mine], want[mine], dtype, "Y")
+    assert (np.delete(got, np.r_[mine], axis=0) == 512.0).all()  # rows of other ranks stay as they were
+    per_row = np.abs(got[mine] - want[mine]).max(axis=1) / np.abs(want[mine]).max()
+    assert per_row.max() <= H.TOL[dtype]
+
+
+RAGGED = (0, 1, 15, 16, 17, 33, 64, 65, 0, 130, 31, 48)
+
+
+# d / F: whole slices for every wave (256 / 512: K = 512, 256 and more); K with a partial slice (264 / 296: 8 elements in
+# the last one); K so short that some waves have no slice (72, 8); F below a feature tile (8, 24)
+@pytest.mark.parametrize("d,F", [(256, 512), (264, 296), (72, 24), (512, 8), (8, 72)])
+@pytest.mark.parametrize("tile,cap", [(30, -1), (31, -1), (32, -1), (30, 8), (32, 3)])
+def test_streamed_tiles_bf16(tile, cap, d, F):
+    got, want, mine = _ffn(RAGGED, d, F, "bf16", knobs=((0, tile), (1, tile), (4, cap)), seed=tile + d)
+    _check(got, want, mine, "bf16")
+
+
+@pytest.mark.parametrize("d,F", [(256, 512), (264, 296), (72, 24), (512, 8), (8, 72)])
+@pytest.mark.parametrize("rows,cap", [(RAGGED, -1), (RAGGED, 8), ((3,) * 12, -1), ((140,) * 12, 5)])
+def test_fp32(rows, cap, d, F):
+    got, want, mine = _ffn(rows, d, F, "fp32", knobs=((4, cap),), seed=d)
+    _check(got, want, mine, "fp32")
+
+
+# the library's own choice over its range of rows per expert, many experts and few, whole slices of K and not
+@pytest.mark.parametrize("rows_per_expert", [1, 19, 20, 39, 40, 191, 192, 383, 384])
+@pytest.mark.parametrize("E,D,d,F", [(32, 1, 256, 192), (4, 2, 200, 136), (2, 1, 384, 256)])
+def test_own_choice(rows_per_expert, E, D, d, F):
+    r = np.random.default_rng(rows_per_expert)
+    rows = np.full(E, rows_per_expert) + r.integers(0, 3, E)
+    rows[0] += int(rows[1]) - 1
+    rows[1] = 1
+    got, want, mine = _ffn(tuple(rows), d, F, "bf16", D=D, rank=D - 1 if D > 1 else -1, seed=rows_per_expert)
+    _check(got, want, mine, "bf16")
+
+
+@pytest.mark.parametrize("n", [1, 64, 160, 161, 256, 257, 400])
+def test_one_set_of_weights(n):
+    """the shared expert on n rows, on both sides of the lines between its tiles"""
+    r = np.random.default_rng(n)
+    d, F = 448, 320
+    X, gu, dn = (torch.from_numpy(s * r.standard_normal(shape, dtype=np.float32)).bfloat16()
+                 for s, shape in ((1.0, (n, d)), (0.05, (2 * F, d)), (0.05, (d, F))))
+    m = S.SemMoE(S.Config(T=n, d=d, E=2, k=1, F=F, D=1, dtype="bf16", cap=n))
+    Y = torch.empty(n, d, dtype=torch.bfloat16, device=H.DEV)
+    m.shared_ffn(X.to(H.DEV), n, gu.to(H.DEV), dn.to(H.DEV), Y)
+    gate, up = X.double() @ gu[:F].double().t(), X.double() @ gu[F:].double().t()
+    H.assert_close(H.to_np(Y), ((gate * torch.sigmoid(gate) * up) @ dn.double().t()).numpy(), "bf16", "Y_shared")
