@@ -69,25 +69,26 @@ static int32_t launch_dma(const GemmArgs& a, int max_rows, int blocks_per_cu, hi
 }
 
 // Four-wave 256 x 256 kernel; shapes it does not take are reported with SEMMOE_EUNSUPPORTED before any launch.
-template <int MODE, int BK, int NSTAGE, int DMA_EVERY>
+template <int MODE, int BK, int NSTAGE, int DMA_EVERY, int TJ = 4>
 static int32_t launch_w4(const GemmArgs& a, int max_rows, hipStream_t stream) {
-  using C = W4Cfg<MODE, BK, NSTAGE, DMA_EVERY>;
+  using C = W4Cfg<MODE, BK, NSTAGE, DMA_EVERY, TJ>;
   const int w_rows = (MODE == kModeSwiglu) ? 2 * a.N : a.N;
   if (a.K % BK != 0 || a.K / BK < NSTAGE) return SEMMOE_EUNSUPPORTED;
   if ((unsigned long long)w_rows * a.ldw * 2 >= (1ull << 32) || (unsigned long long)C::BT * a.ldx * 2 >= (1ull << 32))
     return SEMMOE_EUNSUPPORTED;  // per-lane row offsets are 32-bit
-  if (C::kLdsBytes > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
+  const size_t lds = TJ == 4 ? C::kLdsBytes : C::lds_bytes(a.nq);
+  if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   const int n_ftiles = cdiv(a.N, C::FEAT);
   const long long bound = (long long)(max_rows / C::BT + a.nq) * n_ftiles;
   if (bound <= 0) return SEMMOE_OK;
   const int grid = grid_for(bound, num_cu());
-  auto kern = gemm_bf16_w4_kernel<MODE, BK, NSTAGE, DMA_EVERY>;
+  auto kern = gemm_bf16_w4_kernel<MODE, BK, NSTAGE, DMA_EVERY, TJ>;
   static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
   {
     const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
     if (as != SEMMOE_OK) return as;
   }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), C::kLdsBytes, stream, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), lds, stream, a);
   SEMMOE_LAUNCH_CHECK();
   return SEMMOE_OK;
 }
@@ -173,28 +174,34 @@ static int32_t launch_all_pieces(GemmArgs a, int max_rows, hipStream_t stream) {
   a.sched_sub_f = 2;
   a.sched_fine = 1;  // 128 x 64 pieces when the 128 x 128 ones would leave half the compute units idle
   const int grid = grid_for(bound_p * 8, num_cu());
+  using CF = DmaCfg<MODE, 2, 2, 2, 1, 64, kFineRing>;  // the halved pieces
+  const size_t lds = CF::kLdsBytes > C::kLdsBytes ? CF::kLdsBytes : C::kLdsBytes;
+  if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   auto kern = gemm_bf16_piece_kernel<MODE, 3>;
   static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
   {
     const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
     if (as != SEMMOE_OK) return as;
   }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), C::kLdsBytes, stream, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), lds, stream, a);
   SEMMOE_LAUNCH_CHECK();
   return SEMMOE_OK;
 }
 
 // Head (four-wave 256 x 256 tiles, K slices of 64, ring of 2) and tail (128 x 128 pieces, ring of 3) in one launch.
 // SEMMOE_EUNSUPPORTED when either half does not take the shape: the caller then launches them one after the other.
-template <int MODE>
+template <int MODE, int NSTAGE = 2, int TJ = 4>
 static int32_t launch_w4_split(const GemmArgs& h, int max_rows, hipStream_t stream) {
-  using CH = W4Cfg<MODE, 64, 2, 2>;
+  using CH = W4Cfg<MODE, 64, NSTAGE, 2, TJ>;
   using CP = DmaCfg<MODE, 2, 2, 2, 2, 64, 3>;
   const int w_rows = (MODE == kModeSwiglu) ? 2 * h.N : h.N;
   if (h.K % 64 != 0 || h.K / 64 < 3) return SEMMOE_EUNSUPPORTED;
   if ((unsigned long long)w_rows * h.ldw * 2 >= (1ull << 32) || (unsigned long long)CH::BT * h.ldx * 2 >= (1ull << 32))
     return SEMMOE_EUNSUPPORTED;  // per-lane row offsets are 32-bit
-  const size_t lds = CH::kLdsBytes > CP::kLdsBytes ? CH::kLdsBytes : CP::kLdsBytes;
+  const size_t head_lds = TJ == 4 ? CH::kLdsBytes : CH::lds_bytes(h.nq);
+  using CF = DmaCfg<MODE, 2, 2, 2, 1, 64, kFineRing>;
+  size_t lds = head_lds > CP::kLdsBytes ? head_lds : CP::kLdsBytes;
+  if (CF::kLdsBytes > lds) lds = CF::kLdsBytes;
   if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   const int n_ftiles = cdiv(h.N, CH::FEAT);
   const long long bound = (long long)(max_rows / CH::BT + h.nq) * n_ftiles;
@@ -203,10 +210,10 @@ static int32_t launch_w4_split(const GemmArgs& h, int max_rows, hipStream_t stre
   GemmArgs t = h;  // the tail's view of the same problem: the tiles the head's `grid` workgroups leave over, in pieces
   t.sched_mode = 2;
   t.sched_g = grid;
-  t.sched_sub_t = 256 / CP::BT;
-  t.sched_sub_f = 256 / CP::BW;
+  t.sched_sub_t = CH::BT / CP::BT;
+  t.sched_sub_f = CH::BW / CP::BW;
   t.sched_fine = tuning_value(SEMMOE_TUNE_TAIL_RING) == 2 ? 0 : 1;
-  auto kern = gemm_bf16_w4_split_kernel<MODE, 64, 2, 2, 3>;
+  auto kern = gemm_bf16_w4_split_kernel<MODE, 64, NSTAGE, 2, 3, TJ>;
   static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
   {
     const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
@@ -289,6 +296,15 @@ static int split_threshold() {
   return (t >= 1 && t <= 16) ? t : 8;
 }
 
+// 256 weight rows x 128 tokens, ring of 3, left-over tiles as pieces in the same launch
+template <int MODE>
+static int32_t launch_w4_128(const GemmArgs& a, int max_rows, hipStream_t stream) {
+  GemmArgs h = a;
+  h.sched_mode = 1;
+  h.sched_thr = split_threshold();
+  return launch_w4_split<MODE, 3, 2>(h, max_rows, stream);
+}
+
 // tile shapes: id -> (waves along weight rows, waves along tokens, MFMA tiles per wave, K slice)
 template <int MODE>
 static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc, hipStream_t s) {
@@ -316,6 +332,11 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
       if (st != SEMMOE_EUNSUPPORTED) return st;
       return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);  // panels beyond 32-bit offsets
     }
+    case 33: {  // four waves, 256 x 128
+      const int32_t st = launch_w4_128<MODE>(a, max_rows, s);
+      if (st != SEMMOE_EUNSUPPORTED) return st;
+      return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);  // K not a multiple of 64 or short, or too many groups
+    }
     case 28: {  // 128 x 128 pieces, loads between the MFMAs
       const int32_t st = launch_all_pieces<MODE>(a, max_rows, s);
       if (st != SEMMOE_EUNSUPPORTED) return st;
@@ -339,16 +360,23 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 // Default tile shape from the mean rows per group that the caller expects (the true, ragged row counts live on the
 // device).  Measured over rows per group, us of a whole FFN (gate/up + down, lognormal spread 0.3 of the group sizes):
 //   A: 128 experts, d 2048, F 768;  B: 16 experts, d 4096, F 1536;  C: 8 experts, d 7168, F 2048
-//   rows   streamed 32 rows x 32   streamed 64 x 64    128 x 64, ring of 3
-//   8      A 192 B 102 C 115       197 111 118         228 131 138
-//   16     A 215 B 107 C 124       213 110 129         241 128 138
-//   32     A 302 B 157 C 180       240 116 137         261 132 143
-//   48                             283 143 169         259 147 185
-// The streaming kernel loses as the token rows it drags past every weight tile grow.
-// One set of weights (the shared expert) with so few rows that big tiles would leave most compute units idle is bound by
-// the latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
-// 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).
-static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group, int n_ftiles256) {
+//   rows   streamed 32 rows x 32   streamed 64 x 64    256 x 128        256 x 256        128 x 64, ring of 3
+//   8      A 192 B 102 C 115       197 111 118                          278 167 191      A 228 B 131 C 138
+//   16     A 215 B 107 C 124       213 110 129                          288 164 197      A 241 B 128 C 138
+//   32     A 302 B 157 C 180       240 116 137         256 134 150      299 166 200      A 261 B 132 C 143
+//   48                             283 143 169         254 147 142      301 173 203      A 259 B 147 C 185
+//   64                             329 166 187         280 149 159      314 173 211      A 287 B 169 C 193
+//   110                                                301 159 200      334 183 225      A 372 B 203 C 255
+//   160                                                362 192 220      369 189 239      A 467 B 238 C 275
+//   300                                                509 271 301      522 299 323
+//   400                                                620 328 390      624 346 380
+// The streaming kernel loses as the token rows it drags past every weight tile grow, the 256 x 128 tile as two of them
+// read the weights that one 256 x 256 tile reads once.  tiles128: the 256 x 128 tiles the problem is expected to have.
+// One set of weights (the shared expert) with so few rows that these would leave most compute units idle is bound by the
+// latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
+// 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).  2000 rows of
+// it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.
+static int default_tile(const GemmArgs& a, int est_rows_per_group, int n_ftiles256) {
   const int est = est_rows_per_group;
   const long long tiles128 = (long long)a.nq * cdiv(est < 1 ? 1 : est, 128) * n_ftiles256;
   const bool narrow = a.offsets ? tiles128 * 4 < num_cu() : tiles128 * 4 < 3LL * num_cu();
@@ -359,9 +387,11 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
   }
   if (est < 20) return 30;
   if (est < 40) return 32;
-  if (est < 96) return 26;
-  if (est < 192) return 0;
-  return (long long)(max_rows / 256 + a.nq) * n_ftiles256 * 2 >= num_cu() ? 22 : 28;
+  const bool whole_slices = a.K % 64 == 0 && a.K / 64 >= 3;  // what the tiles with a running load stream need
+  if (!whole_slices) return est < 192 ? 26 : 22;
+  if (est < 384) return 33;
+  const long long tiles256 = (long long)a.nq * cdiv(est, 256) * n_ftiles256;
+  return tiles256 * 4 < 3LL * num_cu() ? 33 : 22;  // half the tokens a tile while those would leave compute units idle
 }
 
 // Head/tail split: for the tile shapes of 256 x 256 with a persistent grid of one workgroup per compute unit.
@@ -397,7 +427,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       case kModeSwiglu: {
         const int id = tuning_value(SEMMOE_TUNE_GATEUP_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_GATEUP_TILE)
-                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 128));
+                           : default_tile(a, est_rows_per_group, cdiv(a.N, 128));
         if (!split_launch(id)) return launch_bf16_tile<kModeSwiglu>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;
@@ -413,7 +443,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       default: {
         const int id = tuning_value(SEMMOE_TUNE_DOWN_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_DOWN_TILE)
-                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 256));
+                           : default_tile(a, est_rows_per_group, cdiv(a.N, 256));
         if (!split_launch(id)) return launch_bf16_tile<kModeStore>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;

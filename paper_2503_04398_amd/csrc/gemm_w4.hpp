@@ -1,5 +1,9 @@
 // Grouped bf16 GEMM for large groups: one 256 x 256 output tile per workgroup, four waves, each wave a
 // 128 x 128 quadrant (4 x 4 MFMA tiles of 32 x 32, 256 accumulator registers), one wave per SIMD.
+// For middling groups (about 40 to 380 rows) the same with 128 tokens: a wave has 128 x 64, and the 48 KB a slice takes
+// leave room for a ring of 3.  There the weights bound the tile, not the MFMAs, and what counts is that half the
+// padding is multiplied and that two slices are always in flight (8 experts of 90 rows, d 7168, F 2048: 227 us as
+// 256 x 256 tiles, 203 as 128 x 64 tiles with a burst of loads per slice, 167 so).
 //
 // Why this shape on gfx950: a quadrant of 128 x 128 needs 8 fragment reads (8 KB) from LDS per 16 MFMAs,
 // half the LDS traffic per flop of a 128 x 64 quadrant, and the MFMA pipe of a SIMD is fed by a single
@@ -74,10 +78,11 @@ __device__ __forceinline__ float silu_mul_fast(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * g)) * u;
 }
 
-template <int MODE, int BK, int NSTAGE, int DMA_EVERY>
+// TJ: MFMA columns (32 tokens) of a wave; the tile is 256 weight rows x 64*TJ tokens
+template <int MODE, int BK, int NSTAGE, int DMA_EVERY, int TJ = 4>
 struct W4Cfg {
   static constexpr int kThreads = 256;
-  static constexpr int BW = 256, BT = 256, ROWS = BW + BT;
+  static constexpr int BW = 256, BT = 64 * TJ, ROWS = BW + BT;
   static constexpr int RB = BK * 2;        // bytes per tile row of a slice
   static constexpr int CPR = BK / 8;       // 16-byte chunks per row
   static constexpr int RPI = 64 / CPR;     // rows written by one wave-level load
@@ -88,11 +93,14 @@ struct W4Cfg {
   static constexpr int kStageBytes = ROWS * RB;
   static constexpr int FEAT = (MODE == kModeSwiglu) ? BW / 2 : BW;
   static constexpr size_t kRingBytes = size_t(NSTAGE) * kStageBytes;
-  static constexpr int kStgRow = 128 + 16;             // staging row: 64 bf16 + pad against bank conflicts
+  static constexpr int NB = TJ == 4 ? 2 : 1;           // blocks of 32 features that an epilogue pass stages
+  static constexpr int kStgRow = NB * 64 + 16;         // staging row: 32*NB bf16 + pad against bank conflicts
   static constexpr int kStgWave = 32 * kStgRow;        // 32 tokens per pass
   static constexpr size_t kLdsBytes = kRingBytes + 4 * kStgWave + 4 * 520 * 4;  // + tile prefix + group table
   static_assert(BK == 32 || BK == 64, "row of 64 or 128 bytes");
-  static_assert(KS * 16 / DMA_EVERY >= IPW, "the loads of a slice fit between two barriers");
+  static constexpr size_t lds_bytes(int nq) { return kRingBytes + 4 * kStgWave + (4 * size_t(nq) + 8) * 4; }
+  static_assert(KS * 4 * TJ / DMA_EVERY >= IPW, "the loads of a slice fit between two barriers");
+  static_assert(TJ == 4 || TJ == 2, "how the rows of a slice are dealt out to the waves");
   static_assert(NSTAGE >= 2 && (NSTAGE - 1) * IPW < 64, "vmcnt range");
 };
 
@@ -123,9 +131,9 @@ __device__ __forceinline__ TileRef locate_tile(const GemmArgs& a, const int* pre
   return t;
 }
 
-template <int MODE, int BK, int NSTAGE, int DMA_EVERY>
+template <int MODE, int BK, int NSTAGE, int DMA_EVERY, int TJ = 4>
 __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned char* lds_raw) {
-  using C = W4Cfg<MODE, BK, NSTAGE, DMA_EVERY>;
+  using C = W4Cfg<MODE, BK, NSTAGE, DMA_EVERY, TJ>;
   // kModeLogits here: raw fp32 sums, no bias terms (the K-split router adds the parts and the biases afterwards)
   const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>(lds_raw));
 
@@ -137,7 +145,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   unsigned char* stg = lds_raw + C::kRingBytes + wave * C::kStgWave;
   int* pre = reinterpret_cast<int*>(lds_raw + C::kRingBytes + 4 * C::kStgWave);
 
-  int* gtab = pre + 520;
+  int* gtab = pre + (TJ == 4 ? 520 : a.nq + 1);
   const int n_ftiles = (a.N + C::FEAT - 1) / C::FEAT;
   const int G = gridDim.x;
   for (int q = tid; q < a.nq; q += C::kThreads) {
@@ -163,11 +171,15 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   // token blocks of 32 alternate between the two token waves (block b -> wave b % 2, its MFMA column b / 2), so
   // that a partly filled tile leaves both with the same number of empty columns to skip
   const unsigned frag_x = (C::BW + wt * 32 + (lane & 31)) * C::RB;
-  // loader geometry: lane fills position d_pos of row d_row inside the 1 KB block of a load.  Waves 0 and 1
-  // load the 256 weight rows of a slice, waves 2 and 3 the 256 token rows.
+  // loader geometry: lane fills position d_pos of row d_row inside the 1 KB block of a load.  256 token rows: waves 0
+  // and 1 load the 256 weight rows of a slice, waves 2 and 3 the token rows.  128 token rows (12 loads a wave):
+  // waves 0 and 1 load weight rows, wave 2 weight rows with its first 8 loads and token rows with the rest, wave 3
+  // token rows.
   const int d_row = lane / C::CPR;
   const int d_pos = lane % C::CPR;
-  const bool loads_w = wave < 2;
+  const bool loads_w = wave < 2;           // ... with every load
+  const bool first_w = TJ == 4 ? loads_w : wave < 3;  // ... with its first loads (below kSplit)
+  constexpr int kSplit = TJ == 4 ? C::IPW : 8;
 
   // ---- load stream state (runs NSTAGE slices ahead of the MFMAs, across tiles)
   int i_tile = 0;  // round of this workgroup
@@ -180,6 +192,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   // same bytes over the same bytes, harmless for a wave reading them.
   unsigned i_dst = 0;                     // uniform: LDS address of this wave's first load of the stream's slice
   const unsigned char* i_base = nullptr;  // uniform: weight panel or token panel of the tile, advanced by RB per slice
+  const unsigned char* i_base2 = nullptr;  // ... of the loads from kSplit on (128 token rows only)
   uint32_t i_off[C::IPW];                 // per lane: byte offset of the row + chunk it fetches
 
   // (the lambdas are forced inline: one left as a call makes the argument block a stack object, and every access
@@ -188,32 +201,44 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   auto i_setup = [&](int tile) __attribute__((always_inline)) {
     const TileRef t = locate_tile(a, pre, gtab, tile, n_ftiles, C::BT, C::FEAT);
     s_tile = t;
-    if (loads_w) {
-      i_base = reinterpret_cast<const unsigned char*>(static_cast<const bf16_t*>(a.W) + size_t(t.widx) * a.w_group_stride);
-#pragma unroll
-      for (int i = 0; i < C::IPW; ++i) {
-        const int sr = (wave * C::IPW + i) * C::RPI + d_row;  // weight row of the tile
-        const int c = d_pos ^ ((sr / C::RPB) % C::CPR);
-        int grow;
-        if constexpr (MODE == kModeSwiglu) {
-          // quadrant wf: MFMA tiles 0,2 are gate rows, 1,3 the matching up rows, of two blocks of 32 features
-          const int tf = (sr >> 5) & 3, fr = sr & 31;
-          const int feat = min(t.f0 + ((sr >> 7) * 2 + (tf >> 1)) * 32 + fr, a.N - 1);
-          grow = (tf & 1) * a.N + feat;
-        } else {
-          grow = min(t.f0 + sr, a.N - 1);
-        }
-        i_off[i] = uint32_t(grow) * uint32_t(a.ldw) * 2u + uint32_t(c) * 16u;
+    const unsigned char* w_panel =
+        reinterpret_cast<const unsigned char*>(static_cast<const bf16_t*>(a.W) + size_t(t.widx) * a.w_group_stride);
+    const unsigned char* x_panel = reinterpret_cast<const unsigned char*>(static_cast<const bf16_t*>(a.X) + size_t(t.row_lo) * a.ldx);
+    // K split: output row q * ksplit_rows + r is row r of X, columns from q * K on
+    if (a.ksplit_rows) x_panel -= (size_t(t.q) * a.ksplit_rows * a.ldx - size_t(t.q) * a.K) * 2;
+    auto w_off = [&](int sr) __attribute__((always_inline)) {  // weight row sr of the tile
+      const int c = d_pos ^ ((sr / C::RPB) % C::CPR);
+      int grow;
+      if constexpr (MODE == kModeSwiglu) {
+        // quadrant wf: MFMA tiles 0,2 are gate rows, 1,3 the matching up rows, of two blocks of 32 features
+        const int tf = (sr >> 5) & 3, fr = sr & 31;
+        const int feat = min(t.f0 + ((sr >> 7) * 2 + (tf >> 1)) * 32 + fr, a.N - 1);
+        grow = (tf & 1) * a.N + feat;
+      } else {
+        grow = min(t.f0 + sr, a.N - 1);
       }
-    } else {
-      i_base = reinterpret_cast<const unsigned char*>(static_cast<const bf16_t*>(a.X) + size_t(t.row_lo) * a.ldx);
-      // K split: output row q * ksplit_rows + r is row r of X, columns from q * K on
-      if (a.ksplit_rows) i_base -= (size_t(t.q) * a.ksplit_rows * a.ldx - size_t(t.q) * a.K) * 2;
+      return uint32_t(grow) * uint32_t(a.ldw) * 2u + uint32_t(c) * 16u;
+    };
+    auto x_off = [&](int sr) __attribute__((always_inline)) {  // token row sr of the tile
+      const int c = d_pos ^ (((sr + C::BW) / C::RPB) % C::CPR);
+      return uint32_t(min(sr, t.n_tok - 1)) * uint32_t(a.ldx) * 2u + uint32_t(c) * 16u;
+    };
+    i_base = first_w ? w_panel : x_panel;
+    if constexpr (TJ != 4) i_base2 = loads_w ? w_panel : x_panel;
+    if (first_w) {
 #pragma unroll
-      for (int i = 0; i < C::IPW; ++i) {
-        const int sr = (wave * C::IPW + i) * C::RPI + d_row - C::BW;  // token row of the tile
-        const int c = d_pos ^ (((sr + C::BW) / C::RPB) % C::CPR);
-        i_off[i] = uint32_t(min(sr, t.n_tok - 1)) * uint32_t(a.ldx) * 2u + uint32_t(c) * 16u;
+      for (int i = 0; i < kSplit; ++i) i_off[i] = w_off((wave * C::IPW + i) * C::RPI + d_row);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kSplit; ++i) i_off[i] = x_off((wave * C::IPW + i) * C::RPI + d_row - C::BW);
+    }
+    if constexpr (TJ != 4) {
+      if (loads_w) {
+#pragma unroll
+        for (int i = kSplit; i < C::IPW; ++i) i_off[i] = w_off((wave * C::IPW + i) * C::RPI + d_row);
+      } else {
+#pragma unroll
+        for (int i = kSplit; i < C::IPW; ++i) i_off[i] = x_off((wave * C::IPW + i) * C::RPI + d_row - C::BW);
       }
     }
   };
@@ -223,6 +248,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
       return;
     }
     i_base += C::RB;
+    if constexpr (TJ != 4) i_base2 += C::RB;
     i_stage = (i_stage + 1 == NSTAGE) ? 0 : i_stage + 1;
     i_dst = lds_base + i_stage * C::kStageBytes + wave * C::IPW * 1024;
     if (++i_slice == nk) {
@@ -234,19 +260,20 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   // load number i of the current slice of the stream; after the last one the stream moves to the next slice
   auto i_issue = [&](auto idx) __attribute__((always_inline)) {
     constexpr int i = decltype(idx)::value;
-    lds_dma16_imm<i * 1024>(i_base, i_off[i], i_dst);
+    const unsigned char* base = i < kSplit ? i_base : i_base2;
+    lds_dma16_imm<i * 1024>(base, i_off[i], i_dst);
     if constexpr (i == C::IPW - 1) i_next_slice();
   };
 
   // ---- fragments
-  bf16x8_t af[2][4], bfr[2][4];
-  auto frag = [&](int stage, int ks, bf16x8_t(&fa)[4], bf16x8_t(&fb)[4]) __attribute__((always_inline)) {
+  bf16x8_t af[2][4], bfr[2][TJ];
+  auto frag = [&](int stage, int ks, bf16x8_t(&fa)[4], bf16x8_t(&fb)[TJ]) __attribute__((always_inline)) {
     const unsigned char* S = lds_raw + stage * C::kStageBytes;
     const int off = ((ks * 2 + (lane >> 5)) ^ frag_swz) * 16;
 #pragma unroll
     for (int i = 0; i < 4; ++i) fa[i] = *reinterpret_cast<const bf16x8_t*>(S + frag_w + i * 32 * C::RB + off);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8_t*>(S + frag_x + j * 64 * C::RB + off);
+    for (int j = 0; j < TJ; ++j) fb[j] = *reinterpret_cast<const bf16x8_t*>(S + frag_x + j * 64 * C::RB + off);
   };
 
   // ---- prologue: the first NSTAGE slices of the first tile
@@ -254,17 +281,19 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   for (int s = 0; s < NSTAGE; ++s) {  // nk >= NSTAGE: these slices belong to the first tile
 #pragma unroll
     for (int i = 0; i < C::IPW; ++i)
-      lds_dma16_s(i_base + s * C::RB, i_off[i], lds_base + s * C::kStageBytes + (wave * C::IPW + i) * 1024);
+      lds_dma16_s((i < kSplit ? i_base : i_base2) + s * C::RB, i_off[i],
+                  lds_base + s * C::kStageBytes + (wave * C::IPW + i) * 1024);
   }
   // The stream stands at slice NSTAGE-1, already fetched.  Where the last load of a window falls behind the
   // window's first k-step, the k-steps before the first barrier carry that tail: they fetch the rest of the
   // standing slice once more and the stream moves on when they are through.  Where a whole window fits into its
   // first k-step no load is placed before the first barrier, and the stream moves on here.
   i_base += (NSTAGE - 1) * C::RB;
+  if constexpr (TJ != 4) i_base2 += (NSTAGE - 1) * C::RB;
   i_slice = NSTAGE - 1;
   i_stage = NSTAGE - 1;
   i_dst = lds_base + i_stage * C::kStageBytes + wave * C::IPW * 1024;
-  if constexpr (C::IPW * DMA_EVERY <= 16) i_next_slice();
+  if constexpr (C::IPW * DMA_EVERY <= 4 * TJ) i_next_slice();
   wait_vmcnt<(NSTAGE - 1) * C::IPW>();
   __syncthreads();
   frag(0, 0, af[0], bfr[0]);
@@ -275,12 +304,12 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
     const TileRef t = s_tile;
     // MFMA columns of this wave that hold tokens (the others are computed on clamped rows and never stored:
     // skipping their MFMAs was measured to gain nothing, the loop is bound by the loads)
-    const int nj = min(4, max(0, (t.n_tok - wt * 32 + 63) >> 6));
-    f32x16_t acc[4][4];
+    const int nj = min(TJ, max(0, (t.n_tok - wt * 32 + 63) >> 6));
+    f32x16_t acc[4][TJ];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < TJ; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
@@ -306,7 +335,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
         const int off_next = ((((ks == kLast) ? 0 : ks + 1) * 2 + (lane >> 5)) ^ frag_swz) * 16;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < TJ; ++j) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
@@ -314,11 +343,11 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
               const int p = j * 4 + i;  // constant after unrolling
               if (p < 4)
                 af[cur ^ 1][p] = *reinterpret_cast<const bf16x8_t*>(S_next + frag_w + p * 32 * C::RB + off_next);
-              else if (p < 8)
+              else if (p < 4 + TJ)
                 bfr[cur ^ 1][p - 4] = *reinterpret_cast<const bf16x8_t*>(S_next + frag_x + (p - 4) * 64 * C::RB + off_next);
             }
             // position in the load stream = MFMAs since the barrier (the last k-step comes first after it)
-            const int m = ((ks == kLast) ? 0 : (ks + 1) * 16) + j * 4 + i;  // constant after unrolling
+            const int m = ((ks == kLast) ? 0 : (ks + 1) * 4 * TJ) + j * 4 + i;  // constant after unrolling
             if (m % DMA_EVERY == DMA_EVERY - 1 && m / DMA_EVERY < C::IPW) {
               switch (m / DMA_EVERY) {   // compile-time after unrolling
 #define SEMMOE_W4_CASE(n) case n: if constexpr (n < C::IPW) i_issue(std::integral_constant<int, n>{}); break;
@@ -352,7 +381,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
       // N is a multiple of 4 (checked by the host), so a chunk is inside the matrix or outside it as a whole.
       float* outf = static_cast<float*>(a.out);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < TJ; ++j) {
         if (j >= nj) break;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -382,9 +411,10 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
       }
       continue;
     }
-    constexpr int kPasses = (MODE == kModeSwiglu) ? 1 : 2;  // 64 output features per pass
+    constexpr int NB = C::NB;
+    constexpr int kPasses = ((MODE == kModeSwiglu) ? 2 : 4) / NB;  // 32*NB output features per pass
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < TJ; ++j) {
       if (j >= nj) break;
 #pragma unroll
       for (int h = 0; h < kPasses; ++h) {
@@ -394,24 +424,24 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (MODE == kModeSwiglu) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) asm volatile("" : "+a"(acc[i][j]));
+          for (int i = 0; i < 2 * NB; ++i) asm volatile("" : "+a"(acc[2 * NB * h + i][j]));
         } else {
-          asm volatile("" : "+a"(acc[2 * h][j]));
-          asm volatile("" : "+a"(acc[2 * h + 1][j]));
+#pragma unroll
+          for (int i = 0; i < NB; ++i) asm volatile("" : "+a"(acc[NB * h + i][j]));
         }
         unsigned char* wp = stg + tok_in * C::kStgRow + half * 8;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {  // block of 32 features inside the pass
+        for (int b = 0; b < NB; ++b) {  // block of 32 features inside the pass
 #pragma unroll
           for (int g4 = 0; g4 < 4; ++g4) {
             uint2 v;
             if constexpr (MODE == kModeSwiglu) {
-              const f32x16_t& g = acc[2 * b][j];
-              const f32x16_t& u = acc[2 * b + 1][j];
+              const f32x16_t& g = acc[2 * (NB * h + b)][j];
+              const f32x16_t& u = acc[2 * (NB * h + b) + 1][j];
               v.x = cvt_pk_bf16(silu_mul_fast(g[g4 * 4 + 0], u[g4 * 4 + 0]), silu_mul_fast(g[g4 * 4 + 1], u[g4 * 4 + 1]));
               v.y = cvt_pk_bf16(silu_mul_fast(g[g4 * 4 + 2], u[g4 * 4 + 2]), silu_mul_fast(g[g4 * 4 + 3], u[g4 * 4 + 3]));
             } else {
-              const f32x16_t& c = acc[2 * h + b][j];
+              const f32x16_t& c = acc[NB * h + b][j];
               v.x = cvt_pk_bf16(c[g4 * 4 + 0], c[g4 * 4 + 1]);
               v.y = cvt_pk_bf16(c[g4 * 4 + 2], c[g4 * 4 + 3]);
             }
@@ -420,12 +450,14 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_wave_barrier();
-        const int feat = t.f0 + (MODE == kModeSwiglu ? wf * 64 : wf * 128 + h * 64) + r_chunk * 8;
+        constexpr int kLpr = 4 * NB, kRpr = 64 / kLpr;  // lanes per staged row, rows per read-back
+        const int b_row = lane / kLpr, b_chunk = lane % kLpr;
+        const int feat = t.f0 + (MODE == kModeSwiglu ? wf * 64 : wf * 128) + h * NB * 32 + b_chunk * 8;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int sr = p * 8 + r_row;
+        for (int p = 0; p < 32 / kRpr; ++p) {
+          const int sr = p * kRpr + b_row;
           const int row = (j * 2 + wt) * 32 + sr;
-          const uint4 v = *reinterpret_cast<const uint4*>(stg + sr * C::kStgRow + r_chunk * 16);
+          const uint4 v = *reinterpret_cast<const uint4*>(stg + sr * C::kStgRow + b_chunk * 16);
           if (row < t.n_tok && feat < a.N)
             *reinterpret_cast<uint4*>(out + (size_t(t.row_lo) + row) * a.ldo + feat) = v;
         }
@@ -631,14 +663,17 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
   }
 }
 
-template <int MODE, int BK, int NSTAGE, int DMA_EVERY>
+template <int MODE, int BK, int NSTAGE, int DMA_EVERY, int TJ = 4>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_bf16_w4_body<MODE, BK, NSTAGE, DMA_EVERY>(a, lds_raw);
+  gemm_bf16_w4_body<MODE, BK, NSTAGE, DMA_EVERY, TJ>(a, lds_raw);
 }
 
 // Pieces as a launch of their own.  With sched_fine set the kernel halves the pieces along the tokens (128 x 64)
 // when twice the number of 128 x 128 pieces still fits the grid, as the split kernel below does for its tail.
+// Ring of the 128 x 64 pieces: 6 x 24 KB.  Where they are all there is (512 rows of one set of weights, d 7168) the walk
+// over K is a chain of loads that land late: 86 us with a ring of 3, 82 with 6.
+constexpr int kFineRing = 6;
 template <int MODE, int NSTAGE>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_piece_kernel(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -646,7 +681,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_piece_kernel(GemmArgs a) {
     const TileWalk probe = make_walk(a, reinterpret_cast<int*>(lds_raw), 128, (MODE == kModeSwiglu) ? 64 : 128);
     __syncthreads();
     if (probe.total > 0 && probe.total * 2 <= int(gridDim.x)) {
-      gemm_bf16_piece_body<MODE, NSTAGE, 1>(a, lds_raw, 4);
+      if (a.K / 64 >= kFineRing) gemm_bf16_piece_body<MODE, kFineRing, 1>(a, lds_raw, 4);
+      else gemm_bf16_piece_body<MODE, NSTAGE, 1>(a, lds_raw, 4);
       return;
     }
   }
@@ -657,19 +693,21 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_piece_kernel(GemmArgs a) {
 // then takes pieces of the left-over tiles.  Pieces and head tiles write disjoint outputs, so nothing has to be waited
 // for in between except this workgroup's own LDS.  Saves the second launch (also when nothing is left over, which
 // only the device knows) and lets a workgroup that is done early start on the pieces.
-template <int MODE, int BK, int NSTAGE, int DMA_EVERY, int PIECE_RING>
+template <int MODE, int BK, int NSTAGE, int DMA_EVERY, int PIECE_RING, int TJ = 4>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_split_kernel(GemmArgs head, GemmArgs tail) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_bf16_w4_body<MODE, BK, NSTAGE, DMA_EVERY>(head, lds_raw);
+  gemm_bf16_w4_body<MODE, BK, NSTAGE, DMA_EVERY, TJ>(head, lds_raw);
   __syncthreads();  // the head's last output staging has been read
   // few parent tiles left over: 128 x 64 pieces, eight per parent tile, so that twice as many compute units take part
   // (a piece walks all of K however few there are: its time does not shrink with their number)
   const TileWalk probe = make_walk(tail, reinterpret_cast<int*>(lds_raw), 128, (MODE == kModeSwiglu) ? 64 : 128);
   __syncthreads();
-  if (tail.sched_fine && probe.total > 0 && probe.total * 2 <= int(gridDim.x))
-    gemm_bf16_piece_body<MODE, PIECE_RING, 1>(tail, lds_raw, 4);
-  else
+  if (tail.sched_fine && probe.total > 0 && probe.total * 2 <= int(gridDim.x)) {
+    if (tail.K / 64 >= kFineRing) gemm_bf16_piece_body<MODE, kFineRing, 1>(tail, lds_raw, TJ);  // 64 tokens a piece
+    else gemm_bf16_piece_body<MODE, PIECE_RING, 1>(tail, lds_raw, TJ);
+  } else {
     gemm_bf16_piece_body<MODE, PIECE_RING, 2>(tail, lds_raw);
+  }
 }
 
 }  // namespace semmoe

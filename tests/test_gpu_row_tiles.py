@@ -69,6 +69,16 @@ def test_fp32(rows, cap, d, F):
     _check(got, want, mine, "fp32")
 
 
+# grid caps: 1 and 3 workgroups walk many tiles (the load stream crosses tile ends, a tile end every 3 slices at K = 192);
+# 16 leaves a few tiles over, which run as pieces; F = 320 fills two and a half feature tiles
+@pytest.mark.parametrize("cap", [-1, 1, 3, 16])
+@pytest.mark.parametrize("d,F", [(256, 320), (192, 448), (448, 192)])
+def test_256x128_tiles(cap, d, F):
+    rows = (0, 1, 127, 128, 129, 300, 64, 65)
+    got, want, mine = _ffn(rows, d, F, "bf16", D=2, rank=1, knobs=((0, 33), (1, 33), (4, cap)), seed=d)
+    _check(got, want, mine, "bf16")
+
+
 # the library's own choice over its range of rows per expert, many experts and few, whole slices of K and not
 @pytest.mark.parametrize("rows_per_expert", [1, 19, 20, 39, 40, 191, 192, 383, 384])
 @pytest.mark.parametrize("E,D,d,F", [(32, 1, 256, 192), (4, 2, 200, 136), (2, 1, 384, 256)])
