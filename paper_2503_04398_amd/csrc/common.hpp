@@ -144,23 +144,30 @@ __device__ __forceinline__ void load_mapped_ids(const int32_t* __restrict__ row,
 }
 
 // Column sums of a [n_rows][n_cols] table of counts: tot[c] += all rows, pre[c] += the rows before `b` (both in LDS,
-// zeroed by the caller, who also places the barriers).  A thread owns one column and every (threads / n_cols)-th
-// row, eight loads in flight: no division per element and two LDS atomics per thread (element by element, with a
-// division and up to two atomics each, a 32 x 128 table took twice as long).  The first eight loads can be requested
-// ahead of time (`column_sums_first`), before other work that has its own chain of dependent loads.
+// zeroed by the caller, who also places the barriers).  Every workgroup of the index kernels reads the whole table, so
+// the time is the number of loads a thread waits for one after the other.  With n_cols a multiple of four a thread owns
+// four columns (one 16-byte load) of every (threads / (n_cols / 4))-th row, eight loads in flight: a 64 x 256 table is
+// two such batches a thread (as single columns it was eight: 16.4 us for dp_fused_kernel on 16384 tokens of 256 experts;
+// a 64 x 288 table, with more columns than the 256 threads and so an atomic per element, 19.4 us for rs_fused_kernel).
+// The first eight loads can be requested ahead of time (`column_sums_first`), before other work that has its own chain
+// of dependent loads.
+typedef __attribute__((ext_vector_type(4))) int32_t i32x4_t;
 struct ColumnBatch {
-  int v[8];
+  i32x4_t v[8];
 };
+
+__device__ __forceinline__ bool column_quads(int n_cols) { return n_cols % 4 == 0 && n_cols / 4 <= int(blockDim.x); }
 
 __device__ __forceinline__ ColumnBatch column_sums_first(const int32_t* __restrict__ table, int n_rows, int n_cols) {
   ColumnBatch f;
-  const int t = threadIdx.x, nt = blockDim.x;
-  const int rpp = n_cols <= nt ? nt / n_cols : 1;
-  const int c = t % n_cols, r0 = t / n_cols;
+  const int t = threadIdx.x, nt = blockDim.x, nq = n_cols / 4;
+  const bool quads = column_quads(n_cols);
+  const int rpp = quads ? nt / nq : 0;  // rows covered per pass
+  const int c = quads ? t % nq : 0, r0 = quads ? t / nq : 0;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
     const int bb = r0 + u * rpp;
-    f.v[u] = (n_cols <= nt && r0 < rpp && bb < n_rows) ? table[size_t(bb) * n_cols + c] : 0;
+    f.v[u] = (r0 < rpp && bb < n_rows) ? reinterpret_cast<const i32x4_t*>(table)[size_t(bb) * nq + c] : i32x4_t{0, 0, 0, 0};
   }
   return f;
 }
@@ -168,18 +175,43 @@ __device__ __forceinline__ ColumnBatch column_sums_first(const int32_t* __restri
 __device__ __forceinline__ void column_sums_before(const int32_t* __restrict__ table, int n_rows, int n_cols, int b,
                                                    int32_t* tot, int32_t* pre, const ColumnBatch* first = nullptr) {
   const int t = threadIdx.x, nt = blockDim.x;
-  if (n_cols <= nt) {
-    const int rpp = nt / n_cols;  // rows covered per pass
-    const int c = t % n_cols, r0 = t / n_cols;
+  if (column_quads(n_cols)) {
+    const int nq = n_cols / 4, rpp = nt / nq;
+    const int c = t % nq, r0 = t / nq;
     if (r0 >= rpp) return;
+    i32x4_t s = {0, 0, 0, 0}, sb = {0, 0, 0, 0};
+    for (int bb0 = r0; bb0 < n_rows; bb0 += 8 * rpp) {
+      i32x4_t v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int bb = bb0 + u * rpp;
+        if (first && bb0 == r0) v[u] = first->v[u];
+        else v[u] = bb < n_rows ? reinterpret_cast<const i32x4_t*>(table)[size_t(bb) * nq + c] : i32x4_t{0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        s += v[u];
+        sb += (bb0 + u * rpp < b) ? v[u] : i32x4_t{0, 0, 0, 0};
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {  // integer sums: the order does not matter
+      if (s[x]) atomicAdd(&tot[4 * c + x], s[x]);
+      if (sb[x]) atomicAdd(&pre[4 * c + x], sb[x]);
+    }
+    return;
+  }
+  for (int c0 = 0; c0 < n_cols; c0 += nt) {  // a column a thread; few columns: several threads share one
+    const int nc = min(nt, n_cols - c0), rpp = nt / nc;
+    const int c = t % nc, r0 = t / nc;
+    if (r0 >= rpp) continue;
     int s = 0, sb = 0;
     for (int bb0 = r0; bb0 < n_rows; bb0 += 8 * rpp) {
       int v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int bb = bb0 + u * rpp;
-        if (first && bb0 == r0) v[u] = first->v[u];
-        else v[u] = bb < n_rows ? table[size_t(bb) * n_cols + c] : 0;
+        v[u] = bb < n_rows ? table[size_t(bb) * n_cols + c0 + c] : 0;
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -187,25 +219,8 @@ __device__ __forceinline__ void column_sums_before(const int32_t* __restrict__ t
         sb += (bb0 + u * rpp < b) ? v[u] : 0;
       }
     }
-    if (s) atomicAdd(&tot[c], s);  // integer sums: the order does not matter
-    if (sb) atomicAdd(&pre[c], sb);
-    return;
-  }
-  for (int base = t; base < n_rows * n_cols; base += 8 * nt) {  // more columns than threads
-    int v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int idx = base + u * nt;
-      v[u] = idx < n_rows * n_cols ? table[idx] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (v[u] == 0) continue;
-      const int idx = base + u * nt;
-      const int bb = idx / n_cols, c = idx - bb * n_cols;
-      atomicAdd(&tot[c], v[u]);
-      if (bb < b) atomicAdd(&pre[c], v[u]);
-    }
+    if (s) atomicAdd(&tot[c0 + c], s);
+    if (sb) atomicAdd(&pre[c0 + c], sb);
   }
 }
 

@@ -188,13 +188,22 @@ __global__ __launch_bounds__(kTokBlock) void dp_fused_kernel(int T, int k, int E
   __syncthreads();
   column_sums_before(w.cnt, NB, E, b, off, pre, &first);
   // send matrix: entry x is summed over the workgroups' partial matrices by workgroup x % NB, one wave per entry
+  // (four entries at a time: their loads are in flight together)
   const int DD = D * D;
-  for (int x = b + (t >> 6) * NB; x < DD; x += (kTokBlock >> 6) * NB) {
-    uint32_t part = 0;
-    for (int bb = t & 63; bb < NB; bb += 64) part += w.send_part[size_t(bb) * DD + x];
+  const int x_step = (kTokBlock >> 6) * NB;
+  for (int x0 = b + (t >> 6) * NB; x0 < DD; x0 += 4 * x_step) {
+    uint32_t part[4] = {0, 0, 0, 0};
+    for (int bb = t & 63; bb < NB; bb += 64)
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-    if ((t & 63) == 0) send_matrix[x] = part;
+      for (int u = 0; u < 4; ++u)
+        if (x0 + u * x_step < DD) part[u] += w.send_part[size_t(bb) * DD + x0 + u * x_step];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) part[u] += __shfl_xor(part[u], o);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if ((t & 63) == 0 && x0 + u * x_step < DD) send_matrix[x0 + u * x_step] = part[u];
   }
   if (b == 0) {  // remote pairs: sum of the workgroups' counts
     unsigned long long part = 0;

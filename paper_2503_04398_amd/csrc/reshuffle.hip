@@ -363,11 +363,15 @@ __global__ __launch_bounds__(kTokBlock) void rs_fused_kernel(int T, int NB, int 
   uint32_t* bm = reinterpret_cast<uint32_t*>(scal + 2);  // [D][kWords]
   uint32_t* spbm = bm + D * kWords;                       // [kWords]
   const int t = threadIdx.x, b = blockIdx.x;
+  // the table and the token's own word are requested before anything that waits
+  const ColumnBatch first = column_sums_first(w.cnt, NB, nkeys);
+  const int i = b * kTokBlock + t;
+  const int my_pc = w.pc[min(i, T - 1)];
 
   for (int x = t; x < 2 * nkeys; x += kTokBlock) tot[x] = 0;
   for (int x = t; x < D * kWords + kWords; x += kTokBlock) bm[x] = 0;
   __syncthreads();
-  column_sums_before(w.cnt, NB, nkeys, b, tot, pre);
+  column_sums_before(w.cnt, NB, nkeys, b, tot, pre, &first);
   __syncthreads();
   if (t < D) {
     const int r = t;
@@ -436,12 +440,10 @@ __global__ __launch_bounds__(kTokBlock) void rs_fused_kernel(int T, int NB, int 
   __syncthreads();
 
   // keep phase: borderline candidates are ranked inside the block by their bitmap
-  const int i = b * kTokBlock + t;
   int pref = 0, conf = 0, th = -1;
   if (i < T) {
-    const int pc = w.pc[i];
-    pref = pc & 0xff;
-    conf = pc >> 8;
+    pref = my_pc & 0xff;
+    conf = my_pc >> 8;
     th = thr[pref];
     if (th >= 0 && conf == th) atomicOr(&bm[pref * kWords + (t >> 5)], 1u << (t & 31));
   }
