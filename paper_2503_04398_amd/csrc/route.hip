@@ -301,8 +301,6 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
   // is clamped, so the loads carry no branch and go out together; what is absent is masked afterwards.  A token is
   // present when it has somewhere to write (idp[ch]).
   int val[NCH][NS];    // key of the selection score
-  float aux[NCH][NS];  // sigmoid: s (softmax reads the logit back from the key)
-  uint32_t live[NCH];
   float x[NCH][NS], sb[NS];
 #pragma unroll
   for (int c = 0; c < NS; ++c) {
@@ -313,46 +311,43 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
   }
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
-    live[ch] = 0;
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
       const bool there = c * 16 + l16 < E && idp[ch] != nullptr;
       if (sigmoid) {
         const float sg = sigmoid_exact_seq(x[ch][c]);
-        aux[ch][c] = there ? sg : 0.0f;
         val[ch][c] = there ? to_key(__fadd_rn(sg, sb[c])) : NEGK;
       } else {
-        aux[ch][c] = 0.0f;
         val[ch][c] = there ? to_key(x[ch][c]) : NEGK;
       }
-      live[ch] |= there ? (1u << c) : 0u;
     }
   }
 
-  // arg-max of a row over the entries that pass `use(ch, c)`: every lane gets the largest key and the lowest
-  // expert id that holds it (kNoExpert when there is no entry).  A lane first finds its own best entry (the
-  // lowest slot among equals: strict compare), then the row agrees on the value and on the lowest id.
-  float own_aux[NCH];  // sigmoid: s of the lane's best entry of the last arg-max
-  auto row_argmax = [&](auto use, int(&vmax)[NCH], int(&arg)[NCH]) __attribute__((always_inline)) {
-    int slot[NCH], own[NCH];
+  // Arg-max of a row over the entries still in (an entry that is out has the key of -inf): every lane gets the largest
+  // key and the lowest expert id that holds it (kNoExpert when there is no entry), and own_slot = the lane's own slot
+  // with its largest key, the lowest among equals.  The maximum over a lane's slots is a tree of three-way maxima and
+  // the slot is found by comparing back: 4 + 16 instructions for 8 slots where a running (key, slot) pair took 24, and
+  // the bookkeeping of an in/out bit per slot goes.
+  int own_slot[NCH];
+  auto row_argmax = [&](int(&vmax)[NCH], int(&arg)[NCH]) __attribute__((always_inline)) {
+    int own[NCH];
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
-      own[ch] = NEGK;
-      slot[ch] = 0;
-      own_aux[ch] = 0.0f;
+      int m = val[ch][0];
 #pragma unroll
-      for (int c = 0; c < NS; ++c) {
-        const bool better = use(ch, c) && val[ch][c] > own[ch];
-        own[ch] = better ? val[ch][c] : own[ch];
-        slot[ch] = better ? c : slot[ch];
-        if constexpr (SIG) own_aux[ch] = better ? aux[ch][c] : own_aux[ch];
-      }
-      vmax[ch] = own[ch];
+      for (int c = 1; c + 1 < NS; c += 2) m = max(max(m, val[ch][c]), val[ch][c + 1]);
+      if constexpr (NS % 2 == 0) m = max(m, val[ch][NS - 1]);
+      own[ch] = vmax[ch] = m;
     }
     SEMMOE_ROW_REDUCE("v_max_i32_dpp", vmax);
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch)
-      arg[ch] = (own[ch] == vmax[ch] && own[ch] != NEGK) ? slot[ch] * 16 + l16 : kNoExpert;
+    for (int ch = 0; ch < NCH; ++ch) {
+      int slot = 0;
+#pragma unroll
+      for (int c = NS - 1; c >= 0; --c) slot = val[ch][c] == own[ch] ? c : slot;
+      own_slot[ch] = slot;
+      arg[ch] = (own[ch] == vmax[ch] && own[ch] != NEGK) ? slot * 16 + l16 : kNoExpert;
+    }
     SEMMOE_ROW_REDUCE("v_min_i32_dpp", arg);
   };
 
@@ -380,7 +375,7 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
         if (whole_slots && (c < g * spg || c >= (g + 1) * spg)) continue;
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch)
-          if (((live[ch] >> c) & 1u) && (whole_slots || grp[c] == g)) {
+          if (whole_slots || grp[c] == g) {  // an absent entry has the lowest key: it changes neither
             const int v = val[ch][c];
             a2[ch] = max(a2[ch], min(a1[ch], v));
             a1[ch] = max(a1[ch], v);
@@ -432,11 +427,8 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
     }
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
-      uint32_t allowed = 0;
 #pragma unroll
-      for (int c = 0; c < NS; ++c)
-        if (c * 16 + l16 < E && ((keep[ch] >> (grp[c] & 31)) & 1u)) allowed |= 1u << c;
-      live[ch] &= allowed;
+      for (int c = 0; c < NS; ++c) val[ch][c] = ((keep[ch] >> (grp[c] & 31)) & 1u) ? val[ch][c] : NEGK;
     }
   }
 
@@ -451,24 +443,29 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
   }
   for (int j = 0; j < k; ++j) {
     int vm[NCH], e[NCH];
-    row_argmax([&](int ch, int c) { return ((live[ch] >> c) & 1u) != 0; }, vm, e);
-    int abits[NCH];
+    row_argmax(vm, e);
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
-      const bool own = e[ch] != kNoExpert && (e[ch] & 15) == l16;
-      const int slot = (e[ch] >> 4) & 31;
-      abits[ch] = (SIG && own) ? __float_as_int(own_aux[ch]) : 0;  // the winner is its lane's best entry
-      if (own) live[ch] &= ~(1u << slot);
-    }
-    if (sigmoid) SEMMOE_ROW_REDUCE("v_or_b32_dpp", abits);  // the owner's s reaches every lane of the row
+      // the winner leaves: it is the best entry of the lane it sits in
+      const int out = e[ch] == own_slot[ch] * 16 + l16 ? own_slot[ch] : NS;
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      const float a = sigmoid ? __int_as_float(abits[ch]) : from_key(vm[ch]);
+      for (int c = 0; c < NS; ++c) val[ch][c] = out == c ? NEGK : val[ch][c];
+      const float a = from_key(vm[ch]);
       if (l16 == j) {
         my_id[ch] = e[ch];
         my_val[ch] = a;
       }
       if (j == 0) mx[ch] = a;  // first winner = row maximum
+    }
+  }
+  if constexpr (SIG) {
+    // the weight is s without the selection bias.  Lane j forms it once more from its winner's logit: carrying s along
+    // per slot costs a move per slot and round and a reduction per round, this one load and one sigmoid.
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      const bool won = l16 < k && my_id[ch] != kNoExpert;
+      const float s = sigmoid_exact_seq(rowp[ch][won ? my_id[ch] : 0]);
+      my_val[ch] = won ? s : 0.0f;
     }
   }
 
@@ -843,7 +840,8 @@ __global__ __launch_bounds__(256) void select_topk_rows_kernel(semmoe_config cfg
 constexpr int kSumSelectMaxE = 256;
 constexpr int kSumSelectChains = 1;                       // four tokens a wave: twice the waves to hide the latencies
 constexpr int kSumSelectTokens = 4 * kSumSelectChains;
-template <int FORM, bool SIG>
+// PB parts of U chunks of four experts are requested before the first is used.
+template <int FORM, bool SIG, int PB, int U>
 __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg, int n_parts,
                                                                const float* __restrict__ partial,
                                                                const float* __restrict__ b_g,
@@ -862,34 +860,52 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
   const int n_tok = min(kSumSelectTokens, cfg.T - base);
   const size_t n = size_t(cfg.T) * E;
   const bool out16 = logits_out && (reinterpret_cast<size_t>(logits_out) & 15) == 0;
-  for (int idx = lane; idx < n_tok * e4; idx += 64) {
-    const int tl = idx / e4, e = (idx - tl * e4) * 4;
-    const size_t at = size_t(base + tl) * E + e;
-    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int p0 = 0; p0 < n_parts; p0 += 8) {  // eight loads in flight
-      f32x4_t x[8];
+  const int n_idx = n_tok * e4;
+  for (int idx0 = lane; idx0 < n_idx; idx0 += 64 * U) {
+    int tl[U], e[U], cls[U];
+    size_t at[U];
+    f32x4_t v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        x[u] = p0 + u < n_parts ? __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(partial + size_t(p0 + u) * n + at))
-                                : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v += x[u];
+    for (int c = 0; c < U; ++c) {  // chunks behind the end stand on the last one and are not written
+      const int idx = min(idx0 + c * 64, n_idx - 1);
+      tl[c] = idx / e4;
+      e[c] = (idx - tl[c] * e4) * 4;
+      at[c] = size_t(base + tl[c]) * E + e[c];
+      cls[c] = token_class ? token_class[base + tl[c]] : -1;
+      v[c] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    if (b_g) {
+    for (int p0 = 0; p0 < n_parts; p0 += PB) {
+      f32x4_t x[U][PB];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] += b_g[e + u];
+      for (int u = 0; u < PB; ++u)
+#pragma unroll
+        for (int c = 0; c < U; ++c)
+          x[c][u] = p0 + u < n_parts
+                        ? __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(partial + size_t(p0 + u) * n + at[c]))
+                        : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < U; ++c)
+#pragma unroll
+        for (int u = 0; u < PB; ++u) v[c] += x[c][u];
     }
-    const int cls = token_class ? token_class[base + tl] : -1;
-    if (cls >= 0 && cls < cfg.num_classes && class_bias) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] += class_bias[size_t(cls) * E + e + u];
-    }
-    *reinterpret_cast<f32x4_t*>(lg + tl * ld + e) = v;
-    if (out16) {
-      *reinterpret_cast<f32x4_t*>(logits_out + at) = v;
-    } else if (logits_out) {
+    for (int c = 0; c < U; ++c) {
+      if (idx0 + c * 64 >= n_idx) break;
+      if (b_g) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) logits_out[at + u] = v[u];
+        for (int u = 0; u < 4; ++u) v[c][u] += b_g[e[c] + u];
+      }
+      if (cls[c] >= 0 && cls[c] < cfg.num_classes && class_bias) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[c][u] += class_bias[size_t(cls[c]) * E + e[c] + u];
+      }
+      *reinterpret_cast<f32x4_t*>(lg + tl[c] * ld + e[c]) = v[c];
+      if (out16) {
+        *reinterpret_cast<f32x4_t*>(logits_out + at[c]) = v[c];
+      } else if (logits_out) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) logits_out[at[c] + u] = v[c][u];
+      }
     }
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -905,22 +921,29 @@ static bool launch_sum_select(const semmoe_config* cfg, hipStream_t s, int n_par
                               const float* sel_bias, float* logits_out, int32_t* topk_ids, float* topk_w) {
   const int form = select_form(*cfg);
   if (form == kSelAny || cfg->E > kSumSelectMaxE || cfg->E % 4 != 0) return false;
-  const int waves = 4;
+  // few tokens: a wave a workgroup, so that they spread over as many compute units as there are, and all loads of a wave
+  // in flight at once (256 tokens, 128 experts, 16 parts: 18.8 -> 15.2 us for the route); many: the waves hide each
+  // other's latencies and registers are what is short (16384 tokens, 256 experts, 4 parts: 111 us so, 114 us with 16
+  // loads in flight)
+  const int waves = cfg->T <= 2048 ? 1 : 4;
   const dim3 grid(cdiv(cfg->T, waves * kSumSelectTokens)), block(64 * waves);
   const bool sig = cfg->score == SEMMOE_SIGMOID;
+#define SEMMOE_SUM_SELECT_AS(FORM_, SIG_, PB_, U_)                                                                  \
+  hipLaunchKernelGGL((route_sum_select_kernel<FORM_, SIG_, PB_, U_>), grid, block, 0, s, *cfg, n_parts, partial,    \
+                     b_g, token_class, class_bias, sel_bias, logits_out, topk_ids, topk_w)
 #define SEMMOE_SUM_SELECT(FORM_)                                                                                    \
   do {                                                                                                              \
-    if (sig)                                                                                                        \
-      hipLaunchKernelGGL((route_sum_select_kernel<FORM_, true>), grid, block, 0, s, *cfg, n_parts, partial, b_g,    \
-                         token_class, class_bias, sel_bias, logits_out, topk_ids, topk_w);                          \
-    else                                                                                                            \
-      hipLaunchKernelGGL((route_sum_select_kernel<FORM_, false>), grid, block, 0, s, *cfg, n_parts, partial, b_g,   \
-                         token_class, class_bias, sel_bias, logits_out, topk_ids, topk_w);                          \
+    if (waves == 4) {                                                                                               \
+      if (sig) SEMMOE_SUM_SELECT_AS(FORM_, true, 8, 1); else SEMMOE_SUM_SELECT_AS(FORM_, false, 8, 1);              \
+    } else {                                                                                                        \
+      if (sig) SEMMOE_SUM_SELECT_AS(FORM_, true, 16, 2); else SEMMOE_SUM_SELECT_AS(FORM_, false, 16, 2);            \
+    }                                                                                                               \
   } while (0)
   if (form == kSel16) SEMMOE_SUM_SELECT(kSel16);
   else if (form == kSel8) SEMMOE_SUM_SELECT(kSel8);
   else SEMMOE_SUM_SELECT(kSelSmall);
 #undef SEMMOE_SUM_SELECT
+#undef SEMMOE_SUM_SELECT_AS
   return true;
 }
 
@@ -1155,8 +1178,13 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
 #undef SEMMOE_ROUTE_LAUNCH
     SEMMOE_LAUNCH_CHECK();
     if (n_parts > 1) {
-      // (route_sum_select_kernel in place of these two was measured on the decode shape: 22.5 against 21.0 us;
-      // with so few tokens its eight-token waves are too few to hide the latency of the partial sums)
+      // adding the parts and selecting in one kernel where the shape has a row form (256 tokens, 128 experts, 16 parts:
+      // 3.4 + 6.2 us as two kernels and the gap between them)
+      if (launch_sum_select(cfg, s, n_parts, partial, b_g, token_class, class_bias, sel_bias, logits_out, topk_ids,
+                            topk_w)) {
+        SEMMOE_LAUNCH_CHECK();
+        return SEMMOE_OK;
+      }
       const size_t n = size_t(cfg->T) * cfg->E;
       hipLaunchKernelGGL(route_reduce_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, *cfg, n_parts, partial,
                          b_g, token_class, class_bias, logits_ws, logits_out);
