@@ -85,7 +85,8 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     28: 128 x 128 pieces throughout (the default for more than 256 rows of one set of weights, as long as bigger
  *     tiles would leave compute units idle);
  *     30, 31, 32: weights streamed through registers, 32 weight rows x 32 tokens, 32 x 64 or 64 x 64 (the default for
- *     few rows per expert); 33: four waves on a 256 x 128 tile (the default for middling groups);
+ *     few rows of one set of weights); 34, 35: groups of up to 64 rows so (32 x 64 or 64 x 64), the others as 26 in the same
+ *     launch (the default for few rows per expert); 33: four waves on a 256 x 128 tile (the default for middling groups);
  *     20, 21, 22: four waves on a 256 x 256 tile with loads placed between the MFMAs; K must be a multiple of the
  *     K slice (32 for 20 and 21, 64 for 22) and hold at least a ring of slices (128); other K run as 16)
  *   SEMMOE_TUNE_BLOCKS_PER_CU: persistent workgroups per compute unit for those GEMMs

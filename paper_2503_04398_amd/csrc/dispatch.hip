@@ -449,7 +449,9 @@ static int32_t dispatch_rows_impl(const semmoe_config* cfg, hipStream_t s, const
   const u32x4_t* Xv = static_cast<const u32x4_t*>(X);
   u32x4_t* Xp = static_cast<u32x4_t*>(X_perm);
   const int P = T * k;
-  const int threads = row_walk_threads(row_chunks);
+  // long rows: four waves, however many chunks the last pass leaves idle (rows of 896 chunks, 16384 tokens x 8: 435 us
+  // with 448 threads, 424 with 256; up to 512 chunks no difference)
+  const int threads = row_chunks > 512 ? 256 : row_walk_threads(row_chunks);
   switch (k) {
     case 1: hipLaunchKernelGGL(dp_rows_kernel<1>, dim3(T), dim3(threads), 0, s, k, row_chunks, P, Xv, slot_of_pair, Xp); break;
     case 2: hipLaunchKernelGGL(dp_rows_kernel<2>, dim3(T), dim3(threads), 0, s, k, row_chunks, P, Xv, slot_of_pair, Xp); break;

@@ -174,16 +174,13 @@ static int32_t launch_all_pieces(GemmArgs a, int max_rows, hipStream_t stream) {
   a.sched_sub_f = 2;
   a.sched_fine = 1;  // 128 x 64 pieces when the 128 x 128 ones would leave half the compute units idle
   const int grid = grid_for(bound_p * 8, num_cu());
-  using CF = DmaCfg<MODE, 2, 2, 2, 1, 64, kFineRing>;  // the halved pieces
-  const size_t lds = CF::kLdsBytes > C::kLdsBytes ? CF::kLdsBytes : C::kLdsBytes;
-  if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   auto kern = gemm_bf16_piece_kernel<MODE, 3>;
   static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
   {
     const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
     if (as != SEMMOE_OK) return as;
   }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), lds, stream, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::kThreads), C::kLdsBytes, stream, a);
   SEMMOE_LAUNCH_CHECK();
   return SEMMOE_OK;
 }
@@ -199,9 +196,7 @@ static int32_t launch_w4_split(const GemmArgs& h, int max_rows, hipStream_t stre
   if ((unsigned long long)w_rows * h.ldw * 2 >= (1ull << 32) || (unsigned long long)CH::BT * h.ldx * 2 >= (1ull << 32))
     return SEMMOE_EUNSUPPORTED;  // per-lane row offsets are 32-bit
   const size_t head_lds = TJ == 4 ? CH::kLdsBytes : CH::lds_bytes(h.nq);
-  using CF = DmaCfg<MODE, 2, 2, 2, 1, 64, kFineRing>;
-  size_t lds = head_lds > CP::kLdsBytes ? head_lds : CP::kLdsBytes;
-  if (CF::kLdsBytes > lds) lds = CF::kLdsBytes;
+  const size_t lds = head_lds > CP::kLdsBytes ? head_lds : CP::kLdsBytes;
   if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   const int n_ftiles = cdiv(h.N, CH::FEAT);
   const long long bound = (long long)(max_rows / CH::BT + h.nq) * n_ftiles;
@@ -271,6 +266,39 @@ static int32_t launch_stream(const GemmArgs& a, int max_rows, int per_cu, hipStr
   return launch_stream_as<MODE, F32, TW, TT, NW, true, false>(a, max_rows, per_cu, stream);
 }
 
+// Groups of up to `few_rows` rows streamed, the others as 128 x 64 tiles, in one launch
+template <int MODE, int TW, int TT, bool KTAIL>
+static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_rows, hipStream_t stream) {
+  using CS = StreamCfg<MODE, TW, TT, 4>;
+  using CD = DmaCfg<MODE, 2, 2, 2, 1, 64, 3>;
+  const long long bound_s = (long long)(max_rows / CS::BT + a.nq) * cdiv(a.N, CS::FEAT);
+  const long long bound_d = (long long)(max_rows / CD::BT + a.nq) * cdiv(a.N, CD::FEAT);
+  const long long bound = bound_s > bound_d ? bound_s : bound_d;
+  if (bound <= 0) return SEMMOE_OK;
+  const size_t lds = CS::lds_bytes(a.nq) > CD::kLdsBytes ? CS::lds_bytes(a.nq) : CD::kLdsBytes;
+  if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
+  const int grid = grid_for(bound, (long long)num_cu() * 2);
+  auto kern = gemm_stream_ring_kernel<MODE, TW, TT, KTAIL>;
+  static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
+  const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
+  if (as != SEMMOE_OK) return as;
+  GemmArgs few = a, many = a;
+  few.rows_max = few_rows;
+  many.rows_min = few_rows;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, stream, few, many);
+  SEMMOE_LAUNCH_CHECK();
+  return SEMMOE_OK;
+}
+
+template <int MODE, int TW, int TT>
+static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows, hipStream_t stream) {
+  const unsigned long long row_bytes = a.K * 2ull, w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N;
+  if (w_rows * a.ldw * 2 >= (1ull << 31) || StreamCfg<MODE, TW, TT, 4>::BT * 2ull * a.ldx >= (1ull << 31))
+    return SEMMOE_EUNSUPPORTED;  // 32-bit offsets do not reach every row
+  if (row_bytes % 128 == 0 && row_bytes >= 512) return launch_stream_ring_as<MODE, TW, TT, false>(a, max_rows, few_rows, stream);
+  return launch_stream_ring_as<MODE, TW, TT, true>(a, max_rows, few_rows, stream);
+}
+
 // fp32: 16 x 4 weight rows and 16 x 4 tokens a workgroup, halved along either while that leaves compute units idle
 template <int MODE>
 static int32_t launch_f32(const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
@@ -332,6 +360,13 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
       if (st != SEMMOE_EUNSUPPORTED) return st;
       return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);  // panels beyond 32-bit offsets
     }
+    // streamed up to so many rows per group that the ring of case 26 reads the weights less often
+    case 34: case 35: {
+      const int32_t st = id == 34 ? launch_stream_ring<MODE, 2, 4>(a, max_rows, 64, s)
+                                  : launch_stream_ring<MODE, 4, 4>(a, max_rows, 64, s);
+      if (st != SEMMOE_EUNSUPPORTED) return st;
+      return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);
+    }
     case 33: {  // four waves, 256 x 128
       const int32_t st = launch_w4_128<MODE>(a, max_rows, s);
       if (st != SEMMOE_EUNSUPPORTED) return st;
@@ -370,28 +405,31 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //   160                                                362 192 220      369 189 239      A 467 B 238 C 275
 //   300                                                509 271 301      522 299 323
 //   400                                                620 328 390      624 346 380
-// The streaming kernel loses as the token rows it drags past every weight tile grow, the 256 x 128 tile as two of them
-// read the weights that one 256 x 256 tile reads once.  tiles128: the 256 x 128 tiles the problem is expected to have.
+// The streaming kernel loses as the token rows it drags past every weight tile grow, so groups beyond 64 rows take the
+// 128 x 64 tiles of the same launch; the 256 x 128 tile loses as two of them read the weights that one 256 x 256 tile
+// reads once.  The mean is that of all experts: it is the launch's own only where the launch has all of them, a rank that
+// an affinity placement loads may have several times as many rows.  So the lines lie lower for one rank's experts
+// (16 experts, d 4096, F 1536, 93 rows each where 23 are expected: 190 us, streamed 205; d 2048, F 768, 1040 rows where
+// 260 are expected: 203 us as 256 x 256 tiles, 208 as 256 x 128).  Rows that are no whole 128 bytes: neighbouring slices
+// share cache lines, and from about ten rows on the ring reads them at the better rate (10 rows of d 2832: 191 / 208).
 // One set of weights (the shared expert) with so few rows that these would leave most compute units idle is bound by the
 // latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
 // 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).  2000 rows of
 // it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.
-static int default_tile(const GemmArgs& a, int est_rows_per_group, int n_ftiles256) {
+static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group, int n_ftiles256) {
   const int est = est_rows_per_group;
-  const long long tiles128 = (long long)a.nq * cdiv(est < 1 ? 1 : est, 128) * n_ftiles256;
-  const bool narrow = a.offsets ? tiles128 * 4 < num_cu() : tiles128 * 4 < 3LL * num_cu();
-  if (narrow) {
-    if (est <= 160) return 30;
-    if (est <= 256) return 31;
-    return 28;
+  const long long cus = num_cu();
+  if (!a.offsets) {
+    if ((long long)cdiv(est, 128) * n_ftiles256 * 4 < 3 * cus) return est <= 160 ? 30 : (est <= 256 ? 31 : 28);
+    if (a.K % 64 != 0 || a.K / 64 < 3) return est < 192 ? 26 : 22;
+    return est < 384 || (long long)cdiv(est, 256) * n_ftiles256 * 4 < 3 * cus ? 33 : 22;
   }
-  if (est < 20) return 30;
-  if (est < 40) return 32;
   const bool whole_slices = a.K % 64 == 0 && a.K / 64 >= 3;  // what the tiles with a running load stream need
-  if (!whole_slices) return est < 192 ? 26 : 22;
-  if (est < 384) return 33;
-  const long long tiles256 = (long long)a.nq * cdiv(est, 256) * n_ftiles256;
-  return tiles256 * 4 < 3LL * num_cu() ? 33 : 22;  // half the tokens a tile while those would leave compute units idle
+  const bool all_rows = (long long)a.nq * (est + 1) >= max_rows;
+  if (est < 10) return 34;
+  if (whole_slices && est < (all_rows ? 40 : 20)) return 35;
+  if (est < (all_rows && whole_slices ? 384 : 192)) return whole_slices && est >= 40 ? 33 : 26;
+  return (long long)(max_rows / 256 + a.nq) * n_ftiles256 * 2 >= cus ? 22 : 28;
 }
 
 // Head/tail split: for the tile shapes of 256 x 256 with a persistent grid of one workgroup per compute unit.
@@ -427,7 +465,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       case kModeSwiglu: {
         const int id = tuning_value(SEMMOE_TUNE_GATEUP_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_GATEUP_TILE)
-                           : default_tile(a, est_rows_per_group, cdiv(a.N, 128));
+                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 128));
         if (!split_launch(id)) return launch_bf16_tile<kModeSwiglu>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;
@@ -443,7 +481,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       default: {
         const int id = tuning_value(SEMMOE_TUNE_DOWN_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_DOWN_TILE)
-                           : default_tile(a, est_rows_per_group, cdiv(a.N, 256));
+                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 256));
         if (!split_launch(id)) return launch_bf16_tile<kModeStore>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;

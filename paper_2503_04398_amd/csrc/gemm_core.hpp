@@ -45,6 +45,9 @@ struct GemmArgs {
   // group q the same ksplit_rows rows of X against columns [q*K, (q+1)*K) of X and of W (K = depth of a part, ldx and
   // ldw the full depth, w_group_stride = K); group q writes output rows q*ksplit_rows ..., that is partial[q][row][n].
   int ksplit_rows;
+  // Groups of more than rows_min rows, and of at most rows_max where that is set, make up the tile list (a launch whose
+  // workgroups run two kernels one after the other, one for the small groups and one for the large).
+  int rows_min, rows_max;
 };
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -52,6 +55,12 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
+
+__device__ __forceinline__ int listed_rows(const GemmArgs& a, int q) {
+  if (a.ksplit_rows) return a.ksplit_rows;
+  const int rows = a.offsets ? a.offsets[a.q_lo + q + 1] - a.offsets[a.q_lo + q] : a.n_rows_single;
+  return rows <= a.rows_min || (a.rows_max > 0 && rows > a.rows_max) ? 0 : rows;
+}
 
 // Tile list: group q (local index) owns tiles [tile_prefix[q], tile_prefix[q+1]); inside a group the
 // feature tile runs fastest.  Returns total tile count.  `pre` is LDS of nq+1 ints.
@@ -63,8 +72,7 @@ __device__ __forceinline__ int build_tile_prefix(const GemmArgs& a, int n_ftiles
     const int lo = min(tid * per, a.nq), hi = min(lo + per, a.nq);
     int s = 0;
     for (int q = lo; q < hi; ++q) {
-      int rows = a.ksplit_rows ? a.ksplit_rows
-                               : (a.offsets ? (a.offsets[a.q_lo + q + 1] - a.offsets[a.q_lo + q]) : a.n_rows_single);
+      const int rows = listed_rows(a, q);
       s += ((rows + BT - 1) / BT) * n_ftiles;
     }
     int incl = s;
@@ -76,8 +84,7 @@ __device__ __forceinline__ int build_tile_prefix(const GemmArgs& a, int n_ftiles
     int run = incl - s;
     if (tid == 0) pre[0] = 0;
     for (int q = lo; q < hi; ++q) {
-      int rows = a.ksplit_rows ? a.ksplit_rows
-                               : (a.offsets ? (a.offsets[a.q_lo + q + 1] - a.offsets[a.q_lo + q]) : a.n_rows_single);
+      const int rows = listed_rows(a, q);
       run += ((rows + BT - 1) / BT) * n_ftiles;
       pre[q + 1] = run;
     }
@@ -109,24 +116,31 @@ __device__ __forceinline__ int find_group(const int* pre, int nq, int t) {
 // is dealt out evenly over the XCDs: left to the first ones alone, 384 weight tiles on 512 workgroups ran on six XCDs
 // and at six eighths of the memory rate.
 struct ItemWalk {
-  int count, first, step, last;  // last: the item of the partly filled round
+  int count, first, step, last;  // last: the item of the partly filled round (-1: none)
   __device__ __forceinline__ int item(int r) const { return r + 1 == count && last >= 0 ? last : first + r * step; }
 };
-__device__ __forceinline__ ItemWalk xcd_share(int total) {
-  const int g = gridDim.x, b = blockIdx.x;
-  const int full = total / g, rem = total - full * g;
+// spread = false: the partly filled round goes to the first XCDs after all.  Better where the items are few, share their
+// panels and wait for L2 rather than memory (192 pieces of one set of weights, d 4096, F 1536: 46 us against 50).
+// skip: so many workgroups of every XCD have other work and take no part (a grid of whole eights).
+__device__ __forceinline__ ItemWalk xcd_share(int total, bool spread = true, int skip = 0) {
+  const int b = blockIdx.x;
   ItemWalk w;
-  w.step = g;
-  if (g % 8 != 0) {
+  if (gridDim.x % 8 != 0) {
+    const int g = gridDim.x, full = total / g;
+    w.step = g;
     w.first = b;
-    w.last = b < rem ? full * g + b : -1;
-  } else {
-    const int x = b & 7, l = b >> 3;
-    const int lo = rem * x / 8, hi = rem * (x + 1) / 8;
-    w.first = x * (g >> 3) + l;
-    w.last = lo + l < hi ? full * g + lo + l : -1;
+    w.last = b < total - full * g ? full * g + b : -1;
+    w.count = full + (w.last >= 0 ? 1 : 0);
+    return w;
   }
-  w.count = full + (w.last >= 0 ? 1 : 0);
+  const int per = int(gridDim.x >> 3) - skip, g = 8 * per;
+  const int full = total / g, rem = total - full * g;
+  const int x = b & 7, l = (b >> 3) - skip;
+  const int lo = spread ? rem * x / 8 : min(rem, x * per), hi = spread ? rem * (x + 1) / 8 : min(rem, (x + 1) * per);
+  w.step = g;
+  w.first = x * per + l;
+  w.last = lo + l < hi ? full * g + lo + l : -1;
+  w.count = l < 0 ? 0 : full + (w.last >= 0 ? 1 : 0);
   return w;
 }
 
@@ -496,10 +510,10 @@ struct DmaCfg {
   static_assert(MODE != kModeSwiglu || TF % 2 == 0, "gate/up tiles come in pairs");
 };
 
-template <int MODE, int NWF, int NWT, int TF, int TT, int BK, int NSTAGE, int MINW>
-__global__ __launch_bounds__(64 * NWF * NWT, MINW) void gemm_bf16_dma_kernel(GemmArgs a) {
+// returns the number of tiles in the list
+template <int MODE, int NWF, int NWT, int TF, int TT, int BK, int NSTAGE>
+__device__ __forceinline__ int gemm_bf16_dma_body(const GemmArgs& a, unsigned char* lds_raw) {
   using C = DmaCfg<MODE, NWF, NWT, TF, TT, BK, NSTAGE>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   int* pre = reinterpret_cast<int*>(lds_raw + C::kTileBytes);
   const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>(lds_raw));
 
@@ -629,6 +643,13 @@ __global__ __launch_bounds__(64 * NWF * NWT, MINW) void gemm_bf16_dma_kernel(Gem
     store_tile_via_lds<MODE, NWF, NWT, TF, TT>(acc, lds_raw, a, row_lo, n_tok, f0, wf, wt);
     __syncthreads();  // the next tile's loads overwrite the staged tile
   }
+  return walk.total;
+}
+
+template <int MODE, int NWF, int NWT, int TF, int TT, int BK, int NSTAGE, int MINW>
+__global__ __launch_bounds__(64 * NWF * NWT, MINW) void gemm_bf16_dma_kernel(GemmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  gemm_bf16_dma_body<MODE, NWF, NWT, TF, TT, BK, NSTAGE>(a, lds_raw);
 }
 
 // host-side launcher: picks the kernel for the dtype, sizes a persistent grid.

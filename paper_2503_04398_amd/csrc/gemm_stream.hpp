@@ -68,13 +68,12 @@ __device__ __forceinline__ f32x4_t stream_mfma(u32x4_t w, u32x4_t x, f32x4_t c) 
 // into the row and what lies behind its end counts as zero.  WIDE: rows so long, or so many, that 32-bit offsets from the
 // panels' first rows do not reach them all (64-bit addresses per lane; with KTAIL only).
 template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE = false>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs a) {
+__device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned char* lds_raw, int skip = 0) {
   static_assert(KTAIL || !WIDE, "the wide form clamps every address");
   using C = StreamCfg<MODE, TW, TT, NW>;
   using off_t = std::conditional_t<WIDE, uint64_t, uint32_t>;
   constexpr int TP = C::TP;
   constexpr int ES = F32 ? 4 : 2;          // bytes of an element
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   f32x4_t* red = reinterpret_cast<f32x4_t*>(lds_raw);  // [wave][weight tile][token tile][lane]
   int* pre = reinterpret_cast<int*>(lds_raw + C::kTileBytes);
   int* gtab = pre + a.nq + 1;
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs 
   }
   const int n_ftiles = (a.N + C::FEAT - 1) / C::FEAT;
   const int total = __builtin_amdgcn_readfirstlane(build_tile_prefix(a, n_ftiles, pre, C::BT));  // ends with a barrier
-  const ItemWalk my = xcd_share(total);  // neighbours share a weight tile: token tile fastest
+  const ItemWalk my = xcd_share(total, true, skip);  // neighbours share a weight tile: token tile fastest
   int round = 0;
   if (my.count == 0) return;  // the whole workgroup leaves, before any further barrier
 
@@ -169,7 +168,8 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs 
       };
       // weights that no other tile reads pass by the caches (a plain read stream: 6.9 TB/s with nt, 6.4 without); those of
       // a group with several token tiles are read again by the neighbouring workgroup
-      if (l_once) weights(std::true_type{}); else weights(std::false_type{});
+      // (nor where slices straddle cache lines: a line's other half is another wave's)
+      if (l_once && !KTAIL) weights(std::true_type{}); else weights(std::false_type{});
 #pragma unroll
       for (int j = 0; j < 2 * TT; ++j)
         if ((j >> 1) < l_ntt) xb[j] = stream_load<false>(xr, min(uint32_t(j * 8) * x_ld + x_lane, x_last) + lane_at, at);
@@ -308,6 +308,27 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs 
       clear();
     }
   }
+}
+
+template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE = false>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  gemm_stream_body<MODE, F32, TW, TT, NW, KTAIL, WIDE>(a, lds_raw);
+}
+
+// The rows of each group live on the device, and the mean the host expects can be far off: the ranks of an affinity
+// placement, one hot expert.  So the groups of more than many.rows_min rows run as 128 x 64 tiles with the LDS ring, which
+// reads a weight tile once for every 64 tokens at a better pace (8 experts of 316 rows each where the host expects 19:
+// 809 us streamed, 435 so), and the others as above.  Few large tiles get workgroups of their own, at most half of the
+// grid; else every workgroup takes its share of both.  The two write disjoint rows; only the workgroup's own LDS is
+// waited for in between.
+template <int MODE, int TW, int TT, bool KTAIL>
+__global__ __launch_bounds__(256, 2) void gemm_stream_ring_kernel(const GemmArgs few, const GemmArgs many) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  const int large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3>(many, lds_raw));
+  __syncthreads();
+  const int skip = gridDim.x % 8 == 0 && large * 2 <= int(gridDim.x) ? (large + 7) / 8 : 0;
+  gemm_stream_body<MODE, false, TW, TT, 4, KTAIL>(few, lds_raw, skip);
 }
 
 }  // namespace semmoe

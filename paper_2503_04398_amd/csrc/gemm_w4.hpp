@@ -483,7 +483,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
 // when so few parent tiles are left over that the bigger pieces would leave most compute units idle; sub_t is then
 // the number of pieces along the tokens of a parent tile (4) in place of the launch's value.
 template <int MODE, int NSTAGE, int TT>
-__device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned char* lds_raw, int sub_t = 0) {
+__device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned char* lds_raw, int sub_t = 0, bool spread = true) {
   using C = DmaCfg<MODE, 2, 2, 2, TT, 64, NSTAGE>;
   static_assert(C::KS == 4 && C::RB == 128 && C::BW == 128 && (TT == 1 || TT == 2), "geometry the loop below is written for");
   constexpr int kIpwW = 8;       // load instructions per slice of a wave that loads weight rows (waves 0, 1: 64 rows each)
@@ -510,7 +510,7 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
   // first LDS byte of this wave's rows inside a stage (an instruction fills 8 rows = 1 KB)
   const unsigned my_rows_lds = loads_w ? wave * kIpwW * 1024 : (C::BW / 8 + (wave - 2) * kIpwX) * 1024;
 
-  const ItemWalk my = xcd_share(walk.total);
+  const ItemWalk my = xcd_share(walk.total, spread);
   for (int r = 0; r < my.count; ++r) {
     const int item = my.item(r);
     TileAt at;
@@ -671,9 +671,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_kernel(GemmArgs a) {
 
 // Pieces as a launch of their own.  With sched_fine set the kernel halves the pieces along the tokens (128 x 64)
 // when twice the number of 128 x 128 pieces still fits the grid, as the split kernel below does for its tail.
-// Ring of the 128 x 64 pieces: 6 x 24 KB.  Where they are all there is (512 rows of one set of weights, d 7168) the walk
-// over K is a chain of loads that land late: 86 us with a ring of 3, 82 with 6.
-constexpr int kFineRing = 6;
 template <int MODE, int NSTAGE>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_piece_kernel(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -681,12 +678,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_piece_kernel(GemmArgs a) {
     const TileWalk probe = make_walk(a, reinterpret_cast<int*>(lds_raw), 128, (MODE == kModeSwiglu) ? 64 : 128);
     __syncthreads();
     if (probe.total > 0 && probe.total * 2 <= int(gridDim.x)) {
-      if (a.K / 64 >= kFineRing) gemm_bf16_piece_body<MODE, kFineRing, 1>(a, lds_raw, 4);
-      else gemm_bf16_piece_body<MODE, NSTAGE, 1>(a, lds_raw, 4);
+      gemm_bf16_piece_body<MODE, NSTAGE, 1>(a, lds_raw, 4, false);
       return;
     }
   }
-  gemm_bf16_piece_body<MODE, NSTAGE, 2>(a, lds_raw);
+  gemm_bf16_piece_body<MODE, NSTAGE, 2>(a, lds_raw, 0, false);
 }
 
 // Head and tail of a split in one launch: every workgroup first works through its 256 x 256 tiles of the full rounds,
@@ -703,8 +699,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_w4_split_kernel(GemmArgs hea
   const TileWalk probe = make_walk(tail, reinterpret_cast<int*>(lds_raw), 128, (MODE == kModeSwiglu) ? 64 : 128);
   __syncthreads();
   if (tail.sched_fine && probe.total > 0 && probe.total * 2 <= int(gridDim.x)) {
-    if (tail.K / 64 >= kFineRing) gemm_bf16_piece_body<MODE, kFineRing, 1>(tail, lds_raw, TJ);  // 64 tokens a piece
-    else gemm_bf16_piece_body<MODE, PIECE_RING, 1>(tail, lds_raw, TJ);
+    gemm_bf16_piece_body<MODE, PIECE_RING, 1>(tail, lds_raw, TJ);  // 64 tokens a piece
   } else {
     gemm_bf16_piece_body<MODE, PIECE_RING, 2>(tail, lds_raw);
   }

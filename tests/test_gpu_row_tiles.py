@@ -56,7 +56,7 @@ RAGGED = (0, 1, 15, 16, 17, 33, 64, 65, 0, 130, 31, 48)
 # d / F: whole slices for every wave (256 / 512: K = 512, 256 and more); K with a partial slice (264 / 296: 8 elements in
 # the last one); K so short that some waves have no slice (72, 8); F below a feature tile (8, 24)
 @pytest.mark.parametrize("d,F", [(256, 512), (264, 296), (72, 24), (512, 8), (8, 72)])
-@pytest.mark.parametrize("tile,cap", [(30, -1), (31, -1), (32, -1), (30, 8), (32, 3)])
+@pytest.mark.parametrize("tile,cap", [(30, -1), (31, -1), (32, -1), (30, 8), (32, 3), (34, -1), (34, 3), (35, -1), (35, 8)])
 def test_streamed_tiles_bf16(tile, cap, d, F):
     got, want, mine = _ffn(RAGGED, d, F, "bf16", knobs=((0, tile), (1, tile), (4, cap)), seed=tile + d)
     _check(got, want, mine, "bf16")
@@ -80,7 +80,7 @@ def test_256x128_tiles(cap, d, F):
 
 
 # the library's own choice over its range of rows per expert, many experts and few, whole slices of K and not
-@pytest.mark.parametrize("rows_per_expert", [1, 19, 20, 39, 40, 191, 192, 383, 384])
+@pytest.mark.parametrize("rows_per_expert", [1, 9, 10, 19, 20, 39, 40, 191, 192, 383, 384])
 @pytest.mark.parametrize("E,D,d,F", [(32, 1, 256, 192), (4, 2, 200, 136), (2, 1, 384, 256)])
 def test_own_choice(rows_per_expert, E, D, d, F):
     r = np.random.default_rng(rows_per_expert)
