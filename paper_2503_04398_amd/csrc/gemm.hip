@@ -411,7 +411,8 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 // an affinity placement loads may have several times as many rows.  So the lines lie lower for one rank's experts
 // (16 experts, d 4096, F 1536, 93 rows each where 23 are expected: 190 us, streamed 205; d 2048, F 768, 1040 rows where
 // 260 are expected: 203 us as 256 x 256 tiles, 208 as 256 x 128).  Rows that are no whole 128 bytes: neighbouring slices
-// share cache lines, and from about ten rows on the ring reads them at the better rate (10 rows of d 2832: 191 / 208).
+// share cache lines, and from about ten rows on the staged tiles read them at the better rate (10 rows of d 2832: 191
+// against 208).
 // One set of weights (the shared expert) with so few rows that these would leave most compute units idle is bound by the
 // latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
 // 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).  2000 rows of
@@ -421,14 +422,18 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
   const long long cus = num_cu();
   if (!a.offsets) {
     if ((long long)cdiv(est, 128) * n_ftiles256 * 4 < 3 * cus) return est <= 160 ? 30 : (est <= 256 ? 31 : 28);
-    if (a.K % 64 != 0 || a.K / 64 < 3) return est < 192 ? 26 : 22;
+    if (a.K % 64 != 0 || a.K / 64 < 3) return est < 96 ? 26 : (est < 192 ? 0 : 22);
     return est < 384 || (long long)cdiv(est, 256) * n_ftiles256 * 4 < 3 * cus ? 33 : 22;
   }
   const bool whole_slices = a.K % 64 == 0 && a.K / 64 >= 3;  // what the tiles with a running load stream need
   const bool all_rows = (long long)a.nq * (est + 1) >= max_rows;
   if (est < 10) return 34;
   if (whole_slices && est < (all_rows ? 40 : 20)) return 35;
-  if (est < (all_rows && whole_slices ? 384 : 192)) return whole_slices && est >= 40 ? 33 : 26;
+  if (!whole_slices) {
+    if (est < 192) return est < 96 ? 26 : 0;
+  } else if (est < (all_rows ? 384 : 192)) {
+    return est < 40 ? 26 : 33;
+  }
   return (long long)(max_rows / 256 + a.nq) * n_ftiles256 * 2 >= cus ? 22 : 28;
 }
 

@@ -325,8 +325,20 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs 
 template <int MODE, int TW, int TT, bool KTAIL>
 __global__ __launch_bounds__(256, 2) void gemm_stream_ring_kernel(const GemmArgs few, const GemmArgs many) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  const int large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3>(many, lds_raw));
+  // a launch without large groups does not build their list
+  int* any = reinterpret_cast<int*>(lds_raw);
+  if (threadIdx.x == 0) *any = 0;
   __syncthreads();
+  for (int q = threadIdx.x; q < many.nq; q += 256)
+    if (listed_rows(many, q)) *any = 1;  // any number of threads write the same value
+  __syncthreads();
+  const bool some = __builtin_amdgcn_readfirstlane(*any) != 0;
+  __syncthreads();
+  int large = 0;
+  if (some) {
+    large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3>(many, lds_raw));
+    __syncthreads();
+  }
   const int skip = gridDim.x % 8 == 0 && large * 2 <= int(gridDim.x) ? (large + 7) / 8 : 0;
   gemm_stream_body<MODE, false, TW, TT, 4, KTAIL>(few, lds_raw, skip);
 }
