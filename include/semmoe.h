@@ -100,7 +100,7 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     128 x 64 pieces with the loads of a slice issued in a burst and an LDS ring of 3 (two workgroups per compute
  *     unit) or 6 (one)
  *   SEMMOE_TUNE_ROUTE_SPLIT: bf16 router with at most 512 tokens: parts the K dimension is split into over workgroups
- *     (partial sums added in order by a second kernel, then the selection kernel); 0 = always the fused kernel,
+ *     (partial sums added in order and selected from by a second kernel); 0 = always the fused kernel,
  *     default: as many parts as fill the chip, at most 16.  With more than 128 experts, where tiles of 256 tokens
  *     times up to 8 parts of K (at least 8 slices each) fill three quarters of the compute units, the logits come from
  *     the 256 x 256 tile of the grouped GEMM, followed by one kernel that adds the parts and selects; 100 + n forces
