@@ -8,6 +8,7 @@
 // fp32 path, and bf16 with few rows per group: gemm_stream.hpp.
 #pragma once
 #include "common.hpp"
+#include "item_walk.hpp"
 
 namespace semmoe {
 
@@ -108,40 +109,8 @@ __device__ __forceinline__ int find_group(const int* pre, int nq, int t) {
   return lo;
 }
 
-// A workgroup's share of a list of `total` items: item(0), item(1), ... item(count - 1).  Workgroups are handed to the 8
-// XCDs round-robin by workgroup id, and each XCD has its own L2 and its own path to memory.  In every full round of the
-// grid an XCD's workgroups take a contiguous run of the list (neighbouring items share weight or token panels, which
-// its L2 then holds) and all XCDs together one run as well, whose panels meet in the memory-side cache: with an eighth
-// of the whole list per XCD instead, 8 experts of d = F = 2880 took 511 us against 484.  The last, partly filled round
-// is dealt out evenly over the XCDs: left to the first ones alone, 384 weight tiles on 512 workgroups ran on six XCDs
-// and at six eighths of the memory rate.
-struct ItemWalk {
-  int count, first, step, last;  // last: the item of the partly filled round (-1: none)
-  __device__ __forceinline__ int item(int r) const { return r + 1 == count && last >= 0 ? last : first + r * step; }
-};
-// spread = false: the partly filled round goes to the first XCDs after all.  Better where the items are few, share their
-// panels and wait for L2 rather than memory (192 pieces of one set of weights, d 4096, F 1536: 46 us against 50).
-// skip: so many workgroups of every XCD have other work and take no part (a grid of whole eights).
 __device__ __forceinline__ ItemWalk xcd_share(int total, bool spread = true, int skip = 0) {
-  const int b = blockIdx.x;
-  ItemWalk w;
-  if (gridDim.x % 8 != 0) {
-    const int g = gridDim.x, full = total / g;
-    w.step = g;
-    w.first = b;
-    w.last = b < total - full * g ? full * g + b : -1;
-    w.count = full + (w.last >= 0 ? 1 : 0);
-    return w;
-  }
-  const int per = int(gridDim.x >> 3) - skip, g = 8 * per;
-  const int full = total / g, rem = total - full * g;
-  const int x = b & 7, l = (b >> 3) - skip;
-  const int lo = spread ? rem * x / 8 : min(rem, x * per), hi = spread ? rem * (x + 1) / 8 : min(rem, (x + 1) * per);
-  w.step = g;
-  w.first = x * per + l;
-  w.last = lo + l < hi ? full * g + lo + l : -1;
-  w.count = l < 0 ? 0 : full + (w.last >= 0 ? 1 : 0);
-  return w;
+  return share_of(total, int(gridDim.x), int(blockIdx.x), spread, skip);
 }
 
 // Inside a group the tile list walks blocks of kFeatBlock feature tiles x all token tiles of the group

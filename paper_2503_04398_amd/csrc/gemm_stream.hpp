@@ -339,8 +339,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_ring_kernel(const GemmArgs
     large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3>(many, lds_raw));
     __syncthreads();
   }
-  const int skip = gridDim.x % 8 == 0 && large * 2 <= int(gridDim.x) ? (large + 7) / 8 : 0;
-  gemm_stream_body<MODE, false, TW, TT, 4, KTAIL>(few, lds_raw, skip);
+  gemm_stream_body<MODE, false, TW, TT, 4, KTAIL>(few, lds_raw, side_workgroups(large, int(gridDim.x)));
 }
 
 }  // namespace semmoe

@@ -24,6 +24,7 @@ def _ffn(rows, d, F, dtype, D=1, rank=-1, knobs=(), seed=0):
     of_phys = r.permutation(E).astype(np.int32)
     m = S.SemMoE(S.Config(T=P, d=d, E=E, k=1, F=F, D=D, dtype=dtype, cap=P))
     Y = torch.full((P, d), 512.0, dtype=act, device=H.DEV)
+    m.ws.fill_(0xff)  # NaN: a hidden activation that nobody writes does not pass for one left by another call
     try:
         for key, value in knobs:
             m.set_tuning(key, value)
@@ -59,6 +60,23 @@ RAGGED = (0, 1, 15, 16, 17, 33, 64, 65, 0, 130, 31, 48)
 @pytest.mark.parametrize("tile,cap", [(30, -1), (31, -1), (32, -1), (30, 8), (32, 3), (34, -1), (34, 3), (35, -1), (35, 8)])
 def test_streamed_tiles_bf16(tile, cap, d, F):
     got, want, mine = _ffn(RAGGED, d, F, "bf16", knobs=((0, tile), (1, tile), (4, cap)), seed=tile + d)
+    _check(got, want, mine, "bf16")
+
+
+# one hot group and small ones on grids of 8 and 16 workgroups, of which the hot group's tiles take some: by the width of
+# the shape itself (one or both products have so few tiles), and by a cap on a wider one with 2, 3, 4 and 5 large tiles
+@pytest.mark.parametrize("rows,d,F", [((70, 10, 10, 10), 64, 256), ((66, 4), 128, 256), ((66, 12), 128, 192),
+                                      ((70, 10, 10, 6), 256, 32), ((65, 9, 0, 7), 8, 8)])
+def test_hot_group_on_a_small_grid(rows, d, F):
+    got, want, mine = _ffn(rows, d, F, "bf16", seed=d + F)
+    _check(got, want, mine, "bf16")
+
+
+@pytest.mark.parametrize("rows", [(65, 3, 17), (130, 9, 64, 1), (65, 20, 65, 33), (200, 9, 5), (65, 8, 130, 40)])
+@pytest.mark.parametrize("tile", [34, 35])
+@pytest.mark.parametrize("cap", [8, 16])
+def test_hot_group_under_a_cap(cap, tile, rows):
+    got, want, mine = _ffn(rows, 64, 64, "bf16", knobs=((0, tile), (1, tile), (4, cap)), seed=len(rows))
     _check(got, want, mine, "bf16")
 
 
