@@ -67,7 +67,7 @@ __device__ __forceinline__ f32x4_t stream_mfma(u32x4_t w, u32x4_t x, f32x4_t c) 
 // KTAIL: K is not a multiple of a slice (128 bytes of a row) or gives some wave no slice at all: addresses are clamped
 // into the row and what lies behind its end counts as zero.  WIDE: rows so long, or so many, that 32-bit offsets from the
 // panels' first rows do not reach them all (64-bit addresses per lane; with KTAIL only).
-template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE = false>
+template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE = false, bool SIZED = false>
 __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned char* lds_raw, int skip = 0) {
   static_assert(KTAIL || !WIDE, "the wide form clamps every address");
   using C = StreamCfg<MODE, TW, TT, NW>;
@@ -89,7 +89,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     gtab[3 * q + 2] = a.group_to_weight ? a.group_to_weight[a.q_lo + q] : a.q_lo + q;
   }
   const int n_ftiles = (a.N + C::FEAT - 1) / C::FEAT;
-  const int total = __builtin_amdgcn_readfirstlane(build_tile_prefix(a, n_ftiles, pre, C::BT));  // ends with a barrier
+  const int total = __builtin_amdgcn_readfirstlane(build_tile_prefix<SIZED>(a, n_ftiles, pre, C::BT));  // ends with a barrier
   const ItemWalk my = xcd_share(total, true, skip);  // neighbours share a weight tile: token tile fastest
   int round = 0;
   if (my.count == 0) return;  // the whole workgroup leaves, before any further barrier
@@ -330,16 +330,16 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_ring_kernel(const GemmArgs
   if (threadIdx.x == 0) *any = 0;
   __syncthreads();
   for (int q = threadIdx.x; q < many.nq; q += 256)
-    if (listed_rows(many, q)) *any = 1;  // any number of threads write the same value
+    if (listed_rows<true>(many, q)) *any = 1;  // any number of threads write the same value
   __syncthreads();
   const bool some = __builtin_amdgcn_readfirstlane(*any) != 0;
   __syncthreads();
   int large = 0;
   if (some) {
-    large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3>(many, lds_raw));
+    large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3, true>(many, lds_raw));
     __syncthreads();
   }
-  gemm_stream_body<MODE, false, TW, TT, 4, KTAIL>(few, lds_raw, side_workgroups(large, int(gridDim.x)));
+  gemm_stream_body<MODE, false, TW, TT, 4, KTAIL, false, true>(few, lds_raw, side_workgroups(large, int(gridDim.x)));
 }
 
 }  // namespace semmoe
