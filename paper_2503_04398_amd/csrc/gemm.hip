@@ -273,7 +273,8 @@ static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_ro
   using CD = DmaCfg<MODE, 2, 2, 2, 1, 64, 3>;
   const long long bound_s = (long long)(max_rows / CS::BT + a.nq) * cdiv(a.N, CS::FEAT);
   const long long bound_d = (long long)(max_rows / CD::BT + a.nq) * cdiv(a.N, CD::FEAT);
-  const long long bound = bound_s > bound_d ? bound_s : bound_d;
+  // room for workgroups that keep to the large tiles (at most half of the grid) beside those that keep to the others
+  const long long bound = bound_s + (max_rows > few_rows ? 2 * bound_d : 0);
   if (bound <= 0) return SEMMOE_OK;
   const size_t lds = CS::lds_bytes(a.nq) > CD::kLdsBytes ? CS::lds_bytes(a.nq) : CD::kLdsBytes;
   if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
