@@ -394,48 +394,78 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 }
 
 // Default tile shape from the mean rows per group that the caller expects (the true, ragged row counts live on the
-// device).  Measured over rows per group, us of a whole FFN (gate/up + down, lognormal spread 0.3 of the group sizes):
+// device), the depth K and the number of tiles.  Whole FFNs (gate/up + down) on cold weights, us; group sizes spread
+// lognormally by 0.3:
 //   A: 128 experts, d 2048, F 768;  B: 16 experts, d 4096, F 1536;  C: 8 experts, d 7168, F 2048
-//   rows   streamed 32 rows x 32   streamed 64 x 64    256 x 128        256 x 256        128 x 64, ring of 3
-//   8      A 192 B 102 C 115       197 111 118                          278 167 191      A 228 B 131 C 138
-//   16     A 215 B 107 C 124       213 110 129                          288 164 197      A 241 B 128 C 138
-//   32     A 302 B 157 C 180       240 116 137         256 134 150      299 166 200      A 261 B 132 C 143
-//   48                             283 143 169         254 147 142      301 173 203      A 259 B 147 C 185
-//   64                             329 166 187         280 149 159      314 173 211      A 287 B 169 C 193
-//   110                                                301 159 200      334 183 225      A 372 B 203 C 255
-//   160                                                362 192 220      369 189 239      A 467 B 238 C 275
-//   300                                                509 271 301      522 299 323
-//   400                                                620 328 390      624 346 380
-// The streaming kernel loses as the token rows it drags past every weight tile grow, so groups beyond 64 rows take the
-// 128 x 64 tiles of the same launch; the 256 x 128 tile loses as two of them read the weights that one 256 x 256 tile
-// reads once.  The mean is that of all experts: it is the launch's own only where the launch has all of them, a rank that
-// an affinity placement loads may have several times as many rows.  So the lines lie lower for one rank's experts
-// (16 experts, d 4096, F 1536, 93 rows each where 23 are expected: 190 us, streamed 205; d 2048, F 768, 1040 rows where
-// 260 are expected: 203 us as 256 x 256 tiles, 208 as 256 x 128).  Rows that are no whole 128 bytes: neighbouring slices
-// share cache lines, and from about ten rows on the staged tiles read them at the better rate (10 rows of d 2832: 191
-// against 208).
+//          streamed alone             streamed up to 64 rows        128 x 64 (26)    256 x 128 (33)   256 x 256 (22)
+//   rows   32 x 32 (30) 64 x 64 (32)  32 x 64 (34) 64 x 64 (35)
+//   8      199 103 120  210 111 121   210 105 122  212 112 122      241 126 133
+//   16     218 107 123  218 112 131   228 111 125  220 114 132      243 128 134      258 133 163
+//   32     295 135 165  242 116 137   272 124 142  244 118 138      248 132 136      265 135 170
+//   48                  285 146 170                286 143 162      263 139 179      275 139 177      309 168 232
+//   64                  326 165 183                318 173 181      288 162 187      285 142 186      318 172 238
+//   110                                                             370 190 234      308 158 202      341 179 251
+//   160                                                             453 227 257      367 192 217      376 198 256
+//   300                                                                              517 264 300      534 299 322
+//   400                                                                              630 311 355      656 339 344
+// (as 128 x 128 tiles (0): 379 204 298 at 110 rows; as pieces (28): 946 414 435 at 400).  30 and 32 have no answer to a
+// hot expert, so what runs is 34 or 35: groups beyond 64 rows take the 128 x 64 tiles in the same launch, which costs
+// 1 to 5 % where there is none.  34 against 35: 105 122 to 112 122 us at 8 rows; at 16 rows 34 is still ahead on B and C
+// (111 125 to 114 132) and 35 on A (220 to 228), at 32 rows 35 throughout.
+// The mean is that of all experts: it is the launch's own only where the launch has all of them, a rank that an affinity
+// placement loads may have several times as many rows.  So the lines lie lower for one rank's experts (16 experts,
+// d 4096, F 1536, 93 rows each where 23 are expected: 190 us, streamed 205; d 2048, F 768, 1040 rows where 260 are
+// expected: 203 us as 256 x 256 tiles, 208 as 256 x 128).
+// K and the number of tiles, over 6000 random shapes (d, F 64 to 7168, 2 to 512 experts; a product's gain or loss as a
+// share of its FFN, against the 128 x 64 tiles):
+//   * a streamed tile ends with a sum over four waves, which a short K does not repay, least of all with many tiles:
+//     up to 9 rows, 32 x 64: K below 192 +88 % beyond 2048 tiles, +24 % at 256 to 512, +3 % up to 64; K 384 to 639 +14,
+//     +3, -14 %; K 1400 to 2100 -4, -5, -27 %.  Few tiles wait for one walk over K, which the four waves share: the line
+//     lies at K 192 up to a tile per four compute units (-6 % above it), 384 up to one per two, 960 beyond.  64 x 64 has
+//     half the sums: from K 640 on where there are more than two tiles a compute unit (K 640 to 959: -4 % where 32 x 64
+//     has +5).  10 to 19 rows, 64 x 64: -2 to -8 % from K 960, with few tiles from 640; where the 128 x 64 tiles just
+//     have a compute unit each it is behind up to K 3200 (+1 to +8 %).  20 to 39 rows: from K 1408 on.
+//   * 256 x 128 tiles need work for every compute unit: 40 to 95 rows, fewer than 96 of them +10 to +20 %, half of the
+//     compute units +1 % at K 1000 and -3 % from K 1400, all of them +6 % below K 384 and 0 to -7 % from 640, two rounds -7 %.
+//     384 experts and more leave no room in its LDS for their table (512 experts, d 1024, F 512, 300 rows: 776 us as
+//     256 x 256 tiles, 1134 as 128 x 64).
+// Rows that are no whole 128 bytes: neighbouring slices share cache lines, and from about ten rows on the staged tiles
+// read them at the better rate (10 rows of d 2832: 191 against 208).
 // One set of weights (the shared expert) with so few rows that these would leave most compute units idle is bound by the
 // latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
 // 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).  2000 rows of
-// it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.
-static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group, int n_ftiles256) {
-  const int est = est_rows_per_group;
+// it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.  256 x 256 tiles are ahead of 256 x 128
+// from three fifths of the compute units on (170 to 190 of them: 2 to 4 %; 130 to 150: 2 % behind); 2514 rows of d 6968,
+// F 1312, gate/up without whole slices: 248 us for the FFN with pieces, 331 with 256 x 256 tiles on less than half of the chip.
+static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group, int w_rows) {
+  const int est = est_rows_per_group, t256 = cdiv(w_rows, 256);
   const long long cus = num_cu();
-  if (!a.offsets) {
-    if ((long long)cdiv(est, 128) * n_ftiles256 * 4 < 3 * cus) return est <= 160 ? 30 : (est <= 256 ? 31 : 28);
-    if (a.K % 64 != 0 || a.K / 64 < 3) return est < 96 ? 26 : (est < 192 ? 0 : 22);
-    return est < 384 || (long long)cdiv(est, 256) * n_ftiles256 * 4 < 3 * cus ? 33 : 22;
-  }
   const bool whole_slices = a.K % 64 == 0 && a.K / 64 >= 3;  // what the tiles with a running load stream need
-  const bool all_rows = (long long)a.nq * (est + 1) >= max_rows;
-  if (est < 10) return 34;
-  if (whole_slices && est < (all_rows ? 40 : 20)) return 35;
-  if (!whole_slices) {
-    if (est < 192) return est < 96 ? 26 : 0;
-  } else if (est < (all_rows ? 384 : 192)) {
-    return est < 40 ? 26 : 33;
+  const int big_tile = (long long)(max_rows / 256 + a.nq) * t256 * 2 >= cus ? 22 : 28;
+  if (!a.offsets) {
+    if ((long long)cdiv(est, 128) * t256 * 4 < 3 * cus) return est <= 160 ? 30 : (est <= 256 ? 31 : 28);
+    if (!whole_slices) return est < 96 ? 26 : (est < 192 ? 0 : big_tile);
+    return est < 384 || (long long)cdiv(est, 256) * t256 * 5 < 3 * cus ? 33 : 22;
   }
-  return (long long)(max_rows / 256 + a.nq) * n_ftiles256 * 2 >= cus ? 22 : 28;
+  const bool all_rows = (long long)a.nq * (est + 1) >= max_rows;
+  const long long ring = (long long)a.nq * cdiv(w_rows, 128);  // 128 x 64 tiles, one per group along the tokens
+  if (est < 10) {
+    if (ring * 2 <= cus) return a.K >= (ring * 4 <= cus ? 192 : 384) ? 34 : 26;
+    if (ring > 2 * cus && a.K < 1536) return a.K >= 640 ? 35 : 26;
+    return a.K >= 960 ? 34 : 26;
+  }
+  if (est < 40) {
+    if (!whole_slices || (est >= 20 && (!all_rows || ring > 4 * cus))) return 26;
+    const int k_min = ring * 2 <= cus ? 640 : (ring <= cus ? 3200 : 960);
+    return a.K >= k_min && (est < 20 || a.K >= 1408) ? 35 : 26;
+  }
+  if (whole_slices && est < 384 && W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds())) {
+    const long long mid = (long long)a.nq * w_rows * cdiv(est, 128) / 256;  // 256 x 128 tiles, as full ones
+    if (est < 192) return mid * 2 >= 3 * cus || (mid >= cus && a.K >= 640) || (mid * 2 >= cus && a.K >= 1408) ? 33 : 26;
+    if (all_rows && a.K >= 640 && mid * 2 >= cus) return 33;
+  }
+  if (est < 192) return est < 96 ? 26 : 0;
+  return big_tile;
 }
 
 // Head/tail split: for the tile shapes of 256 x 256 with a persistent grid of one workgroup per compute unit.
@@ -471,7 +501,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       case kModeSwiglu: {
         const int id = tuning_value(SEMMOE_TUNE_GATEUP_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_GATEUP_TILE)
-                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 128));
+                           : default_tile(a, max_rows, est_rows_per_group, 2 * a.N);
         if (!split_launch(id)) return launch_bf16_tile<kModeSwiglu>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;
@@ -487,7 +517,7 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       default: {
         const int id = tuning_value(SEMMOE_TUNE_DOWN_TILE) >= 0
                            ? tuning_value(SEMMOE_TUNE_DOWN_TILE)
-                           : default_tile(a, max_rows, est_rows_per_group, cdiv(a.N, 256));
+                           : default_tile(a, max_rows, est_rows_per_group, a.N);
         if (!split_launch(id)) return launch_bf16_tile<kModeStore>(id, a, max_rows, bpc, stream);
         GemmArgs h = a;
         h.sched_mode = 1;

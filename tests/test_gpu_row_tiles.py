@@ -109,6 +109,20 @@ def test_own_choice(rows_per_expert, E, D, d, F):
     _check(got, want, mine, "bf16")
 
 
+# ... on both sides of its lines in K and in the number of tiles: streamed (1 and 12 rows per expert), 256 x 128 tiles, and
+# more experts than those have room for.  One expert has most of its neighbour's rows as well
+@pytest.mark.parametrize("rows_per_expert,E,d,F", [
+    (1, 8, 184, 192), (1, 8, 192, 384), (1, 64, 384, 376), (1, 96, 64, 960), (1, 128, 640, 632), (1, 128, 1536, 64),
+    (12, 4, 640, 576), (12, 64, 320, 960), (12, 128, 960, 128), (25, 16, 1408, 64), (25, 16, 64, 1408),
+    (45, 64, 640, 512), (45, 40, 1408, 256), (130, 16, 192, 1408), (200, 32, 640, 512), (100, 384, 192, 64), (192, 384, 64, 192)])
+def test_own_choice_by_depth_and_tiles(rows_per_expert, E, d, F):
+    rows = np.full(E, rows_per_expert + 1)
+    rows[0] += int(rows[1]) - 1
+    rows[1] = 1
+    got, want, mine = _ffn(tuple(rows), d, F, "bf16", seed=d)
+    _check(got, want, mine, "bf16")
+
+
 @pytest.mark.parametrize("n", [1, 64, 160, 161, 256, 257, 400])
 def test_one_set_of_weights(n):
     """the shared expert on n rows, on both sides of the lines between its tiles"""
