@@ -88,7 +88,10 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     few rows of one set of weights); 34, 35: groups of up to 64 rows so (32 x 64 or 64 x 64), the others as 26 in the same
  *     launch (the default for few rows per expert); 33: four waves on a 256 x 128 tile (the default for middling groups);
  *     20, 21, 22: four waves on a 256 x 256 tile with loads placed between the MFMAs; K must be a multiple of the
- *     K slice (32 for 20 and 21, 64 for 22) and hold at least a ring of slices (128); other K run as 16)
+ *     K slice (32 for 20 and 21, 64 for 22) and hold at least a ring of slices (128); other K run as 16).
+ *     In fp32 (the router's GEMM follows SEMMOE_TUNE_GATEUP_TILE) 30, 31, 32 are the same shapes, 36 is 32 weight rows x 16
+ *     tokens and 37 that with 64-bit addresses (the default for weight panels of 2 GiB); other ids leave the choice to
+ *     the library
  *   SEMMOE_TUNE_BLOCKS_PER_CU: persistent workgroups per compute unit for those GEMMs
  *   SEMMOE_TUNE_HEAD_TAIL: with the 256 x 256 tile shapes (16, 20, 21, 22) a GEMM runs as two launches: the tiles that
  *     fill whole rounds of the persistent grid, then the rest as quarter tiles over the whole chip, when at most

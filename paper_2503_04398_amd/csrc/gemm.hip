@@ -300,9 +300,19 @@ static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows,
   return launch_stream_ring_as<MODE, TW, TT, true>(a, max_rows, few_rows, stream);
 }
 
-// fp32: 16 x 4 weight rows and 16 x 4 tokens a workgroup, halved along either while that leaves compute units idle
+// fp32: 16 x 4 weight rows and 16 x 4 tokens a workgroup, halved along either while that leaves compute units idle.
+// id: a shape by its tuning id; others are for bf16 and leave the choice here.
 template <int MODE>
-static int32_t launch_f32(const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
+static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
+  const bool rows_reachable = (unsigned long long)a.K * 4 < (1ull << 32) - 1024;  // a row below 4 GB
+  switch (id) {
+    case 30: return launch_stream<MODE, true, 2, 2, 4>(a, max_rows, 2, stream);
+    case 31: return launch_stream<MODE, true, 2, 4, 4>(a, max_rows, 2, stream);
+    case 32: return launch_stream<MODE, true, 4, 4, 4>(a, max_rows, 2, stream);
+    case 36: return launch_stream<MODE, true, 2, 1, 4>(a, max_rows, 2, stream);
+    case 37: return rows_reachable ? launch_stream_as<MODE, true, 2, 1, 4, true, true>(a, max_rows, 2, stream) : SEMMOE_EUNSUPPORTED;
+    default: break;
+  }
   const int est = est_rows_per_group < 1 ? 1 : est_rows_per_group;
   auto items = [&](int tw, int tt) {
     return (long long)a.nq * cdiv(est, 16 * tt) * cdiv(a.N, (MODE == kModeSwiglu) ? 8 * tw : 16 * tw);
@@ -315,7 +325,7 @@ static int32_t launch_f32(const GemmArgs& a, int max_rows, int est_rows_per_grou
   else if (tt >= 2 && items(2, 2) >= fill) st = launch_stream<MODE, true, 2, 2, 4>(a, max_rows, 2, stream);
   else st = launch_stream<MODE, true, 2, 1, 4>(a, max_rows, 2, stream);
   if (st != SEMMOE_EUNSUPPORTED) return st;
-  if ((unsigned long long)a.K * 4 >= (1ull << 32) - 1024) return SEMMOE_EUNSUPPORTED;  // a row of 4 GB
+  if (!rows_reachable) return SEMMOE_EUNSUPPORTED;
   return launch_stream_as<MODE, true, 2, 1, 4, true, true>(a, max_rows, 2, stream);
 }
 
@@ -532,10 +542,11 @@ int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int es
       }
     }
   }
+  const int gate_id = tuning_value(SEMMOE_TUNE_GATEUP_TILE), down_id = tuning_value(SEMMOE_TUNE_DOWN_TILE);
   switch (mode) {
-    case kModeLogits: return launch_f32<kModeLogits>(a, max_rows, est_rows_per_group, stream);
-    case kModeSwiglu: return launch_f32<kModeSwiglu>(a, max_rows, est_rows_per_group, stream);
-    default: return launch_f32<kModeStore>(a, max_rows, est_rows_per_group, stream);
+    case kModeLogits: return launch_f32<kModeLogits>(gate_id, a, max_rows, est_rows_per_group, stream);
+    case kModeSwiglu: return launch_f32<kModeSwiglu>(gate_id, a, max_rows, est_rows_per_group, stream);
+    default: return launch_f32<kModeStore>(down_id, a, max_rows, est_rows_per_group, stream);
   }
 }
 

@@ -87,6 +87,63 @@ def test_fp32(rows, cap, d, F):
     _check(got, want, mine, "fp32")
 
 
+# every fp32 form by its id; 37 holds 64-bit addresses, which the library takes for panels of 2 GiB
+@pytest.mark.parametrize("d,F", [(256, 512), (264, 296), (72, 24), (512, 8), (8, 72)])
+@pytest.mark.parametrize("tile,cap", [(30, -1), (31, 5), (32, -1), (36, -1), (37, -1), (37, 5)])
+def test_fp32_forms(tile, cap, d, F):
+    got, want, mine = _ffn(RAGGED, d, F, "fp32", knobs=((0, tile), (1, tile), (4, cap)), seed=tile + d)
+    _check(got, want, mine, "fp32")
+
+
+@pytest.mark.parametrize("T,d,E", [(70, 72, 24), (130, 512, 50), (17, 8, 7), (33, 264, 256)])
+@pytest.mark.parametrize("tile", [-1, 30, 31, 32, 36, 37])
+def test_fp32_router_forms(tile, T, d, E):
+    r = np.random.default_rng(T)
+    X, W = torch.from_numpy(r.standard_normal((T, d), dtype=np.float32)), torch.from_numpy(0.1 * r.standard_normal((E, d), dtype=np.float32))
+    b_g, bias = (torch.from_numpy(r.standard_normal(n, dtype=np.float32)) for n in (E, (3, E)))
+    cls = torch.from_numpy(r.integers(-1, 3, T).astype(np.int32))
+    m = S.SemMoE(S.Config(T=T, d=d, E=E, k=2, F=8, D=1, dtype="fp32", cap=T, num_classes=3))
+    ids, w = torch.empty(T, 2, dtype=torch.int32, device=H.DEV), torch.empty(T, 2, device=H.DEV)
+    logits = torch.full((T, E), 512.0, device=H.DEV)
+    try:
+        m.set_tuning(0, tile)
+        m.route(X.to(H.DEV), W.to(H.DEV), ids, w, b_g=b_g.to(H.DEV), token_class=cls.to(H.DEV), class_bias=bias.to(H.DEV),
+                logits_out=logits)
+        torch.cuda.synchronize()
+    finally:
+        m.set_tuning(0, -1)
+    want = X.double() @ W.double().t() + b_g.double() + torch.cat([bias, torch.zeros(1, E)]).double()[cls.long()]  # -1: the zeros
+    H.assert_close(H.to_np(logits), want.numpy(), "fp32", "logits")
+
+
+# gate and up of one set of weights in 2 GiB and a little more: beyond 32-bit offsets.  fp32 takes 64-bit addresses, the
+# streamed bf16 tiles hand over to the 128 x 64 ones; the down projection (half as large) stays as it is
+@pytest.mark.parametrize("dtype,d,F", [("fp32", 16384, 16392), ("bf16", 16384, 32776)])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_weights_of_two_gib(dtype, d, F, grouped):
+    act, n = (torch.float32 if dtype == "fp32" else torch.bfloat16), 5
+    g = torch.Generator(device=H.DEV).manual_seed(d + F)
+    def randn(*shape, std):
+        return torch.empty(shape, dtype=act, device=H.DEV).normal_(0.0, std, generator=g)
+    X, gu, dn = randn(n, d, std=1.0), randn(2 * F, d, std=0.01), randn(d, F, std=0.01)
+    assert gu.numel() * gu.element_size() >= 2 ** 31
+    m = S.SemMoE(S.Config(T=n, d=d, E=1, k=1, F=F, D=1, dtype=dtype, cap=n))
+    Y = torch.empty(n, d, dtype=act, device=H.DEV)
+    if grouped:
+        m.expert_ffn(-1, X, torch.tensor([0, n], dtype=torch.int32, device=H.DEV),
+                     torch.zeros(1, dtype=torch.int32, device=H.DEV), gu, dn, Y)
+    else:
+        m.shared_ffn(X, n, gu, dn, Y)
+    got = H.to_np(Y)
+    hidden = torch.empty(n, F, dtype=torch.float64, device=H.DEV)
+    for lo in range(0, F, 4096):  # float64 a slice at a time
+        hi = min(lo + 4096, F)
+        gate, up = X.double() @ gu[lo:hi].double().t(), X.double() @ gu[F + lo:F + hi].double().t()
+        hidden[:, lo:hi] = gate * torch.sigmoid(gate) * up
+    want = torch.cat([hidden @ dn[lo:lo + 4096].double().t() for lo in range(0, d, 4096)], dim=1)
+    H.assert_close(got, want.cpu().numpy(), dtype, "Y")
+
+
 # grid caps: 1 and 3 workgroups walk many tiles (the load stream crosses tile ends, a tile end every 3 slices at K = 192);
 # 16 leaves a few tiles over, which run as pieces; F = 320 fills two and a half feature tiles
 @pytest.mark.parametrize("cap", [-1, 1, 3, 16])
