@@ -92,16 +92,17 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     In fp32 (the router's GEMM follows SEMMOE_TUNE_GATEUP_TILE) 30, 31, 32 are the same shapes, 36 is 32 weight rows x 16
  *     tokens and 37 that with 64-bit addresses (the default for weight panels of 2 GiB); other ids leave the choice to
  *     the library
- *   SEMMOE_TUNE_BLOCKS_PER_CU: persistent workgroups per compute unit for those GEMMs
- *   SEMMOE_TUNE_HEAD_TAIL: with the 256 x 256 tile shapes (16, 20, 21, 22) a GEMM runs as two launches: the tiles that
- *     fill whole rounds of the persistent grid, then the rest as quarter tiles over the whole chip, when at most
- *     value/16 of a round is left over (default 8); 0 = always one launch
- *   SEMMOE_TUNE_TAIL_RING: how the rest is run.  Default: 128 x 128 pieces with the loads placed between the MFMAs, in
- *     the same launch as the big tiles (a workgroup takes pieces once its tiles are done; 128 x 64 pieces instead when
- *     so few tiles are left over that they fit the grid once; K a multiple of 64 with at least three slices, else
- *     the next).  2: the same without the smaller pieces.  1: 128 x 128 pieces as a second launch.  3 or 6: a second launch of
- *     128 x 64 pieces with the loads of a slice issued in a burst and an LDS ring of 3 (two workgroups per compute
- *     unit) or 6 (one)
+ *   SEMMOE_TUNE_BLOCKS_PER_CU: persistent workgroups per compute unit for those GEMMs (20, 21, 22, 28 and 33 are built for
+ *     one and stay at it, and so does 16 where the next knob cuts it in two)
+ *   SEMMOE_TUNE_HEAD_TAIL: with the tile shapes 16, 20, 21, 22 (256 x 256) and 33 (256 x 128) a GEMM is cut in two: the tiles
+ *     that fill whole rounds of the persistent grid, then the rest in smaller pieces over the whole chip, when at most
+ *     value/16 of a round is left over (default 8); 0 = never
+ *   SEMMOE_TUNE_TAIL_RING: how the rest of 256 x 256 tiles is run (that of 33: by the default or by 2).  Default: 128 x 128
+ *     pieces with the loads placed between the MFMAs, in the same launch as the big tiles (a workgroup takes pieces once its
+ *     tiles are done; 128 x 64 pieces instead when so few tiles are left over that they fit the grid once; K a multiple
+ *     of 64 with at least three slices, else the next).  2: the same without the smaller pieces.  1: 128 x 128 pieces as a
+ *     second launch.  3 or 6: a second launch of 128 x 64 pieces with the loads of a slice issued in a burst and an LDS
+ *     ring of 3 (two workgroups per compute unit) or 6 (one)
  *   SEMMOE_TUNE_ROUTE_SPLIT: bf16 router with at most 512 tokens: parts the K dimension is split into over workgroups
  *     (partial sums added in order and selected from by a second kernel); 0 = always the fused kernel,
  *     default: as many parts as fill the chip, at most 16.  With more than 128 experts, where tiles of 256 tokens
@@ -119,7 +120,7 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
 #define SEMMOE_TUNE_DOWN_TILE 1
 #define SEMMOE_TUNE_BLOCKS_PER_CU 2
 #define SEMMOE_TUNE_INDEX_PATH 3 /* reshuffle / dispatch index: 1 = one kernel per phase, 2 = single workgroup, 3 = two launches */
-#define SEMMOE_TUNE_HEAD_TAIL 5  /* 0: one launch per GEMM; default: big tiles for the full rounds + quarter tiles */
+#define SEMMOE_TUNE_HEAD_TAIL 5  /* 0: whole tiles only; default: big tiles for the full rounds + smaller pieces for the rest */
 #define SEMMOE_TUNE_TAIL_RING 6  /* tail: default 128 x 128 pieces in the head's launch; 1: as a second launch; 3, 6: 128 x 64 pieces */
 #define SEMMOE_TUNE_ROUTE_SPLIT 7 /* parts of K in the few-token router; 0 = fused kernel */
 #define SEMMOE_TUNE_GRID_CAP 4   /* upper limit of the persistent GEMM grids (tests: many tiles per workgroup) */

@@ -268,7 +268,7 @@ static int32_t launch_stream(const GemmArgs& a, int max_rows, int per_cu, hipStr
 
 // Groups of up to `few_rows` rows streamed, the others as 128 x 64 tiles, in one launch
 template <int MODE, int TW, int TT, bool KTAIL>
-static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_rows, hipStream_t stream) {
+static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_rows, int per_cu, hipStream_t stream) {
   using CS = StreamCfg<MODE, TW, TT, 4>;
   using CD = DmaCfg<MODE, 2, 2, 2, 1, 64, 3>;
   const long long bound_s = (long long)(max_rows / CS::BT + a.nq) * cdiv(a.N, CS::FEAT);
@@ -278,7 +278,7 @@ static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_ro
   if (bound <= 0) return SEMMOE_OK;
   const size_t lds = CS::lds_bytes(a.nq) > CD::kLdsBytes ? CS::lds_bytes(a.nq) : CD::kLdsBytes;
   if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
-  const int grid = grid_for(bound, (long long)num_cu() * 2);
+  const int grid = grid_for(bound, (long long)num_cu() * per_cu);
   auto kern = gemm_stream_ring_kernel<MODE, TW, TT, KTAIL>;
   static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
   const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
@@ -292,12 +292,12 @@ static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_ro
 }
 
 template <int MODE, int TW, int TT>
-static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows, hipStream_t stream) {
+static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows, int per_cu, hipStream_t stream) {
   const unsigned long long row_bytes = a.K * 2ull, w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N;
   if (w_rows * a.ldw * 2 >= (1ull << 31) || StreamCfg<MODE, TW, TT, 4>::BT * 2ull * a.ldx >= (1ull << 31))
     return SEMMOE_EUNSUPPORTED;  // 32-bit offsets do not reach every row
-  if (row_bytes % 128 == 0 && row_bytes >= 512) return launch_stream_ring_as<MODE, TW, TT, false>(a, max_rows, few_rows, stream);
-  return launch_stream_ring_as<MODE, TW, TT, true>(a, max_rows, few_rows, stream);
+  if (row_bytes % 128 == 0 && row_bytes >= 512) return launch_stream_ring_as<MODE, TW, TT, false>(a, max_rows, few_rows, per_cu, stream);
+  return launch_stream_ring_as<MODE, TW, TT, true>(a, max_rows, few_rows, per_cu, stream);
 }
 
 // fp32: 16 x 4 weight rows and 16 x 4 tokens a workgroup, halved along either while that leaves compute units idle.  The
@@ -345,6 +345,7 @@ static int split_threshold() {
 // 256 weight rows x 128 tokens, ring of 3, left-over tiles as pieces in the same launch
 template <int MODE>
 static int32_t launch_w4_128(const GemmArgs& a, int max_rows, hipStream_t stream) {
+  if (tuning_value(SEMMOE_TUNE_HEAD_TAIL) == 0) return launch_w4<MODE, 64, 3, 2, 2>(a, max_rows, stream);  // no pieces
   GemmArgs h = a;
   h.sched_mode = 1;
   h.sched_thr = split_threshold();
@@ -380,8 +381,8 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
     }
     // streamed up to so many rows per group that the ring of case 26 reads the weights less often
     case 34: case 35: {
-      const int32_t st = id == 34 ? launch_stream_ring<MODE, 2, 4>(a, max_rows, 64, s)
-                                  : launch_stream_ring<MODE, 4, 4>(a, max_rows, 64, s);
+      const int32_t st = id == 34 ? launch_stream_ring<MODE, 2, 4>(a, max_rows, 64, bpc > 0 ? bpc : 2, s)
+                                  : launch_stream_ring<MODE, 4, 4>(a, max_rows, 64, bpc > 0 ? bpc : 2, s);
       if (st != SEMMOE_EUNSUPPORTED) return st;
       return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);
     }

@@ -154,6 +154,16 @@ def test_256x128_tiles(cap, d, F):
     _check(got, want, mine, "bf16")
 
 
+# the same tiles uncut (knob 5 at 0), and the workgroups per compute unit of the tiles that run two kernels in a launch
+@pytest.mark.parametrize("tile,knob", [(33, (5, 0)), (34, (2, 1)), (35, (2, 4))])
+@pytest.mark.parametrize("cap", [-1, 3, 16])
+@pytest.mark.parametrize("d,F", [(256, 320), (448, 192)])
+def test_knobs_of_the_default_tiles(cap, tile, knob, d, F):
+    rows = (0, 1, 127, 128, 129, 300, 64, 65)
+    got, want, mine = _ffn(rows, d, F, "bf16", knobs=((0, tile), (1, tile), (4, cap), knob), seed=d)
+    _check(got, want, mine, "bf16")
+
+
 # the library's own choice over its range of rows per expert, many experts and few, whole slices of K and not
 @pytest.mark.parametrize("rows_per_expert", [1, 9, 10, 19, 20, 39, 40, 191, 192, 383, 384])
 @pytest.mark.parametrize("E,D,d,F", [(32, 1, 256, 192), (4, 2, 200, 136), (2, 1, 384, 256)])
