@@ -236,14 +236,14 @@ static int big_tile_grid(const GemmArgs& a, int max_rows, int feat) {
   return grid_for(bound, num_cu());
 }
 
-template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE>
+template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE>
 static int32_t launch_stream_as(const GemmArgs& a, int max_rows, int per_cu, hipStream_t stream) {
-  using C = StreamCfg<MODE, TW, TT, NW>;
+  using C = StreamCfg<MODE, TW, TT>;
   const long long bound = (long long)(max_rows / C::BT + a.nq) * cdiv(a.N, C::FEAT);
   if (bound <= 0) return SEMMOE_OK;
   const size_t lds = C::lds_bytes(a.nq);
   const int grid = grid_for(bound, (long long)num_cu() * per_cu);
-  auto kern = gemm_stream_kernel<MODE, F32, TW, TT, NW, KTAIL, WIDE>;
+  auto kern = gemm_stream_kernel<MODE, F32, TW, TT, KTAIL, WIDE>;
   if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   if (lds > 48 * 1024) {
     static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
@@ -256,20 +256,20 @@ static int32_t launch_stream_as(const GemmArgs& a, int max_rows, int per_cu, hip
 }
 
 // SEMMOE_EUNSUPPORTED where 32-bit offsets do not reach every row: fp32 then takes the wide form, bf16 another tile
-template <int MODE, bool F32, int TW, int TT, int NW>
+template <int MODE, bool F32, int TW, int TT>
 static int32_t launch_stream(const GemmArgs& a, int max_rows, int per_cu, hipStream_t stream) {
   const unsigned long long es = F32 ? 4 : 2, row_bytes = a.K * es;
-  const unsigned long long w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N, x_rows = StreamCfg<MODE, TW, TT, NW>::BT;
+  const unsigned long long w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N, x_rows = StreamCfg<MODE, TW, TT>::BT;
   if (w_rows * a.ldw * es >= (1ull << 31) || x_rows * a.ldx * es >= (1ull << 31)) return SEMMOE_EUNSUPPORTED;
-  if (row_bytes % 128 == 0 && row_bytes >= 128 * NW)
-    return launch_stream_as<MODE, F32, TW, TT, NW, false, false>(a, max_rows, per_cu, stream);
-  return launch_stream_as<MODE, F32, TW, TT, NW, true, false>(a, max_rows, per_cu, stream);
+  if (row_bytes % 128 == 0 && row_bytes >= 128 * StreamCfg<MODE, TW, TT>::NW)
+    return launch_stream_as<MODE, F32, TW, TT, false, false>(a, max_rows, per_cu, stream);
+  return launch_stream_as<MODE, F32, TW, TT, true, false>(a, max_rows, per_cu, stream);
 }
 
 // Groups of up to `few_rows` rows streamed, the others as 128 x 64 tiles, in one launch
 template <int MODE, int TW, int TT, bool KTAIL>
 static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_rows, int per_cu, hipStream_t stream) {
-  using CS = StreamCfg<MODE, TW, TT, 4>;
+  using CS = StreamCfg<MODE, TW, TT>;
   using CD = DmaCfg<MODE, 2, 2, 2, 1, 64, 3>;
   const long long bound_s = (long long)(max_rows / CS::BT + a.nq) * cdiv(a.N, CS::FEAT);
   const long long bound_d = (long long)(max_rows / CD::BT + a.nq) * cdiv(a.N, CD::FEAT);
@@ -294,7 +294,7 @@ static int32_t launch_stream_ring_as(const GemmArgs& a, int max_rows, int few_ro
 template <int MODE, int TW, int TT>
 static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows, int per_cu, hipStream_t stream) {
   const unsigned long long row_bytes = a.K * 2ull, w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N;
-  if (w_rows * a.ldw * 2 >= (1ull << 31) || StreamCfg<MODE, TW, TT, 4>::BT * 2ull * a.ldx >= (1ull << 31))
+  if (w_rows * a.ldw * 2 >= (1ull << 31) || StreamCfg<MODE, TW, TT>::BT * 2ull * a.ldx >= (1ull << 31))
     return SEMMOE_EUNSUPPORTED;  // 32-bit offsets do not reach every row
   if (row_bytes % 128 == 0 && row_bytes >= 512) return launch_stream_ring_as<MODE, TW, TT, false>(a, max_rows, few_rows, per_cu, stream);
   return launch_stream_ring_as<MODE, TW, TT, true>(a, max_rows, few_rows, per_cu, stream);
@@ -311,11 +311,11 @@ template <int MODE>
 static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
   const bool rows_reachable = (unsigned long long)a.K * 4 < (1ull << 32) - 1024;  // a row below 4 GB
   switch (id) {
-    case 30: return launch_stream<MODE, true, 2, 2, 4>(a, max_rows, 2, stream);
-    case 31: return launch_stream<MODE, true, 2, 4, 4>(a, max_rows, 2, stream);
-    case 32: return launch_stream<MODE, true, 4, 4, 4>(a, max_rows, 2, stream);
-    case 36: return launch_stream<MODE, true, 2, 1, 4>(a, max_rows, 2, stream);
-    case 37: return rows_reachable ? launch_stream_as<MODE, true, 2, 1, 4, true, true>(a, max_rows, 2, stream) : SEMMOE_EUNSUPPORTED;
+    case 30: return launch_stream<MODE, true, 2, 2>(a, max_rows, 2, stream);
+    case 31: return launch_stream<MODE, true, 2, 4>(a, max_rows, 2, stream);
+    case 32: return launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
+    case 36: return launch_stream<MODE, true, 2, 1>(a, max_rows, 2, stream);
+    case 37: return rows_reachable ? launch_stream_as<MODE, true, 2, 1, true, true>(a, max_rows, 2, stream) : SEMMOE_EUNSUPPORTED;
     default: break;
   }
   const int est = est_rows_per_group < 1 ? 1 : est_rows_per_group;
@@ -326,14 +326,14 @@ static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_
   const long long fill = 2LL * num_cu();
   int32_t st;
   if (est >= 4 && (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64) >= 2 * fill)
-    st = launch_stream<MODE, true, 4, 4, 4>(a, max_rows, 2, stream);
-  else if (tt == 4 && items(4, 4) >= fill) st = launch_stream<MODE, true, 4, 4, 4>(a, max_rows, 2, stream);
-  else if (tt == 4 && items(2, 4) >= fill) st = launch_stream<MODE, true, 2, 4, 4>(a, max_rows, 2, stream);
-  else if (tt >= 2 && items(2, 2) >= fill) st = launch_stream<MODE, true, 2, 2, 4>(a, max_rows, 2, stream);
-  else st = launch_stream<MODE, true, 2, 1, 4>(a, max_rows, 2, stream);
+    st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
+  else if (tt == 4 && items(4, 4) >= fill) st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
+  else if (tt == 4 && items(2, 4) >= fill) st = launch_stream<MODE, true, 2, 4>(a, max_rows, 2, stream);
+  else if (tt >= 2 && items(2, 2) >= fill) st = launch_stream<MODE, true, 2, 2>(a, max_rows, 2, stream);
+  else st = launch_stream<MODE, true, 2, 1>(a, max_rows, 2, stream);
   if (st != SEMMOE_EUNSUPPORTED) return st;
   if (!rows_reachable) return SEMMOE_EUNSUPPORTED;
-  return launch_stream_as<MODE, true, 2, 1, 4, true, true>(a, max_rows, 2, stream);
+  return launch_stream_as<MODE, true, 2, 1, true, true>(a, max_rows, 2, stream);
 }
 
 // left-over share of a round (in sixteenths) up to which the split happens
@@ -373,9 +373,9 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
     case 27: return launch_dma<MODE, 2, 2, 2, 1, 64, 4>(a, max_rows, bpc > 0 ? bpc : 1, s);     // 128 x 64, ring of 4
     // weights streamed through registers: 16 x TW weight rows, 16 x TT tokens
     case 30: case 31: case 32: {
-      const int32_t st = id == 30   ? launch_stream<MODE, false, 2, 2, 4>(a, max_rows, bpc > 0 ? bpc : 2, s)
-                         : id == 31 ? launch_stream<MODE, false, 2, 4, 4>(a, max_rows, bpc > 0 ? bpc : 2, s)
-                                    : launch_stream<MODE, false, 4, 4, 4>(a, max_rows, bpc > 0 ? bpc : 2, s);
+      const int32_t st = id == 30   ? launch_stream<MODE, false, 2, 2>(a, max_rows, bpc > 0 ? bpc : 2, s)
+                         : id == 31 ? launch_stream<MODE, false, 2, 4>(a, max_rows, bpc > 0 ? bpc : 2, s)
+                                    : launch_stream<MODE, false, 4, 4>(a, max_rows, bpc > 0 ? bpc : 2, s);
       if (st != SEMMOE_EUNSUPPORTED) return st;
       return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);  // panels beyond 32-bit offsets
     }

@@ -9,7 +9,7 @@
 //     slowest line of a slice that four waves share;
 //   * a load instruction covers 8 rows x 128 bytes (four neighbouring lanes in one 64-byte segment; loading MFMA
 //     fragments directly puts them into four rows, and the address unit then passes 16 bytes a cycle instead of 64),
-//     D steps ahead into registers; waits are counted by the compiler per register;
+//     one step ahead into registers; waits are counted by the compiler per register;
 //   * a step's registers go through a few KB of LDS that belong to the wave alone, to change from load layout to
 //     fragment layout (16-byte chunks swizzled by the row: no bank conflicts);
 //   * the load stream does not stop at a tile's end: the steps past it are the first ones of the workgroup's next
@@ -24,18 +24,16 @@ namespace semmoe {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
-template <int MODE, int TW, int TT, int NW_>
+template <int MODE, int TW, int TT>
 struct StreamCfg {
-  static constexpr int NW = NW_, kThreads = 64 * NW;
+  static constexpr int NW = 4, kThreads = 64 * NW;
   static constexpr int BT = 16 * TT;
   static constexpr int FEAT = (MODE == kModeSwiglu) ? TW * 8 : TW * 16;
-  static constexpr int TP = TT < 4 ? TT : 4;         // token tiles that go through the LDS together
-  static constexpr int kStgWave = (TW + TP) * 2048;  // one step of one wave
-  static constexpr int kRedBytes = NW * TW * TP * 1024;
+  static constexpr int kStgWave = (TW + TT) * 2048;  // one step of one wave
+  static constexpr int kRedBytes = NW * TW * TT * 1024;
   static constexpr int kTileBytes = NW * kStgWave > kRedBytes ? NW * kStgWave : kRedBytes;  // the two share their place
   static size_t lds_bytes(int nq) { return size_t(kTileBytes) + (size_t(nq) * 4 + 1) * 4; }  // + tile prefix + group table
   static_assert(MODE != kModeSwiglu || TW % 2 == 0, "gate and up tiles in pairs");
-  static_assert(TT % TP == 0, "whole passes");
 };
 
 // 16 bytes at uniform base + per-lane offset + uniform offset.  A buffer load and not a plain one: whether it passes by
@@ -67,12 +65,12 @@ __device__ __forceinline__ f32x4_t stream_mfma(u32x4_t w, u32x4_t x, f32x4_t c) 
 // KTAIL: K is not a multiple of a slice (128 bytes of a row) or gives some wave no slice at all: addresses are clamped
 // into the row and what lies behind its end counts as zero.  WIDE: rows so long, or so many, that 32-bit offsets from the
 // panels' first rows do not reach them all (64-bit addresses per lane; with KTAIL only).
-template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE = false, bool SIZED = false>
+template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false, bool SIZED = false>
 __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned char* lds_raw, int skip = 0) {
   static_assert(KTAIL || !WIDE, "the wide form clamps every address");
-  using C = StreamCfg<MODE, TW, TT, NW>;
+  using C = StreamCfg<MODE, TW, TT>;
+  constexpr int NW = C::NW;
   using off_t = std::conditional_t<WIDE, uint64_t, uint32_t>;
-  constexpr int TP = C::TP;
   constexpr int ES = F32 ? 4 : 2;          // bytes of an element
   f32x4_t* red = reinterpret_cast<f32x4_t*>(lds_raw);  // [wave][weight tile][token tile][lane]
   int* pre = reinterpret_cast<int*>(lds_raw + C::kTileBytes);
@@ -195,56 +193,52 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
   // accumulator of (weight tile, token tile): lane holds weight rows 4*(lane/16) + 0..3 for token lane%16
   auto finish = [&](int t) __attribute__((always_inline)) {
     const Tile r = locate(t);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // every wave is through with its staging area
 #pragma unroll
-    for (int j0 = 0; j0 < TT; j0 += TP) {
-      if (j0 * 16 >= r.n_tok) break;
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();  // every wave is through with its staging area (or with the sums of the pass before)
+    for (int i = 0; i < TW; ++i)
 #pragma unroll
-      for (int i = 0; i < TW; ++i)
+      for (int j = 0; j < TT; ++j) red[((wave * TW + i) * TT + j) * 64 + lane] = acc[i][j];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    auto total_of = [&](int i, int j) __attribute__((always_inline)) {
+      f32x4_t v = red[(i * TT + j) * 64 + lane];
 #pragma unroll
-        for (int j = 0; j < TP; ++j) red[((wave * TW + i) * TP + j) * 64 + lane] = acc[i][j0 + j];
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      auto total_of = [&](int i, int j) __attribute__((always_inline)) {
-        f32x4_t v = red[(i * TP + j) * 64 + lane];
+      for (int w = 1; w < NW; ++w) v += red[((w * TW + i) * TT + j) * 64 + lane];
+      return v;
+    };
+    constexpr int FT = (MODE == kModeSwiglu) ? TW / 2 : TW;  // 16-feature tiles of the output
+    for (int unit = wave; unit < FT * TT; unit += NW) {
+      const int j = unit / FT, p = unit - j * FT;
+      const int tok = j * 16 + l16, feat = r.f0 + p * 16 + g * 4;
+      if (j * 16 >= r.n_tok) break;
+      f32x4_t v;
+      if constexpr (MODE == kModeSwiglu) {
+        const f32x4_t gt = total_of(2 * p, j), up = total_of(2 * p + 1, j);
 #pragma unroll
-        for (int w = 1; w < NW; ++w) v += red[((w * TW + i) * TP + j) * 64 + lane];
-        return v;
-      };
-      constexpr int FT = (MODE == kModeSwiglu) ? TW / 2 : TW;  // 16-feature tiles of the output
-      for (int unit = wave; unit < FT * TP; unit += NW) {
-        const int j = unit / FT, p = unit - j * FT;
-        const int tok = (j0 + j) * 16 + l16, feat = r.f0 + p * 16 + g * 4;
-        if ((j0 + j) * 16 >= r.n_tok) break;
-        f32x4_t v;
-        if constexpr (MODE == kModeSwiglu) {
-          const f32x4_t gt = total_of(2 * p, j), up = total_of(2 * p + 1, j);
+        for (int e = 0; e < 4; ++e) v[e] = F32 ? gt[e] / (1.0f + expf(-gt[e])) * up[e] : silu_mul(gt[e], up[e]);
+      } else {
+        v = total_of(p, j);
+      }
+      if (tok >= r.n_tok || feat >= a.N) continue;
+      const size_t row = size_t(r.row_lo) + tok;
+      if constexpr (MODE == kModeLogits) {  // N need not be a multiple of four
+        const int cls = a.token_class ? a.token_class[row] : -1;
+        const float* cb = (cls >= 0 && cls < a.n_classes && a.class_bias) ? a.class_bias + size_t(cls) * a.N : nullptr;
+        float* o = static_cast<float*>(a.out) + row * size_t(a.N);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = F32 ? gt[e] / (1.0f + expf(-gt[e])) * up[e] : silu_mul(gt[e], up[e]);
-        } else {
-          v = total_of(p, j);
-        }
-        if (tok >= r.n_tok || feat >= a.N) continue;
-        const size_t row = size_t(r.row_lo) + tok;
-        if constexpr (MODE == kModeLogits) {  // N need not be a multiple of four
-          const int cls = a.token_class ? a.token_class[row] : -1;
-          const float* cb = (cls >= 0 && cls < a.n_classes && a.class_bias) ? a.class_bias + size_t(cls) * a.N : nullptr;
-          float* o = static_cast<float*>(a.out) + row * size_t(a.N);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (feat + e < a.N) {
-              float s = v[e];
-              if (a.b_g) s += a.b_g[feat + e];
-              if (cb) s += cb[feat + e];
-              o[feat + e] = s;
-            }
-        } else if constexpr (F32) {
-          *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.out) + row * a.ldo + feat) = v;
-        } else {
-          *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.out) + row * a.ldo + feat) =
-              make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-        }
+        for (int e = 0; e < 4; ++e)
+          if (feat + e < a.N) {
+            float s = v[e];
+            if (a.b_g) s += a.b_g[feat + e];
+            if (cb) s += cb[feat + e];
+            o[feat + e] = s;
+          }
+      } else if constexpr (F32) {
+        *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.out) + row * a.ldo + feat) = v;
+      } else {
+        *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.out) + row * a.ldo + feat) =
+            make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -269,37 +263,28 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     for (int i = 0; i < 2 * TW; ++i)
       *reinterpret_cast<u32x4_t*>((i & 1 ? put1 : put0) + i * 1024) = in ? wb[i] : u32x4_t{0, 0, 0, 0};
 #pragma unroll
-    for (int j0 = 0; j0 < TT; j0 += TP) {
-      if (j0 < ntt) {
+    for (int j = 0; j < 2 * TT; ++j)
+      if (j < 2 || (j >> 1) < ntt)  // a tile has at least one token
+        *reinterpret_cast<u32x4_t*>((j & 1 ? put1 : put0) + (2 * TW + j) * 1024) = in ? xb[j] : u32x4_t{0, 0, 0, 0};
+    __builtin_amdgcn_sched_barrier(0);
+    fetch();  // every register of the step has been written down
+    __builtin_amdgcn_sched_barrier(0);
+    // the wave's own LDS operations complete in order: no wait between its writes and its reads
 #pragma unroll
-        for (int j = 0; j < 2 * TP; ++j)
-          if (j0 + (j >> 1) < ntt)
-            *reinterpret_cast<u32x4_t*>((j & 1 ? put1 : put0) + (2 * TW + j) * 1024) = in ? xb[2 * j0 + j] : u32x4_t{0, 0, 0, 0};
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (j0 + TP >= TT || j0 + TP >= ntt) {  // the last pass: every register of the step has been written down
-        if (j0 < ntt) fetch();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // the wave's own LDS operations complete in order: no wait between its writes and its reads
-      if (j0 < ntt) {
+    for (int h = 0; h < 2; ++h) {
+      u32x4_t wf[TW];
+      const unsigned char* from = get + ((h * 4 + g) ^ swz) * 16;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          u32x4_t wf[TW];
-          const unsigned char* from = get + ((h * 4 + g) ^ swz) * 16;
+      for (int i = 0; i < TW; ++i) wf[i] = *reinterpret_cast<const u32x4_t*>(from + i * 2048);
 #pragma unroll
-          for (int i = 0; i < TW; ++i) wf[i] = *reinterpret_cast<const u32x4_t*>(from + i * 2048);
+      for (int j = 0; j < TT; ++j)
+        if (j == 0 || j < ntt) {  // the first without a test: its MFMAs then wait for one fragment at a time
+          const u32x4_t xf = *reinterpret_cast<const u32x4_t*>(from + (TW + j) * 2048);
 #pragma unroll
-          for (int j = 0; j < TP; ++j)
-            if (j0 + j < ntt) {
-              const u32x4_t xf = *reinterpret_cast<const u32x4_t*>(from + (TW + j) * 2048);
-#pragma unroll
-              for (int i = 0; i < TW; ++i) acc[i][j0 + j] = stream_mfma<F32>(wf[i], xf, acc[i][j0 + j]);
-            }
+          for (int i = 0; i < TW; ++i) acc[i][j] = stream_mfma<F32>(wf[i], xf, acc[i][j]);
         }
-      }
-      __builtin_amdgcn_sched_barrier(0);
     }
+    __builtin_amdgcn_sched_barrier(0);
     slice += NW;
     if (slice >= nst) {  // also where this wave has no slice of its own (KTAIL): it has added zeros once
       finish(my.item(round));
@@ -310,10 +295,10 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
   }
 }
 
-template <int MODE, bool F32, int TW, int TT, int NW, bool KTAIL, bool WIDE = false>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs a) {
+template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false>
+__global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_stream_body<MODE, F32, TW, TT, NW, KTAIL, WIDE>(a, lds_raw);
+  gemm_stream_body<MODE, F32, TW, TT, KTAIL, WIDE>(a, lds_raw);
 }
 
 // The rows of each group live on the device, and the mean the host expects can be far off: the ranks of an affinity
@@ -339,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_ring_kernel(const GemmArgs
     large = __builtin_amdgcn_readfirstlane(gemm_bf16_dma_body<MODE, 2, 2, 2, 1, 64, 3, true>(many, lds_raw));
     __syncthreads();
   }
-  gemm_stream_body<MODE, false, TW, TT, 4, KTAIL, false, true>(few, lds_raw, side_workgroups(large, int(gridDim.x)));
+  gemm_stream_body<MODE, false, TW, TT, KTAIL, false, true>(few, lds_raw, side_workgroups(large, int(gridDim.x)));
 }
 
 }  // namespace semmoe

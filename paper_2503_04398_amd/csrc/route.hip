@@ -1193,7 +1193,7 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     }
     return SEMMOE_OK;
   }
-  // fp32: tiled FMA GEMM into the logits buffer, then the selection kernel
+  // fp32: the streamed GEMM (fp32 MFMAs) into the logits buffer, then the selection kernel
   float* logits = logits_out;
   if (!logits) {
     Carver c(ws, ws_bytes);
