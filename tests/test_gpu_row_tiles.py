@@ -1,7 +1,14 @@
 """Grouped FFN kernels for few and for middling rows per expert, on group sizes at the edges of their tiles.
 
-The expert FFN is called with offsets written by hand and compared row by row with a float64 product on the CPU.  Bounds:
-fp32 1e-5, bf16 2e-2 of the largest value (the hidden activation and the result are rounded to the activation type)."""
+The expert FFN is called with offsets written by hand and compared with a float64 product on the CPU: all rows together
+(fp32 1e-5, bf16 2e-2 of the largest value) and each row by itself, against its own norm.
+
+Bound of a row.  A value y = sum_f h_f w_f has the norm |h||w| to go by, and a row of them about sqrt(d) times that, which
+is the row's own norm for weights drawn at random.  bf16 (u = 2^-9, the largest relative error of one rounding): the hidden
+activation and the result are rounded, errors that are independent from entry to entry, so a row is off by sqrt(2) u = 0.28 %
+of its norm at most; fp32 sums of up to 1536 terms and the fast exponential add less than 1e-5.  fp32: a sum of K terms in
+four parts is off by sqrt(K) 2^-24 of its norm where roundings are independent, twice in a row (gate/up, down), 4.7e-6 in
+all at K = 1536; the bounds below are about twice these."""
 import numpy as np
 import pytest
 import torch
@@ -10,6 +17,7 @@ import paper_2503_04398_amd as S
 from tests import harness as H
 
 pytestmark = pytest.mark.gpu
+ROW_TOL = {"fp32": 1e-5, "bf16": 6e-3}  # see above
 
 
 def _ffn(rows, d, F, dtype, D=1, rank=-1, knobs=(), seed=0):
@@ -47,8 +55,8 @@ def _ffn(rows, d, F, dtype, D=1, rank=-1, knobs=(), seed=0):
 def _check(got, want, mine, dtype):
     H.assert_close(got[mine], want[mine], dtype, "Y")
     assert (np.delete(got, np.r_[mine], axis=0) == 512.0).all()  # rows of other ranks stay as they were
-    per_row = np.abs(got[mine] - want[mine]).max(axis=1) / np.abs(want[mine]).max()
-    assert per_row.max() <= H.TOL[dtype]
+    off = np.linalg.norm(got[mine] - want[mine], axis=1) / np.linalg.norm(want[mine], axis=1)
+    assert off.max() <= ROW_TOL[dtype], "row %d of the rank: |a-b|/|b| = %.3e" % (off.argmax(), off.max())
 
 
 RAGGED = (0, 1, 15, 16, 17, 33, 64, 65, 0, 130, 31, 48)
