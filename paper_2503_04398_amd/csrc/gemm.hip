@@ -445,6 +445,9 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //     have a compute unit each it is behind up to K 3200 (+1 to +8 %).  20 to 39 rows: from K 1408 on.
 //   * 256 x 128 tiles need work for every compute unit: 40 to 95 rows, fewer than 96 of them +10 to +20 %, half of the
 //     compute units +1 % at K 1000 and -3 % from K 1400, all of them +6 % below K 384 and 0 to -7 % from 640, two rounds -7 %.
+//     One rank's launch counts the tiles of three times the mean: a loaded rank has that many, and if it has not the loss is
+//     smaller than the gain (5995 random shapes with half to eight times the mean on the rank; 40 to 95 rows expected and 8 times
+//     as many there: 5 % over counting the mean's, even loads: 1 % behind it).
 //     384 experts and more leave no room in its LDS for their table (512 experts, d 1024, F 512, 300 rows: 776 us as
 //     256 x 256 tiles, 1134 as 128 x 64).
 // Rows that are no whole 128 bytes: neighbouring slices share cache lines, and from about ten rows on the staged tiles
@@ -478,7 +481,8 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
     return a.K >= k_min && (est < 20 || a.K >= 1408) ? 35 : 26;
   }
   if (whole_slices && est < 384 && W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds())) {
-    const long long mid = (long long)a.nq * w_rows * cdiv(est, 128) / 256;  // 256 x 128 tiles, as full ones
+    // 256 x 128 tiles, as full ones
+    const long long mid = (long long)a.nq * w_rows * cdiv(all_rows ? est : 3 * est, 128) / 256;
     if (est < 192) return mid * 2 >= 3 * cus || (mid >= cus && a.K >= 640) || (mid * 2 >= cus && a.K >= 1408) ? 33 : 26;
     if (all_rows && a.K >= 640 && mid * 2 >= cus) return 33;
   }
