@@ -78,15 +78,15 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  * Tuning knobs for tests and sweeps.  Process-wide state: a knob holds until it is set again and applies to every
  * call of every thread (each knob is one atomic integer; a call reads the knobs it needs once, when it picks its
  * kernels).  value < 0 restores the default, which the library picks per shape.  Results never depend on them beyond
- * fp32 summation order inside a GEMM tile.  semmoe_get_tuning reads a knob back (-1: default).
+ * fp32 rounding inside a GEMM tile (the order of sums, the exponential of the activation).  semmoe_get_tuning reads a knob back (-1: default).
  *   SEMMOE_TUNE_GATEUP_TILE / SEMMOE_TUNE_DOWN_TILE: tile-shape id of the bf16 grouped GEMMs
  *     (0, 3, 4, 6: register-staged; 11, 12, 14, 15, 16: direct-to-LDS ring; 17, 18: skinny register-staged tiles;
  *     19, 25, 26, 27: skinny tiles with a direct-to-LDS ring for decode;
- *     28: 128 x 128 pieces throughout (the default for more than 256 rows of one set of weights, as long as bigger
- *     tiles would leave compute units idle);
- *     30, 31, 32: weights streamed through registers, 32 weight rows x 32 tokens, 32 x 64 or 64 x 64 (the default for
- *     few rows of one set of weights); 34, 35: groups of up to 64 rows so (32 x 64 or 64 x 64), the others as 26 in the same
- *     launch (the default for few rows per expert); 33: four waves on a 256 x 128 tile (the default for middling groups);
+ *     28: 128 x 128 pieces throughout (the default for many rows while bigger tiles would leave compute units idle);
+ *     30, 31, 32: weights streamed through registers, 32 weight rows x 32 tokens, 32 x 64 or 64 x 64 (30 and 31: the
+ *     default for few rows of one set of weights); 34, 35: groups of up to 64 rows so (32 x 64 or 64 x 64), the others as
+ *     26 in the same launch (the default for few rows per expert and a deep product); 33: four waves on a 256 x 128 tile
+ *     (the default for middling groups with tiles for the whole chip);
  *     20, 21, 22: four waves on a 256 x 256 tile with loads placed between the MFMAs; K must be a multiple of the
  *     K slice (32 for 20 and 21, 64 for 22) and hold at least a ring of slices (128); other K run as 16).
  *     In fp32 (the router's GEMM follows SEMMOE_TUNE_GATEUP_TILE) 30, 31, 32 are the same shapes, 36 is 32 weight rows x 16
