@@ -306,6 +306,9 @@ static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows,
 // the tokens stay at 16 x 4: that is the faster shape there with even groups too (256 experts and more, mean up to 16: 9 %),
 // and not below (512 to 1023 tiles, hot groups: 4 % behind).  512 experts, d = F = 512, mean 11, nearly all rows on one:
 // 212 -> 140 us.
+// Against plain FMAs on 64 x 64 tiles that share every slice: 0.41 of the time over 834 random shapes; behind by 10 to 36 %
+// only where a row is two slices (K up to 96) and 128 experts or more make the sum over the waves the most of the work
+// (leaving the waves without a slice out of that sum changed nothing).
 // id: a shape by its tuning id; others are for bf16 and leave the choice here.
 template <int MODE>
 static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
