@@ -445,9 +445,13 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //     lies at K 192 up to a tile per four compute units (-6 % above it), 384 up to one per two, 960 beyond.  64 x 64 has
 //     half the sums: from K 640 on where there are more than two tiles a compute unit (K 640 to 959: -4 % where 32 x 64
 //     has +5).  10 to 19 rows, 64 x 64: -2 to -8 % from K 960, with few tiles from 640; where the 128 x 64 tiles just
-//     have a compute unit each it is behind up to K 3200 (+1 to +8 %).  20 to 39 rows: from K 1408 on, not with a compute unit each
-//     (+1 to +10 %), and up to fewer tiles the more rows it drags along: K 1408 to 2099 20 to 24 rows -3 % up to 2048 tiles,
-//     +1 % beyond, 25 to 29 rows level up to 1024, +1 % beyond, 30 to 39 rows -2 % up to 512, +4 % beyond.
+//     have a compute unit each from K 2560 (-1 to -3 %; up to 1408 +3 to +6 %).  20 to 39 rows: from K 1408 on, not with a
+//     compute unit each (+1 to +10 %), and up to fewer tiles the more rows it drags along: K 1408 to 2099 20 to 24 rows -3 % up
+//     to 2048 tiles, +1 % beyond, 25 to 29 rows level up to 1024, +1 % beyond, 30 to 39 rows -2 % up to 512, +4 % beyond.
+//   * K 2048 and 4096: the rows of a panel lie a power of two apart, and a slice of the 128 x 64 tile, 128 bytes of each of 192
+//     rows, falls on few memory channels; a streamed step reads 512 consecutive bytes of a row.  64 x 64 is ahead of it
+//     at any number of tiles, 10 to 19 rows K 2048 -4 to -13 %, K 4096 -7 to -20 %, 20 to 39 rows -2 to -13 % (K 1536, 2560,
+//     3072 and 6144 in the same 6649 launches of common widths: as the lines above).
 //   * 256 x 128 tiles need work for every compute unit: 40 to 95 rows, fewer than 96 of them +10 to +20 %, half of the
 //     compute units +1 % at K 1000 and -3 % from K 1400, all of them +6 % below K 384 and 0 to -7 % from 640, two rounds -7 %.
 //     One rank's launch counts the tiles of three times the mean: a loaded rank has that many, and if it has not the loss is
@@ -480,10 +484,12 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
     if (ring > 2 * cus && a.K < 1536) return a.K >= 640 ? 35 : 26;
     return a.K >= 960 ? 34 : 26;
   }
-  if (est < 20) return whole_slices && a.K >= (ring * 2 <= cus ? 640 : (ring <= cus ? 3200 : 960)) ? 35 : 26;
   if (est < 40) {
+    if (!whole_slices || (est >= 20 && !all_rows)) return 26;
+    if (a.K >= 2048 && (a.K & (a.K - 1)) == 0) return 35;
     const bool one_each = ring * 2 > cus && ring <= cus;
-    return whole_slices && all_rows && a.K >= 1408 && !one_each && ring <= (est < 25 ? 8 : est < 30 ? 4 : 2) * cus ? 35 : 26;
+    if (est < 20) return a.K >= (ring * 2 <= cus ? 640 : (one_each ? 2560 : 960)) ? 35 : 26;
+    return a.K >= 1408 && !one_each && ring <= (est < 25 ? 8 : est < 30 ? 4 : 2) * cus ? 35 : 26;
   }
   if (whole_slices && est < 384 && W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds())) {
     // 256 x 128 tiles, as full ones
