@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <stddef.h>
+#include <type_traits>
 
 #include "semmoe.h"
 
@@ -109,6 +110,54 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return static_cast<uint32_t>(f32_to_bf16(lo)) | (static_cast<uint32_t>(f32_to_bf16(hi)) << 16);
 }
 
+// The k expert ids of a token: KU >= k registers, positions from k on repeat earlier ids (map_ids masks them).  No load sits
+// behind a branch, so they all go out together.  quads (k a multiple of four, rows 16-byte aligned): a quarter of the
+// instructions; a wave's 64 rows lie anywhere, and each 4-byte instruction costs the address unit as much as a 16-byte one.
+// `row` must be readable for k entries even for a token that is not there (callers pass the row of one that is).
+typedef __attribute__((ext_vector_type(4))) int32_t i32x4_t;
+
+__host__ __device__ inline bool id_quads(const int32_t* ids, int k) {
+  return k % 4 == 0 && (reinterpret_cast<uintptr_t>(ids) & 15u) == 0;
+}
+
+// calls f with the register width for k ids as a compile-time constant: loops over 16 positions for 4 experts a token spend
+// most of their time on positions that are not there
+template <typename F>
+inline int32_t with_id_width(int k, F f) {
+  if (k <= 4) return f(std::integral_constant<int, 4>{});
+  if (k <= 8) return f(std::integral_constant<int, 8>{});
+  static_assert(SEMMOE_MAX_K == 16, "the widths here");
+  return f(std::integral_constant<int, 16>{});
+}
+
+template <int KU>
+__device__ __forceinline__ void load_id_row(const int32_t* __restrict__ row, int k, bool quads, int (&e)[KU]) {
+  static_assert(KU % 4 == 0, "whole quads");
+  if (quads) {
+#pragma unroll
+    for (int j = 0; j < KU; j += 4) {
+      const i32x4_t v = *reinterpret_cast<const i32x4_t*>(row + min(j, k - 4));
+#pragma unroll
+      for (int x = 0; x < 4; ++x) e[j + x] = v[x];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < KU; ++j) e[j] = row[min(j, k - 1)];
+  }
+}
+
+// r[j] = map[e[j]] for j < k when the token is there and the expert lies in [0,E), else -1.  The map (expert -> rank, or
+// expert -> physical position; -1: outside its range) lies in LDS: gathered from memory it is a second exposed latency.
+template <int KU>
+__device__ __forceinline__ void map_ids(const int (&e)[KU], bool have, int k, int E, const int32_t* map, int (&r)[KU]) {
+#pragma unroll
+  for (int j = 0; j < KU; ++j) {
+    const bool ok = have && j < k && (unsigned)e[j] < (unsigned)E;
+    const int m = map[ok ? e[j] : 0];
+    r[j] = ok ? m : -1;
+  }
+}
+
 // The k experts of a token mapped through a table (expert -> rank, or expert -> physical position):
 //   r[j] = map[row[j]] for j < k when the token is there, the expert lies in [0,E) and the mapped value in [0,limit),
 //   else -1 (also for j >= k).
@@ -143,6 +192,24 @@ __device__ __forceinline__ void load_mapped_ids(const int32_t* __restrict__ row,
   else load_mapped_ids_n<16>(row, have, k, E, map, limit, r);
 }
 
+// Number of bits below position t in a bitmap of WORDS 32-bit words in LDS (16-byte aligned): whole words masked by their
+// place, four a load, no loop over the words before t that every lane leaves somewhere else.
+template <int WORDS>
+__device__ __forceinline__ int bits_below(const uint32_t* words, int t) {
+  static_assert(WORDS % 4 == 0, "whole quads");
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  const int w = t >> 5;
+  const uint32_t below = (1u << (t & 31)) - 1u;
+  int n = 0;
+#pragma unroll
+  for (int x = 0; x < WORDS; x += 4) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(words + x);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) n += __popc(x + y < w ? v[y] : (x + y == w ? v[y] & below : 0u));
+  }
+  return n;
+}
+
 // Column sums of a [n_rows][n_cols] table of counts: tot[c] += all rows, pre[c] += the rows before `b` (both in LDS,
 // zeroed by the caller, who also places the barriers).  Every workgroup of the index kernels reads the whole table, so
 // the time is the number of loads a thread waits for one after the other.  With n_cols a multiple of four a thread owns
@@ -151,7 +218,6 @@ __device__ __forceinline__ void load_mapped_ids(const int32_t* __restrict__ row,
 // a 64 x 288 table, with more columns than the 256 threads and so an atomic per element, 19.4 us for rs_fused_kernel).
 // The first eight loads can be requested ahead of time (`column_sums_first`), before other work that has its own chain
 // of dependent loads.
-typedef __attribute__((ext_vector_type(4))) int32_t i32x4_t;
 struct ColumnBatch {
   i32x4_t v[8];
 };

@@ -17,89 +17,127 @@ struct DispatchWs {
   uint32_t* remote_part;  // [NB]    per-block pairs whose expert sits on another rank than the token
 };
 
-__device__ __forceinline__ int bitmap_rank(const uint32_t* words, int t) {
-  int r = 0;
-  const int w = t >> 5;
-  for (int x = 0; x < w; ++x) r += __popc(words[x]);
-  r += __popc(words[w] & ((1u << (t & 31)) - 1u));
-  return r;
+// A workgroup's token chain: its token (shf), then in one go the token's ids and its rank; the expert -> physical position
+// table and everything else a workgroup has to set up are requested and done while the chain runs.  The map entry of an
+// expert is its position | its rank << 16 (-1: outside the range), so that no pair divides by the experts per rank.
+__device__ __forceinline__ int token_at(int T, int pos, const int32_t* __restrict__ shf) {
+  const int tok = pos < T ? shf[pos] : -1;
+  return (unsigned)tok < (unsigned)T ? tok : -1;
 }
 
-// the thread's token at its shuffled position (or -1) and the physical experts of its k pairs (-1: none): a chain
-// of three dependent loads (shf -> ids -> phys), so callers start it before anything else they have to do
-__device__ __forceinline__ int load_pairs(int T, int k, int E, const int32_t* __restrict__ ids,
-                                          const int32_t* __restrict__ shf, const int32_t* __restrict__ phys,
-                                          int* q_out) {
-  const int pos = blockIdx.x * kTokBlock + threadIdx.x;
-  int tok = -1;
-  if (pos < T) {
-    tok = shf[pos];
-    if ((unsigned)tok >= (unsigned)T) tok = -1;
+__device__ __forceinline__ void load_phys_map(int E, int m, const int32_t* __restrict__ phys, int32_t* map) {
+  for (int x = threadIdx.x; x < E; x += blockDim.x) {
+    const int q = phys[x];
+    map[x] = (unsigned)q < (unsigned)E ? (q | (q / m) << 16) : -1;
   }
-  int q[SEMMOE_MAX_K];
-  load_mapped_ids(ids + size_t(max(tok, 0)) * k, tok >= 0, k, E, phys, E, q);
-#pragma unroll
-  for (int j = 0; j < SEMMOE_MAX_K; ++j) q_out[j] = q[j];
-  return tok;
 }
 
-// set the thread's bits in the [E][kWords] bitmaps of this block's 256 shuffled positions (zeroed here)
-__device__ __forceinline__ void set_bitmaps(int E, uint32_t* bm, const int* q) {
-  for (int x = threadIdx.x; x < E * kWords; x += blockDim.x) bm[x] = 0;
-  __syncthreads();
+__device__ __forceinline__ void zero_quads(void* lds, int n_quads) {
+  for (int x = threadIdx.x; x < n_quads; x += blockDim.x) reinterpret_cast<uint4*>(lds)[x] = make_uint4(0, 0, 0, 0);
+}
+
+// Pairs of a workgroup's tokens per (rank of the token, rank of the expert).  The tokens of a workgroup sit on one rank or
+// two, so its pairs fall on few entries, and LDS adds to one address run one after the other: every entry has several
+// copies side by side (in neighbouring banks), and neighbouring lanes add to different ones.
+__host__ __device__ inline int send_copies(int D) { return D <= 8 ? 8 : (D <= 32 ? 2 : 1); }
+
+template <int KU>
+__device__ __forceinline__ int count_send(int D, int s, const int (&q)[KU], uint32_t* send, int copies) {
+  int remote = 0;
+  if ((unsigned)s >= (unsigned)D) return 0;
+  const int mine = int(threadIdx.x) & (copies - 1);
+#pragma unroll
+  for (int j = 0; j < KU; ++j)
+    if (q[j] >= 0) {
+      const int r = q[j] >> 16;
+      atomicAdd(&send[(s * D + r) * copies + mine], 1u);
+      remote += r != s;
+    }
+  return remote;
+}
+
+__device__ __forceinline__ uint32_t send_total(const uint32_t* send, int x, int copies) {
+  uint32_t v = 0;
+  for (int c = 0; c < copies; ++c) v += send[x * copies + c];
+  return v;
+}
+
+template <int KU, int WORDS>
+__device__ __forceinline__ void set_bits(const int (&q)[KU], uint32_t* bm) {
   const int t = threadIdx.x;
 #pragma unroll
-  for (int j = 0; j < SEMMOE_MAX_K; ++j)
-    if (q[j] >= 0) atomicOr(&bm[q[j] * kWords + (t >> 5)], 1u << (t & 31));
-  __syncthreads();
+  for (int j = 0; j < KU; ++j)
+    if (q[j] >= 0) atomicOr(&bm[(q[j] & 0xffff) * WORDS + (t >> 5)], 1u << (t & 31));
 }
 
-// fill the [E][kWords] bitmaps of this block's 256 shuffled positions; returns the thread's token (or -1)
-__device__ __forceinline__ int fill_bitmaps(int T, int k, int E, const int32_t* __restrict__ ids,
-                                            const int32_t* __restrict__ shf, const int32_t* __restrict__ phys,
-                                            uint32_t* bm, int* q_out) {
-  const int tok = load_pairs(T, k, E, ids, shf, phys, q_out);
-  set_bitmaps(E, bm, q_out);
-  return tok;
+template <int WORDS>
+__device__ __forceinline__ int bits_of(const uint32_t* words) {
+  int c = 0;
+#pragma unroll
+  for (int y = 0; y < WORDS; y += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(words + y);
+    c += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+  }
+  return c;
+}
+
+// slot_of_pair of a token's k pairs (a run of 4k bytes) and its inverse.  slot[j] < 0: no pair
+template <int KU>
+__device__ __forceinline__ void store_slots(int tok, int k, const int (&slot)[KU], bool quads,
+                                            int32_t* __restrict__ slot_of_pair, int32_t* __restrict__ pair_of_slot) {
+  const int pair0 = tok * k;
+  if (quads) {
+#pragma unroll
+    for (int j = 0; j < KU; j += 4)
+      if (j < k) {
+        if (slot[j] >= 0 && slot[j + 1] >= 0 && slot[j + 2] >= 0 && slot[j + 3] >= 0) {
+          *reinterpret_cast<i32x4_t*>(slot_of_pair + size_t(pair0) + j) = i32x4_t{slot[j], slot[j + 1], slot[j + 2], slot[j + 3]};
+        } else {
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+            if (slot[j + x] >= 0) slot_of_pair[pair0 + j + x] = slot[j + x];
+        }
+      }
+  } else {
+#pragma unroll
+    for (int j = 0; j < KU; ++j)
+      if (slot[j] >= 0) slot_of_pair[pair0 + j] = slot[j];
+  }
+#pragma unroll
+  for (int j = 0; j < KU; ++j)
+    if (slot[j] >= 0) pair_of_slot[slot[j]] = pair0 + j;
 }
 
 // D1: per-block counts per physical expert and per-block send matrix
+template <int KU>
 __global__ __launch_bounds__(kTokBlock) void dp_count_kernel(int T, int k, int E, int D,
                                                              const int32_t* __restrict__ ids,
                                                              const int32_t* __restrict__ token_rank,
                                                              const int32_t* __restrict__ shf,
                                                              const int32_t* __restrict__ phys, DispatchWs w) {
-  extern __shared__ uint32_t lds[];  // [E][kWords] bitmaps, [D*D] send counts, [1] remote pairs
-  uint32_t* bm = lds;
-  uint32_t* send = lds + E * kWords;
-  for (int x = threadIdx.x; x < D * D + 1; x += blockDim.x) send[x] = 0;
-  int q[SEMMOE_MAX_K];
-  const int tok = fill_bitmaps(T, k, E, ids, shf, phys, bm, q);
-  int remote = 0;
-  if (tok >= 0) {
-    const int s = token_rank[tok];
-    const int m = E / D;
-    if ((unsigned)s < (unsigned)D) {
-#pragma unroll
-      for (int j = 0; j < SEMMOE_MAX_K; ++j)
-        if (q[j] >= 0) {
-          atomicAdd(&send[s * D + q[j] / m], 1u);
-          remote += (q[j] / m != s);
-        }
-    }
-  }
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  // [E][kWords] bitmaps | [D*D][copies] send counts + remote pairs, whole quads | [E] map
+  const int copies = send_copies(D), n_send = D * D * copies, send_quads = (n_send + 1 + 3) / 4;
+  uint32_t* bm = reinterpret_cast<uint32_t*>(lds_raw);
+  uint32_t* send = bm + E * kWords;
+  int32_t* map = reinterpret_cast<int32_t*>(send + send_quads * 4);
+  const int tok = token_at(T, blockIdx.x * kTokBlock + threadIdx.x, shf);
+  load_phys_map(E, E / D, phys, map);
+  zero_quads(bm, E * kWords / 4 + send_quads);
+  int e[KU], q[KU];
+  load_id_row(ids + size_t(max(tok, 0)) * k, k, id_quads(ids, k), e);
+  const int s = token_rank[max(tok, 0)];
+  __syncthreads();
+  map_ids(e, tok >= 0, k, E, map, q);
+  set_bits<KU, kWords>(q, bm);
+  int remote = count_send(D, tok >= 0 ? s : -1, q, send, copies);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) remote += __shfl_xor(remote, o);
-  if ((threadIdx.x & 63) == 0 && remote) atomicAdd(&send[D * D], (uint32_t)remote);
-  for (int x = threadIdx.x; x < E; x += blockDim.x) {
-    int c = 0;
-#pragma unroll
-    for (int y = 0; y < kWords; ++y) c += __popc(bm[x * kWords + y]);
-    w.cnt[size_t(blockIdx.x) * E + x] = c;
-  }
+  if ((threadIdx.x & 63) == 0 && remote) atomicAdd(&send[n_send], (uint32_t)remote);
   __syncthreads();
-  for (int x = threadIdx.x; x < D * D; x += blockDim.x) w.send_part[size_t(blockIdx.x) * D * D + x] = send[x];
-  if (threadIdx.x == 0) w.remote_part[blockIdx.x] = send[D * D];
+  for (int x = threadIdx.x; x < E; x += kTokBlock) w.cnt[size_t(blockIdx.x) * E + x] = bits_of<kWords>(bm + x * kWords);
+  for (int x = threadIdx.x; x < D * D; x += kTokBlock) w.send_part[size_t(blockIdx.x) * D * D + x] = send_total(send, x, copies);
+  if (threadIdx.x == 0) w.remote_part[blockIdx.x] = send[n_send];
 }
 
 // D2: expert_offsets, rank_offsets, slot base of (block, expert) relative to the expert's first slot,
@@ -136,31 +174,70 @@ __global__ __launch_bounds__(kScanThreads) void dp_scan_kernel(int NB, int E, in
 }
 
 // D3: slot of every pair and its inverse
-__global__ __launch_bounds__(kTokBlock) void dp_slot_kernel(int T, int k, int E, const int32_t* __restrict__ ids,
+template <int KU>
+__global__ __launch_bounds__(kTokBlock) void dp_slot_kernel(int T, int k, int E, int D, const int32_t* __restrict__ ids,
                                                             const int32_t* __restrict__ shf,
                                                             const int32_t* __restrict__ phys,
                                                             int32_t* __restrict__ slot_of_pair,
                                                             int32_t* __restrict__ pair_of_slot,
                                                             const int32_t* __restrict__ expert_offsets, DispatchWs w) {
-  extern __shared__ uint32_t lds[];  // [E][kWords]
-  int q[SEMMOE_MAX_K];
-  const int tok = fill_bitmaps(T, k, E, ids, shf, phys, lds, q);
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];  // [E][kWords] bitmaps | [E] map
+  uint32_t* bm = reinterpret_cast<uint32_t*>(lds_raw);
+  int32_t* map = reinterpret_cast<int32_t*>(bm + E * kWords);
+  const int tok = token_at(T, blockIdx.x * kTokBlock + threadIdx.x, shf);
+  load_phys_map(E, E / D, phys, map);
+  zero_quads(bm, E * kWords / 4);
+  int e[KU], q[KU];
+  load_id_row(ids + size_t(max(tok, 0)) * k, k, id_quads(ids, k), e);
+  __syncthreads();
+  map_ids(e, tok >= 0, k, E, map, q);
+  set_bits<KU, kWords>(q, bm);
+  __syncthreads();
   if (tok < 0) return;
-  const int t = threadIdx.x;
+  int slot[KU];
 #pragma unroll
-  for (int j = 0; j < SEMMOE_MAX_K; ++j) {
-    if (q[j] < 0) continue;
-    const int slot = expert_offsets[q[j]] + w.cnt[size_t(blockIdx.x) * E + q[j]] + bitmap_rank(lds + q[j] * kWords, t);
-    const int pair = tok * k + j;
-    slot_of_pair[pair] = slot;
-    pair_of_slot[slot] = pair;
+  for (int j = 0; j < KU; ++j) {
+    const int at = max(q[j], 0) & 0xffff;
+    slot[j] = q[j] < 0 ? -1
+                       : expert_offsets[at] + w.cnt[size_t(blockIdx.x) * E + at] +
+                             bits_below<kWords>(bm + at * kWords, threadIdx.x);
+  }
+  store_slots(tok, k, slot, id_quads(slot_of_pair, k), slot_of_pair, pair_of_slot);
+}
+
+// Columns c_lo .. c_lo + n_cols - 1 of a [n_rows][stride] table summed into acc (LDS, zeroed by the caller) by all threads:
+// with V = 4 whole quads (c_lo, n_cols and stride multiples of four), four loads a thread in flight.
+template <int V>
+__device__ __forceinline__ void sum_some_columns(const uint32_t* __restrict__ table, int n_rows, int stride, int c_lo,
+                                                 int n_cols, uint32_t* acc) {
+  typedef __attribute__((ext_vector_type(V))) uint32_t vec_t;
+  const int t = threadIdx.x, nt = blockDim.x;
+  for (int c0 = 0; c0 < n_cols; c0 += nt * V) {
+    const int nv = min(nt, (n_cols - c0) / V), rpp = nt / nv;  // columns (of V) in this pass, rows at a time
+    const int c = c0 + t % nv * V, r0 = t / nv;
+    if (r0 >= rpp) continue;
+    vec_t s = {};
+    for (int r = r0; r < n_rows; r += 4 * rpp) {
+      vec_t x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        x[u] = r + u * rpp < n_rows ? *reinterpret_cast<const vec_t*>(table + size_t(r + u * rpp) * stride + c_lo + c) : vec_t{};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += x[u];
+    }
+#pragma unroll
+    for (int x = 0; x < V; ++x)
+      if (s[x]) atomicAdd(&acc[c + x], s[x]);
   }
 }
 
 // D2 + D3 in one launch: every workgroup sums the [NB][E] count table itself (column totals -> expert offsets,
-// prefix over the workgroups before it -> its base inside each expert) instead of waiting for a scan kernel;
-// the entries of the send matrix are summed by the workgroups in turn; workgroup 0 writes the offsets and the
-// remote-pair count.
+// prefix over the workgroups before it -> its base inside each expert) instead of waiting for a scan kernel; the entries
+// of the send matrix are dealt out to the workgroups in runs, summed by all threads of each (an entry a wave, as it was
+// before, took 1024 entries on 8 workgroups 32 rounds of exposed latency: 2048 tokens of 32 ranks as two launches 29 us, now 13).  The chain of dependent loads, the
+// tables and the LDS set-up all start together, and there are three barriers (16384 tokens, 256 experts: 13.2 -> 9.4 us);
+// workgroup 0 writes the offsets and the remote-pair count.
+template <int KU>
 __global__ __launch_bounds__(kTokBlock) void dp_fused_kernel(int T, int k, int E, int D, int NB,
                                                              const int32_t* __restrict__ ids,
                                                              const int32_t* __restrict__ shf,
@@ -172,39 +249,32 @@ __global__ __launch_bounds__(kTokBlock) void dp_fused_kernel(int T, int k, int E
                                                              uint32_t* __restrict__ send_matrix,
                                                              unsigned long long* __restrict__ remote_pairs,
                                                              DispatchWs w) {
-  extern __shared__ uint32_t lds[];  // [E][kWords] bitmaps | off[E+1] | pre[E] | remote (u64, 8-byte aligned)
-  uint32_t* bm = lds;
-  int32_t* off = reinterpret_cast<int32_t*>(lds + E * kWords);
-  int32_t* pre = off + (E + 1);
-  unsigned long long* remote_sh = reinterpret_cast<unsigned long long*>(
-      (reinterpret_cast<uintptr_t>(pre + E) + 7) & ~uintptr_t(7));
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  // [E][kWords] bitmaps | off[E+4] | pre[E] | send sums of this workgroup | remote (u64) | [E] map; all but the map zeroed
+  const int Ep = (E + 3) / 4 * 4, DD = D * D;
+  const int my_cols = DD % 4 == 0 ? (DD / 4 + NB - 1) / NB * 4 : (DD + NB - 1) / NB, colsp = (my_cols + 3) / 4 * 4;
+  uint32_t* bm = reinterpret_cast<uint32_t*>(lds_raw);
+  int32_t* off = reinterpret_cast<int32_t*>(bm + E * kWords);
+  int32_t* pre = off + Ep + 4;
+  uint32_t* send = reinterpret_cast<uint32_t*>(pre + Ep);
+  unsigned long long* remote_sh = reinterpret_cast<unsigned long long*>(send + colsp);
+  int32_t* map = reinterpret_cast<int32_t*>(send + colsp + 4);
   const int t = threadIdx.x, b = blockIdx.x;
-  // the first rows of the count table are requested before the chain of three dependent loads (shf -> ids -> phys)
+  const int tok = token_at(T, b * kTokBlock + t, shf);
   const ColumnBatch first = column_sums_first(w.cnt, NB, E);
-  int q[SEMMOE_MAX_K];
-  const int tok = load_pairs(T, k, E, ids, shf, phys, q);
-  for (int x = t; x < 2 * E + 1; x += kTokBlock) off[x] = 0;
-  if (t == 0) *remote_sh = 0ull;
+  load_phys_map(E, E / D, phys, map);
+  zero_quads(bm, (E * kWords + Ep + 4 + Ep + colsp + 4) / 4);
+  int e[KU], q[KU];
+  load_id_row(ids + size_t(max(tok, 0)) * k, k, id_quads(ids, k), e);
   __syncthreads();
-  column_sums_before(w.cnt, NB, E, b, off, pre, &first);
-  // send matrix: entry x is summed over the workgroups' partial matrices by workgroup x % NB, one wave per entry
-  // (four entries at a time: their loads are in flight together)
-  const int DD = D * D;
-  const int x_step = (kTokBlock >> 6) * NB;
-  for (int x0 = b + (t >> 6) * NB; x0 < DD; x0 += 4 * x_step) {
-    uint32_t part[4] = {0, 0, 0, 0};
-    for (int bb = t & 63; bb < NB; bb += 64)
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (x0 + u * x_step < DD) part[u] += w.send_part[size_t(bb) * DD + x0 + u * x_step];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) part[u] += __shfl_xor(part[u], o);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if ((t & 63) == 0 && x0 + u * x_step < DD) send_matrix[x0 + u * x_step] = part[u];
+  const int c_lo = b * my_cols, c_n = max(0, min(my_cols, DD - c_lo));  // a last run that is cut short is whole quads too
+  if (c_n > 0) {
+    if (DD % 4 == 0) sum_some_columns<4>(w.send_part, NB, DD, c_lo, c_n, send);
+    else sum_some_columns<1>(w.send_part, NB, DD, c_lo, c_n, send);
   }
+  column_sums_before(w.cnt, NB, E, b, off, pre, &first);
+  map_ids(e, tok >= 0, k, E, map, q);
+  set_bits<KU, kWords>(q, bm);
   if (b == 0) {  // remote pairs: sum of the workgroups' counts
     unsigned long long part = 0;
     for (int bb = t; bb < NB; bb += kTokBlock) part += w.remote_part[bb];
@@ -213,137 +283,129 @@ __global__ __launch_bounds__(kTokBlock) void dp_fused_kernel(int T, int k, int E
     if ((t & 63) == 0 && part) atomicAdd(remote_sh, part);
   }
   __syncthreads();
-  wave_exclusive_scan_lds(off, E);  // ends with a barrier
+  first_wave_exclusive_scan(off, E);
+  for (int x = t; x < c_n; x += kTokBlock) send_matrix[c_lo + x] = send[x];
+  __syncthreads();
   if (b == 0) {
     const int m = E / D;
-    for (int q = t; q <= E; q += kTokBlock) {
-      expert_offsets[q] = off[q];
-      if (q % m == 0) rank_offsets[q / m] = off[q];
+    for (int x = t; x <= E; x += kTokBlock) {
+      expert_offsets[x] = off[x];
+      if (x % m == 0) rank_offsets[x / m] = off[x];
     }
     if (t == 0) *remote_pairs = *remote_sh;
   }
-  set_bitmaps(E, bm, q);
   if (tok < 0) return;
+  int slot[KU];
 #pragma unroll
-  for (int j = 0; j < SEMMOE_MAX_K; ++j) {
-    if (q[j] < 0) continue;
-    const int slot = off[q[j]] + pre[q[j]] + bitmap_rank(bm + q[j] * kWords, t);
-    const int pair = tok * k + j;
-    slot_of_pair[pair] = slot;
-    pair_of_slot[slot] = pair;
+  for (int j = 0; j < KU; ++j) {
+    const int at = max(q[j], 0) & 0xffff;
+    slot[j] = q[j] < 0 ? -1 : off[at] + pre[at] + bits_below<kWords>(bm + at * kWords, t);
   }
+  store_slots(tok, k, slot, id_quads(slot_of_pair, k), slot_of_pair, pair_of_slot);
 }
 
-static size_t dp_fused_lds(int E) { return size_t(E) * kWords * 4 + size_t(2 * E + 1) * 4 + 16; }
+static size_t dp_count_lds(int E, int D) {
+  return size_t(E) * kWords * 4 + size_t(cdiv(D * D * send_copies(D) + 1, 4)) * 16 + size_t(E) * 4;
+}
+static size_t dp_fused_lds(int E, int D, int NB) {
+  const size_t Ep = align_up(E, 4), cols = align_up(size_t(cdiv(cdiv(D * D, 4), NB)) * 4, 4);
+  return size_t(E) * kWords * 4 + (2 * Ep + 4 + cols + 4) * 4 + size_t(E) * 4;
+}
 constexpr int kFusedMaxNB = 512;  // beyond, every block reading the whole table costs more than the scan kernel
 
-// Single-workgroup variant of the index half for T <= kSingleMaxT (one launch instead of three; small
-// kernels cost a fixed few microseconds each).  Positions are walked in chunks of 1024 in shuffled order.
-constexpr int kSingleMaxT = 32768;  // what the single-workgroup kernel can hold
-constexpr int kSingleAutoT = 2048;  // up to here it is also the faster choice (measured: one CU is slow beyond)
-constexpr int kChunk = 1024;
-
-__global__ __launch_bounds__(kChunk) void dp_single_kernel(int T, int k, int E, int D,
-                                                           const int32_t* __restrict__ ids,
-                                                           const int32_t* __restrict__ token_rank,
-                                                           const int32_t* __restrict__ shf,
-                                                           const int32_t* __restrict__ phys,
-                                                           int32_t* __restrict__ slot_of_pair,
-                                                           int32_t* __restrict__ pair_of_slot,
-                                                           int32_t* __restrict__ expert_offsets,
-                                                           int32_t* __restrict__ rank_offsets,
-                                                           uint32_t* __restrict__ send_matrix,
-                                                           unsigned long long* __restrict__ remote_pairs) {
+// One workgroup for everything, a thread a token (T <= BLK): one launch, no tables.  A small kernel's time is its chain of
+// dependent loads and barriers: one pass over the tokens, four barriers.  The bits below a token's place: with 8 words a
+// key they are counted in the bitmap, with 16 they come from a prefix over the words.
+template <int KU, int BLK>
+__global__ __launch_bounds__(BLK) void dp_small_kernel(int T, int k, int E, int D, const int32_t* __restrict__ ids,
+                                                       const int32_t* __restrict__ token_rank,
+                                                       const int32_t* __restrict__ shf,
+                                                       const int32_t* __restrict__ phys,
+                                                       int32_t* __restrict__ slot_of_pair,
+                                                       int32_t* __restrict__ pair_of_slot,
+                                                       int32_t* __restrict__ expert_offsets,
+                                                       int32_t* __restrict__ rank_offsets,
+                                                       uint32_t* __restrict__ send_matrix,
+                                                       unsigned long long* __restrict__ remote_pairs) {
+  constexpr int W = BLK / 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  // layout: off[E+1] | run[E] | ktot[E] | send[D*D] | bm[E][32] | wpre[E][32] | remote (u64)
-  int32_t* off = reinterpret_cast<int32_t*>(lds_raw);
-  int32_t* run = off + (E + 1);
-  int32_t* ktot = run + E;
-  uint32_t* send = reinterpret_cast<uint32_t*>(ktot + E);
-  uint32_t* bm = send + D * D;
-  int32_t* wpre = reinterpret_cast<int32_t*>(bm + E * 32);
-  unsigned long long* remote_sh = reinterpret_cast<unsigned long long*>(
-      (reinterpret_cast<uintptr_t>(wpre + E * 32) + 7) & ~uintptr_t(7));
-  const int t = threadIdx.x;
-  const int m = E / D;
-  for (int x = t; x <= E; x += kChunk) off[x] = 0;
-  for (int x = t; x < E; x += kChunk) run[x] = 0;
-  for (int x = t; x < D * D; x += kChunk) send[x] = 0;
-  if (t == 0) *remote_sh = 0ull;
-  __syncthreads();
-  // pair counts per physical expert and the send matrix
-  for (int pos = t; pos < T; pos += kChunk) {
-    const int tok = shf[pos];
-    if ((unsigned)tok >= (unsigned)T) continue;
-    const int s = token_rank[tok];
-    for (int j = 0; j < k; ++j) {
-      const int e = ids[size_t(tok) * k + j];
-      if ((unsigned)e >= (unsigned)E) continue;
-      const int q = phys[e];
-      if ((unsigned)q >= (unsigned)E) continue;
-      atomicAdd(&off[q], 1);
-      if ((unsigned)s < (unsigned)D) atomicAdd(&send[s * D + q / m], 1u);
-    }
-  }
-  __syncthreads();
-  wave_exclusive_scan_lds(off, E);
-  for (int q = t; q <= E; q += kChunk) {
-    expert_offsets[q] = off[q];
-    if (q % m == 0) rank_offsets[q / m] = off[q];
-  }
-  unsigned long long remote = 0;
-  for (int x = t; x < D * D; x += kChunk) {
-    send_matrix[x] = send[x];
-    if (x / D != x % D) remote += send[x];
-  }
-  if (remote) atomicAdd(remote_sh, remote);
-  __syncthreads();
-  if (t == 0) *remote_pairs = *remote_sh;
-
-  const int hw = t >> 5, w = t & 31;
-  for (int c0 = 0; c0 < T; c0 += kChunk) {
-    for (int x = t; x < E * 32; x += kChunk) bm[x] = 0;
-    __syncthreads();
-    const int pos = c0 + t;
-    int tok = -1;
-    if (pos < T) {
-      tok = shf[pos];
-      if ((unsigned)tok >= (unsigned)T) tok = -1;
-    }
-    int q[SEMMOE_MAX_K];
-    load_mapped_ids(ids + size_t(max(tok, 0)) * k, tok >= 0, k, E, phys, E, q);
+  // [E][W] bitmaps | [D*D][copies] send counts + remote pairs, whole quads | off[E+4] | [E] map | [E][W] word prefix (u16)
+  const int copies = send_copies(D), n_send = D * D * copies, send_quads = (n_send + 1 + 3) / 4;
+  const int Ep = (E + 3) / 4 * 4;
+  uint32_t* bm = reinterpret_cast<uint32_t*>(lds_raw);
+  uint32_t* send = bm + E * W;
+  int32_t* off = reinterpret_cast<int32_t*>(send + send_quads * 4);
+  int32_t* map = off + Ep + 4;
+  uint16_t* wpre = reinterpret_cast<uint16_t*>(map + E);
+  const int t = threadIdx.x, m = E / D;
+  const int tok = token_at(T, t, shf);
+  load_phys_map(E, m, phys, map);
+  zero_quads(bm, E * W / 4 + send_quads + Ep / 4 + 1);
+  int e[KU], q[KU];
+  int s = -1;
+  if (T > 0) {  // a token that is not there reads token 0's row
+    load_id_row(ids + size_t(max(tok, 0)) * k, k, id_quads(ids, k), e);
+    s = token_rank[max(tok, 0)];
+  } else {
 #pragma unroll
-    for (int j = 0; j < SEMMOE_MAX_K; ++j)
-      if (q[j] >= 0) atomicOr(&bm[q[j] * 32 + (t >> 5)], 1u << (t & 31));
-    __syncthreads();
-    for (int key = hw; key < E; key += kChunk / 32) {  // 32-word popcount prefix per expert, one half-wave each
-      const int v = __popc(bm[key * 32 + w]);
-      int incl = v;
+    for (int j = 0; j < KU; ++j) e[j] = -1;
+  }
+  __syncthreads();
+  map_ids(e, tok >= 0, k, E, map, q);
+  set_bits<KU, W>(q, bm);
+  int remote = count_send(D, tok >= 0 ? s : -1, q, send, copies);
 #pragma unroll
-      for (int o = 1; o < 32; o <<= 1) {
-        const int u = __shfl_up(incl, o, 32);
-        if (w >= o) incl += u;
+  for (int o = 32; o >= 1; o >>= 1) remote += __shfl_xor(remote, o);
+  if ((t & 63) == 0 && remote) atomicAdd(&send[n_send], (uint32_t)remote);
+  __syncthreads();
+  if constexpr (W == 8) {
+    for (int x = t; x < E; x += BLK) off[x] = bits_of<W>(bm + x * W);
+  } else {
+    static_assert(W == 16, "a key's words are a row of 16 lanes");
+    const int w = t & 15;
+    for (int key = t >> 4; key < Ep; key += BLK / 16) {  // four keys a wave: all or none of them below Ep
+      const int c = key < E ? __popc(bm[key * W + w]) : 0;
+      int incl = c;
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
+      if (key < E) {
+        wpre[key * W + w] = uint16_t(incl - c);
+        if (w == W - 1) off[key] = incl;
       }
-      wpre[key * 32 + w] = incl - v;
-      if (w == 31) ktot[key] = incl;
     }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < SEMMOE_MAX_K; ++j) {
-      if (q[j] < 0) continue;
-      const int slot = off[q[j]] + run[q[j]] + wpre[q[j] * 32 + (t >> 5)] +
-                       __popc(bm[q[j] * 32 + (t >> 5)] & ((1u << (t & 31)) - 1u));
-      const int pair = tok * k + j;
-      slot_of_pair[pair] = slot;
-      pair_of_slot[slot] = pair;
-    }
-    __syncthreads();
-    for (int x = t; x < E; x += kChunk) run[x] += ktot[x];
   }
+  for (int x = t; x < D * D; x += BLK) send_matrix[x] = send_total(send, x, copies);
+  if (t == 0) *remote_pairs = send[n_send];
+  __syncthreads();
+  first_wave_exclusive_scan(off, E);
+  __syncthreads();
+  for (int x = t; x <= E; x += BLK) {
+    expert_offsets[x] = off[x];
+    if (x % m == 0) rank_offsets[x / m] = off[x];
+  }
+  if (tok < 0) return;
+  int slot[KU];
+#pragma unroll
+  for (int j = 0; j < KU; ++j) {
+    const int at = max(q[j], 0) & 0xffff;
+    int below;
+    if constexpr (W == 8) below = bits_below<W>(bm + at * W, t);
+    else below = wpre[at * W + (t >> 5)] + __popc(bm[at * W + (t >> 5)] & ((1u << (t & 31)) - 1u));
+    slot[j] = q[j] < 0 ? -1 : off[at] + below;
+  }
+  store_slots(tok, k, slot, id_quads(slot_of_pair, k), slot_of_pair, pair_of_slot);
 }
 
-static size_t dp_single_lds(int E, int D) {
-  return size_t(E + 1 + E + E) * 4 + size_t(D) * D * 4 + size_t(E) * 32 * 4 * 2 + 16 + 8;
+// Up to here one launch is the faster form (8 experts a token, 256 experts, kernels alone: 256 tokens 6.4 us against 4.0 +
+// 7.5 as two, 512 tokens 9.4 against 4.7 + 7.8; as one workgroup of 1024 threads 1024 tokens took 17.6 against 4.7 + 7.9).
+constexpr int kSmallMaxT = 512;
+
+static size_t dp_small_lds(int E, int D, int blk) {
+  const size_t W = blk / 32, Ep = align_up(E, 4);
+  return size_t(E) * W * 4 + size_t(cdiv(D * D * send_copies(D) + 1, 4)) * 16 + (Ep + 4) * 4 + size_t(E) * 4 +
+         (blk == 512 ? size_t(E) * W * 2 : 0);
 }
 
 // D4: move rows.  One workgroup per token; each thread owns 16-byte chunks of the row.
@@ -403,41 +465,43 @@ static int32_t dispatch_index_impl(const semmoe_config* cfg, hipStream_t s, cons
   const int T = cfg->T, k = cfg->k, E = cfg->E, D = cfg->D;
   const int NB = cdiv(T, kTokBlock);
   const int path = tuning_value(SEMMOE_TUNE_INDEX_PATH);
-  if ((path != 1 && T <= kSingleAutoT) || path == 2) {
-    if (T > kSingleMaxT) return SEMMOE_EUNSUPPORTED;
-    const size_t lds = dp_single_lds(E, D);
-    static std::atomic<uint64_t> lds_allowed{0};
-    {
-      const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(dp_single_kernel));
+  unsigned long long* remote = reinterpret_cast<unsigned long long*>(remote_pairs);
+  return with_id_width(k, [&](auto ku) -> int32_t {  // KU: registers for a token's k experts
+    constexpr int KU = decltype(ku)::value;
+    if (T <= kSmallMaxT && path != 1 && path != 3) {
+      const bool narrow = T <= 256;
+      auto kern = narrow ? dp_small_kernel<KU, 256> : dp_small_kernel<KU, 512>;
+      const size_t lds = dp_small_lds(E, D, narrow ? 256 : 512);
+      static std::atomic<uint64_t> lds_allowed[2];  // one flag word per kernel, a bit per device
+      const int32_t as = allow_max_dynamic_lds(&lds_allowed[narrow], reinterpret_cast<const void*>(kern));
       if (as != SEMMOE_OK) return as;
+      hipLaunchKernelGGL(kern, dim3(1), dim3(narrow ? 256 : 512), lds, s, T, k, E, D, topk_ids, token_rank, shf,
+                         phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, rank_offsets, send_matrix, remote);
+      SEMMOE_LAUNCH_CHECK();
+      return SEMMOE_OK;
     }
-    hipLaunchKernelGGL(dp_single_kernel, dim3(1), dim3(kChunk), lds, s, T, k, E, D, topk_ids, token_rank, shf,
-                       phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, rank_offsets, send_matrix,
-                       reinterpret_cast<unsigned long long*>(remote_pairs));
+    if (NB > 0) {
+      hipLaunchKernelGGL(dp_count_kernel<KU>, dim3(NB), dim3(kTokBlock), dp_count_lds(E, D), s, T, k, E, D, topk_ids,
+                         token_rank, shf, phys_of_expert, w);
+      SEMMOE_LAUNCH_CHECK();
+    }
+    if (NB > 0 && ((path != 1 && NB <= kFusedMaxNB) || path == 3)) {
+      hipLaunchKernelGGL(dp_fused_kernel<KU>, dim3(NB), dim3(kTokBlock), dp_fused_lds(E, D, NB), s, T, k, E, D, NB,
+                         topk_ids, shf, phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, rank_offsets,
+                         send_matrix, remote, w);
+      SEMMOE_LAUNCH_CHECK();
+      return SEMMOE_OK;
+    }
+    hipLaunchKernelGGL(dp_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, NB, E, D, expert_offsets, rank_offsets,
+                       send_matrix, remote, w);
+    SEMMOE_LAUNCH_CHECK();
+    if (NB > 0) {
+      hipLaunchKernelGGL(dp_slot_kernel<KU>, dim3(NB), dim3(kTokBlock), size_t(E) * (kWords + 1) * 4, s, T, k, E, D,
+                         topk_ids, shf, phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, w);
+    }
     SEMMOE_LAUNCH_CHECK();
     return SEMMOE_OK;
-  }
-  if (NB > 0) {
-    hipLaunchKernelGGL(dp_count_kernel, dim3(NB), dim3(kTokBlock), (E * kWords + D * D + 1) * 4, s, T, k, E, D, topk_ids,
-                       token_rank, shf, phys_of_expert, w);
-    SEMMOE_LAUNCH_CHECK();
-  }
-  if (NB > 0 && ((path != 1 && NB <= kFusedMaxNB) || path == 3)) {
-    hipLaunchKernelGGL(dp_fused_kernel, dim3(NB), dim3(kTokBlock), dp_fused_lds(E), s, T, k, E, D, NB, topk_ids, shf,
-                       phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, rank_offsets, send_matrix,
-                       reinterpret_cast<unsigned long long*>(remote_pairs), w);
-    SEMMOE_LAUNCH_CHECK();
-    return SEMMOE_OK;
-  }
-  hipLaunchKernelGGL(dp_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, NB, E, D, expert_offsets, rank_offsets, send_matrix,
-                     reinterpret_cast<unsigned long long*>(remote_pairs), w);
-  SEMMOE_LAUNCH_CHECK();
-  if (NB > 0) {
-    hipLaunchKernelGGL(dp_slot_kernel, dim3(NB), dim3(kTokBlock), E * kWords * 4, s, T, k, E, topk_ids, shf,
-                       phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, w);
-  }
-  SEMMOE_LAUNCH_CHECK();
-  return SEMMOE_OK;
+  });
 }
 
 static int32_t dispatch_rows_impl(const semmoe_config* cfg, hipStream_t s, const void* X,

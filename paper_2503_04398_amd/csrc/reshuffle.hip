@@ -35,36 +35,56 @@ __device__ __forceinline__ int bitmap_rank(const uint32_t* words, int t) {
   return r;
 }
 
+// preferred rank of a token among the ranks r[] of its experts (-1: none) and how many of them sit there
+template <int KU>
+__device__ __forceinline__ void pref_of(const int (&r)[KU], int home, int* pref, int* conf) {
+  int best_r = home, best_c = 0;  // g[i, home] first: it wins every tie
+#pragma unroll
+  for (int j = 0; j < KU; ++j) best_c += (r[j] == home);
+#pragma unroll
+  for (int j = 0; j < KU; ++j) {
+    if (r[j] < 0) continue;
+    int c = 0;
+#pragma unroll
+    for (int j2 = 0; j2 < KU; ++j2) c += (r[j2] == r[j]);
+    // larger gain wins; among equal gains home stays, otherwise the smallest rank
+    if (c > best_c || (c == best_c && best_r != home && r[j] < best_r)) {
+      best_c = c;
+      best_r = r[j];
+    }
+  }
+  *pref = best_r;
+  *conf = best_c;
+}
+
+// expert -> rank into LDS (-1: outside [0, D))
+__device__ __forceinline__ void load_rank_map(int E, int D, const int32_t* __restrict__ e2r, int32_t* map) {
+  for (int x = threadIdx.x; x < E; x += blockDim.x) {
+    const int r = e2r[x];
+    map[x] = (unsigned)r < (unsigned)D ? r : -1;
+  }
+}
+
 // K1: pref / conf per token, per-block (pref, conf) histogram
+template <int KU>
 __global__ __launch_bounds__(kTokBlock) void rs_pref_kernel(int T, int k, int D, int E, int per_home,
                                                             const int32_t* __restrict__ ids,
                                                             const int32_t* __restrict__ e2r, ReshuffleWs w) {
-  extern __shared__ int32_t hist[];  // D*(k+1)
+  extern __shared__ int32_t hist[];  // D*(k+1) | [E] map
   const int nkeys = D * (k + 1);
+  int32_t* map = hist + nkeys;
+  const int i = blockIdx.x * kTokBlock + threadIdx.x;
+  int e[KU], r[KU];
+  load_id_row(ids + size_t(min(i, T - 1)) * k, k, id_quads(ids, k), e);
+  load_rank_map(E, D, e2r, map);
   for (int x = threadIdx.x; x < nkeys; x += blockDim.x) hist[x] = 0;
   __syncthreads();
-  const int i = blockIdx.x * kTokBlock + threadIdx.x;
-  int r[SEMMOE_MAX_K];
-  load_mapped_ids(ids + size_t(min(i, T - 1)) * k, i < T, k, E, e2r, D, r);
+  map_ids(e, i < T, k, E, map, r);
   if (i < T) {
-    const int home = i / per_home;
-    int best_r = home, best_c = 0;  // g[i, home] first: it wins every tie
-#pragma unroll
-    for (int j = 0; j < SEMMOE_MAX_K; ++j) best_c += (r[j] == home);
-#pragma unroll
-    for (int j = 0; j < SEMMOE_MAX_K; ++j) {
-      if (r[j] < 0) continue;
-      int c = 0;
-#pragma unroll
-      for (int j2 = 0; j2 < SEMMOE_MAX_K; ++j2) c += (r[j2] == r[j]);
-      // larger gain wins; among equal gains home stays, otherwise the smallest rank
-      if (c > best_c || (c == best_c && best_r != home && r[j] < best_r)) {
-        best_c = c;
-        best_r = r[j];
-      }
-    }
-    w.pc[i] = best_r | (best_c << 8);
-    atomicAdd(&hist[best_r * (k + 1) + best_c], 1);
+    int pref, conf;
+    pref_of(r, i / per_home, &pref, &conf);
+    w.pc[i] = pref | (conf << 8);
+    atomicAdd(&hist[pref * (k + 1) + conf], 1);
   }
   __syncthreads();
   for (int x = threadIdx.x; x < nkeys; x += blockDim.x) w.cnt[size_t(blockIdx.x) * nkeys + x] = hist[x];
@@ -340,143 +360,178 @@ __global__ __launch_bounds__(kTokBlock) void rs_scatter_kernel(int T, int D, con
 //     this block, plus every candidate below the threshold: that is the block's first global spill index S_b;
 //   * spilled tokens take the free slots in rank order, so the tokens of rank r that come before this block are
 //     its kept ones (from the prefix) plus |[0, S_b) cut with rank r's range of spill indices|.
-// Five dependent launches fewer; each costs about as much as this whole kernel.
+// Five dependent launches fewer; each costs about as much as this whole kernel.  What bounds it is the chain table -> sums ->
+// ranks -> tokens: the ranks are one wave's work in registers, the keys of a rank read at once, and between two
+// barriers no thread walks a list (16384 tokens, 32 ranks: 11.4 -> 8.0 us; 8 ranks 8.2 -> 6.2).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kTokBlock) void rs_fused_kernel(int T, int NB, int k, int D, int cap,
-                                                             int32_t* __restrict__ token_rank,
-                                                             int32_t* __restrict__ shf, int32_t* __restrict__ inv_shf,
-                                                             int32_t* __restrict__ rank_count, ReshuffleWs w) {
-  extern __shared__ int32_t fused_sm[];
-  const int nkeys = D * (k + 1);
-  int32_t* tot = fused_sm;            // [nkeys] column totals
-  int32_t* pre = tot + nkeys;         // [nkeys] totals over the blocks before this one
-  int32_t* thr = pre + nkeys;         // [D]
-  int32_t* quota = thr + D;           // [D]
-  int32_t* free_pre = quota + D;      // [D+1] free slots per rank -> exclusive prefix
-  int32_t* sp_tot = free_pre + D + 1; // [D] spilled candidates of rank r, all blocks
-  int32_t* sp_pre = sp_tot + D;       // [D] ... in the blocks before this one
-  int32_t* kept_tot = sp_pre + D;     // [D] kept candidates of rank r, all blocks
-  int32_t* kept_pre = kept_tot + D;   // [D]
-  int32_t* rstart = kept_pre + D;     // [D+1] first shuffled position of rank r
-  int32_t* rbefore = rstart + D + 1;  // [D] tokens of final rank r in the blocks before this one
-  int32_t* scal = rbefore + D;        // [2] S_b, spill bitmap guard
-  uint32_t* bm = reinterpret_cast<uint32_t*>(scal + 2);  // [D][kWords]
-  uint32_t* spbm = bm + D * kWords;                       // [kWords]
-  const int t = threadIdx.x, b = blockIdx.x;
-  // the table and the token's own word are requested before anything that waits
-  const ColumnBatch first = column_sums_first(w.cnt, NB, nkeys);
-  const int i = b * kTokBlock + t;
-  const int my_pc = w.pc[min(i, T - 1)];
+// LDS of the kernels below: tot[nkeys] | pre[nkeys] column totals, and totals over the blocks before this one; thr[D] |
+// quota[D] | free_pre[D] free slots of the ranks before | rstart[D] first shuffled position of rank r for this block; spill
+// index of the block's first spilled token; and the bitmaps of a block of BLK tokens.
+template <int BLK>
+struct AlignLds {
+  static constexpr int W = BLK / 32;
+  int32_t *tot, *pre, *thr, *quota, *free_pre, *rstart, *spill0;
+  uint32_t *border, *fin, *spill;  // [D][W] borderline candidates, [D][W] final ranks, [W] spilled tokens
+  int zero_quads;                  // from tot on: the sums and the bitmaps start at zero
+  __device__ __forceinline__ AlignLds(unsigned char* lds, int D, int nkeys) {
+    border = reinterpret_cast<uint32_t*>(lds);
+    fin = border + D * W;
+    spill = fin + D * W;
+    tot = reinterpret_cast<int32_t*>(spill + W);
+    pre = tot + nkeys;
+    zero_quads = ((2 * D + 1) * W + 2 * nkeys + 3) / 4;
+    thr = reinterpret_cast<int32_t*>(lds) + zero_quads * 4;
+    quota = thr + D;
+    free_pre = quota + D;
+    rstart = free_pre + D;
+    spill0 = rstart + D;
+  }
+  static size_t bytes(int D, int nkeys) { return size_t(((2 * D + 1) * W + 2 * nkeys + 3) / 4) * 16 + size_t(4 * D + 1) * 4; }
+};
 
-  for (int x = t; x < 2 * nkeys; x += kTokBlock) tot[x] = 0;
-  for (int x = t; x < D * kWords + kWords; x += kTokBlock) bm[x] = 0;
-  __syncthreads();
-  column_sums_before(w.cnt, NB, nkeys, b, tot, pre, &first);
-  __syncthreads();
-  if (t < D) {
-    const int r = t;
+// From the sums: what every token of the block needs to know.  By the first wave alone, a lane a rank (D <= 64), with
+// nothing written to LDS in between.
+template <int KU, int BLK>
+__device__ __forceinline__ void align_ranks(const AlignLds<BLK>& L, int k, int D, int cap, int32_t* __restrict__ rank_count) {
+  const int r = threadIdx.x;
+  if (r >= 64) return;
+  int fr = 0, s_tot = 0, s_b = 0, kept = 0, kept_b = 0;
+  if (r < D) {
+    int nt[KU + 1], np[KU + 1];
+#pragma unroll
+    for (int c = 0; c <= KU; ++c) {
+      const int at = r * (k + 1) + min(c, k);
+      nt[c] = c <= k ? L.tot[at] : 0;
+      np[c] = c <= k ? L.pre[at] : 0;
+    }
     // the confidence level at which rank r's candidates overflow cap is its borderline level (-1: all kept)
     int cum = 0, th = -1, q = 0;
-    for (int c = k; c >= 0; --c) {
-      const int n = tot[r * (k + 1) + c];
-      if (cum + n > cap) {
+#pragma unroll
+    for (int c = KU; c >= 0; --c) {
+      if (th >= 0) {  // below the borderline level: spilled
+        s_tot += nt[c];
+        s_b += np[c];
+      } else if (cum + nt[c] > cap) {
         th = c;
         q = cap - cum;
         cum = cap;
-        break;
+        s_tot += nt[c] - q;
+        s_b += max(0, np[c] - q);
+        kept_b += min(q, np[c]);
+      } else {
+        cum += nt[c];
+        kept_b += np[c];
       }
-      cum += n;
     }
-    thr[r] = th;
-    quota[r] = q;
-    free_pre[r] = cap - cum;
-    kept_tot[r] = cum;
-    int st = 0, sp = 0, kp = 0;
-    for (int c = 0; c <= k; ++c) {
-      const int nt = tot[r * (k + 1) + c], np = pre[r * (k + 1) + c];
-      if (th < 0 || c > th) kp += np;
-      else if (c < th) { st += nt; sp += np; }
-      else { st += nt - q; sp += max(0, np - q); kp += min(q, np); }
-    }
-    sp_tot[r] = st;
-    sp_pre[r] = sp;
-    kept_pre[r] = kp;
+    fr = cap - cum;
+    kept = cum;
+    L.thr[r] = th;
+    L.quota[r] = q;
   }
-  __syncthreads();
-  if (t < 64) {  // one wave: scans over the D <= 64 ranks
-    const int r = t;
-    const int fr = r < D ? free_pre[r] : 0;
-    int incl = fr, s_tot = r < D ? sp_tot[r] : 0, s_b = r < D ? sp_pre[r] : 0;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int u = __shfl_up(incl, off);
-      if (t >= off) incl += u;
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      s_tot += __shfl_xor(s_tot, off);
-      s_b += __shfl_xor(s_b, off);
-    }
-    const int fpre = incl - fr;  // spill indices [fpre, fpre + fr) land on rank r; the last rank takes any overflow
-    const bool last = r == D - 1;
-    const int a_tot = r < D ? (last ? max(0, s_tot - fpre) : min(max(s_tot - fpre, 0), fr)) : 0;
-    const int a_pre = r < D ? (last ? max(0, s_b - fpre) : min(max(s_b - fpre, 0), fr)) : 0;
-    const int cnt = r < D ? kept_tot[r] + a_tot : 0;
-    int cincl = cnt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int u = __shfl_up(cincl, off);
-      if (t >= off) cincl += u;
-    }
-    if (r < D) {
-      free_pre[r] = fpre;
-      rstart[r] = cincl - cnt;
-      rbefore[r] = kept_pre[r] + a_pre;
-      if (b == 0) rank_count[r] = cnt;
-    }
-    if (r == D - 1) free_pre[D] = incl;
-    if (t == 0) scal[0] = s_b;
+  const int incl = wave_inclusive_sum(fr);
+  const int all = __builtin_amdgcn_readlane(wave_inclusive_sum(s_tot), 63);
+  const int before = __builtin_amdgcn_readlane(wave_inclusive_sum(s_b), 63);
+  const int fpre = incl - fr;  // spill indices [fpre, fpre + fr) land on rank r; the last rank takes any overflow
+  const bool last = r == D - 1;
+  const int a_tot = r < D ? (last ? max(0, all - fpre) : min(max(all - fpre, 0), fr)) : 0;
+  const int a_pre = r < D ? (last ? max(0, before - fpre) : min(max(before - fpre, 0), fr)) : 0;
+  const int cnt = kept + a_tot;
+  const int cincl = wave_inclusive_sum(cnt);
+  if (r < D) {
+    L.free_pre[r] = fpre;
+    L.rstart[r] = cincl - cnt + kept_b + a_pre;
+    if (blockIdx.x == 0) rank_count[r] = cnt;
   }
-  __syncthreads();
+  if (r == 0) *L.spill0 = before;
+}
 
-  // keep phase: borderline candidates are ranked inside the block by their bitmap
-  int pref = 0, conf = 0, th = -1;
-  if (i < T) {
-    pref = my_pc & 0xff;
-    conf = my_pc >> 8;
-    th = thr[pref];
-    if (th >= 0 && conf == th) atomicOr(&bm[pref * kWords + (t >> 5)], 1u << (t & 31));
-  }
+// Keep, spill and scatter for the block's token `t` (i, where here): the barriers are the workgroup's.
+template <int BLK>
+__device__ __forceinline__ void align_token(const AlignLds<BLK>& L, bool here, int i, int pref, int conf, int k, int D,
+                                            int32_t* __restrict__ token_rank, int32_t* __restrict__ shf,
+                                            int32_t* __restrict__ inv_shf) {
+  constexpr int W = BLK / 32;
+  const int t = threadIdx.x;
+  const uint32_t bit = 1u << (t & 31);
+  // borderline candidates are ranked inside the block by their bitmap
+  const int th = here ? L.thr[pref] : -1;
+  const bool border = th >= 0 && conf == th;
+  if (border) atomicOr(&L.border[pref * W + (t >> 5)], bit);
   __syncthreads();
   int rank = -1;
-  if (i < T) {
-    bool kept;
-    if (th < 0 || conf > th) kept = true;
-    else if (conf < th) kept = false;
-    else kept = pre[pref * (k + 1) + th] + bitmap_rank(bm + pref * kWords, t) < quota[pref];
+  if (here) {
+    bool kept = th < 0 || conf > th;
+    if (border) kept = L.pre[pref * (k + 1) + th] + bits_below<W>(L.border + pref * W, t) < L.quota[pref];
     if (kept) rank = pref;
-    else atomicOr(&spbm[t >> 5], 1u << (t & 31));
+    atomicOr(kept ? &L.fin[pref * W + (t >> 5)] : &L.spill[t >> 5], bit);
   }
   __syncthreads();
-  for (int x = t; x < D * kWords; x += kTokBlock) bm[x] = 0;  // the bitmaps now take the final ranks
-  if (i < T && rank < 0) {
-    const int s = scal[0] + bitmap_rank(spbm, t);
-    int r = 0;
-    while (r + 1 < D && free_pre[r + 1] <= s) ++r;  // free_pre[r] <= s < free_pre[r+1]
-    rank = r;
+  if (here && rank < 0) {
+    const int s = *L.spill0 + bits_below<W>(L.spill, t);
+    rank = 0;  // the last rank with free_pre[rank] <= s
+    for (int step = 32; step > 0; step >>= 1)
+      if (rank + step < D && L.free_pre[rank + step] <= s) rank += step;
+    atomicOr(&L.fin[rank * W + (t >> 5)], bit);
   }
   __syncthreads();
-  if (i < T) {
+  if (here) {
+    const int pos = L.rstart[rank] + bits_below<W>(L.fin + rank * W, t);
     token_rank[i] = rank;
-    atomicOr(&bm[rank * kWords + (t >> 5)], 1u << (t & 31));
-  }
-  __syncthreads();
-  if (i < T) {
-    const int pos = rstart[rank] + rbefore[rank] + bitmap_rank(bm + rank * kWords, t);
     inv_shf[i] = pos;
     shf[pos] = i;
   }
 }
+
+template <int KU>
+__global__ __launch_bounds__(kTokBlock) void rs_fused_kernel(int T, int NB, int k, int D, int cap,
+                                                             int32_t* __restrict__ token_rank,
+                                                             int32_t* __restrict__ shf, int32_t* __restrict__ inv_shf,
+                                                             int32_t* __restrict__ rank_count, ReshuffleWs w) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char align_sm[];
+  const int nkeys = D * (k + 1), b = blockIdx.x, i = b * kTokBlock + threadIdx.x;
+  const AlignLds<kTokBlock> L(align_sm, D, nkeys);
+  // the table and the token's own word are requested before anything that waits
+  const ColumnBatch first = column_sums_first(w.cnt, NB, nkeys);
+  const int my_pc = w.pc[min(i, T - 1)];
+  for (int x = threadIdx.x; x < L.zero_quads; x += kTokBlock) reinterpret_cast<uint4*>(align_sm)[x] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  column_sums_before(w.cnt, NB, nkeys, b, L.tot, L.pre, &first);
+  __syncthreads();
+  align_ranks<KU>(L, k, D, cap, rank_count);
+  __syncthreads();
+  align_token(L, i < T, i, my_pc & 0xff, my_pc >> 8, k, D, token_rank, shf, inv_shf);
+}
+
+// The whole of rebatch_tokens in one workgroup, a thread a token (T <= BLK): one launch, the histogram in LDS.
+template <int KU, int BLK>
+__global__ __launch_bounds__(BLK) void rs_small_kernel(int T, int k, int D, int E, int cap, int per_home,
+                                                       const int32_t* __restrict__ ids, const int32_t* __restrict__ e2r,
+                                                       int32_t* __restrict__ token_rank, int32_t* __restrict__ shf,
+                                                       int32_t* __restrict__ inv_shf, int32_t* __restrict__ rank_count) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char align_sm[];
+  const int nkeys = D * (k + 1), i = threadIdx.x;
+  const AlignLds<BLK> L(align_sm, D, nkeys);
+  int32_t* map = L.spill0 + 1;  // [E]
+  int e[KU], r[KU];
+  load_id_row(ids + size_t(min(i, T - 1)) * k, k, id_quads(ids, k), e);
+  load_rank_map(E, D, e2r, map);
+  for (int x = i; x < L.zero_quads; x += BLK) reinterpret_cast<uint4*>(align_sm)[x] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  map_ids(e, i < T, k, E, map, r);
+  int pref = 0, conf = 0;
+  if (i < T) {
+    pref_of(r, i / per_home, &pref, &conf);
+    atomicAdd(&L.tot[pref * (k + 1) + conf], 1);
+  }
+  __syncthreads();
+  align_ranks<KU>(L, k, D, cap, rank_count);
+  __syncthreads();
+  align_token(L, i < T, i, pref, conf, k, D, token_rank, shf, inv_shf);
+}
+
+// Up to here one launch is the faster form (8 experts a token, 32 ranks, kernels alone: 256 tokens 5.2 us against 3.1 + 5.2 as
+// two, 512 tokens 6.3 against 3.4 + 5.6; as one workgroup of 1024 threads 1024 tokens took 11.1 against 3.6 + 5.7).
+constexpr int kSmallMaxT = 512;
 
 // ------------------------------------------------------------------------------------------------
 // Gain-aware spill rounds (the refinement of `align` towards the objective of Sec. 3.3: the most local pairs
@@ -693,187 +748,7 @@ static size_t rs_round_lds(int D, int k) {
   return (size_t(3) * D * (k + 1) + size_t(D) * 8 + 2 + 2 + size_t(D) * kWords + kWords) * 4;
 }
 
-static size_t rs_fused_lds(int D, int k) {
-  return (size_t(2) * D * (k + 1) + size_t(D) * 9 + 2 + 2 + size_t(D) * kWords + kWords) * 4;
-}
 constexpr int kFusedMaxNB = 512;  // beyond, every block reading the whole table costs more than the scan kernels
-
-// ------------------------------------------------------------------------------------------------
-// Single-workgroup variant for T <= kSingleMaxT: the whole of rebatch_tokens in one launch, every
-// intermediate in LDS.  Tokens are walked in chunks of 1024 (one per thread) in index order; inside a chunk
-// the stable rank of a token among equal keys is again "popcount of the key's bitmap below the token",
-// with a 32-word prefix per key computed by half-waves; across chunks a running count per key.
-// Small kernels here cost a fixed few microseconds each, so for small batches one launch beats seven.
-// ------------------------------------------------------------------------------------------------
-constexpr int kSingleMaxT = 32768;  // what the single-workgroup kernel can hold
-constexpr int kSingleAutoT = 2048;  // up to here it is also the faster choice (measured: one CU is slow beyond)
-constexpr int kChunk = 1024;
-
-struct SingleLds {
-  uint16_t pc[kSingleMaxT];                 // pref | conf << 8
-  uint8_t tr[kSingleMaxT];                  // rank of the token, 0xFF while spilled
-  uint32_t bm[SEMMOE_MAX_D + 1][32];        // chunk bitmaps per key (last row: spilled tokens)
-  int32_t wpre[SEMMOE_MAX_D + 1][32];       // exclusive popcount prefix over the 32 words of a key
-  int32_t ktot[SEMMOE_MAX_D + 1];           // tokens of the key in the chunk
-  int32_t hist[SEMMOE_MAX_D * (SEMMOE_MAX_K + 1)];
-  int32_t thr[SEMMOE_MAX_D], quota[SEMMOE_MAX_D], free_pre[SEMMOE_MAX_D + 1];
-  int32_t border_run[SEMMOE_MAX_D], rank_cnt[SEMMOE_MAX_D + 1], rank_run[SEMMOE_MAX_D];
-  int32_t spill_run, any_border, any_spill;
-};
-
-// bitmaps of keys [key_lo, key_hi) are set: per key the exclusive prefix of word popcounts and the key total.
-// Half-wave h of the workgroup handles keys key_lo + h, key_lo + h + 32, ...  Ends with a barrier.
-__device__ __forceinline__ void chunk_word_prefix(SingleLds& L, int key_lo, int key_hi) {
-  const int hw = threadIdx.x >> 5, w = threadIdx.x & 31;
-  for (int key = key_lo + hw; key < key_hi; key += kChunk / 32) {
-    const int v = __popc(L.bm[key][w]);
-    int incl = v;
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1) {
-      const int t = __shfl_up(incl, off, 32);
-      if (w >= off) incl += t;
-    }
-    L.wpre[key][w] = incl - v;
-    if (w == 31) L.ktot[key] = incl;
-  }
-  __syncthreads();
-}
-
-__device__ __forceinline__ int chunk_rank(const SingleLds& L, int key, int t) {
-  return L.wpre[key][t >> 5] + __popc(L.bm[key][t >> 5] & ((1u << (t & 31)) - 1u));
-}
-
-__global__ __launch_bounds__(kChunk) void rs_single_kernel(int T, int k, int D, int E, int cap, int per_home,
-                                                           const int32_t* __restrict__ ids,
-                                                           const int32_t* __restrict__ e2r,
-                                                           int32_t* __restrict__ token_rank,
-                                                           int32_t* __restrict__ shf, int32_t* __restrict__ inv_shf,
-                                                           int32_t* __restrict__ rank_count) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  SingleLds& L = *reinterpret_cast<SingleLds*>(lds_raw);
-  const int t = threadIdx.x;
-  const int nkeys = D * (k + 1);
-  for (int x = t; x < nkeys; x += kChunk) L.hist[x] = 0;
-  if (t <= D) L.rank_cnt[t] = 0;
-  if (t < D) { L.border_run[t] = 0; L.rank_run[t] = 0; }
-  if (t == 0) { L.spill_run = 0; L.any_border = 0; L.any_spill = 0; }
-  __syncthreads();
-
-  // pref / conf per token and the (pref, conf) histogram
-  for (int i = t; i < T; i += kChunk) {
-    int r[SEMMOE_MAX_K];
-    load_mapped_ids(ids + size_t(i) * k, true, k, E, e2r, D, r);
-    const int home = i / per_home;
-    int best_r = home, best_c = 0;
-#pragma unroll
-    for (int j = 0; j < SEMMOE_MAX_K; ++j) best_c += (r[j] == home);
-#pragma unroll
-    for (int j = 0; j < SEMMOE_MAX_K; ++j) {
-      if (r[j] < 0) continue;
-      int c = 0;
-#pragma unroll
-      for (int j2 = 0; j2 < SEMMOE_MAX_K; ++j2) c += (r[j2] == r[j]);
-      if (c > best_c || (c == best_c && best_r != home && r[j] < best_r)) {
-        best_c = c;
-        best_r = r[j];
-      }
-    }
-    L.pc[i] = (uint16_t)(best_r | (best_c << 8));
-    atomicAdd(&L.hist[best_r * (k + 1) + best_c], 1);
-  }
-  __syncthreads();
-
-  // thresholds per rank (see rs_threshold_kernel), free-slot prefix
-  if (t < D) {
-    int cum = 0, thr = -1, quota = 0;
-    for (int c = k; c >= 0; --c) {
-      const int n = L.hist[t * (k + 1) + c];
-      if (cum + n > cap) {
-        thr = c;
-        quota = cap - cum;
-        cum = cap;
-        break;
-      }
-      cum += n;
-    }
-    L.thr[t] = thr;
-    L.quota[t] = quota;
-    L.free_pre[t] = cap - cum;
-    if (thr >= 0) L.any_border = 1;
-  }
-  __syncthreads();
-  wave_exclusive_scan_lds(L.free_pre, D);
-  const bool any_border = L.any_border != 0;
-
-  // keep + spill, chunk by chunk
-  for (int c0 = 0; c0 < T; c0 += kChunk) {
-    const int i = c0 + t;
-    int pref = 0, conf = 0, thr = -1;
-    bool kept = true, border = false;
-    if (i < T) {
-      pref = L.pc[i] & 0xff;
-      conf = L.pc[i] >> 8;
-      thr = L.thr[pref];
-      border = thr >= 0 && conf == thr;
-      kept = thr < 0 || conf > thr;  // borderline tokens are decided below
-    }
-    if (any_border) {
-      for (int x = t; x < (D + 1) * 32; x += kChunk) (&L.bm[0][0])[x] = 0;
-      __syncthreads();
-      if (border) atomicOr(&L.bm[pref][t >> 5], 1u << (t & 31));
-      __syncthreads();
-      chunk_word_prefix(L, 0, D);
-      if (border) kept = L.border_run[pref] + chunk_rank(L, pref, t) < L.quota[pref];
-      const bool spilled = i < T && !kept;
-      if (spilled) atomicOr(&L.bm[D][t >> 5], 1u << (t & 31));
-      __syncthreads();
-      if (t < D) L.border_run[t] += L.ktot[t];
-      chunk_word_prefix(L, D, D + 1);
-      int rank = pref;
-      if (spilled) {
-        const int sidx = L.spill_run + chunk_rank(L, D, t);
-        int r = 0;
-        while (r + 1 < D && L.free_pre[r + 1] <= sidx) ++r;
-        rank = r;
-      }
-      if (i < T) {
-        L.tr[i] = (uint8_t)rank;
-        atomicAdd(&L.rank_cnt[rank], 1);
-      }
-      __syncthreads();
-      if (t == 0) L.spill_run += L.ktot[D];
-    } else if (i < T) {
-      L.tr[i] = (uint8_t)pref;
-      atomicAdd(&L.rank_cnt[pref], 1);
-    }
-  }
-  __syncthreads();
-  for (int r = t; r < D; r += kChunk) rank_count[r] = L.rank_cnt[r];
-  __syncthreads();
-  wave_exclusive_scan_lds(L.rank_cnt, D);  // now the first position of each rank
-
-  // stable scatter by rank
-  for (int c0 = 0; c0 < T; c0 += kChunk) {
-    const int i = c0 + t;
-    for (int x = t; x < D * 32; x += kChunk) (&L.bm[0][0])[x] = 0;
-    __syncthreads();
-    int rank = 0;
-    if (i < T) {
-      rank = L.tr[i];
-      atomicOr(&L.bm[rank][t >> 5], 1u << (t & 31));
-    }
-    __syncthreads();
-    chunk_word_prefix(L, 0, D);
-    if (i < T) {
-      const int pos = L.rank_cnt[rank] + L.rank_run[rank] + chunk_rank(L, rank, t);
-      token_rank[i] = rank;
-      inv_shf[i] = pos;
-      shf[pos] = i;
-    }
-    __syncthreads();
-    if (t < D) L.rank_run[t] += L.ktot[t];
-  }
-}
 
 // ---- moves of placed tokens until the assignment has the most local pairs the capacity bound allows ----------------
 // (communication term of the Sec. 3.3 objective for a fixed placement; `align` of Alg. 3 as the bound.)  An assignment
@@ -1253,6 +1128,30 @@ size_t ws_reshuffle(const semmoe_config* cfg) {
 
 using namespace semmoe;
 
+static void launch_pref(const semmoe_config* cfg, hipStream_t s, int per_home, const int32_t* topk_ids,
+                        const int32_t* expert_to_rank, const ReshuffleWs& w) {
+  const size_t lds = (size_t(cfg->D) * (cfg->k + 1) + cfg->E) * 4;
+  with_id_width(cfg->k, [&](auto ku) -> int32_t {
+    hipLaunchKernelGGL(rs_pref_kernel<decltype(ku)::value>, dim3(cdiv(cfg->T, kTokBlock)), dim3(kTokBlock), lds, s, cfg->T,
+                       cfg->k, cfg->D, cfg->E, per_home, topk_ids, expert_to_rank, w);
+    return SEMMOE_OK;
+  });
+}
+
+static int32_t launch_fused(const semmoe_config* cfg, hipStream_t s, int32_t* token_rank, int32_t* shf, int32_t* inv_shf,
+                            int32_t* rank_count, const ReshuffleWs& w) {
+  const int NB = cdiv(cfg->T, kTokBlock);
+  if (cfg->D > 64) return SEMMOE_EUNSUPPORTED;  // a lane a rank
+  const size_t lds = AlignLds<kTokBlock>::bytes(cfg->D, cfg->D * (cfg->k + 1));
+  with_id_width(cfg->k, [&](auto ku) -> int32_t {
+    hipLaunchKernelGGL(rs_fused_kernel<decltype(ku)::value>, dim3(NB), dim3(kTokBlock), lds, s, cfg->T, NB, cfg->k, cfg->D,
+                       cfg->cap, token_rank, shf, inv_shf, rank_count, w);
+    return SEMMOE_OK;
+  });
+  SEMMOE_LAUNCH_CHECK();
+  return SEMMOE_OK;
+}
+
 static int32_t reshuffle_with_scratch(const semmoe_config* cfg, void* stream, const int32_t* topk_ids,
                                       const int32_t* expert_to_rank, int32_t* token_rank, int32_t* shf,
                                       int32_t* inv_shf, int32_t* rank_count, void* ws, size_t ws_bytes) {
@@ -1275,27 +1174,20 @@ static int32_t reshuffle_with_scratch(const semmoe_config* cfg, void* stream, co
   const int per_home = cdiv(T, D);
   const int nkeys = D * (k + 1);
   const int path = tuning_value(SEMMOE_TUNE_INDEX_PATH);
-  if ((path != 1 && T <= kSingleAutoT && D < 255) || path == 2) {
-    if (T > kSingleMaxT || D >= 255) return SEMMOE_EUNSUPPORTED;
-    static std::atomic<uint64_t> lds_allowed{0};
-    {
-      const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(rs_single_kernel));
-      if (as != SEMMOE_OK) return as;
-    }
-    hipLaunchKernelGGL(rs_single_kernel, dim3(1), dim3(kChunk), sizeof(SingleLds), s, T, k, D, cfg->E, cfg->cap,
-                       per_home, topk_ids, expert_to_rank, token_rank, shf, inv_shf, rank_count);
-    SEMMOE_LAUNCH_CHECK();
-    return SEMMOE_OK;
+  if (T <= kSmallMaxT && path != 1 && path != 3) {
+    return with_id_width(k, [&](auto ku) -> int32_t {  // KU: registers for a token's k experts
+      constexpr int KU = decltype(ku)::value;
+      const bool narrow = T <= 256;
+      auto kern = narrow ? rs_small_kernel<KU, 256> : rs_small_kernel<KU, 512>;
+      const size_t lds = (narrow ? AlignLds<256>::bytes(D, nkeys) : AlignLds<512>::bytes(D, nkeys)) + size_t(cfg->E) * 4;
+      hipLaunchKernelGGL(kern, dim3(1), dim3(narrow ? 256 : 512), lds, s, T, k, D, cfg->E, cfg->cap, per_home, topk_ids,
+                         expert_to_rank, token_rank, shf, inv_shf, rank_count);
+      SEMMOE_LAUNCH_CHECK();
+      return SEMMOE_OK;
+    });
   }
-  hipLaunchKernelGGL(rs_pref_kernel, dim3(NB), dim3(kTokBlock), nkeys * 4, s, T, k, D, cfg->E, per_home, topk_ids,
-                     expert_to_rank, w);
-  if ((path != 1 && NB <= kFusedMaxNB) || path == 3) {
-    if (D > 64) return SEMMOE_EUNSUPPORTED;
-    hipLaunchKernelGGL(rs_fused_kernel, dim3(NB), dim3(kTokBlock), rs_fused_lds(D, k), s, T, NB, k, D, cfg->cap,
-                       token_rank, shf, inv_shf, rank_count, w);
-    SEMMOE_LAUNCH_CHECK();
-    return SEMMOE_OK;
-  }
+  launch_pref(cfg, s, per_home, topk_ids, expert_to_rank, w);
+  if ((path != 1 && NB <= kFusedMaxNB) || path == 3) return launch_fused(cfg, s, token_rank, shf, inv_shf, rank_count, w);
   hipLaunchKernelGGL(rs_threshold_kernel, dim3(1), dim3(kScanThreads), 0, s, NB, k, D, cfg->cap, w);
   hipLaunchKernelGGL(rs_keep_kernel, dim3(NB), dim3(kTokBlock), (D * kWords + 1) * 4, s, T, D, token_rank, w);
   hipLaunchKernelGGL(rs_assign_kernel, dim3(NB), dim3(kTokBlock), (kWords + D + 1) * 4, s, T, D, token_rank, w);
@@ -1378,10 +1270,8 @@ extern "C" int32_t semmoe_reshuffle_rounds(const semmoe_config* cfg, void* strea
   if (NB > kFusedMaxNB) return SEMMOE_EUNSUPPORTED;  // every workgroup reads the whole count table
   if (rounds > D) rounds = D;                        // D rounds place everything a proposal can place
   const int per_home = cdiv(T, D);
-  const int nkeys = D * (k + 1);
   const size_t lds = rs_round_lds(D, k);
-  hipLaunchKernelGGL(rs_pref_kernel, dim3(NB), dim3(kTokBlock), nkeys * 4, s, T, k, D, cfg->E, per_home, topk_ids,
-                     expert_to_rank, w);
+  launch_pref(cfg, s, per_home, topk_ids, expert_to_rank, w);
   for (int r = 0; r < rounds; ++r) {
     const int32_t* tin = (r % 2 == 0) ? w.cnt : w.cnt2;
     int32_t* tout = (r % 2 == 0) ? w.cnt2 : w.cnt;
@@ -1405,10 +1295,7 @@ static int32_t finish_from_preferences(const semmoe_config* cfg, hipStream_t s, 
                                        int32_t* shf, int32_t* inv_shf, int32_t* rank_count, const ReshuffleWs& w) {
   const int T = cfg->T, D = cfg->D, k = cfg->k;
   if (NB <= kFusedMaxNB && D <= 64) {
-    hipLaunchKernelGGL(rs_fused_kernel, dim3(NB), dim3(kTokBlock), rs_fused_lds(D, k), s, T, NB, k, D, cfg->cap,
-                       token_rank, shf, inv_shf, rank_count, w);
-    SEMMOE_LAUNCH_CHECK();
-    return SEMMOE_OK;
+    return launch_fused(cfg, s, token_rank, shf, inv_shf, rank_count, w);
   }
   hipLaunchKernelGGL(rs_threshold_kernel, dim3(1), dim3(kScanThreads), 0, s, NB, k, D, cfg->cap, w);
   hipLaunchKernelGGL(rs_keep_kernel, dim3(NB), dim3(kTokBlock), (D * kWords + 1) * 4, s, T, D, token_rank, w);

@@ -77,4 +77,32 @@ __device__ __forceinline__ void wave_exclusive_scan_lds(int32_t* v, int n) {
   __syncthreads();
 }
 
+// inclusive sum over the lanes of a wave (all 64 active): row shifts, then lane 15 of rows 0 / 2 into rows 1 / 3 and lane
+// 31 into rows 2 and 3
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// exclusive scan of n <= 512 ints in LDS by the first wave (the others return at once; the caller places the barrier);
+// v is 16-byte aligned, has room for n + 4 entries and zeros from n to the next multiple of four; v[n] = total
+__device__ __forceinline__ void first_wave_exclusive_scan(int32_t* v, int n) {
+  if (threadIdx.x >= 64) return;
+  const int nq = (n + 3) / 4, per = nq > 64 ? 2 : 1, q0 = int(threadIdx.x) * per;
+  i32x4_t* v4 = reinterpret_cast<i32x4_t*>(v);
+  const i32x4_t zero = {0, 0, 0, 0};
+  const i32x4_t a = q0 < nq ? v4[q0] : zero, b = per == 2 && q0 + 1 < nq ? v4[q0 + 1] : zero;
+  const int sa = a[0] + a[1] + a[2] + a[3], sb = b[0] + b[1] + b[2] + b[3];
+  const int incl = wave_inclusive_sum(sa + sb);
+  const int ra = incl - sa - sb, rb = ra + sa;
+  if (q0 < nq) v4[q0] = i32x4_t{ra, ra + a[0], ra + a[0] + a[1], ra + a[0] + a[1] + a[2]};
+  if (per == 2 && q0 + 1 < nq) v4[q0 + 1] = i32x4_t{rb, rb + b[0], rb + b[0] + b[1], rb + b[0] + b[1] + b[2]};
+  if (threadIdx.x == 63) v[n] = incl;
+}
+
 }  // namespace semmoe
