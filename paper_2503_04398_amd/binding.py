@@ -7,6 +7,7 @@ device memory and streams, nothing else.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -32,6 +33,9 @@ class _CConfig(C.Structure):
                 ("D", C.c_int32), ("dtype", C.c_int32), ("score", C.c_int32), ("renorm", C.c_int32),
                 ("n_group", C.c_int32), ("topk_group", C.c_int32), ("routed_scale", C.c_float),
                 ("cap", C.c_int32), ("num_classes", C.c_int32)]
+
+
+_config_values = operator.attrgetter(*(name for name, _ in _CConfig._fields_))
 
 
 class CoschedParams(C.Structure):
@@ -145,16 +149,22 @@ def _ptr(t):
     """device (or host) pointer of a torch tensor / numpy array / None / int"""
     if t is None:
         return None
+    get = getattr(t, "data_ptr", None)
+    if get is not None:
+        assert t.is_contiguous(), "tensors must be contiguous"
+        return get()
     if isinstance(t, int):
         return t
-    if hasattr(t, "data_ptr"):
-        assert t.is_contiguous(), "tensors must be contiguous"
-        return t.data_ptr()
     return t.ctypes.data
 
 
 def _stream():
+    """handle of torch's current stream on the current device.  A call costs the host a few microseconds, as much as a
+    small kernel; once torch has initialised the GPU the handle comes without the availability check and the stream
+    object around it (2.4 us of a call that took 9.7)."""
     import torch
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
 
 
@@ -168,6 +178,7 @@ class SemMoE:
         self.ws = None
         self.ws_bytes = 0
         self.ws_shared = None
+        self._c_config = None  # (values, C struct of them)
         if allocate_workspace:
             import torch
             self.ws_bytes = self.workspace_bytes()
@@ -179,6 +190,14 @@ class SemMoE:
             raise SemMoEError(name, st, self.lib.semmoe_last_hip_error())
 
     def _cfg(self, **over):
+        # the C struct of the config's present values: built again when any of them has changed, read by the library and
+        # written by nobody, so that a call does not fill fourteen fields through ctypes
+        values = _config_values(self.cfg)
+        kept = self._c_config
+        if kept is None or kept[0] != values:
+            self._c_config = kept = (values, self.cfg.c())
+        if not over:
+            return kept[1]
         c = self.cfg.c()
         for k_, v in over.items():
             setattr(c, k_, v)
