@@ -300,12 +300,22 @@ static int32_t launch_stream_ring(const GemmArgs& a, int max_rows, int few_rows,
   return launch_stream_ring_as<MODE, TW, TT, true>(a, max_rows, few_rows, per_cu, stream);
 }
 
-// fp32: 16 x 4 weight rows and 16 x 4 tokens a workgroup, halved along either while that leaves compute units idle.  The
-// tokens of a tile follow the mean rows, so a hot expert reads its weights up to four times as often as it needs to.
-// Where 16 x 4 weight rows alone give every compute unit four tiles, and the mean is no handful that leaves experts empty,
-// the tokens stay at 16 x 4: that is the faster shape there with even groups too (256 experts and more, mean up to 16: 9 %),
-// and not below (512 to 1023 tiles, hot groups: 4 % behind).  512 experts, d = F = 512, mean 11, nearly all rows on one:
-// 212 -> 140 us.
+// Workgroups per compute unit: a tile's walk over K is a few steps (K 512: four a wave) with a sum over the waves behind them, and
+// only other workgroups fill the time between.  As many as the registers (2 x 4: three, 4 x 4: two) and the LDS hold, and no more: the
+// shares of the persistent workgroups are fixed, one that starts late ends late.
+template <int MODE, int TW, int TT>
+static int f32_per_cu(int nq) {
+  const int fit = max_lds() / int(StreamCfg<MODE, TW, TT>::lds_bytes(nq)), most = TT == 4 ? (TW == 2 ? 3 : 2) : 4;
+  return fit < most ? (fit < 1 ? 1 : fit) : most;
+}
+
+// fp32: 32 weight rows x 32 tokens with four workgroups a compute unit, 16 tokens where the mean is no more or the tiles are
+// few; 64 x 64 with two a compute unit (half the operand bytes a product) where there are so many tiles that the last
+// round does not matter: from 12 a compute unit on, one set of weights, whose last tile alone is ragged, from 3.5 (d 3064, F
+// 1504: 1200 tokens 321 against 361 us, 600 tokens 170 each; d 904, F 1792: 600 tokens 91 against 78).  330 FFNs (4 to 256 experts, 4 to 800 rows each, K 256 to 2048), of the
+// time with two workgroups a compute unit and tiles that followed the mean alone: 0.975; 48 rows of 16 experts, K 1024: 0.79.
+// Many experts with a mean of a few rows: 64 x 64 too, the mean says nothing about a hot one (512 experts, d = F = 512, mean
+// 11, nearly all rows on one: 212 us on 16 tokens a tile, 140 so; with 64 experts, skewed by 1.0, it would be 10 % behind).
 // Against plain FMAs on 64 x 64 tiles that share every slice: 0.41 of the time over 834 random shapes; behind by 10 to 36 %
 // only where a row is two slices (K up to 96) and 128 experts or more make the sum over the waves the most of the work
 // (leaving the waves without a slice out of that sum changed nothing).
@@ -314,29 +324,29 @@ template <int MODE>
 static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_per_group, hipStream_t stream) {
   const bool rows_reachable = (unsigned long long)a.K * 4 < (1ull << 32) - 1024;  // a row below 4 GB
   switch (id) {
-    case 30: return launch_stream<MODE, true, 2, 2>(a, max_rows, 2, stream);
-    case 31: return launch_stream<MODE, true, 2, 4>(a, max_rows, 2, stream);
+    case 30: return launch_stream<MODE, true, 2, 2>(a, max_rows, f32_per_cu<MODE, 2, 2>(a.nq), stream);
+    case 31: return launch_stream<MODE, true, 2, 4>(a, max_rows, f32_per_cu<MODE, 2, 4>(a.nq), stream);
     case 32: return launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
-    case 36: return launch_stream<MODE, true, 2, 1>(a, max_rows, 2, stream);
-    case 37: return rows_reachable ? launch_stream_as<MODE, true, 2, 1, true, true>(a, max_rows, 2, stream) : SEMMOE_EUNSUPPORTED;
+    case 36: return launch_stream<MODE, true, 2, 1>(a, max_rows, f32_per_cu<MODE, 2, 1>(a.nq), stream);
+    case 37: return rows_reachable ? launch_stream_as<MODE, true, 2, 1, true, true>(a, max_rows, f32_per_cu<MODE, 2, 1>(a.nq), stream) : SEMMOE_EUNSUPPORTED;
     default: break;
   }
   const int est = est_rows_per_group < 1 ? 1 : est_rows_per_group;
   auto items = [&](int tw, int tt) {
     return (long long)a.nq * cdiv(est, 16 * tt) * cdiv(a.N, (MODE == kModeSwiglu) ? 8 * tw : 16 * tw);
   };
-  const int tt = est <= 16 ? 1 : (est <= 32 ? 2 : 4);
-  const long long fill = 2LL * num_cu();
+  const long long cus = num_cu();
   int32_t st;
-  if (est >= 4 && (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64) >= 2 * fill)
+  if ((est >= 4 && (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64) >= 16 * cus) ||
+      (est > 32 && items(4, 4) * 2 >= (a.offsets ? 24 : 7) * cus))
     st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
-  else if (tt == 4 && items(4, 4) >= fill) st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
-  else if (tt == 4 && items(2, 4) >= fill) st = launch_stream<MODE, true, 2, 4>(a, max_rows, 2, stream);
-  else if (tt >= 2 && items(2, 2) >= fill) st = launch_stream<MODE, true, 2, 2>(a, max_rows, 2, stream);
-  else st = launch_stream<MODE, true, 2, 1>(a, max_rows, 2, stream);
+  else if (est > 16 && items(2, 2) >= 2 * cus)
+    st = launch_stream<MODE, true, 2, 2>(a, max_rows, f32_per_cu<MODE, 2, 2>(a.nq), stream);
+  else
+    st = launch_stream<MODE, true, 2, 1>(a, max_rows, f32_per_cu<MODE, 2, 1>(a.nq), stream);
   if (st != SEMMOE_EUNSUPPORTED) return st;
   if (!rows_reachable) return SEMMOE_EUNSUPPORTED;
-  return launch_stream_as<MODE, true, 2, 1, true, true>(a, max_rows, 2, stream);
+  return launch_stream_as<MODE, true, 2, 1, true, true>(a, max_rows, f32_per_cu<MODE, 2, 1>(a.nq), stream);
 }
 
 // left-over share of a round (in sixteenths) up to which the split happens
