@@ -83,8 +83,8 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     (0, 3, 4, 6: register-staged; 11, 12, 14, 15, 16: direct-to-LDS ring; 17, 18: skinny register-staged tiles;
  *     19, 25, 26, 27: skinny tiles with a direct-to-LDS ring for decode;
  *     28: 128 x 128 pieces throughout (the default for many rows while bigger tiles would leave compute units idle);
- *     30, 31, 32: weights streamed through registers, 32 weight rows x 32 tokens, 32 x 64 or 64 x 64 (30 and 31: the
- *     default for few rows of one set of weights); 34, 35: groups of up to 64 rows so (32 x 64 or 64 x 64), the others as
+ *     30, 31, 32: weights streamed through registers, 32 weight rows x 32 tokens, 32 x 64 or 64 x 64; 38, 39,
+ *     40: the same with eight waves a workgroup, 32 x 32, 64 x 32 or 64 x 64 (the default for few rows of one set of weights); 34, 35: groups of up to 64 rows so (32 x 64 or 64 x 64), the others as
  *     26 in the same launch (the default for few rows per expert and a deep product); 33: four waves on a 256 x 128 tile
  *     (the default for middling groups with tiles for the whole chip);
  *     20, 21, 22: four waves on a 256 x 256 tile with loads placed between the MFMAs; K must be a multiple of the

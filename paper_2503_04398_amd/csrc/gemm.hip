@@ -236,14 +236,14 @@ static int big_tile_grid(const GemmArgs& a, int max_rows, int feat) {
   return grid_for(bound, num_cu());
 }
 
-template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE>
+template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE, int NW = 4>
 static int32_t launch_stream_as(const GemmArgs& a, int max_rows, int per_cu, hipStream_t stream) {
-  using C = StreamCfg<MODE, TW, TT>;
+  using C = StreamCfg<MODE, TW, TT, NW>;
   const long long bound = (long long)(max_rows / C::BT + a.nq) * cdiv(a.N, C::FEAT);
   if (bound <= 0) return SEMMOE_OK;
   const size_t lds = C::lds_bytes(a.nq);
   const int grid = grid_for(bound, (long long)num_cu() * per_cu);
-  auto kern = gemm_stream_kernel<MODE, F32, TW, TT, KTAIL, WIDE>;
+  auto kern = gemm_stream_kernel<MODE, F32, TW, TT, KTAIL, WIDE, NW>;
   if (lds > size_t(max_lds())) return SEMMOE_EUNSUPPORTED;
   if (lds > 48 * 1024) {
     static std::atomic<uint64_t> lds_allowed{0};  // one flag word per instantiation, a bit per device
@@ -256,14 +256,14 @@ static int32_t launch_stream_as(const GemmArgs& a, int max_rows, int per_cu, hip
 }
 
 // SEMMOE_EUNSUPPORTED where 32-bit offsets do not reach every row: fp32 then takes the wide form, bf16 another tile
-template <int MODE, bool F32, int TW, int TT>
+template <int MODE, bool F32, int TW, int TT, int NW = 4>
 static int32_t launch_stream(const GemmArgs& a, int max_rows, int per_cu, hipStream_t stream) {
   const unsigned long long es = F32 ? 4 : 2, row_bytes = a.K * es;
   const unsigned long long w_rows = (MODE == kModeSwiglu) ? 2ull * a.N : a.N, x_rows = StreamCfg<MODE, TW, TT>::BT;
   if (w_rows * a.ldw * es >= (1ull << 31) || x_rows * a.ldx * es >= (1ull << 31)) return SEMMOE_EUNSUPPORTED;
-  if (row_bytes % 128 == 0 && row_bytes >= 128 * StreamCfg<MODE, TW, TT>::NW)
-    return launch_stream_as<MODE, F32, TW, TT, false, false>(a, max_rows, per_cu, stream);
-  return launch_stream_as<MODE, F32, TW, TT, true, false>(a, max_rows, per_cu, stream);
+  if (row_bytes % 128 == 0 && row_bytes >= 128 * NW)
+    return launch_stream_as<MODE, F32, TW, TT, false, false, NW>(a, max_rows, per_cu, stream);
+  return launch_stream_as<MODE, F32, TW, TT, true, false, NW>(a, max_rows, per_cu, stream);
 }
 
 // Groups of up to `few_rows` rows streamed, the others as 128 x 64 tiles, in one launch
@@ -392,6 +392,14 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
       if (st != SEMMOE_EUNSUPPORTED) return st;
       return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);  // panels beyond 32-bit offsets
     }
+    // ... with eight waves a workgroup, one workgroup a compute unit
+    case 38: case 39: case 40: {
+      const int32_t st = id == 38   ? launch_stream<MODE, false, 2, 2, 8>(a, max_rows, bpc > 0 ? bpc : 1, s)
+                         : id == 39 ? launch_stream<MODE, false, 4, 2, 8>(a, max_rows, bpc > 0 ? bpc : 1, s)
+                                    : launch_stream<MODE, false, 4, 4, 8>(a, max_rows, bpc > 0 ? bpc : 1, s);
+      if (st != SEMMOE_EUNSUPPORTED) return st;
+      return launch_bf16_tile<MODE>(26, a, max_rows, 0, s);
+    }
     // streamed up to so many rows per group that the ring of case 26 reads the weights less often
     case 34: case 35: {
       const int32_t st = id == 34 ? launch_stream_ring<MODE, 2, 4>(a, max_rows, 64, bpc > 0 ? bpc : 2, s)
@@ -471,9 +479,17 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //     256 x 256 tiles, 1134 as 128 x 64).
 // Rows that are no whole 128 bytes: neighbouring slices share cache lines, and from about ten rows on the staged tiles
 // read them at the better rate (10 rows of d 2832: 191 against 208).
-// One set of weights (the shared expert) with so few rows that these would leave most compute units idle is bound by the
-// latency of its walk over K: streamed in small tiles with K cut between the waves (64 rows of C: 39 us against 85 as
-// 128 x 64 tiles), and beyond 256 rows on 128 x 128 pieces (300 rows: A 30 B 47 C 78; streamed 21 42 98).  2000 rows of
+// One set of weights (the shared expert) on few rows has so few tiles that a compute unit gets one, and its speed is what
+// the waves of that one keep in flight: eight waves a workgroup, each an eighth of K, and the smallest tile that still
+// leaves one a compute unit (38: 32 x 32, 39: 64 x 32, 40: 64 x 64; each step halves or so the operand bytes that all
+// tiles draw from L2, 15 TB/s of which is what they then wait for).  Four waves -> eight, FFN in us: C 16 rows 37 -> 28, 64
+// rows 42 -> 35; 64 x 64 against 32 x 32 with four waves: C 256 rows 68 -> 54, B 300 rows 48 -> 36, against 128 x 64 pieces A 300
+// rows 29 -> 21, d 4096, F 256, 512 rows 39 -> 20.  Sixteen waves have fewer registers each than the loads need (C 16 rows
+// 33); K below 1024 is three steps a wave or less (d 640, F 384: 11.0 with four waves, 12.4 with eight).  Beyond
+// one tile a compute unit: up to 128 rows four waves on 32 x 32, two workgroups a compute unit; else 128 x 128 pieces as long as
+// they are one round (C, down, 640 rows: 140 tiles of 256 x 128 are 8 % ahead of two rounds of pieces; B, 1024 rows: 128
+// tiles 15 % behind one); 64 x 64 with four waves where the weight rows lie 8 KB or a multiple apart (as K 2048 below; B, gate/up,
+// 640 rows: 63 us with pieces, 53 so).  188 shapes (d, F 256 to 20000, 1 to 2048 rows): 0.83 of the time before.  2000 rows of
 // it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.  256 x 256 tiles are ahead of 256 x 128
 // from three fifths of the compute units on (170 to 190 of them: 2 to 4 %; 130 to 150: 2 % behind); 2514 rows of d 6968,
 // F 1312, gate/up without whole slices: 248 us for the FFN with pieces, 331 with 256 x 256 tiles on less than half of the chip.
@@ -483,7 +499,13 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
   const bool whole_slices = a.K % 64 == 0 && a.K / 64 >= 3;  // what the tiles with a running load stream need
   const int big_tile = (long long)(max_rows / 256 + a.nq) * t256 * 2 >= cus ? 22 : 28;
   if (!a.offsets) {
-    if ((long long)cdiv(est, 128) * t256 * 4 < 3 * cus) return est <= 160 ? 30 : (est <= 256 ? 31 : 28);
+    auto tiles = [&](int w, int t) { return (long long)cdiv(w_rows, w) * cdiv(est, t); };
+    if (tiles(32, 32) <= cus) return a.K >= 1024 ? 38 : 30;
+    if (tiles(64, 32) <= cus) return 39;
+    if (tiles(64, 64) <= cus) return 40;
+    if (tiles(64, 64) <= 2 * cus && a.K >= 4096 && (a.K & (a.K - 1)) == 0 && w_rows >= 2 * est) return 32;
+    if (est <= 128 && t256 * 4 < 3 * cus) return 30;
+    if (tiles(256, 128) * 2 <= cus) return est <= 256 && !whole_slices ? 31 : 28;
     if (!whole_slices) return est < 96 ? 26 : (est < 192 ? 0 : big_tile);
     return est < 384 || (long long)cdiv(est, 256) * t256 * 5 < 3 * cus ? 33 : 22;
   }

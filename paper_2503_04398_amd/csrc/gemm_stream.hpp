@@ -12,6 +12,8 @@
 //     one step ahead into registers; waits are counted by the compiler per register;
 //   * a step's registers go through a few KB of LDS that belong to the wave alone, to change from load layout to
 //     fragment layout (16-byte chunks swizzled by the row: no bank conflicts);
+//   * eight waves (bf16, one set of weights) where the tiles are so few that each compute unit gets one: then the waves of one
+//     workgroup are all that is in flight;
 //   * the load stream does not stop at a tile's end: the steps past it are the first ones of the workgroup's next
 //     tile, so the epilogue (partial sums of the four waves through LDS) runs under loads in flight.
 // fp32 (v_mfma_f32_16x16x4_f32: full fp32 products and sums): a lane's 16 bytes are four k of its row, used by four
@@ -24,9 +26,9 @@ namespace semmoe {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
-template <int MODE, int TW, int TT>
+template <int MODE, int TW, int TT, int NWAVES = 4>
 struct StreamCfg {
-  static constexpr int NW = 4, kThreads = 64 * NW;
+  static constexpr int NW = NWAVES, kThreads = 64 * NW;
   static constexpr int BT = 16 * TT;
   static constexpr int FEAT = (MODE == kModeSwiglu) ? TW * 8 : TW * 16;
   static constexpr int kStgWave = (TW + TT) * 2048;  // one step of one wave
@@ -65,10 +67,10 @@ __device__ __forceinline__ f32x4_t stream_mfma(u32x4_t w, u32x4_t x, f32x4_t c) 
 // KTAIL: K is not a multiple of a slice (128 bytes of a row) or gives some wave no slice at all: addresses are clamped
 // into the row and what lies behind its end counts as zero.  WIDE: rows so long, or so many, that 32-bit offsets from the
 // panels' first rows do not reach them all (64-bit addresses per lane; with KTAIL only).
-template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false, bool SIZED = false>
+template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false, bool SIZED = false, int NWAVES = 4>
 __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned char* lds_raw, int skip = 0) {
   static_assert(KTAIL || !WIDE, "the wide form clamps every address");
-  using C = StreamCfg<MODE, TW, TT>;
+  using C = StreamCfg<MODE, TW, TT, NWAVES>;
   constexpr int NW = C::NW;
   using off_t = std::conditional_t<WIDE, uint64_t, uint32_t>;
   constexpr int ES = F32 ? 4 : 2;          // bytes of an element
@@ -295,10 +297,10 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
   }
 }
 
-template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false>
-__global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmArgs a) {
+template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW, NW > 8 ? 4 : 2) void gemm_stream_kernel(const GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_stream_body<MODE, F32, TW, TT, KTAIL, WIDE>(a, lds_raw);
+  gemm_stream_body<MODE, F32, TW, TT, KTAIL, WIDE, false, NW>(a, lds_raw);
 }
 
 // The rows of each group live on the device, and the mean the host expects can be far off: the ranks of an affinity

@@ -220,3 +220,32 @@ def test_one_set_of_weights(n):
     m.shared_ffn(X.to(H.DEV), n, gu.to(H.DEV), dn.to(H.DEV), Y)
     gate, up = X.double() @ gu[:F].double().t(), X.double() @ gu[F:].double().t()
     H.assert_close(H.to_np(Y), ((gate * torch.sigmoid(gate) * up) @ dn.double().t()).numpy(), "bf16", "Y_shared")
+
+
+# eight waves a workgroup: whole slices for every wave (512 / 1024), a partial one, fewer slices than waves; by id on ragged
+# groups, so that tiles of many sizes follow each other, and as the shared expert's own choice on both sides of its lines
+@pytest.mark.parametrize("d,F", [(512, 1024), (264, 296), (72, 24), (1032, 8)])
+@pytest.mark.parametrize("tile,cap", [(38, -1), (38, 3), (39, -1), (39, 8), (40, -1), (40, 5)])
+def test_eight_waves(tile, cap, d, F):
+    knobs = ((0, tile), (1, tile), (4, cap))
+    got, want, mine = _ffn(RAGGED, d, F, "bf16", knobs=knobs, seed=tile + d)
+    _check(got, want, mine, "bf16")
+    again, _, _ = _ffn(RAGGED, d, F, "bf16", knobs=knobs, seed=tile + d)
+    assert (got[mine] == again[mine]).all()
+
+
+@pytest.mark.parametrize("n,d,F", [(1, 1024, 1032), (129, 1024, 1032), (130, 1000, 2048), (256, 1024, 2048), (257, 1024, 4096),
+                                   (520, 4096, 2048), (128, 256, 8200), (130, 200, 8200), (700, 256, 2600)])
+def test_one_set_of_weights_by_tiles(n, d, F):
+    g = torch.Generator().manual_seed(n + d)
+    X, gu, dn = (torch.empty(shape).normal_(0, std, generator=g).bfloat16()
+                 for std, shape in ((1.0, (n, d)), (0.05, (2 * F, d)), (0.05, (d, F))))
+    m = S.SemMoE(S.Config(T=n, d=d, E=2, k=1, F=F, D=1, dtype="bf16", cap=n))
+    Y = torch.empty(n, d, dtype=torch.bfloat16, device=H.DEV)
+    m.shared_ffn(X.to(H.DEV), n, gu.to(H.DEV), dn.to(H.DEV), Y)
+    x, w, v = (t.to(H.DEV).double() for t in (X, gu, dn))
+    gate, up = x @ w[:F].t(), x @ w[F:].t()
+    want = (gate * torch.sigmoid(gate) * up) @ v.t()
+    H.assert_close(H.to_np(Y), want.cpu().numpy(), "bf16", "Y_shared")
+    off = ((Y.double() - want).norm(dim=1) / want.norm(dim=1)).max().item()
+    assert off <= ROW_TOL["bf16"], off
