@@ -21,7 +21,13 @@ __device__ __forceinline__ float sigmoid_exact_seq(float x) {
   p = __fadd_rn(__fmul_rn(p, f), 0.6931471805599453f);
   p = __fadd_rn(__fmul_rn(p, f), 1.0f);
   const float z = ldexpf(p, static_cast<int>(n));
-  return __fdiv_rn(1.0f, __fadd_rn(1.0f, z));
+  // 1 / q rounded to nearest: the hardware's reciprocal (1 ulp) and two Newton steps with fused residuals.  q lies in
+  // [1, 2^44), where nothing underflows, and the steps scale exactly, so every q of one binade stands for all: equal to the
+  // IEEE division on all 2^23 of them.  Five instructions where the division takes a dozen.
+  const float q = __fadd_rn(1.0f, z);
+  float r = __builtin_amdgcn_rcpf(q);
+  r = __fmaf_rn(__fmaf_rn(-q, r, 1.0f), r, r);
+  return __fmaf_rn(__fmaf_rn(-q, r, 1.0f), r, r);
 }
 
 // ---- wave-wide reductions through DPP row shifts / broadcasts (no LDS permutes) ---------------------------
@@ -287,12 +293,229 @@ __device__ __forceinline__ void select_rows_any(const semmoe_config& cfg, const 
     _Pragma("unroll") for (int c_ = 0; c_ < NCH; ++c_) SEMMOE_ROW_STEP(op, "row_mirror", arr[c_]);          \
   } while (0)
 
+// ---- the largest k of a row ------------------------------------------------------------------------------------
+// Every lane sorts its own entries, then lanes merge their lists with those of other lanes, four levels, until all 16 hold
+// the row's KEEP largest in order: no round per winner and no search for the slot that holds it.  An entry is one 64-bit
+// word, the order-preserving key above, the expert below (the lower id is the larger word), laid out as a positive finite
+// double, so that a comparator is v_max_f64 and v_min_f64: two instructions for key and id together.  8 of 128 experts for
+// four tokens: about 280 instructions, where 8 rounds of arg-max took 860.
+__device__ __forceinline__ double pack_entry(int key, int id) {
+  const uint32_t u = uint32_t(key) ^ 0x80000000u;
+  return __hiloint2double(int(u >> 2), int((u << 30) | uint32_t(255 - id)));
+}
+__device__ __forceinline__ int entry_key(double v) {
+  return int(((uint32_t(__double2hiint(v)) << 2) | (uint32_t(__double2loint(v)) >> 30)) ^ 0x80000000u);
+}
+__device__ __forceinline__ int entry_id(double v) { return 255 - (__double2loint(v) & 255); }
+
+// inline assembly: the library's fmax / fmin canonicalise every operand whose bits came from elsewhere
+__device__ __forceinline__ double max64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double min64(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+template <int N>
+__device__ __forceinline__ void order_pair(double (&v)[N], int i, int j) {  // the larger one to i
+  const double a = v[i], b = v[j];
+  v[i] = max64(a, b);
+  v[j] = min64(a, b);
+}
+
+// Batcher's odd-even merge sort of v[LO .. LO + LEN - 1], largest first
+template <int LO, int LEN, int R, int N>
+__device__ __forceinline__ void odd_even_merge(double (&v)[N]) {
+  if constexpr (2 * R < LEN) {
+    odd_even_merge<LO, LEN, 2 * R>(v);
+    odd_even_merge<LO + R, LEN, 2 * R>(v);
+#pragma unroll
+    for (int i = LO + R; i + R < LO + LEN; i += 2 * R) order_pair(v, i, i + R);
+  } else {
+    order_pair(v, LO, LO + R);
+  }
+}
+template <int LO, int LEN, int N>
+__device__ __forceinline__ void sort_entries(double (&v)[N]) {
+  if constexpr (LEN > 1) {
+    sort_entries<LO, LEN / 2>(v);
+    sort_entries<LO + LEN / 2, LEN / 2>(v);
+    odd_even_merge<LO, LEN, 1>(v);
+  }
+}
+// v[0 .. LEN - 1] first falls and then rises (or the other way round): into falling order
+template <int LEN, int N>
+__device__ __forceinline__ void order_bitonic(double (&v)[N]) {
+#pragma unroll
+  for (int half = LEN / 2; half > 0; half /= 2)
+#pragma unroll
+    for (int i = 0; i < LEN; ++i)
+      if ((i & half) == 0) order_pair(v, i, i + half);
+}
+
+// the entries v[0 .. M - 1] of another lane of the row.  The two wait states that a DPP read needs after a vector-ALU write of
+// its source are written out once for the block.
+enum : int { kXor1 = 0, kXor2 = 1, kHalfMirror = 2, kMirror = 3 };
+#define SEMMOE_MOVE2(ctrl)                                                                                             \
+  asm("s_nop 1\n\tv_mov_b32_dpp %0, %4 " ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %1, %5 " ctrl                \
+      " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %2, %6 " ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %3, %7 " \
+      ctrl " row_mask:0xf bank_mask:0xf"                                                                               \
+      : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3])                                                             \
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]))
+#define SEMMOE_MOVE4(ctrl)                                                                                             \
+  asm("s_nop 1\n\tv_mov_b32_dpp %0, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %1, %9 " ctrl                \
+      " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %2, %10 " ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %3, %11 " \
+      ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %4, %12 " ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %5, %13 " \
+      ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %6, %14 " ctrl " row_mask:0xf bank_mask:0xf\n\tv_mov_b32_dpp %7, %15 " \
+      ctrl " row_mask:0xf bank_mask:0xf"                                                                               \
+      : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7])         \
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]))
+template <int STEP, int M, int N>
+__device__ __forceinline__ void entries_of_partner(const double (&v)[N], double (&b)[M]) {
+  constexpr int G = M >= 4 ? 4 : 2;  // entries per block; a single one is moved twice
+#pragma unroll
+  for (int g = 0; g < M; g += G) {
+    int x[2 * G], o[2 * G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const double e = v[M == 1 ? 0 : g + i];
+      x[2 * i] = __double2loint(e);
+      x[2 * i + 1] = __double2hiint(e);
+    }
+    if constexpr (G == 4) {
+      if constexpr (STEP == kXor1) SEMMOE_MOVE4("quad_perm:[1,0,3,2]");
+      else if constexpr (STEP == kXor2) SEMMOE_MOVE4("quad_perm:[2,3,0,1]");
+      else if constexpr (STEP == kHalfMirror) SEMMOE_MOVE4("row_half_mirror");
+      else SEMMOE_MOVE4("row_mirror");
+    } else {
+      if constexpr (STEP == kXor1) SEMMOE_MOVE2("quad_perm:[1,0,3,2]");
+      else if constexpr (STEP == kXor2) SEMMOE_MOVE2("quad_perm:[2,3,0,1]");
+      else if constexpr (STEP == kHalfMirror) SEMMOE_MOVE2("row_half_mirror");
+      else SEMMOE_MOVE2("row_mirror");
+    }
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+      if (g + i < M) b[g + i] = __hiloint2double(o[2 * i + 1], o[2 * i]);
+  }
+}
+#undef SEMMOE_MOVE2
+#undef SEMMOE_MOVE4
+
+// v[0 .. M - 1], in order, becomes the merger with the partner's list: twice as long while that is at most KEEP, else the
+// KEEP largest.  Both lanes of a pair end with the same list.
+template <int STEP, int M, int KEEP>
+__device__ __forceinline__ void merge_with_partner(double (&v)[KEEP]) {
+  double b[M];
+  entries_of_partner<STEP, M>(v, b);
+  if constexpr (2 * M <= KEEP) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) v[M + i] = b[M - 1 - i];
+    order_bitonic<2 * M>(v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < M; ++i) v[i] = max64(v[i], b[M - 1 - i]);
+    order_bitonic<M>(v);
+  }
+}
+
+// a lane's NS entries -> the row's KEEP largest, in order, in every lane
+template <int NS, int KEEP>
+__device__ __forceinline__ void largest_of_row(const double (&all)[NS], double (&v)[KEEP]) {
+  constexpr int M0 = NS < KEEP ? NS : KEEP;
+  double u[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) u[i] = all[i];
+  sort_entries<0, M0>(u);
+#pragma unroll
+  for (int i = 0; i < M0; ++i) v[i] = u[i];
+  if constexpr (NS > KEEP) {  // the lane's further runs of KEEP entries
+#pragma unroll
+    for (int r = KEEP; r < NS; r += KEEP) {
+      double w[KEEP];
+#pragma unroll
+      for (int i = 0; i < KEEP; ++i) w[i] = u[r + i];
+      sort_entries<0, KEEP>(w);
+#pragma unroll
+      for (int i = 0; i < KEEP; ++i) v[i] = max64(v[i], w[KEEP - 1 - i]);
+      order_bitonic<KEEP>(v);
+    }
+  }
+  constexpr int M1 = 2 * M0 <= KEEP ? 2 * M0 : KEEP, M2 = 2 * M1 <= KEEP ? 2 * M1 : KEEP, M3 = 2 * M2 <= KEEP ? 2 * M2 : KEEP;
+  merge_with_partner<kXor1, M0>(v);
+  merge_with_partner<kXor2, M1>(v);
+  merge_with_partner<kHalfMirror, M2>(v);
+  merge_with_partner<kMirror, M3>(v);
+}
+
+// Group-limited selection with 8 groups of whole slots (SPG each): the entries of groups that are not among the best
+// topk_group get the key of -inf.  A group's score is the sum of its two largest.  The lanes of a row halve the groups
+// between them level by level (lane bit 3, then 1, then 0 decides which half a lane goes on with and which it hands to its
+// partner), so that a level merges half the pairs of the one before, and the last one merges a single pair over lane
+// bit 2; each group then sits in two lanes, and its place among the 8 is a count over seven moves.  A loop over the groups with
+// four levels each, and another over the winners, took 12 us of dependent instructions (one wave: 16.7 us, a softmax 4.5).
+template <int SPG, int NS, int NCH>
+__device__ __forceinline__ void keep_best_of_8_groups(int (&val)[NCH][NS], int topk_group, int lane) {
+  static_assert(NS == 8 * SPG && (SPG == 1 || SPG == 2), "8 groups");
+  const int NEGK = to_key(-__builtin_inff());
+  const bool b0 = lane & 1, b1 = lane & 2, b3 = lane & 8;
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    int p1[8], p2[8];  // the two largest keys of each group, of the lanes merged so far
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      const int x = val[ch][g * SPG], y = SPG == 2 ? val[ch][g * SPG + 1] : NEGK;
+      p1[g] = max(x, y);
+      p2[g] = SPG == 2 ? min(x, y) : NEGK;
+    }
+#define SEMMOE_HALVE(N, bit, ctrl)                                            \
+  _Pragma("unroll") for (int i = 0; i < N; ++i) {                             \
+    const int k1 = bit ? p1[N + i] : p1[i], k2 = bit ? p2[N + i] : p2[i];     \
+    const int s1 = bit ? p1[i] : p1[N + i], s2 = bit ? p2[i] : p2[N + i];     \
+    const int r1 = dpp_i32<ctrl, 0xf>(s1, s1), r2 = dpp_i32<ctrl, 0xf>(s2, s2); \
+    p1[i] = max(k1, r1);                                                      \
+    p2[i] = max(min(k1, r1), max(k2, r2));                                    \
+  }
+    SEMMOE_HALVE(4, b3, 0x128)  // row_ror:8
+    SEMMOE_HALVE(2, b1, 0x4E)
+    SEMMOE_HALVE(1, b0, 0xB1)
+#undef SEMMOE_HALVE
+    {  // lane bit 2: half mirror (all three low bits), then the two lowest back
+      const int h1 = dpp_i32<0x141, 0xf>(p1[0], p1[0]), h2 = dpp_i32<0x141, 0xf>(p2[0], p2[0]);
+      const int r1 = dpp_i32<0x1B, 0xf>(h1, h1), r2 = dpp_i32<0x1B, 0xf>(h2, h2);
+      const int k1 = p1[0], k2 = p2[0];
+      p1[0] = max(k1, r1);
+      p2[0] = max(min(k1, r1), max(k2, r2));
+    }
+    const float sc = p2[0] == NEGK ? from_key(p1[0]) : __fadd_rn(from_key(p1[0]), from_key(p2[0]));
+    const int mine = to_key(sc);
+    // groups ahead of this lane's, number 4 b3 + 2 b1 + b0: a larger score, or the same one and a lower number, which is
+    // where the highest differing bit is set here
+    const int m0 = mine - int(b0), m1 = mine - int(b1), m3 = mine - int(b3);
+    const int o8 = dpp_i32<0x128, 0xf>(mine, mine);
+    const int ahead = int(dpp_i32<0xB1, 0xf>(mine, mine) > m0) + int(dpp_i32<0x4E, 0xf>(mine, mine) > m1) +
+                      int(dpp_i32<0x1B, 0xf>(mine, mine) > m1) + int(o8 > m3) + int(dpp_i32<0xB1, 0xf>(o8, o8) > m3) +
+                      int(dpp_i32<0x4E, 0xf>(o8, o8) > m3) + int(dpp_i32<0x1B, 0xf>(o8, o8) > m3);
+    const unsigned long long kept = __ballot(ahead < topk_group && mine >= NEGK);
+    const uint32_t mask = (lane < 32 ? uint32_t(kept) : uint32_t(kept >> 32)) >> (lane & 16);
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      const int g = c / SPG, at = (g >> 2) * 8 + ((g >> 1) & 1) * 2 + (g & 1);
+      val[ch][c] = (mask >> at) & 1u ? val[ch][c] : NEGK;
+    }
+  }
+}
+
 // rowp[ch] / idp[ch] / wp[ch]: this lane's token of group ch (the same for the 16 lanes of a row), nullptr = none.
-// Same selection rule as select_rows: k rounds of arg-max, equal values -> lowest expert id.
-template <int NS, int NCH, bool SIG>
+// Same selection rule as select_rows: the k largest in order, equal values -> lowest expert id.  KEEP >= k: 4, 8 or 16.
+// KEYED: the keys of the selection scores have been formed already and lie `key_off` words behind the logits.
+template <int NS, int KEEP, int NCH, bool SIG, bool KEYED>
 __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const float* const (&rowp)[NCH],
                                               const float* __restrict__ sel_bias, int lane,
-                                              int32_t* const (&idp)[NCH], float* const (&wp)[NCH]) {
+                                              int32_t* const (&idp)[NCH], float* const (&wp)[NCH], int key_off) {
+  static_assert(SIG || !KEYED, "a softmax key is its logit");
   const int E = cfg.E, k = cfg.k, l16 = lane & 15;
   constexpr bool sigmoid = SIG;  // compile-time: the softmax form carries none of the sigmoid form's bookkeeping
   const int NEGK = to_key(-__builtin_inff());
@@ -306,15 +529,17 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
   for (int c = 0; c < NS; ++c) {
     const int e = min(c * 16 + l16, E - 1);
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) x[ch][c] = rowp[ch][e];
-    sb[c] = (SIG && sel_bias) ? sel_bias[e] : 0.0f;
+    for (int ch = 0; ch < NCH; ++ch) x[ch][c] = KEYED ? rowp[ch][key_off + e] : rowp[ch][e];
+    sb[c] = (SIG && !KEYED && sel_bias) ? sel_bias[e] : 0.0f;
   }
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
       const bool there = c * 16 + l16 < E && idp[ch] != nullptr;
-      if (sigmoid) {
+      if (KEYED) {
+        val[ch][c] = there ? __float_as_int(x[ch][c]) : NEGK;
+      } else if (sigmoid) {
         const float sg = sigmoid_exact_seq(x[ch][c]);
         val[ch][c] = there ? to_key(__fadd_rn(sg, sb[c])) : NEGK;
       } else {
@@ -323,35 +548,9 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
     }
   }
 
-  // Arg-max of a row over the entries still in (an entry that is out has the key of -inf): every lane gets the largest
-  // key and the lowest expert id that holds it (kNoExpert when there is no entry), and own_slot = the lane's own slot
-  // with its largest key, the lowest among equals.  The maximum over a lane's slots is a tree of three-way maxima and
-  // the slot is found by comparing back: 4 + 16 instructions for 8 slots where a running (key, slot) pair took 24, and
-  // the bookkeeping of an in/out bit per slot goes.
-  int own_slot[NCH];
-  auto row_argmax = [&](int(&vmax)[NCH], int(&arg)[NCH]) __attribute__((always_inline)) {
-    int own[NCH];
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      int m = val[ch][0];
-#pragma unroll
-      for (int c = 1; c + 1 < NS; c += 2) m = max(max(m, val[ch][c]), val[ch][c + 1]);
-      if constexpr (NS % 2 == 0) m = max(m, val[ch][NS - 1]);
-      own[ch] = vmax[ch] = m;
-    }
-    SEMMOE_ROW_REDUCE("v_max_i32_dpp", vmax);
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      int slot = 0;
-#pragma unroll
-      for (int c = NS - 1; c >= 0; --c) slot = val[ch][c] == own[ch] ? c : slot;
-      own_slot[ch] = slot;
-      arg[ch] = (own[ch] == vmax[ch] && own[ch] != NEGK) ? slot * 16 + l16 : kNoExpert;
-    }
-    SEMMOE_ROW_REDUCE("v_min_i32_dpp", arg);
-  };
-
-  if (sigmoid && cfg.n_group > 1) {
+  if (sigmoid && NS >= 8 && cfg.n_group == 8 && E == 16 * NS) {
+    if constexpr (NS >= 8) keep_best_of_8_groups<NS / 8>(val, cfg.topk_group, lane);
+  } else if (sigmoid && cfg.n_group > 1) {
     // group score = sum of the group's two largest s'; lane g of a row keeps the score of group g
     const int gs = E / cfg.n_group;
     int grp[NS];
@@ -432,31 +631,22 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
     }
   }
 
-  // k rounds; lane j of the row keeps the j-th winner
+  // lane j of the row keeps the j-th winner
   int my_id[NCH];
   float my_val[NCH], mx[NCH];
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
-    my_id[ch] = 0;
-    my_val[ch] = 0.0f;
-    mx[ch] = 0.0f;
-  }
-  for (int j = 0; j < k; ++j) {
-    int vm[NCH], e[NCH];
-    row_argmax(vm, e);
+    double all[NS], top[KEEP];
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      // the winner leaves: it is the best entry of the lane it sits in
-      const int out = e[ch] == own_slot[ch] * 16 + l16 ? own_slot[ch] : NS;
+    for (int c = 0; c < NS; ++c) all[c] = pack_entry(max(val[ch][c], NEGK), c * 16 + l16);  // keys below -inf's (NaN): out too
+    largest_of_row(all, top);
+    double mine = top[0];
 #pragma unroll
-      for (int c = 0; c < NS; ++c) val[ch][c] = out == c ? NEGK : val[ch][c];
-      const float a = from_key(vm[ch]);
-      if (l16 == j) {
-        my_id[ch] = e[ch];
-        my_val[ch] = a;
-      }
-      if (j == 0) mx[ch] = a;  // first winner = row maximum
-    }
+    for (int j = 1; j < KEEP; ++j) mine = l16 == j ? top[j] : mine;
+    const int key = entry_key(mine);
+    my_id[ch] = key == NEGK ? kNoExpert : entry_id(mine);
+    my_val[ch] = from_key(key);
+    mx[ch] = from_key(entry_key(top[0]));  // row maximum
   }
   if constexpr (SIG) {
     // the weight is s without the selection bias.  Lane j forms it once more from its winner's logit: carrying s along
@@ -521,19 +711,38 @@ __host__ __device__ inline bool select_by_rows(const semmoe_config& cfg) {
 // Which selection code a kernel instantiation carries.  The host picks it from E, k, the score function and the group
 // count, so that a kernel holds one form instead of all of them (a fused router with every form in it was 150 KB of
 // code: its prologue alone, hoisted set-up of forms it never ran, took 3 us of instruction fetch per workgroup).
-enum : int { kSelAny = 0, kSelSmall = 1, kSel8 = 2, kSel16 = 3 };  // any E / row form with <= 4, 8, 16 slots per lane
-inline int select_form(const semmoe_config& cfg) {
-  if (!select_by_rows(cfg)) return kSelAny;
-  return cfg.E <= 64 ? kSelSmall : (cfg.E <= 128 ? kSel8 : kSel16);
+// SLOTS: 0 any E, k and number of groups; else the row form with up to 4, 8 or 16 slots per lane.  KEEP: length of the lists
+// of the row form, 4, 8 or 16 (>= k).
+template <int SLOTS, int KEEP>
+struct SelForm {
+  static constexpr int kSlots = SLOTS, kKeep = KEEP;
+  static constexpr bool kRows = SLOTS > 0;
+};
+using SelAny = SelForm<0, 0>;
+inline int select_slots(const semmoe_config& cfg) {
+  if (!select_by_rows(cfg)) return 0;
+  return cfg.E <= 64 ? 4 : (cfg.E <= 128 ? 8 : 16);
+}
+// f(form, sigmoid) with the form of the configuration, of those with SLOTS slots, and the score function as types
+template <int SLOTS, typename F>
+inline int32_t with_select_form(const semmoe_config& cfg, F f) {
+  auto with_score = [&](auto form) -> int32_t {
+    return cfg.score == SEMMOE_SIGMOID ? f(form, std::true_type{}) : f(form, std::false_type{});
+  };
+  if (cfg.k <= 4) return with_score(SelForm<SLOTS, 4>{});
+  if (cfg.k <= 8) return with_score(SelForm<SLOTS, 8>{});
+  return with_score(SelForm<SLOTS, 16>{});
 }
 
 // Tokens base .. base + kRowTokens - 1 (those below n_tok) by one wave: token = base + ch*4 + row.
 // row_of(token) -> pointer to its E logits; ids / weights are written to topk_ids / topk_w at tok_global0 + token.
-template <int FORM, bool SIG, int NCH = kRowChains, typename RowOf>
+template <typename FORM, bool SIG, int NCH = kRowChains, bool KEYED = false, typename RowOf>
 __device__ __forceinline__ void select_tokens_by_rows(const semmoe_config& cfg, int base, int n_tok, RowOf row_of,
                                                       int tok_global0, const float* __restrict__ sel_bias, int lane,
-                                                      int32_t* __restrict__ topk_ids, float* __restrict__ topk_w) {
-  static_assert(FORM == kSelSmall || FORM == kSel8 || FORM == kSel16, "a row form");
+                                                      int32_t* __restrict__ topk_ids, float* __restrict__ topk_w,
+                                                      int key_off = 0) {
+  static_assert(FORM::kRows, "a row form");
+  constexpr int KEEP = FORM::kKeep;
   const float* rowp[NCH];
   int32_t* idp[NCH];
   float* wp[NCH];
@@ -545,14 +754,12 @@ __device__ __forceinline__ void select_tokens_by_rows(const semmoe_config& cfg, 
     idp[ch] = ok ? topk_ids + size_t(tok_global0 + tl) * cfg.k : nullptr;
     wp[ch] = ok ? topk_w + size_t(tok_global0 + tl) * cfg.k : nullptr;
   }
-  if constexpr (FORM == kSel16) {
-    select_rows16<16, NCH, SIG>(cfg, rowp, sel_bias, lane, idp, wp);
-  } else if constexpr (FORM == kSel8) {
-    select_rows16<8, NCH, SIG>(cfg, rowp, sel_bias, lane, idp, wp);
+  if constexpr (FORM::kSlots > 4) {
+    select_rows16<FORM::kSlots, KEEP, NCH, SIG, KEYED>(cfg, rowp, sel_bias, lane, idp, wp, key_off);
   } else {
-    if (cfg.E <= 16) select_rows16<1, NCH, SIG>(cfg, rowp, sel_bias, lane, idp, wp);
-    else if (cfg.E <= 32) select_rows16<2, NCH, SIG>(cfg, rowp, sel_bias, lane, idp, wp);
-    else select_rows16<4, NCH, SIG>(cfg, rowp, sel_bias, lane, idp, wp);
+    if (cfg.E <= 16) select_rows16<1, KEEP, NCH, SIG, KEYED>(cfg, rowp, sel_bias, lane, idp, wp, key_off);
+    else if (cfg.E <= 32) select_rows16<2, KEEP, NCH, SIG, KEYED>(cfg, rowp, sel_bias, lane, idp, wp, key_off);
+    else select_rows16<4, KEEP, NCH, SIG, KEYED>(cfg, rowp, sel_bias, lane, idp, wp, key_off);
   }
 }
 
@@ -599,7 +806,7 @@ struct RouteCfg {
   static_assert((NSTAGE - 1) * IPW < 64, "vmcnt range");
 };
 
-template <int TF, int TT, int NSTAGE, int FORM, bool SIG>
+template <int TF, int TT, int NSTAGE, typename FORM, bool SIG>
 __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, const bf16_t* __restrict__ X,
                                                           const bf16_t* __restrict__ W_r,
                                                           const float* __restrict__ b_g,
@@ -797,7 +1004,7 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
       }
     }
     __syncthreads();
-    if constexpr (FORM != kSelAny) {
+    if constexpr (FORM::kRows) {
       for (int base = wave * kRowTokens; base < C::BT; base += 4 * kRowTokens)
         select_tokens_by_rows<FORM, SIG>(
             cfg, base, C::BT, [&](int tl) { return lg + tl * ldl; }, tok0, sel_bias, lane, topk_ids, topk_w);
@@ -822,7 +1029,7 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
   }
 }
 
-template <int FORM, bool SIG>
+template <typename FORM, bool SIG>
 __global__ __launch_bounds__(256) void select_topk_rows_kernel(semmoe_config cfg, const float* __restrict__ logits,
                                                                const float* __restrict__ sel_bias,
                                                                int32_t* __restrict__ topk_ids,
@@ -841,7 +1048,7 @@ constexpr int kSumSelectMaxE = 256;
 constexpr int kSumSelectChains = 1;                       // four tokens a wave: twice the waves to hide the latencies
 constexpr int kSumSelectTokens = 4 * kSumSelectChains;
 // PB parts of U chunks of four experts are requested before the first is used.
-template <int FORM, bool SIG, int PB, int U>
+template <typename FORM, bool SIG, int PB, int U>
 __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg, int n_parts,
                                                                const float* __restrict__ partial,
                                                                const float* __restrict__ b_g,
@@ -851,12 +1058,15 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
                                                                float* __restrict__ logits_out,
                                                                int32_t* __restrict__ topk_ids,
                                                                float* __restrict__ topk_w) {
-  __shared__ __attribute__((aligned(16))) float lg_all[4 * kSumSelectTokens * (kSumSelectMaxE + 4)];
+  // logits, and behind them (sigmoid) the keys of the selection scores: formed here, four a loop round, because the sixteen
+  // of a lane one after the other in the selection are 3 KB of code that every wave waits for
+  __shared__ __attribute__((aligned(16))) float lg_all[4 * kSumSelectTokens * (kSumSelectMaxE + 4) * (SIG ? 2 : 1)];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int base = (blockIdx.x * int(blockDim.x >> 6) + wave) * kSumSelectTokens;  // up to four waves per workgroup
   if (base >= cfg.T) return;  // whole wave leaves together (no workgroup barrier below)
   const int E = cfg.E, e4 = E / 4, ld = E + 4;
   float* lg = lg_all + wave * kSumSelectTokens * (kSumSelectMaxE + 4);
+  constexpr int kKeyOff = 4 * kSumSelectTokens * (kSumSelectMaxE + 4);
   const int n_tok = min(kSumSelectTokens, cfg.T - base);
   const size_t n = size_t(cfg.T) * E;
   const bool out16 = logits_out && (reinterpret_cast<size_t>(logits_out) & 15) == 0;
@@ -900,6 +1110,13 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
         for (int u = 0; u < 4; ++u) v[c][u] += class_bias[size_t(cls[c]) * E + e[c] + u];
       }
       *reinterpret_cast<f32x4_t*>(lg + tl[c] * ld + e[c]) = v[c];
+      if constexpr (SIG) {
+        i32x4_t key;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          key[u] = to_key(__fadd_rn(sigmoid_exact_seq(v[c][u]), sel_bias ? sel_bias[e[c] + u] : 0.0f));
+        *reinterpret_cast<i32x4_t*>(lg + kKeyOff + tl[c] * ld + e[c]) = key;
+      }
       if (out16) {
         *reinterpret_cast<f32x4_t*>(logits_out + at[c]) = v[c];
       } else if (logits_out) {
@@ -910,8 +1127,8 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_wave_barrier();
-  select_tokens_by_rows<FORM, SIG, kSumSelectChains>(
-      cfg, 0, n_tok, [&](int tl) { return lg + tl * ld; }, base, sel_bias, lane, topk_ids, topk_w);
+  select_tokens_by_rows<FORM, SIG, kSumSelectChains, SIG>(
+      cfg, 0, n_tok, [&](int tl) { return lg + tl * ld; }, base, sel_bias, lane, topk_ids, topk_w, kKeyOff);
 }
 
 // launches route_sum_select_kernel when the shape has a row form of the selection and E is a multiple of four;
@@ -919,31 +1136,25 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
 static bool launch_sum_select(const semmoe_config* cfg, hipStream_t s, int n_parts, const float* partial,
                               const float* b_g, const int32_t* token_class, const float* class_bias,
                               const float* sel_bias, float* logits_out, int32_t* topk_ids, float* topk_w) {
-  const int form = select_form(*cfg);
-  if (form == kSelAny || cfg->E > kSumSelectMaxE || cfg->E % 4 != 0) return false;
+  const int slots = select_slots(*cfg);
+  if (slots == 0 || cfg->E > kSumSelectMaxE || cfg->E % 4 != 0) return false;
   // few tokens: a wave a workgroup, so that they spread over as many compute units as there are, and all loads of a wave
   // in flight at once (256 tokens, 128 experts, 16 parts: 18.8 -> 15.2 us for the route); many: the waves hide each
   // other's latencies and registers are what is short (16384 tokens, 256 experts, 4 parts: 111 us so, 114 us with 16
   // loads in flight)
   const int waves = cfg->T <= 2048 ? 1 : 4;
   const dim3 grid(cdiv(cfg->T, waves * kSumSelectTokens)), block(64 * waves);
-  const bool sig = cfg->score == SEMMOE_SIGMOID;
-#define SEMMOE_SUM_SELECT_AS(FORM_, SIG_, PB_, U_)                                                                  \
-  hipLaunchKernelGGL((route_sum_select_kernel<FORM_, SIG_, PB_, U_>), grid, block, 0, s, *cfg, n_parts, partial,    \
-                     b_g, token_class, class_bias, sel_bias, logits_out, topk_ids, topk_w)
-#define SEMMOE_SUM_SELECT(FORM_)                                                                                    \
-  do {                                                                                                              \
-    if (waves == 4) {                                                                                               \
-      if (sig) SEMMOE_SUM_SELECT_AS(FORM_, true, 8, 1); else SEMMOE_SUM_SELECT_AS(FORM_, false, 8, 1);              \
-    } else {                                                                                                        \
-      if (sig) SEMMOE_SUM_SELECT_AS(FORM_, true, 16, 2); else SEMMOE_SUM_SELECT_AS(FORM_, false, 16, 2);            \
-    }                                                                                                               \
-  } while (0)
-  if (form == kSel16) SEMMOE_SUM_SELECT(kSel16);
-  else if (form == kSel8) SEMMOE_SUM_SELECT(kSel8);
-  else SEMMOE_SUM_SELECT(kSelSmall);
-#undef SEMMOE_SUM_SELECT
-#undef SEMMOE_SUM_SELECT_AS
+  auto launch = [&](auto form, auto sig) -> int32_t {
+    using FORM = decltype(form);
+    constexpr bool SIG = decltype(sig)::value;
+    auto kern = waves == 4 ? route_sum_select_kernel<FORM, SIG, 8, 1> : route_sum_select_kernel<FORM, SIG, 16, 2>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s, *cfg, n_parts, partial, b_g, token_class, class_bias, sel_bias, logits_out,
+                       topk_ids, topk_w);
+    return SEMMOE_OK;
+  };
+  if (slots == 16) with_select_form<16>(*cfg, launch);
+  else if (slots == 8) with_select_form<8>(*cfg, launch);
+  else with_select_form<4>(*cfg, launch);
   return true;
 }
 
@@ -1028,23 +1239,17 @@ static int32_t launch_select(const semmoe_config* cfg, hipStream_t stream, const
                              const float* sel_bias, int32_t* topk_ids, float* topk_w) {
   if (cfg->T == 0) return SEMMOE_OK;
   const int waves_per_block = 4;
-  const int form = select_form(*cfg);
-  if (form != kSelAny) {
+  const int slots = select_slots(*cfg);
+  if (slots > 0) {
     const dim3 grid(cdiv(cfg->T, waves_per_block * kRowTokens)), block(64 * waves_per_block);
-    const bool sig = cfg->score == SEMMOE_SIGMOID;
-#define SEMMOE_SELECT_LAUNCH(FORM_)                                                                                \
-  do {                                                                                                             \
-    if (sig)                                                                                                       \
-      hipLaunchKernelGGL((select_topk_rows_kernel<FORM_, true>), grid, block, 0, stream, *cfg, logits, sel_bias,   \
-                         topk_ids, topk_w);                                                                        \
-    else                                                                                                           \
-      hipLaunchKernelGGL((select_topk_rows_kernel<FORM_, false>), grid, block, 0, stream, *cfg, logits, sel_bias,  \
-                         topk_ids, topk_w);                                                                        \
-  } while (0)
-    if (form == kSelSmall) SEMMOE_SELECT_LAUNCH(kSelSmall);
-    else if (form == kSel8) SEMMOE_SELECT_LAUNCH(kSel8);
-    else SEMMOE_SELECT_LAUNCH(kSel16);
-#undef SEMMOE_SELECT_LAUNCH
+    auto launch = [&](auto form, auto sig) -> int32_t {
+      hipLaunchKernelGGL((select_topk_rows_kernel<decltype(form), decltype(sig)::value>), grid, block, 0, stream, *cfg, logits,
+                         sel_bias, topk_ids, topk_w);
+      return SEMMOE_OK;
+    };
+    if (slots == 16) with_select_form<16>(*cfg, launch);
+    else if (slots == 8) with_select_form<8>(*cfg, launch);
+    else with_select_form<4>(*cfg, launch);
     SEMMOE_LAUNCH_CHECK();
     return SEMMOE_OK;
   }
@@ -1081,7 +1286,6 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cfg->T == 0) return SEMMOE_OK;
   if (cfg->dtype == SEMMOE_BF16) {
-    // fused MFMA router: tokens per workgroup = 64 when that still fills the chip, else 32
     const bf16_t* Xb = static_cast<const bf16_t*>(X);
     const bf16_t* Wb = static_cast<const bf16_t*>(W_r);
     const int tf = cfg->E <= 128 ? 1 : (cfg->E <= 256 ? 2 : 4);
@@ -1118,64 +1322,54 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       logits_ws = c.take<float>(size_t(cfg->T) * cfg->E);
       if (!c.ok) return SEMMOE_EWORKSPACE;
     }
-    // tokens per workgroup: as many as still give every compute unit a tile (every workgroup streams all of W_r past its
-    // tokens, so W_r traffic per token falls with the tile): 128 (up to 128 experts), 64 (up to 256), else 32
+    // tokens per workgroup: 32 while that is one round of the chip, then 64 (up to 256 experts), and 128 (up to 128 experts) from
+    // where that still gives every compute unit a tile: every workgroup streams all of W_r past its tokens, and a second
+    // round of it costs more than the wider tile (10000 tokens, d 2048, 128 experts: 28 us as 32, 24 as 64)
     const bool wide = n_parts == 1 && cdiv(cfg->T, 64) >= 256 && tf <= 2;
     const bool wider = wide && tf == 1 && cdiv(cfg->T, 128) >= 256;
     const int bt = wider ? 128 : (wide ? 64 : 32);
     const int n_tiles = cdiv(cfg->T, bt);
-    const int form = select_form(*cfg);
-    const bool sig = cfg->score == SEMMOE_SIGMOID;
-#define SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, FORM_, SIG_)                                                             \
-  do {                                                                                                              \
-    using RC = RouteCfg<TF_, TT_, NS_>;                                                                             \
-    size_t lds = size_t(NS_) * RC::kStageBytes;                                                                     \
-    const size_t lg_bytes = size_t(RC::BT) * (cfg->E + 4) * 4;                                                      \
-    if (lg_bytes > lds) lds = lg_bytes;                                                                             \
-    const int per_cu = lds <= 80 * 1024 ? 2 : 1;                                                                    \
-    const int items = n_tiles * n_parts;                                                                            \
-    const int grid = items < ncu * per_cu ? items : ncu * per_cu;                                                   \
-    static std::atomic<uint64_t> lds_allowed{0}; /* one per instantiation named below */                            \
-    st = allow_max_dynamic_lds(&lds_allowed,                                                                        \
-                               reinterpret_cast<const void*>(route_fused_kernel<TF_, TT_, NS_, FORM_, SIG_>));      \
-    if (st != SEMMOE_OK) return st;                                                                                 \
-    hipLaunchKernelGGL((route_fused_kernel<TF_, TT_, NS_, FORM_, SIG_>), dim3(grid), dim3(256), lds, s, *cfg, Xb,   \
-                       Wb, b_g, token_class, class_bias, sel_bias, logits_out, topk_ids, topk_w, n_parts, partial); \
-  } while (0)
-// the selection forms a shape can need: with E <= 128 the small and the 8-slot row forms, with E <= 256 the 16-slot one
-#define SEMMOE_ROUTE_FORMS_128(TF_, TT_, NS_)                                                                       \
-  do {                                                                                                              \
-    if (form == kSelSmall) {                                                                                        \
-      if (sig) SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSelSmall, true);                                                 \
-      else SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSelSmall, false);                                                    \
-    } else if (form == kSel8) {                                                                                     \
-      if (sig) SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSel8, true);                                                     \
-      else SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSel8, false);                                                        \
-    } else {                                                                                                        \
-      SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSelAny, false);                                                           \
-    }                                                                                                               \
-  } while (0)
-#define SEMMOE_ROUTE_FORMS_256(TF_, TT_, NS_)                                                                       \
-  do {                                                                                                              \
-    if (form == kSel16) {                                                                                           \
-      if (sig) SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSel16, true);                                                    \
-      else SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSel16, false);                                                       \
-    } else {                                                                                                        \
-      SEMMOE_ROUTE_LAUNCH(TF_, TT_, NS_, kSelAny, false);                                                           \
-    }                                                                                                               \
-  } while (0)
-    if (tf == 1) {
-      if (wider) SEMMOE_ROUTE_FORMS_128(1, 4, 4);
-      else if (wide) SEMMOE_ROUTE_FORMS_128(1, 2, 5);
-      else SEMMOE_ROUTE_FORMS_128(1, 1, 6);
-    } else if (tf == 2) {
-      if (wide) SEMMOE_ROUTE_FORMS_256(2, 2, 3); else SEMMOE_ROUTE_FORMS_256(2, 1, 4);
-    } else {
-      SEMMOE_ROUTE_LAUNCH(4, 1, 2, kSelAny, false);
-    }
-#undef SEMMOE_ROUTE_FORMS_128
-#undef SEMMOE_ROUTE_FORMS_256
-#undef SEMMOE_ROUTE_LAUNCH
+    const int slots = select_slots(*cfg);
+    // TF x 128 experts and TT x 32 tokens a workgroup, a ring of NS
+    auto launch = [&](auto tf_, auto tt_, auto ns_, auto form, auto sig) -> int32_t {
+      constexpr int TF = decltype(tf_)::value, TT = decltype(tt_)::value, NS = decltype(ns_)::value;
+      using RC = RouteCfg<TF, TT, NS>;
+      auto kern = route_fused_kernel<TF, TT, NS, decltype(form), decltype(sig)::value>;
+      size_t lds = size_t(NS) * RC::kStageBytes;
+      const size_t lg_bytes = size_t(RC::BT) * (cfg->E + 4) * 4;
+      if (lg_bytes > lds) lds = lg_bytes;
+      const int per_cu = lds <= 80 * 1024 ? 2 : 1;
+      const int items = n_tiles * n_parts;
+      const int grid = items < ncu * per_cu ? items : ncu * per_cu;
+      static std::atomic<uint64_t> lds_allowed{0};  // one per instantiation
+      const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
+      if (as != SEMMOE_OK) return as;
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, *cfg, Xb, Wb, b_g, token_class, class_bias, sel_bias, logits_out,
+                         topk_ids, topk_w, n_parts, partial);
+      return SEMMOE_OK;
+    };
+    // the forms a shape can need: up to 128 experts 4 and 8 slots, up to 256 experts 16, or none of them
+    auto launch_128 = [&](auto tf_, auto tt_, auto ns_) -> int32_t {
+      auto with = [&](auto form, auto sig) { return launch(tf_, tt_, ns_, form, sig); };
+      if (slots == 4) return with_select_form<4>(*cfg, with);
+      if (slots == 8) return with_select_form<8>(*cfg, with);
+      return launch(tf_, tt_, ns_, SelAny{}, std::false_type{});
+    };
+    auto launch_256 = [&](auto tf_, auto tt_, auto ns_) -> int32_t {
+      auto with = [&](auto form, auto sig) { return launch(tf_, tt_, ns_, form, sig); };
+      if (slots == 16) return with_select_form<16>(*cfg, with);
+      return launch(tf_, tt_, ns_, SelAny{}, std::false_type{});
+    };
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, 2> c2{};
+    constexpr std::integral_constant<int, 3> c3{};
+    constexpr std::integral_constant<int, 4> c4{};
+    constexpr std::integral_constant<int, 5> c5{};
+    constexpr std::integral_constant<int, 6> c6{};
+    if (tf == 1) st = wider ? launch_128(c1, c4, c4) : (wide ? launch_128(c1, c2, c5) : launch_128(c1, c1, c6));
+    else if (tf == 2) st = wide ? launch_256(c2, c2, c3) : launch_256(c2, c1, c4);
+    else st = launch(c4, c1, c2, SelAny{}, std::false_type{});
+    if (st != SEMMOE_OK) return st;
     SEMMOE_LAUNCH_CHECK();
     if (n_parts > 1) {
       // adding the parts and selecting in one kernel where the shape has a row form (256 tokens, 128 experts, 16 parts:

@@ -1,0 +1,59 @@
+"""Router: the selection on ties, on rows with fewer experts than it asks for and on groups of equal score."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_04398_amd as S
+from oracle import semmoe_oracle as O
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+NONE = 0x7fffffff  # an expert that is not there
+
+
+def _select(L, k, sb=None, **kw):
+    T, E = L.shape
+    m = S.SemMoE(S.Config(T=T, d=8, E=E, k=k, F=8, D=1, cap=T, **kw), allocate_workspace=False)
+    ids, w = torch.empty(T, k, dtype=torch.int32, device=H.DEV), torch.empty(T, k, device=H.DEV)
+    m.route_from_logits(H.to_dev(L), ids, w, sel_bias=None if sb is None else H.to_dev(sb))
+    torch.cuda.synchronize()
+    return H.to_np(ids), H.to_np(w)
+
+
+# lists of 4, 8 and 16 per lane, 1 to 16 slots a lane, a last slot that is partly there
+@pytest.mark.parametrize("E", [1, 7, 16, 33, 64, 100, 128, 130, 250, 256])
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 8, 9, 16])
+def test_ties_and_absent_experts(E, k):
+    if k > E:
+        pytest.skip("more experts asked for than there are")
+    r = np.random.default_rng(E * 17 + k)
+    L = r.integers(-3, 3, (41, E)).astype(np.float32)
+    L[1::4] += r.standard_normal((len(L[1::4]), E)).astype(np.float32)
+    L[2, :] = 0.0
+    L[2, ::2] = -0.0  # equal to +0: the lower expert first, whatever the sign
+    for i in range(5, 41, 5):  # so many experts are there, the others' logits are -inf
+        L[i, r.permutation(E)[1 + i % k:]] = -np.inf
+    ids, w = _select(L, k, renorm=True)
+    order = np.argsort(-L, axis=1, kind="stable")[:, :k]
+    top = np.take_along_axis(L, order, 1)
+    there = np.isfinite(top)
+    assert (ids == np.where(there, order, NONE)).all()
+    e = np.where(there, np.exp(top - top[:, :1]), 0.0)
+    assert np.abs(w - e / e.sum(1, keepdims=True)).max() < 1e-6  # a few roundings of numbers up to 1
+
+
+@pytest.mark.parametrize("E", [128, 256, 64])
+@pytest.mark.parametrize("tg", [1, 3, 4, 7, 8])
+def test_best_of_8_groups(E, tg):
+    r = np.random.default_rng(E + tg)
+    k = min(8, tg * (E // 8))
+    L = np.round(2 * r.standard_normal((70, E))).astype(np.float32)  # equal scores in and across groups
+    L[0] = 0.0
+    L[1] = np.repeat(np.arange(8)[::-1], E // 8)
+    L[2] = r.standard_normal(E)
+    sb = np.round(4 * r.standard_normal(E)).astype(np.float32) / 4
+    for bias in (None, sb):
+        ids, w = _select(L, k, sb=bias, score="sigmoid", renorm=True, n_group=8, topk_group=tg, routed_scale=2.5)
+        want_ids, want_w = O.select_topk(L, k, "sigmoid", True, 8, tg, 2.5, bias)
+        assert (ids == want_ids).all()
+        assert O.max_rel_err(w, want_w) <= 1e-5
