@@ -1184,42 +1184,65 @@ __global__ __launch_bounds__(256) void route_reduce_kernel(semmoe_config cfg, in
   if (logits_out) logits_out[idx] = v;
 }
 
-// Many tokens and more than 128 experts: the fused kernel's workgroup (64 tokens) streams all of W_r past its tokens,
-// five rows of operands per token and slice.  The 256 x 256 tile of the grouped GEMM takes two, with K cut into as
-// many parts as fill the chip; the parts are then added in order and the selection runs as a kernel of its own.
+// More than 128 experts and tokens enough: the fused kernel's workgroup (32 or 64 tokens) streams all of W_r past its tokens, nine or
+// five rows of operands per token and slice.  The 256 x 128 tile of the grouped GEMM takes three, with K cut into as
+// many parts as fill the chip; the parts are then added in order and the selection runs as a kernel of its own.  (256 x 256
+// tiles take two, but twice the parts: 16384 tokens, d 7168, 256 experts: 73 us + 134 MB of partial sums written and read, 68
+// + 67 MB so; the whole 94 -> 88 us.)  From 12 token tiles on, 8 parts each; below, the fused kernel with parts (1024 tokens:
+// 25 us either way).  Before, the form began at 8192 tokens where three quarters of the chip were filled and the fused kernel
+// walked all of K for the others: 4096 tokens 75 -> 35 us, 12000 tokens 164 -> 78.
 // tune (SEMMOE_TUNE_ROUTE_SPLIT): -1 automatic, 0 never, 100 + n this form with n parts whatever the token count.
+static int route_big_cap(const semmoe_config* cfg) {  // what the workspace is sized for
+  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
+  return tiles >= 1024 ? 1 : int(1024 / tiles < 8 ? 1024 / tiles : 8);
+}
+
 static int route_big_parts(const semmoe_config* cfg, int ncu) {
   const int tune = tuning_value(SEMMOE_TUNE_ROUTE_SPLIT);
   if (cfg->dtype != SEMMOE_BF16 || tune == 0 || cfg->E <= 128 || cfg->E % 4 != 0 || cfg->d % 64 != 0) return 0;
-  const int nk = cfg->d / 64;
-  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
-  const int cap = tiles >= 1024 ? 1 : int(1024 / tiles < 8 ? 1024 / tiles : 8);  // what the workspace is sized for
+  const int nk = cfg->d / 64, cap = route_big_cap(cfg);
   if (tune >= 100) {
     const int parts = tune - 100;
-    return (parts >= 1 && parts <= cap && nk % parts == 0 && nk / parts >= 2) ? parts : 0;
+    return (parts >= 1 && parts <= cap && nk % parts == 0 && nk / parts >= 3) ? parts : 0;
   }
   if (tune > 0) return 0;  // a forced split of the fused kernel
-  if (tiles * 8 < ncu) return 0;  // too few tokens to fill the chip with 256-token tiles and K parts of useful depth
-  int parts = int(ncu / tiles);
-  if (parts < 1) parts = 1;
+  const long long items = (long long)cdiv(cfg->T, 128) * cdiv(cfg->E, 256);
+  int parts = items > ncu ? 1 : int(ncu / items);
   if (parts > cap) parts = cap;
   while (parts > 1 && (nk % parts != 0 || nk / parts < 8)) --parts;
-  if (tiles * parts * 4 < (long long)ncu * 3) return 0;  // K too short to cut into enough parts: the fused kernel fills the chip
-  return nk / parts >= 2 ? parts : 0;
+  return items * parts * 8 >= 3LL * ncu && nk / parts >= 3 ? parts : 0;
 }
 
-constexpr int kRouteSplitMaxTiles = 16;  // up to this many token tiles of 32 the K dimension is split over workgroups
-constexpr int kRouteSplitMaxParts = 16;
+// A workspace too small for the partial sums: refused where tiles of 256 tokens times the parts fill three quarters of the
+// chip (and where the form is asked for); the others run without, on the fused kernel.
+static bool route_big_needs_workspace(const semmoe_config* cfg, int ncu) {
+  if (tuning_value(SEMMOE_TUNE_ROUTE_SPLIT) >= 100) return true;
+  const int nk = cfg->d / 64, cap = route_big_cap(cfg);
+  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
+  int parts = tiles > ncu ? 1 : int(ncu / tiles);
+  if (parts > cap) parts = cap;
+  while (parts > 1 && (nk % parts != 0 || nk / parts < 8)) --parts;
+  return tiles * 8 >= ncu && tiles * parts * 4 >= 3LL * ncu;
+}
 
-// parts of K for the split router, 1 = the fused kernel.  tune: -1 automatic, 0 never, n > 1 that many parts
+// Parts of K for the fused router, 1 = none.  With at most a 32-token tile for every second compute unit the rest of the chip
+// takes parts of K.  Beyond 256 tokens a part has at least 6 slices (512 tokens of d 4096: 16 parts 13.4 us, 10 parts 12.4:
+// partial sums are written and read), and what the walk gets shorter by has to repay the second kernel: 20 slices
+// (4096 tokens, two parts: d 2048 15.4 -> 15.8 us, d 2880 18.0 -> 17.1, d 4096 23.6 -> 20.1; 1024 tokens: d 2048 15.0 -> 12.3,
+// d 4096 23.5 -> 13.4, d 7168 with 256 experts 64 -> 25.5).
+// tune: -1 automatic, 0 never, n > 1 that many parts
 static int route_parts(const semmoe_config* cfg, int ncu) {
   const int tune = tuning_value(SEMMOE_TUNE_ROUTE_SPLIT);
   const int n_tiles = cdiv(cfg->T, 32), nk = cdiv(cfg->d, 64);
-  if (cfg->dtype != SEMMOE_BF16 || tune == 0 || n_tiles > kRouteSplitMaxTiles) return 1;
-  int parts = tune > 1 ? tune : ncu / n_tiles;
-  if (parts > kRouteSplitMaxParts) parts = kRouteSplitMaxParts;
+  const int most = route_max_parts(cfg->T);
+  if (cfg->dtype != SEMMOE_BF16 || tune == 0 || most < 2) return 1;
+  const bool forced = tune > 1 && tune < 100;
+  int parts = forced ? tune : ncu / n_tiles;
+  if (!forced && cfg->T > 256 && parts > nk / 6) parts = nk / 6;
+  if (parts > most) parts = most;
   if (parts > nk / 2) parts = nk / 2;  // at least two slices per part
-  return parts < 2 ? 1 : parts;
+  if (parts < 2) return 1;
+  return !forced && cfg->T > 512 && nk - nk / parts < 20 ? 1 : parts;
 }
 
 static int32_t validate_select(const semmoe_config* cfg) {
@@ -1297,8 +1320,8 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       Carver c(ws, ws_bytes);
       float* part = c.take<float>(size_t(big_parts) * cfg->T * cfg->E);
       float* lg = c.take<float>(size_t(cfg->T) * cfg->E);
-      if (!c.ok) return SEMMOE_EWORKSPACE;
-      st = launch_ksplit_gemm(X, W_r, cfg->T, cfg->E, cfg->d, big_parts, part, s);
+      if (!c.ok && route_big_needs_workspace(cfg, ncu)) return SEMMOE_EWORKSPACE;
+      st = c.ok ? launch_ksplit_gemm(X, W_r, cfg->T, cfg->E, cfg->d, big_parts, part, s) : SEMMOE_EUNSUPPORTED;
       if (st == SEMMOE_OK && launch_sum_select(cfg, s, big_parts, part, b_g, token_class, class_bias, sel_bias,
                                                logits_out, topk_ids, topk_w)) {
         SEMMOE_LAUNCH_CHECK();
@@ -1313,19 +1336,23 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       }
       if (st != SEMMOE_EUNSUPPORTED) return st;
     }
-    const int n_parts = route_parts(cfg, ncu);
+    int n_parts = route_parts(cfg, ncu);
     float* partial = nullptr;
     float* logits_ws = nullptr;
     if (n_parts > 1) {
       Carver c(ws, ws_bytes);
       partial = c.take<float>(size_t(n_parts) * cfg->T * cfg->E);
       logits_ws = c.take<float>(size_t(cfg->T) * cfg->E);
-      if (!c.ok) return SEMMOE_EWORKSPACE;
+      if (!c.ok) {  // beyond 512 tokens the parts are worth a workspace, but not needed
+        if (cfg->T <= 512) return SEMMOE_EWORKSPACE;
+        n_parts = 1;
+        partial = nullptr;
+      }
     }
     // tokens per workgroup: 32 while that is one round of the chip, then 64 (up to 256 experts), and 128 (up to 128 experts) from
     // where that still gives every compute unit a tile: every workgroup streams all of W_r past its tokens, and a second
     // round of it costs more than the wider tile (10000 tokens, d 2048, 128 experts: 28 us as 32, 24 as 64)
-    const bool wide = n_parts == 1 && cdiv(cfg->T, 64) >= 256 && tf <= 2;
+    const bool wide = n_parts == 1 && cdiv(cfg->T, 32) > ncu && tf <= 2;
     const bool wider = wide && tf == 1 && cdiv(cfg->T, 128) >= 256;
     const int bt = wider ? 128 : (wide ? 64 : 32);
     const int n_tiles = cdiv(cfg->T, bt);

@@ -1,9 +1,11 @@
-"""Router: the selection on ties, on rows with fewer experts than it asks for and on groups of equal score."""
+"""Router: the selection on ties, on rows with fewer experts than it asks for and on groups of equal score, and the GEMM where
+its form changes (parts of K, tokens per workgroup, tile), with the workspace it asks for and with the logits' alone."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2503_04398_amd as S
+import workloads as WL
 from oracle import semmoe_oracle as O
 from tests import harness as H
 
@@ -57,3 +59,26 @@ def test_best_of_8_groups(E, tg):
         want_ids, want_w = O.select_topk(L, k, "sigmoid", True, 8, tg, 2.5, bias)
         assert (ids == want_ids).all()
         assert O.max_rel_err(w, want_w) <= 1e-5
+
+
+# fused with parts of K (512 | 513 tokens, few and many parts, up to a tile for half of the chip), without (4097), 64 tokens a
+# workgroup (8193); more than 128 experts: 128 x 256 tiles from 12 token tiles on (1409), ragged last tiles
+@pytest.mark.parametrize("T,d,E,k", [(257, 512, 128, 8), (512, 1000, 64, 4), (513, 1000, 128, 8), (1024, 2048, 128, 8),
+                                     (4096, 264, 128, 8), (4097, 264, 128, 8), (8193, 136, 96, 4), (1407, 1536, 256, 8),
+                                     (1409, 1536, 256, 8), (4500, 1792, 256, 8), (8193, 136, 256, 8), (8300, 1024, 160, 6)])
+def test_gemm_where_its_form_changes(T, d, E, k):
+    w = WL.small(T=T, d=d, E=E, k=k, D=1, C=4, dtype="bf16")
+    inp = H.make_inputs(w)
+    lay = H.Layer(w)
+    logits, ids, tw = lay.route(inp)
+    want = O.route_logits(inp.X, inp.W_r, None, inp.token_class, inp.class_bias)
+    assert O.max_rel_err(logits, want) <= 1e-5  # exact inputs; the order of fp32 sums
+    want_ids, want_w = H.oracle_select(w, logits)
+    assert (ids == want_ids).all() and O.max_rel_err(tw, want_w) <= 1e-5
+    if T > 512 and E <= 128:  # a workspace for one set of logits is enough
+        lay.m.ws_bytes = T * E * 4 + 512
+        lay.m.ws[lay.m.ws_bytes:].fill_(0x5a)
+        logits, ids, tw = lay.route(inp)
+        assert O.max_rel_err(logits, want) <= 1e-5
+        assert (ids == H.oracle_select(w, logits)[0]).all()
+        assert (lay.m.ws[lay.m.ws_bytes:] == 0x5a).all()
