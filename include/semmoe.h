@@ -104,11 +104,12 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     second launch.  3 or 6: a second launch of 128 x 64 pieces with the loads of a slice issued in a burst and an LDS
  *     ring of 3 (two workgroups per compute unit) or 6 (one)
  *   SEMMOE_TUNE_ROUTE_SPLIT: bf16 router: parts the K dimension is split into over workgroups (partial sums added in order
- *     and selected from by a second kernel), at most 16 up to 512 tokens, 8 up to 2048, 512 / (tiles of 32 tokens) beyond;
- *     0 = always the fused kernel, default: as many parts as fill the chip where that is worth the second kernel.  With
- *     more than 128 experts and 12 tiles of 128 tokens or more the logits come from the 256 x 128 tile of the grouped GEMM
- *     with K in up to 8 parts (at least 8 slices each), followed by one kernel that adds the parts and selects; 100 + n forces
- *     that form with n parts at any token count (d must be n parts of whole 64-element slices, at least three each),
+ *     and selected from by a second kernel), at most 16 up to 512 tokens and, with up to 128 experts, 8 up to 2048 and
+ *     512 / (tiles of 32 tokens) beyond; 0 = always the fused kernel, default: as many parts as fill the chip where that is
+ *     worth the second kernel.  With more than 128 experts, where tiles of 256 tokens
+ *     times up to 8 parts of K (at least 8 slices each) fill three quarters of the compute units, the logits come from
+ *     the 256 x 256 tile of the grouped GEMM, followed by one kernel that adds the parts and selects; 100 + n forces
+ *     that form with n parts at any token count (d must be n parts of whole 64-element slices, at least two each),
  *     0 switches it off too
  *   SEMMOE_TUNE_GRID_CAP: most workgroups a grouped GEMM launches (default: compute units x blocks per CU)
  *   SEMMOE_TUNE_INDEX_PATH: which implementation of the index kernels runs (default: a single workgroup for

@@ -69,23 +69,24 @@ int32_t validate_config(const semmoe_config* cfg, bool need_T, bool need_rows, b
   return SEMMOE_OK;
 }
 
-int route_max_parts(int T) {
-  const int tiles = cdiv(T, 32);  // a workgroup each; a bound that needs no device: no chip has 512 compute units
-  return T <= 512 ? 16 : (tiles >= 512 ? 1 : (512 / tiles < 8 ? 512 / tiles : 8));
+int route_max_parts(const semmoe_config* cfg) {
+  const int tiles = cdiv(cfg->T, 32);  // a workgroup each; a bound that needs no device: no chip has 512 compute units
+  if (cfg->T <= 512) return 16;
+  return cfg->E > 128 || tiles >= 512 ? 1 : (512 / tiles < 8 ? 512 / tiles : 8);
 }
 
 size_t ws_route(const semmoe_config* cfg) {
   const size_t logits = align_up(size_t(cfg->T) * cfg->E * 4, 256);
-  // few tokens: the router splits K over workgroups and keeps so many partial sums per logit
-  long long parts = route_max_parts(cfg->T);
-  if (cfg->E > 128 && cfg->T > 512) {
-    // the tiles of the grouped GEMM with K split over as many parts as fill the chip, at most 8 and (no chip has 1024
-    // compute units) at most 1024 / tiles
-    const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
-    const long long big = tiles >= 1024 ? 1 : (1024 / tiles < 8 ? 1024 / tiles : 8);
-    if (big > parts) parts = big;
+  // the router splits K over workgroups where the token tiles leave the chip idle, and keeps so many partial sums per logit
+  if (cfg->E <= 128 || cfg->T <= 512) {
+    const int parts = route_max_parts(cfg);
+    return (parts > 1 ? parts + 1 : 1) * logits + 512;
   }
-  return (parts > 1 || cfg->E > 128 ? size_t(parts + 1) : 1) * logits + 512;
+  // more than 128 experts: K split of the 256 x 256 tile over as many parts as fill the chip, at most 8 and (a bound
+  // that needs no device: no chip has 1024 compute units) at most 1024 / tiles
+  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
+  const long long parts = tiles >= 1024 ? 1 : (1024 / tiles < 8 ? 1024 / tiles : 8);
+  return size_t(parts + 1) * logits + 512;
 }
 
 }  // namespace semmoe

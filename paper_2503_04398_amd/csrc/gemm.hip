@@ -552,7 +552,7 @@ int32_t launch_ksplit_gemm(const void* X, const void* W, int T, int N, int d, in
   a.group_to_weight = nullptr;
   a.out = partial; a.ldo = N;
   a.ksplit_rows = T;
-  return launch_w4<kModeLogits, 64, 3, 2, 2>(a, T * n_parts, stream);
+  return launch_w4<kModeLogits, 64, 2, 2>(a, T * n_parts, stream);
 }
 
 int32_t launch_gemm(int mode, int dtype, const GemmArgs& a, int max_rows, int est_rows_per_group,

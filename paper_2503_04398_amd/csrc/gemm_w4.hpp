@@ -377,10 +377,8 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
     const int tok_in = lane & 31, half = lane >> 5;
     const int r_row = lane >> 3, r_chunk = lane & 7;  // read-back: 8 lanes per staged row
     if constexpr (MODE == kModeLogits) {
-      // fp32 sums: 32 features x 16 tokens per pass, a staged row = 32 floats = 8 chunks of 16 bytes (32 tokens would not fit
-      // beside the ring).  N is a multiple of 4 (checked by the host), so a chunk is inside the matrix or outside it as a whole.
-      constexpr int kRowF = 32 * 4 + 16;
-      static_assert(16 * kRowF <= C::kStgWave, "the staging area of a wave");
+      // fp32 sums: one MFMA tile (32 features x 32 tokens) per pass, a staged row = 32 floats = 8 chunks of 16 bytes.
+      // N is a multiple of 4 (checked by the host), so a chunk is inside the matrix or outside it as a whole.
       float* outf = static_cast<float*>(a.out);
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
@@ -389,31 +387,26 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
         for (int i = 0; i < 4; ++i) {
           __builtin_amdgcn_sched_barrier(0);
           asm volatile("" : "+a"(acc[i][j]));
-          unsigned char* wp = stg + (tok_in & 15) * kRowF + half * 16;
+          unsigned char* wp = stg + tok_in * C::kStgRow + half * 16;
           const f32x16_t& c = acc[i][j];
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            f32x4_t v = {c[g4 * 4 + 0], c[g4 * 4 + 1], c[g4 * 4 + 2], c[g4 * 4 + 3]};
+            *reinterpret_cast<f32x4_t*>(wp + g4 * 32) = v;
+          }
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_wave_barrier();
           const int feat = t.f0 + wf * 128 + i * 32 + r_chunk * 4;
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {  // tokens 16 h .. 16 h + 15 of the MFMA tile
-            if ((tok_in >> 4) == h) {
-#pragma unroll
-              for (int g4 = 0; g4 < 4; ++g4) {
-                f32x4_t v = {c[g4 * 4 + 0], c[g4 * 4 + 1], c[g4 * 4 + 2], c[g4 * 4 + 3]};
-                *reinterpret_cast<f32x4_t*>(wp + g4 * 32) = v;
-              }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-              const int sr = p * 8 + r_row;
-              const int row = (j * 2 + wt) * 32 + h * 16 + sr;
-              const f32x4_t v = *reinterpret_cast<const f32x4_t*>(stg + sr * kRowF + r_chunk * 16);
-              if (row < t.n_tok && feat < a.N)  // read once, soon: not worth a place in the memory-side cache
-                __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(outf + (size_t(t.row_lo) + row) * a.ldo + feat));
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_wave_barrier();
+          for (int p = 0; p < 4; ++p) {
+            const int sr = p * 8 + r_row;
+            const int row = (j * 2 + wt) * 32 + sr;
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(stg + sr * C::kStgRow + r_chunk * 16);
+            if (row < t.n_tok && feat < a.N)  // read once, soon: not worth a place in the memory-side cache
+              __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(outf + (size_t(t.row_lo) + row) * a.ldo + feat));
           }
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_wave_barrier();
         }
       }
       continue;

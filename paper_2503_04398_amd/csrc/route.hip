@@ -806,7 +806,11 @@ struct RouteCfg {
   static_assert((NSTAGE - 1) * IPW < 64, "vmcnt range");
 };
 
-template <int TF, int TT, int NSTAGE, typename FORM, bool SIG>
+// PARTS (the token tiles alone would leave much of the chip idle): a workgroup takes (token tile, part of K) and writes its raw
+// fp32 sums to partial[part][token][expert]; a second kernel adds the parts up in order, adds the bias terms and selects.
+// A kernel of its own without the selection, and one tile a workgroup: a short kernel waits for its code, and a loop over
+// tiles has the compiler set up in front of it what the selection behind it needs (spilled scalars and all).
+template <int TF, int TT, int NSTAGE, typename FORM, bool SIG, bool PARTS>
 __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, const bf16_t* __restrict__ X,
                                                           const bf16_t* __restrict__ W_r,
                                                           const float* __restrict__ b_g,
@@ -817,9 +821,6 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
                                                           int32_t* __restrict__ topk_ids,
                                                           float* __restrict__ topk_w, int n_parts,
                                                           float* __restrict__ partial) {
-  // n_parts > 1 (few tokens: the token tiles alone would leave most of the chip idle): a work item is (token tile,
-  // part of K); it writes its raw fp32 sums to partial[part][token][expert] and a second kernel adds the parts up
-  // in order, adds the bias terms and hands the logits to the selection kernel.
   using C = RouteCfg<TF, TT, NSTAGE>;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const unsigned lds_base = static_cast<unsigned>(reinterpret_cast<size_t>(lds_raw));
@@ -833,199 +834,194 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
   const int k_tail = K - (nk - 1) * C::BK;
   const int frag_swz = (lrow / C::RPB) % C::CPR;
   const int d_row = lane / C::CPR, d_pos = lane % C::CPR;
-  const int n_tiles = (T + C::BT - 1) / C::BT;
 
-  const int spp = (nk + n_parts - 1) / n_parts;  // slices per part
-  for (int item = blockIdx.x; item < n_tiles * n_parts; item += gridDim.x) {
-    const int tile = item / n_parts, part = item - tile * n_parts;
-    const int s_lo = min(part * spp, nk), n_it = min(nk, s_lo + spp) - s_lo;
-    const int tok0 = tile * C::BT;
-    const bf16_t* src[C::IPW];
-    int src_chunk[C::IPW];
+  const int spp = PARTS ? (nk + n_parts - 1) / n_parts : nk;  // slices per part
+  const int tile = PARTS ? int(blockIdx.x) / n_parts : int(blockIdx.x), part = PARTS ? int(blockIdx.x) - tile * n_parts : 0;
+  const int s_lo = PARTS ? min(part * spp, nk) : 0, n_it = min(nk, s_lo + spp) - s_lo;
+  const int tok0 = tile * C::BT;
+  const bf16_t* src[C::IPW];
+  int src_chunk[C::IPW];
 #pragma unroll
-    for (int i = 0; i < C::IPW; ++i) {
-      const int sr = (wave * C::IPW + i) * C::RPI + d_row;
-      const int c = d_pos ^ ((sr / C::RPB) % C::CPR);
-      src_chunk[i] = c;
-      src[i] = (sr < C::BW) ? W_r + size_t(min(sr, E - 1)) * K + c * 8
-                            : X + size_t(min(tok0 + sr - C::BW, T - 1)) * K + c * 8;
-    }
-    auto issue = [&](int it_) {  // slice s_lo + it_ of K into ring stage it_ % NSTAGE
-      const int slice = s_lo + it_;
-      const unsigned dst0 = lds_base + (it_ % NSTAGE) * C::kStageBytes + wave * C::IPW * 1024;
-      const int k0 = slice * C::BK;
-      if (slice + 1 < nk || k_tail == C::BK) {
+  for (int i = 0; i < C::IPW; ++i) {
+    const int sr = (wave * C::IPW + i) * C::RPI + d_row;
+    const int c = d_pos ^ ((sr / C::RPB) % C::CPR);
+    src_chunk[i] = c;
+    src[i] = (sr < C::BW) ? W_r + size_t(min(sr, E - 1)) * K + c * 8
+                          : X + size_t(min(tok0 + sr - C::BW, T - 1)) * K + c * 8;
+  }
+  auto issue = [&](int it_) {  // slice s_lo + it_ of K into ring stage it_ % NSTAGE
+    const int slice = s_lo + it_;
+    const unsigned dst0 = lds_base + (it_ % NSTAGE) * C::kStageBytes + wave * C::IPW * 1024;
+    const int k0 = slice * C::BK;
+    if (slice + 1 < nk || k_tail == C::BK) {
 #pragma unroll
-        for (int i = 0; i < C::IPW; ++i) lds_dma16(src[i] + k0, dst0 + i * 1024);
-      } else {
+      for (int i = 0; i < C::IPW; ++i) lds_dma16(src[i] + k0, dst0 + i * 1024);
+    } else {
 #pragma unroll
-        for (int i = 0; i < C::IPW; ++i) {
-          if (src_chunk[i] * 8 < k_tail) lds_dma16(src[i] + k0, dst0 + i * 1024);
-          else *reinterpret_cast<uint4*>(lds_raw + (dst0 - lds_base) + i * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
-        }
+      for (int i = 0; i < C::IPW; ++i) {
+        if (src_chunk[i] * 8 < k_tail) lds_dma16(src[i] + k0, dst0 + i * 1024);
+        else *reinterpret_cast<uint4*>(lds_raw + (dst0 - lds_base) + i * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
       }
-    };
+    }
+  };
 
-    // two accumulator sets (even / odd k-steps): halves the chain of dependent MFMAs inside a slice
-    f32x16_t acc[TF][TT], acc2[TF][TT];
+  // two accumulator sets (even / odd k-steps): halves the chain of dependent MFMAs inside a slice
+  f32x16_t acc[TF][TT], acc2[TF][TT];
 #pragma unroll
-    for (int i = 0; i < TF; ++i)
+  for (int i = 0; i < TF; ++i)
 #pragma unroll
-      for (int j = 0; j < TT; ++j)
+    for (int j = 0; j < TT; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[i][j][r] = 0.0f;
-          acc2[i][j][r] = 0.0f;
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] = 0.0f;
+        acc2[i][j][r] = 0.0f;
+      }
+
+  // the tokens' classes are requested before the ring: they have arrived long before the logits need them
+  int cls_of[TT];
+#pragma unroll
+  for (int j = 0; j < TT; ++j) {
+    const int tok = tok0 + j * 32 + lrow;
+    cls_of[j] = (!PARTS && token_class && tok < T) ? token_class[tok] : -1;
+  }
+#pragma unroll
+  for (int s0 = 0; s0 < NSTAGE - 1; ++s0)
+    if (s0 < n_it) issue(s0);
+  for (int it = 0; it < n_it; ++it) {
+    const int younger = min(NSTAGE - 2, n_it - 1 - it);
+    if (younger >= 4) wait_vmcnt<4 * C::IPW>();
+    else if (younger == 3) wait_vmcnt<3 * C::IPW>();
+    else if (younger == 2) wait_vmcnt<2 * C::IPW>();
+    else if (younger == 1) wait_vmcnt<1 * C::IPW>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    const unsigned char* Ws = lds_raw + (it % NSTAGE) * C::kStageBytes;
+    const unsigned char* Xs = Ws + C::BW * C::RB;
+    const unsigned char* wrow = Ws + (wave * TF * 32 + lrow) * C::RB;
+    const unsigned char* xrow = Xs + lrow * C::RB;
+    // all fragment reads of the slice are requested before the first MFMA (the per-slice work is small: the
+    // loop is bound by latencies, not by throughput)
+    bf16x8_t af[4][TF], bfr[4][TT];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      const int off = ((st * 2 + half) ^ frag_swz) * 16;
+#pragma unroll
+      for (int i = 0; i < TF; ++i) af[st][i] = *reinterpret_cast<const bf16x8_t*>(wrow + i * 32 * C::RB + off);
+#pragma unroll
+      for (int j = 0; j < TT; ++j) bfr[st][j] = *reinterpret_cast<const bf16x8_t*>(xrow + j * 32 * C::RB + off);
+    }
+    // the refill of the stage freed by the barrier goes out while the fragment reads are in flight
+    __builtin_amdgcn_sched_barrier(0);
+    if (it + NSTAGE - 1 < n_it) issue(it + NSTAGE - 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < 4; st += 2) {
+#pragma unroll
+      for (int i = 0; i < TF; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[st][i], bfr[st][j], acc[i][j], 0, 0, 0);
+          acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[st + 1][i], bfr[st + 1][j], acc2[i][j], 0, 0, 0);
         }
-
-    // the tokens' classes are requested before the ring: they have arrived long before the logits need them
-    int cls_of[TT];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TF; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[i][j] += acc2[i][j];
+  if constexpr (PARTS) {  // raw sums of this part of K
 #pragma unroll
     for (int j = 0; j < TT; ++j) {
       const int tok = tok0 + j * 32 + lrow;
-      cls_of[j] = (token_class && !partial && tok < T) ? token_class[tok] : -1;
-    }
-#pragma unroll
-    for (int s0 = 0; s0 < NSTAGE - 1; ++s0)
-      if (s0 < n_it) issue(s0);
-    for (int it = 0; it < n_it; ++it) {
-      const int younger = min(NSTAGE - 2, n_it - 1 - it);
-      if (younger >= 4) wait_vmcnt<4 * C::IPW>();
-      else if (younger == 3) wait_vmcnt<3 * C::IPW>();
-      else if (younger == 2) wait_vmcnt<2 * C::IPW>();
-      else if (younger == 1) wait_vmcnt<1 * C::IPW>();
-      else wait_vmcnt<0>();
-      __syncthreads();
-      const unsigned char* Ws = lds_raw + (it % NSTAGE) * C::kStageBytes;
-      const unsigned char* Xs = Ws + C::BW * C::RB;
-      const unsigned char* wrow = Ws + (wave * TF * 32 + lrow) * C::RB;
-      const unsigned char* xrow = Xs + lrow * C::RB;
-      // all fragment reads of the slice are requested before the first MFMA (the per-slice work is small: the
-      // loop is bound by latencies, not by throughput)
-      bf16x8_t af[4][TF], bfr[4][TT];
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        const int off = ((st * 2 + half) ^ frag_swz) * 16;
-#pragma unroll
-        for (int i = 0; i < TF; ++i) af[st][i] = *reinterpret_cast<const bf16x8_t*>(wrow + i * 32 * C::RB + off);
-#pragma unroll
-        for (int j = 0; j < TT; ++j) bfr[st][j] = *reinterpret_cast<const bf16x8_t*>(xrow + j * 32 * C::RB + off);
-      }
-      // the refill of the stage freed by the barrier goes out while the fragment reads are in flight
-      __builtin_amdgcn_sched_barrier(0);
-      if (it + NSTAGE - 1 < n_it) issue(it + NSTAGE - 1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int st = 0; st < 4; st += 2) {
-#pragma unroll
-        for (int i = 0; i < TF; ++i)
-#pragma unroll
-          for (int j = 0; j < TT; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[st][i], bfr[st][j], acc[i][j], 0, 0, 0);
-            acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[st + 1][i], bfr[st + 1][j], acc2[i][j], 0, 0, 0);
-          }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < TF; ++i)
-#pragma unroll
-      for (int j = 0; j < TT; ++j) acc[i][j] += acc2[i][j];
-    if (partial) {  // raw sums of this part of K; no wave reads LDS any more, the next item's loads may start
-#pragma unroll
-      for (int j = 0; j < TT; ++j) {
-        const int tok = tok0 + j * 32 + lrow;
-#pragma unroll
-        for (int i = 0; i < TF; ++i) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int e = (wave * TF + i) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-            if (e < E && tok < T) partial[(size_t(part) * T + tok) * E + e] = acc[i][j][r];
-          }
-        }
-      }
-      __syncthreads();
-      continue;
-    }
-    __syncthreads();  // every wave is done with the ring: its first bytes now hold the logits
-
-    // A lane holds, per 32 x 32 block, four groups of four consecutive experts of one token.  With E a multiple of
-    // four and 16-byte aligned bias arrays a group's bias terms are one 16-byte load each, all requested before the
-    // first is used (one exposed latency per token tile instead of one per element), and a group's logits are
-    // one 16-byte LDS write and one 16-byte store.
-    const bool vec4 = (E & 3) == 0 && ((reinterpret_cast<size_t>(b_g) | reinterpret_cast<size_t>(class_bias) |
-                                        reinterpret_cast<size_t>(logits_out)) & 15) == 0;
-#pragma unroll
-    for (int j = 0; j < TT; ++j) {
-      const int tl = j * 32 + lrow;
-      const int tok = tok0 + tl;
-      const int cls = cls_of[j];
-      const float* cb = (cls >= 0 && cls < cfg.num_classes && class_bias) ? class_bias + size_t(cls) * E : nullptr;
-      if (vec4) {
-        f32x4_t add[TF][4];
-#pragma unroll
-        for (int i = 0; i < TF; ++i)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int e0 = (wave * TF + i) * 32 + g * 8 + half * 4;
-            f32x4_t a = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (e0 < E) {
-              if (b_g) a = *reinterpret_cast<const f32x4_t*>(b_g + e0);
-              if (cb) a += *reinterpret_cast<const f32x4_t*>(cb + e0);
-            }
-            add[i][g] = a;
-          }
-#pragma unroll
-        for (int i = 0; i < TF; ++i)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int e0 = (wave * TF + i) * 32 + g * 8 + half * 4;
-            if (e0 < E) {
-              f32x4_t v = {acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]};
-              v += add[i][g];
-              *reinterpret_cast<f32x4_t*>(lg + tl * ldl + e0) = v;
-              if (logits_out && tok < T) *reinterpret_cast<f32x4_t*>(logits_out + size_t(tok) * E + e0) = v;
-            }
-          }
-        continue;
-      }
 #pragma unroll
       for (int i = 0; i < TF; ++i) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int e = (wave * TF + i) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-          if (e < E) {
-            float v = acc[i][j][r];
-            if (b_g) v += b_g[e];
-            if (cb) v += cb[e];
-            lg[tl * ldl + e] = v;
-            if (logits_out && tok < T) logits_out[size_t(tok) * E + e] = v;
+          if (e < E && tok < T) partial[(size_t(part) * T + tok) * E + e] = acc[i][j][r];
+        }
+      }
+    }
+    return;
+  }
+  __syncthreads();  // every wave is done with the ring: its first bytes now hold the logits
+
+  // A lane holds, per 32 x 32 block, four groups of four consecutive experts of one token.  With E a multiple of
+  // four and 16-byte aligned bias arrays a group's bias terms are one 16-byte load each, all requested before the
+  // first is used (one exposed latency per token tile instead of one per element), and a group's logits are
+  // one 16-byte LDS write and one 16-byte store.
+  const bool vec4 = (E & 3) == 0 && ((reinterpret_cast<size_t>(b_g) | reinterpret_cast<size_t>(class_bias) |
+                                      reinterpret_cast<size_t>(logits_out)) & 15) == 0;
+#pragma unroll
+  for (int j = 0; j < TT; ++j) {
+    const int tl = j * 32 + lrow;
+    const int tok = tok0 + tl;
+    const int cls = cls_of[j];
+    const float* cb = (cls >= 0 && cls < cfg.num_classes && class_bias) ? class_bias + size_t(cls) * E : nullptr;
+    if (vec4) {
+      f32x4_t add[TF][4];
+#pragma unroll
+      for (int i = 0; i < TF; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int e0 = (wave * TF + i) * 32 + g * 8 + half * 4;
+          f32x4_t a = {0.0f, 0.0f, 0.0f, 0.0f};
+          if (e0 < E) {
+            if (b_g) a = *reinterpret_cast<const f32x4_t*>(b_g + e0);
+            if (cb) a += *reinterpret_cast<const f32x4_t*>(cb + e0);
+          }
+          add[i][g] = a;
+        }
+#pragma unroll
+      for (int i = 0; i < TF; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int e0 = (wave * TF + i) * 32 + g * 8 + half * 4;
+          if (e0 < E) {
+            f32x4_t v = {acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]};
+            v += add[i][g];
+            *reinterpret_cast<f32x4_t*>(lg + tl * ldl + e0) = v;
+            if (logits_out && tok < T) *reinterpret_cast<f32x4_t*>(logits_out + size_t(tok) * E + e0) = v;
           }
         }
-      }
+      continue;
     }
-    __syncthreads();
-    if constexpr (FORM::kRows) {
-      for (int base = wave * kRowTokens; base < C::BT; base += 4 * kRowTokens)
-        select_tokens_by_rows<FORM, SIG>(
-            cfg, base, C::BT, [&](int tl) { return lg + tl * ldl; }, tok0, sel_bias, lane, topk_ids, topk_w);
-    } else {
-      for (int tl0 = wave; tl0 < C::BT; tl0 += 4 * kSelTokens) {
-        const float* rows[kSelTokens];
-        int32_t* ids_out[kSelTokens];
-        float* w_out[kSelTokens];
 #pragma unroll
-        for (int t = 0; t < kSelTokens; ++t) {
-          const int tl = tl0 + 4 * t;
-          const int tok = tok0 + tl;
-          const bool ok = tl < C::BT && tok < T;
-          rows[t] = ok ? lg + tl * ldl : nullptr;
-          ids_out[t] = ok ? topk_ids + size_t(tok) * cfg.k : nullptr;
-          w_out[t] = ok ? topk_w + size_t(tok) * cfg.k : nullptr;
+    for (int i = 0; i < TF; ++i) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int e = (wave * TF + i) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        if (e < E) {
+          float v = acc[i][j][r];
+          if (b_g) v += b_g[e];
+          if (cb) v += cb[e];
+          lg[tl * ldl + e] = v;
+          if (logits_out && tok < T) logits_out[size_t(tok) * E + e] = v;
         }
-        select_rows_any<kSelTokens>(cfg, rows, sel_bias, lane, ids_out, w_out);
       }
     }
-    __syncthreads();  // the next tile's loads overwrite the logits
+  }
+  __syncthreads();
+  if constexpr (FORM::kRows) {
+    for (int base = wave * kRowTokens; base < C::BT; base += 4 * kRowTokens)
+      select_tokens_by_rows<FORM, SIG>(
+          cfg, base, C::BT, [&](int tl) { return lg + tl * ldl; }, tok0, sel_bias, lane, topk_ids, topk_w);
+  } else {
+    for (int tl0 = wave; tl0 < C::BT; tl0 += 4 * kSelTokens) {
+      const float* rows[kSelTokens];
+      int32_t* ids_out[kSelTokens];
+      float* w_out[kSelTokens];
+#pragma unroll
+      for (int t = 0; t < kSelTokens; ++t) {
+        const int tl = tl0 + 4 * t;
+        const int tok = tok0 + tl;
+        const bool ok = tl < C::BT && tok < T;
+        rows[t] = ok ? lg + tl * ldl : nullptr;
+        ids_out[t] = ok ? topk_ids + size_t(tok) * cfg.k : nullptr;
+        w_out[t] = ok ? topk_w + size_t(tok) * cfg.k : nullptr;
+      }
+      select_rows_any<kSelTokens>(cfg, rows, sel_bias, lane, ids_out, w_out);
+    }
   }
 }
 
@@ -1184,65 +1180,50 @@ __global__ __launch_bounds__(256) void route_reduce_kernel(semmoe_config cfg, in
   if (logits_out) logits_out[idx] = v;
 }
 
-// More than 128 experts and tokens enough: the fused kernel's workgroup (32 or 64 tokens) streams all of W_r past its tokens, nine or
-// five rows of operands per token and slice.  The 256 x 128 tile of the grouped GEMM takes three, with K cut into as
-// many parts as fill the chip; the parts are then added in order and the selection runs as a kernel of its own.  (256 x 256
-// tiles take two, but twice the parts: 16384 tokens, d 7168, 256 experts: 73 us + 134 MB of partial sums written and read, 68
-// + 67 MB so; the whole 94 -> 88 us.)  From 12 token tiles on, 8 parts each; below, the fused kernel with parts (1024 tokens:
-// 25 us either way).  Before, the form began at 8192 tokens where three quarters of the chip were filled and the fused kernel
-// walked all of K for the others: 4096 tokens 75 -> 35 us, 12000 tokens 164 -> 78.
+// Many tokens and more than 128 experts: the fused kernel's workgroup (64 tokens) streams all of W_r past its tokens,
+// five rows of operands per token and slice.  The 256 x 256 tile of the grouped GEMM takes two, with K cut into as
+// many parts as fill the chip; the parts are then added in order and the selection runs as a kernel of its own.  Which
+// token counts take how many parts decides the order of the sums, and with it which of two groups of experts with nearly
+// equal scores a token goes to: half the parts on 256 x 128 tiles are 7 us faster on 16384 tokens (94 -> 87) and 8 of them would
+// halve the time of 1024 to 8191, but one token in 16384 then goes elsewhere.
 // tune (SEMMOE_TUNE_ROUTE_SPLIT): -1 automatic, 0 never, 100 + n this form with n parts whatever the token count.
-static int route_big_cap(const semmoe_config* cfg) {  // what the workspace is sized for
-  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
-  return tiles >= 1024 ? 1 : int(1024 / tiles < 8 ? 1024 / tiles : 8);
-}
-
 static int route_big_parts(const semmoe_config* cfg, int ncu) {
   const int tune = tuning_value(SEMMOE_TUNE_ROUTE_SPLIT);
   if (cfg->dtype != SEMMOE_BF16 || tune == 0 || cfg->E <= 128 || cfg->E % 4 != 0 || cfg->d % 64 != 0) return 0;
-  const int nk = cfg->d / 64, cap = route_big_cap(cfg);
+  const int nk = cfg->d / 64;
+  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
+  const int cap = tiles >= 1024 ? 1 : int(1024 / tiles < 8 ? 1024 / tiles : 8);  // what the workspace is sized for
   if (tune >= 100) {
     const int parts = tune - 100;
-    return (parts >= 1 && parts <= cap && nk % parts == 0 && nk / parts >= 3) ? parts : 0;
+    return (parts >= 1 && parts <= cap && nk % parts == 0 && nk / parts >= 2) ? parts : 0;
   }
   if (tune > 0) return 0;  // a forced split of the fused kernel
-  const long long items = (long long)cdiv(cfg->T, 128) * cdiv(cfg->E, 256);
-  int parts = items > ncu ? 1 : int(ncu / items);
+  if (tiles * 8 < ncu) return 0;  // too few tokens to fill the chip with 256-token tiles and K parts of useful depth
+  int parts = int(ncu / tiles);
+  if (parts < 1) parts = 1;
   if (parts > cap) parts = cap;
   while (parts > 1 && (nk % parts != 0 || nk / parts < 8)) --parts;
-  return items * parts * 8 >= 3LL * ncu && nk / parts >= 3 ? parts : 0;
-}
-
-// A workspace too small for the partial sums: refused where tiles of 256 tokens times the parts fill three quarters of the
-// chip (and where the form is asked for); the others run without, on the fused kernel.
-static bool route_big_needs_workspace(const semmoe_config* cfg, int ncu) {
-  if (tuning_value(SEMMOE_TUNE_ROUTE_SPLIT) >= 100) return true;
-  const int nk = cfg->d / 64, cap = route_big_cap(cfg);
-  const long long tiles = (long long)cdiv(cfg->T, 256) * cdiv(cfg->E, 256);
-  int parts = tiles > ncu ? 1 : int(ncu / tiles);
-  if (parts > cap) parts = cap;
-  while (parts > 1 && (nk % parts != 0 || nk / parts < 8)) --parts;
-  return tiles * 8 >= ncu && tiles * parts * 4 >= 3LL * ncu;
+  if (tiles * parts * 4 < (long long)ncu * 3) return 0;  // K too short to cut into enough parts: the fused kernel fills the chip
+  return nk / parts >= 2 ? parts : 0;
 }
 
 // Parts of K for the fused router, 1 = none.  With at most a 32-token tile for every second compute unit the rest of the chip
-// takes parts of K.  Beyond 256 tokens a part has at least 6 slices (512 tokens of d 4096: 16 parts 13.4 us, 10 parts 12.4:
-// partial sums are written and read), and what the walk gets shorter by has to repay the second kernel: 20 slices
-// (4096 tokens, two parts: d 2048 15.4 -> 15.8 us, d 2880 18.0 -> 17.1, d 4096 23.6 -> 20.1; 1024 tokens: d 2048 15.0 -> 12.3,
-// d 4096 23.5 -> 13.4, d 7168 with 256 experts 64 -> 25.5).
+// takes parts of K: up to 512 tokens at least two slices each; beyond (up to 128 experts) at least 6, and what the walk gets
+// shorter by has to repay the second kernel: 20 slices (4096 tokens, two parts: d 2048 15.4 -> 15.8 us, d 2880 18.0 -> 17.1,
+// d 4096 23.6 -> 20.1; 1024 tokens: d 2048 15.0 -> 12.3, d 4096 23.5 -> 13.4).
 // tune: -1 automatic, 0 never, n > 1 that many parts
 static int route_parts(const semmoe_config* cfg, int ncu) {
   const int tune = tuning_value(SEMMOE_TUNE_ROUTE_SPLIT);
   const int n_tiles = cdiv(cfg->T, 32), nk = cdiv(cfg->d, 64);
-  const int most = route_max_parts(cfg->T);
+  const int most = route_max_parts(cfg);
   if (cfg->dtype != SEMMOE_BF16 || tune == 0 || most < 2) return 1;
-  const bool forced = tune > 1 && tune < 100;
+  const bool forced = tune > 1 && tune < 100, many = cfg->T > 512 && !forced;
   int parts = forced ? tune : ncu / n_tiles;
-  if (!forced && cfg->T > 256 && parts > nk / 6) parts = nk / 6;
+  if (many && parts > nk / 6) parts = nk / 6;
   if (parts > most) parts = most;
   if (parts > nk / 2) parts = nk / 2;  // at least two slices per part
   if (parts < 2) return 1;
-  return !forced && cfg->T > 512 && nk - nk / parts < 20 ? 1 : parts;
+  return many && nk - nk / parts < 20 ? 1 : parts;
 }
 
 static int32_t validate_select(const semmoe_config* cfg) {
@@ -1320,8 +1301,8 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       Carver c(ws, ws_bytes);
       float* part = c.take<float>(size_t(big_parts) * cfg->T * cfg->E);
       float* lg = c.take<float>(size_t(cfg->T) * cfg->E);
-      if (!c.ok && route_big_needs_workspace(cfg, ncu)) return SEMMOE_EWORKSPACE;
-      st = c.ok ? launch_ksplit_gemm(X, W_r, cfg->T, cfg->E, cfg->d, big_parts, part, s) : SEMMOE_EUNSUPPORTED;
+      if (!c.ok) return SEMMOE_EWORKSPACE;
+      st = launch_ksplit_gemm(X, W_r, cfg->T, cfg->E, cfg->d, big_parts, part, s);
       if (st == SEMMOE_OK && launch_sum_select(cfg, s, big_parts, part, b_g, token_class, class_bias, sel_bias,
                                                logits_out, topk_ids, topk_w)) {
         SEMMOE_LAUNCH_CHECK();
@@ -1358,34 +1339,31 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     const int n_tiles = cdiv(cfg->T, bt);
     const int slots = select_slots(*cfg);
     // TF x 128 experts and TT x 32 tokens a workgroup, a ring of NS
-    auto launch = [&](auto tf_, auto tt_, auto ns_, auto form, auto sig) -> int32_t {
+    auto launch = [&](auto tf_, auto tt_, auto ns_, auto form, auto sig, auto in_parts) -> int32_t {
       constexpr int TF = decltype(tf_)::value, TT = decltype(tt_)::value, NS = decltype(ns_)::value;
       using RC = RouteCfg<TF, TT, NS>;
-      auto kern = route_fused_kernel<TF, TT, NS, decltype(form), decltype(sig)::value>;
+      auto kern = route_fused_kernel<TF, TT, NS, decltype(form), decltype(sig)::value, decltype(in_parts)::value>;
       size_t lds = size_t(NS) * RC::kStageBytes;
       const size_t lg_bytes = size_t(RC::BT) * (cfg->E + 4) * 4;
       if (lg_bytes > lds) lds = lg_bytes;
-      const int per_cu = lds <= 80 * 1024 ? 2 : 1;
-      const int items = n_tiles * n_parts;
-      const int grid = items < ncu * per_cu ? items : ncu * per_cu;
       static std::atomic<uint64_t> lds_allowed{0};  // one per instantiation
       const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
       if (as != SEMMOE_OK) return as;
-      hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, *cfg, Xb, Wb, b_g, token_class, class_bias, sel_bias, logits_out,
-                         topk_ids, topk_w, n_parts, partial);
+      hipLaunchKernelGGL(kern, dim3(n_tiles * n_parts), dim3(256), lds, s, *cfg, Xb, Wb, b_g, token_class, class_bias, sel_bias,
+                         logits_out, topk_ids, topk_w, n_parts, partial);
       return SEMMOE_OK;
     };
     // the forms a shape can need: up to 128 experts 4 and 8 slots, up to 256 experts 16, or none of them
     auto launch_128 = [&](auto tf_, auto tt_, auto ns_) -> int32_t {
-      auto with = [&](auto form, auto sig) { return launch(tf_, tt_, ns_, form, sig); };
+      auto with = [&](auto form, auto sig) { return launch(tf_, tt_, ns_, form, sig, std::false_type{}); };
       if (slots == 4) return with_select_form<4>(*cfg, with);
       if (slots == 8) return with_select_form<8>(*cfg, with);
-      return launch(tf_, tt_, ns_, SelAny{}, std::false_type{});
+      return launch(tf_, tt_, ns_, SelAny{}, std::false_type{}, std::false_type{});
     };
     auto launch_256 = [&](auto tf_, auto tt_, auto ns_) -> int32_t {
-      auto with = [&](auto form, auto sig) { return launch(tf_, tt_, ns_, form, sig); };
+      auto with = [&](auto form, auto sig) { return launch(tf_, tt_, ns_, form, sig, std::false_type{}); };
       if (slots == 16) return with_select_form<16>(*cfg, with);
-      return launch(tf_, tt_, ns_, SelAny{}, std::false_type{});
+      return launch(tf_, tt_, ns_, SelAny{}, std::false_type{}, std::false_type{});
     };
     constexpr std::integral_constant<int, 1> c1{};
     constexpr std::integral_constant<int, 2> c2{};
@@ -1393,9 +1371,16 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     constexpr std::integral_constant<int, 4> c4{};
     constexpr std::integral_constant<int, 5> c5{};
     constexpr std::integral_constant<int, 6> c6{};
-    if (tf == 1) st = wider ? launch_128(c1, c4, c4) : (wide ? launch_128(c1, c2, c5) : launch_128(c1, c1, c6));
-    else if (tf == 2) st = wide ? launch_256(c2, c2, c3) : launch_256(c2, c1, c4);
-    else st = launch(c4, c1, c2, SelAny{}, std::false_type{});
+    if (n_parts > 1) {
+      auto parts = [&](auto tf_, auto ns_) { return launch(tf_, c1, ns_, SelAny{}, std::false_type{}, std::true_type{}); };
+      st = tf == 1 ? parts(c1, c6) : (tf == 2 ? parts(c2, c4) : parts(c4, c2));
+    } else if (tf == 1) {
+      st = wider ? launch_128(c1, c4, c4) : (wide ? launch_128(c1, c2, c5) : launch_128(c1, c1, c6));
+    } else if (tf == 2) {
+      st = wide ? launch_256(c2, c2, c3) : launch_256(c2, c1, c4);
+    } else {
+      st = launch(c4, c1, c2, SelAny{}, std::false_type{}, std::false_type{});
+    }
     if (st != SEMMOE_OK) return st;
     SEMMOE_LAUNCH_CHECK();
     if (n_parts > 1) {
