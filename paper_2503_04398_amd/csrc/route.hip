@@ -806,8 +806,9 @@ struct RouteCfg {
   static_assert((NSTAGE - 1) * IPW < 64, "vmcnt range");
 };
 
-// PARTS (the token tiles alone would leave much of the chip idle): a workgroup takes (token tile, part of K) and writes its raw
-// fp32 sums to partial[part][token][expert]; a second kernel adds the parts up in order, adds the bias terms and selects.
+// PARTS (the token tiles alone would leave much of the chip idle): a workgroup takes (token tile, tile of 128 TF experts,
+// part of K) and writes its raw fp32 sums to partial[part][token][expert]; a second kernel adds the parts up in order, adds the
+// bias terms and selects.
 // A kernel of its own without the selection, and one tile a workgroup: a short kernel waits for its code, and a loop over
 // tiles has the compiler set up in front of it what the selection behind it needs (spilled scalars and all).
 template <int TF, int TT, int NSTAGE, typename FORM, bool SIG, bool PARTS>
@@ -836,7 +837,9 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
   const int d_row = lane / C::CPR, d_pos = lane % C::CPR;
 
   const int spp = PARTS ? (nk + n_parts - 1) / n_parts : nk;  // slices per part
-  const int tile = PARTS ? int(blockIdx.x) / n_parts : int(blockIdx.x), part = PARTS ? int(blockIdx.x) - tile * n_parts : 0;
+  const int n_et = PARTS ? (E + C::BW - 1) / C::BW : 1;  // tiles of experts; without PARTS one holds them all
+  const int item = PARTS ? int(blockIdx.x) / n_parts : int(blockIdx.x), part = PARTS ? int(blockIdx.x) - item * n_parts : 0;
+  const int tile = item / n_et, e0 = (item - tile * n_et) * C::BW;
   const int s_lo = PARTS ? min(part * spp, nk) : 0, n_it = min(nk, s_lo + spp) - s_lo;
   const int tok0 = tile * C::BT;
   const bf16_t* src[C::IPW];
@@ -846,7 +849,7 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
     const int sr = (wave * C::IPW + i) * C::RPI + d_row;
     const int c = d_pos ^ ((sr / C::RPB) % C::CPR);
     src_chunk[i] = c;
-    src[i] = (sr < C::BW) ? W_r + size_t(min(sr, E - 1)) * K + c * 8
+    src[i] = (sr < C::BW) ? W_r + size_t(min(e0 + sr, E - 1)) * K + c * 8
                           : X + size_t(min(tok0 + sr - C::BW, T - 1)) * K + c * 8;
   }
   auto issue = [&](int it_) {  // slice s_lo + it_ of K into ring stage it_ % NSTAGE
@@ -937,7 +940,7 @@ __global__ __launch_bounds__(256) void route_fused_kernel(semmoe_config cfg, con
       for (int i = 0; i < TF; ++i) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int e = (wave * TF + i) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+          const int e = e0 + (wave * TF + i) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
           if (e < E && tok < T) partial[(size_t(part) * T + tok) * E + e] = acc[i][j][r];
         }
       }
@@ -1318,15 +1321,23 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       if (st != SEMMOE_EUNSUPPORTED) return st;
     }
     int n_parts = route_parts(cfg, ncu);
+    const int slots = select_slots(*cfg);
+    // 129 to 256 experts: two workgroups share a tile of 32 tokens, 128 experts each, while all of them are one round of the
+    // chip; the sums stay as they are.  A workgroup then streams 160 rows a slice instead of 288, and the selection's kernel has
+    // the whole chip (group-limited sigmoid, d 7168: 16 tokens 16.8 -> 14.1 us, 256 19.8 -> 17.2, 1024 59.5 -> 41.6, 4096 59.7 ->
+    // 44.7).  Not with 64 tokens (5000: 60.0 us fused, 68.9 so) or 128 (10000: 95.7, 98.1).
+    bool split_e = tf == 2 && slots == 16 && cfg->E % 4 == 0 && tuning_value(SEMMOE_TUNE_ROUTE_SPLIT) != 0 &&
+                   2 * cdiv(cfg->T, 32) * n_parts <= ncu;
     float* partial = nullptr;
     float* logits_ws = nullptr;
-    if (n_parts > 1) {
+    if (n_parts > 1 || split_e) {
       Carver c(ws, ws_bytes);
       partial = c.take<float>(size_t(n_parts) * cfg->T * cfg->E);
       logits_ws = c.take<float>(size_t(cfg->T) * cfg->E);
-      if (!c.ok) {  // beyond 512 tokens the parts are worth a workspace, but not needed
-        if (cfg->T <= 512) return SEMMOE_EWORKSPACE;
+      if (!c.ok) {  // beyond 512 tokens a second kernel is worth a workspace, but not needed
+        if (n_parts > 1 && cfg->T <= 512) return SEMMOE_EWORKSPACE;
         n_parts = 1;
+        split_e = false;
         partial = nullptr;
       }
     }
@@ -1336,20 +1347,19 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     const bool wide = n_parts == 1 && cdiv(cfg->T, 32) > ncu && tf <= 2;
     const bool wider = wide && tf == 1 && cdiv(cfg->T, 128) >= 256;
     const int bt = wider ? 128 : (wide ? 64 : 32);
-    const int n_tiles = cdiv(cfg->T, bt);
-    const int slots = select_slots(*cfg);
+    const int items = cdiv(cfg->T, bt) * n_parts * (split_e ? 2 : 1);
     // TF x 128 experts and TT x 32 tokens a workgroup, a ring of NS
     auto launch = [&](auto tf_, auto tt_, auto ns_, auto form, auto sig, auto in_parts) -> int32_t {
       constexpr int TF = decltype(tf_)::value, TT = decltype(tt_)::value, NS = decltype(ns_)::value;
       using RC = RouteCfg<TF, TT, NS>;
       auto kern = route_fused_kernel<TF, TT, NS, decltype(form), decltype(sig)::value, decltype(in_parts)::value>;
       size_t lds = size_t(NS) * RC::kStageBytes;
-      const size_t lg_bytes = size_t(RC::BT) * (cfg->E + 4) * 4;
+      const size_t lg_bytes = partial ? 0 : size_t(RC::BT) * (cfg->E + 4) * 4;
       if (lg_bytes > lds) lds = lg_bytes;
       static std::atomic<uint64_t> lds_allowed{0};  // one per instantiation
       const int32_t as = allow_max_dynamic_lds(&lds_allowed, reinterpret_cast<const void*>(kern));
       if (as != SEMMOE_OK) return as;
-      hipLaunchKernelGGL(kern, dim3(n_tiles * n_parts), dim3(256), lds, s, *cfg, Xb, Wb, b_g, token_class, class_bias, sel_bias,
+      hipLaunchKernelGGL(kern, dim3(items), dim3(256), lds, s, *cfg, Xb, Wb, b_g, token_class, class_bias, sel_bias,
                          logits_out, topk_ids, topk_w, n_parts, partial);
       return SEMMOE_OK;
     };
@@ -1371,9 +1381,9 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     constexpr std::integral_constant<int, 4> c4{};
     constexpr std::integral_constant<int, 5> c5{};
     constexpr std::integral_constant<int, 6> c6{};
-    if (n_parts > 1) {
-      auto parts = [&](auto tf_, auto ns_) { return launch(tf_, c1, ns_, SelAny{}, std::false_type{}, std::true_type{}); };
-      st = tf == 1 ? parts(c1, c6) : (tf == 2 ? parts(c2, c4) : parts(c4, c2));
+    if (partial) {
+      auto sums = [&](auto tf_, auto ns_) { return launch(tf_, c1, ns_, SelAny{}, std::false_type{}, std::true_type{}); };
+      st = tf == 1 || split_e ? sums(c1, c6) : (tf == 2 ? sums(c2, c4) : sums(c4, c2));
     } else if (tf == 1) {
       st = wider ? launch_128(c1, c4, c4) : (wide ? launch_128(c1, c2, c5) : launch_128(c1, c1, c6));
     } else if (tf == 2) {
@@ -1383,7 +1393,7 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     }
     if (st != SEMMOE_OK) return st;
     SEMMOE_LAUNCH_CHECK();
-    if (n_parts > 1) {
+    if (partial) {
       // adding the parts and selecting in one kernel where the shape has a row form (256 tokens, 128 experts, 16 parts:
       // 3.4 + 6.2 us as two kernels and the gap between them)
       if (launch_sum_select(cfg, s, n_parts, partial, b_g, token_class, class_bias, sel_bias, logits_out, topk_ids,

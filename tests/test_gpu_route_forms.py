@@ -62,9 +62,11 @@ def test_best_of_8_groups(E, tg):
 
 
 # fused with parts of K (512 | 513 tokens, few and many parts, up to a tile for half of the chip), without (4097), 64 tokens a
-# workgroup (8193), ragged last tiles; more than 128 experts: no parts, 64 tokens a workgroup from 8193 on
+# workgroup (8193), ragged last tiles; more than 128 experts: no parts beyond 512 tokens,
+# two workgroups a tile up to 4096 tokens (and 15 parts of K: 40 tokens), 64 tokens a workgroup from 8193 on
 @pytest.mark.parametrize("T,d,E,k", [(257, 512, 128, 8), (512, 1000, 64, 4), (513, 1000, 128, 8), (1024, 2048, 128, 8),
-                                     (4096, 264, 128, 8), (4097, 264, 128, 8), (8193, 136, 96, 4), (1030, 1536, 256, 8),
+                                     (4096, 264, 128, 8), (4097, 264, 128, 8), (8193, 136, 96, 4), (40, 1984, 160, 8), (200, 1024, 252, 8),
+                                     (500, 264, 256, 8), (1030, 1536, 256, 8), (4096, 136, 132, 4), (4100, 136, 132, 4),
                                      (8193, 136, 256, 8), (8300, 1024, 160, 6)])
 def test_gemm_where_its_form_changes(T, d, E, k):
     w = WL.small(T=T, d=d, E=E, k=k, D=1, C=4, dtype="bf16")
@@ -75,8 +77,8 @@ def test_gemm_where_its_form_changes(T, d, E, k):
     assert O.max_rel_err(logits, want) <= 1e-5  # exact inputs; the order of fp32 sums
     want_ids, want_w = H.oracle_select(w, logits)
     assert (ids == want_ids).all() and O.max_rel_err(tw, want_w) <= 1e-5
-    if T > 512 and E <= 128:  # a workspace for one set of logits is enough
-        lay.m.ws_bytes = T * E * 4 + 512
+    if T > 512:  # a workspace for one set of logits, and with more than 128 experts none at all, is enough
+        lay.m.ws_bytes = T * E * 4 + 512 if E <= 128 else 0
         lay.m.ws[lay.m.ws_bytes:].fill_(0x5a)
         logits, ids, tw = lay.route(inp)
         assert O.max_rel_err(logits, want) <= 1e-5
