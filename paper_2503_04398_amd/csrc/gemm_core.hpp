@@ -68,6 +68,16 @@ __device__ __forceinline__ int listed_rows(const GemmArgs& a, int q) {
   return rows <= a.rows_min || (a.rows_max > 0 && rows > a.rows_max) ? 0 : rows;
 }
 
+// Where the walk over K begins in a group, of `steps` steps: spread evenly over groups that follow each other.  Rows of a
+// multiple of 4 KB (d or F 2048, 4096, 6144 in bf16) start on the same memory channels, and with every tile at the same columns
+// the whole chip reads a few of the channels at a time: a stream of 128 bytes a row through an LDS ring on every compute unit
+// reads 4.5 TB/s of rows 4 or 8 KB apart, 6.0 to 6.2 with the starts spread, and so of any other distance; of 512 bytes a row
+// 5.7 (8 KB) and 6.6.  The tiles of one group go on in step, which is how they share token and weight rows in the caches.
+__device__ __forceinline__ int first_step(const GemmArgs& a, int q, int elem_bytes, int steps) {
+  if (a.ksplit_rows || (size_t(a.ldw) * elem_bytes) % 4096 != 0) return 0;
+  return int((uint64_t(uint32_t(a.q_lo + q) * 0x9E3779B9u) * uint32_t(steps)) >> 32);  // multiples of the golden ratio
+}
+
 // Tile list: group q (local index) owns tiles [tile_prefix[q], tile_prefix[q+1]); inside a group the
 // feature tile runs fastest.  Returns total tile count.  `pre` is LDS of nq+1 ints.
 template <bool SIZED = false>
@@ -565,9 +575,11 @@ __device__ __forceinline__ int gemm_bf16_dma_body(const GemmArgs& a, unsigned ch
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
+    const int k_first = first_step(a, q, 2, nk);  // 0 where the last slice is a partial one
+    auto slice_of = [&](int it_) { return it_ + k_first < nk ? it_ + k_first : it_ + k_first - nk; };
 #pragma unroll
     for (int s0 = 0; s0 < NSTAGE - 1; ++s0)
-      if (s0 < nk) issue_to(s0, s0);
+      if (s0 < nk) issue_to(slice_of(s0), s0);
 
     for (int it = 0; it < nk; ++it) {
       // slices it+1 .. min(it+NSTAGE-2, nk-1) were issued after slice `it` and may stay in flight
@@ -580,7 +592,7 @@ __device__ __forceinline__ int gemm_bf16_dma_body(const GemmArgs& a, unsigned ch
       __syncthreads();  // slice `it` is complete in LDS; every wave is done with slice it-1
       // refill the stage slice it-1 lived in.  All loads of the slice are issued at once, as early as possible:
       // spreading them over the k-steps was measured slower (the lead over the next barrier is what counts)
-      if (it + NSTAGE - 1 < nk) issue_to(it + NSTAGE - 1, it + NSTAGE - 1);
+      if (it + NSTAGE - 1 < nk) issue_to(slice_of(it + NSTAGE - 1), it + NSTAGE - 1);
       const unsigned char* Ws = lds_raw + (it % NSTAGE) * C::kStageBytes;
       const unsigned char* Xs = Ws + C::BW * C::RB;
       const unsigned char* wrow = Ws + (wf * TF * 32 + (lane & 31)) * C::RB;

@@ -95,7 +95,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
   if (my.count == 0) return;  // the whole workgroup leaves, before any further barrier
 
   struct Tile {
-    int row_lo, n_tok, f0, widx;
+    int row_lo, n_tok, f0, widx, q;
     bool once;  // the group has one token tile: nobody else reads these weights
   };
   auto locate = [&](int t) __attribute__((always_inline)) {
@@ -111,6 +111,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     r.f0 = ft * C::FEAT;
     r.widx = __builtin_amdgcn_readfirstlane(gtab[3 * q + 2]);
     r.once = n_tt == 1;
+    r.q = q;
     return r;
   };
 
@@ -126,9 +127,9 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
   const off_t x_lane = off_t(l_row) * x_ld + lane_k;
   const unsigned char *wbase, *xbase;
   off_t w_first = 0, x_last = 0;
-  int l_round = 0, l_left = n, l_ntt = 0, f_ntt = 0;
+  int l_round = 0, l_left = n, l_at = 0, l_ntt = 0, f_ntt = 0;  // l_at: which of the wave's slices is next
   bool l_once = true;
-  uint32_t koff = wave * 128;
+  uint32_t koff = 0;
   auto aim = [&](int t) __attribute__((always_inline)) {
     const Tile r = locate(t);
     wbase = static_cast<const unsigned char*>(a.W) + size_t(r.widx) * a.w_group_stride * ES;
@@ -137,6 +138,9 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     x_last = off_t(r.n_tok - 1) * x_ld + lane_k;
     l_ntt = (r.n_tok + 15) >> 4;
     l_once = r.once;
+    // where K is cut evenly (what a last, partial slice holds is masked by its place in the walk)
+    l_at = KTAIL || nst % NW != 0 ? 0 : first_step(a, r.q, ES, n);
+    koff = wave * 128 + l_at * (NW * 128);
   };
   u32x4_t wb[2 * TW], xb[2 * TT];
   auto fetch = [&]() __attribute__((always_inline)) {
@@ -176,9 +180,12 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     }
     f_ntt = l_ntt;
     koff += NW * 128;
+    if (++l_at == n) {
+      l_at = 0;
+      koff = wave * 128;
+    }
     if (--l_left == 0) {
       l_left = n;
-      koff = wave * 128;
       if (l_round + 1 < my.count) ++l_round;  // past the last tile: its slices once more, which nobody uses
       aim(my.item(l_round));
     }

@@ -184,6 +184,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   // ---- load stream state (runs NSTAGE slices ahead of the MFMAs, across tiles)
   int i_tile = 0;  // round of this workgroup
   int i_slice = 0;
+  int i_k = 0;  // place of that slice in K: a group's walk begins where first_step says and wraps around
   int i_stage = 0;
   bool i_done = false;
   // The loads between the MFMAs are issued unconditionally (a branch per load costs more than the load).  Where the
@@ -223,8 +224,9 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
       const int c = d_pos ^ (((sr + C::BW) / C::RPB) % C::CPR);
       return uint32_t(min(sr, t.n_tok - 1)) * uint32_t(a.ldx) * 2u + uint32_t(c) * 16u;
     };
-    i_base = first_w ? w_panel : x_panel;
-    if constexpr (TJ != 4) i_base2 = loads_w ? w_panel : x_panel;
+    i_k = first_step(a, t.q, 2, nk);
+    i_base = (first_w ? w_panel : x_panel) + i_k * C::RB;
+    if constexpr (TJ != 4) i_base2 = (loads_w ? w_panel : x_panel) + i_k * C::RB;
     if (first_w) {
 #pragma unroll
       for (int i = 0; i < kSplit; ++i) i_off[i] = w_off((wave * C::IPW + i) * C::RPI + d_row);
@@ -247,8 +249,10 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
       i_done = true;
       return;
     }
-    i_base += C::RB;
-    if constexpr (TJ != 4) i_base2 += C::RB;
+    const int step = ++i_k == nk ? 1 - nk : 1;
+    if (i_k == nk) i_k = 0;
+    i_base += step * C::RB;
+    if constexpr (TJ != 4) i_base2 += step * C::RB;
     i_stage = (i_stage + 1 == NSTAGE) ? 0 : i_stage + 1;
     i_dst = lds_base + i_stage * C::kStageBytes + wave * C::IPW * 1024;
     if (++i_slice == nk) {
@@ -281,15 +285,17 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   for (int s = 0; s < NSTAGE; ++s) {  // nk >= NSTAGE: these slices belong to the first tile
 #pragma unroll
     for (int i = 0; i < C::IPW; ++i)
-      lds_dma16_s((i < kSplit ? i_base : i_base2) + s * C::RB, i_off[i],
+      lds_dma16_s((i < kSplit ? i_base : i_base2) + (i_k + s < nk ? s : s - nk) * C::RB, i_off[i],
                   lds_base + s * C::kStageBytes + (wave * C::IPW + i) * 1024);
   }
   // The stream stands at slice NSTAGE-1, already fetched.  Where the last load of a window falls behind the
   // window's first k-step, the k-steps before the first barrier carry that tail: they fetch the rest of the
   // standing slice once more and the stream moves on when they are through.  Where a whole window fits into its
   // first k-step no load is placed before the first barrier, and the stream moves on here.
-  i_base += (NSTAGE - 1) * C::RB;
-  if constexpr (TJ != 4) i_base2 += (NSTAGE - 1) * C::RB;
+  const int ahead = i_k + NSTAGE - 1 < nk ? NSTAGE - 1 : NSTAGE - 1 - nk;
+  i_base += ahead * C::RB;
+  if constexpr (TJ != 4) i_base2 += ahead * C::RB;
+  i_k += ahead;
   i_slice = NSTAGE - 1;
   i_stage = NSTAGE - 1;
   i_dst = lds_base + i_stage * C::kStageBytes + wave * C::IPW * 1024;
@@ -546,6 +552,8 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
       }
     }
     int i_slice = 0, i_stage = 0;
+    int i_k = first_step(a, at.q, 2, nk);  // place of the slice in K
+    i_base += i_k * C::RB;
     bool i_done = false;
     unsigned i_dst = 0;
     auto i_next_slice = [&]() __attribute__((always_inline)) {
@@ -554,7 +562,9 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
         return;
       }
       ++i_slice;
-      i_base += C::RB;
+      const int step = ++i_k == nk ? 1 - nk : 1;
+      if (i_k == nk) i_k = 0;
+      i_base += step * C::RB;
       i_stage = (i_stage + 1 == NSTAGE) ? 0 : i_stage + 1;
       i_dst = lds_base + i_stage * C::kStageBytes + my_rows_lds;
     };
@@ -587,9 +597,13 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
     for (int s0 = 0; s0 < NSTAGE; ++s0) {
 #pragma unroll
       for (int i = 0; i < kIpwW; ++i)
-        if (i < n_my) lds_dma16_s(i_base + s0 * C::RB, i_off[i], lds_base + s0 * C::kStageBytes + my_rows_lds + i * 1024);
+        if (i < n_my)
+          lds_dma16_s(i_base + (i_k + s0 < nk ? s0 : s0 - nk) * C::RB, i_off[i],
+                      lds_base + s0 * C::kStageBytes + my_rows_lds + i * 1024);
     }
-    i_base += (NSTAGE - 1) * C::RB;
+    const int ahead = i_k + NSTAGE - 1 < nk ? NSTAGE - 1 : NSTAGE - 1 - nk;
+    i_base += ahead * C::RB;
+    i_k += ahead;
     i_slice = NSTAGE - 1;
     i_stage = NSTAGE - 1;
     i_dst = lds_base + i_stage * C::kStageBytes + my_rows_lds;
