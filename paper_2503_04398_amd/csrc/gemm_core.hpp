@@ -575,11 +575,14 @@ __device__ __forceinline__ int gemm_bf16_dma_body(const GemmArgs& a, unsigned ch
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    const int k_first = first_step(a, q, 2, nk);  // 0 where the last slice is a partial one
-    auto slice_of = [&](int it_) { return it_ + k_first < nk ? it_ + k_first : it_ + k_first - nk; };
+    int at_k = first_step(a, q, 2, nk);  // slice of the next load; begins at 0 where the last slice is a partial one
+    auto issue_next = [&](int it_) {
+      issue_to(at_k, it_);
+      if (++at_k == nk) at_k = 0;
+    };
 #pragma unroll
     for (int s0 = 0; s0 < NSTAGE - 1; ++s0)
-      if (s0 < nk) issue_to(slice_of(s0), s0);
+      if (s0 < nk) issue_next(s0);
 
     for (int it = 0; it < nk; ++it) {
       // slices it+1 .. min(it+NSTAGE-2, nk-1) were issued after slice `it` and may stay in flight
@@ -592,7 +595,7 @@ __device__ __forceinline__ int gemm_bf16_dma_body(const GemmArgs& a, unsigned ch
       __syncthreads();  // slice `it` is complete in LDS; every wave is done with slice it-1
       // refill the stage slice it-1 lived in.  All loads of the slice are issued at once, as early as possible:
       // spreading them over the k-steps was measured slower (the lead over the next barrier is what counts)
-      if (it + NSTAGE - 1 < nk) issue_to(slice_of(it + NSTAGE - 1), it + NSTAGE - 1);
+      if (it + NSTAGE - 1 < nk) issue_next(it + NSTAGE - 1);
       const unsigned char* Ws = lds_raw + (it % NSTAGE) * C::kStageBytes;
       const unsigned char* Xs = Ws + C::BW * C::RB;
       const unsigned char* wrow = Ws + (wf * TF * 32 + (lane & 31)) * C::RB;

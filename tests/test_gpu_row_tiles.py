@@ -249,3 +249,24 @@ def test_one_set_of_weights_by_tiles(n, d, F):
     H.assert_close(H.to_np(Y), want.cpu().numpy(), "bf16", "Y_shared")
     off = ((Y.double() - want).norm(dim=1) / want.norm(dim=1)).max().item()
     assert off <= ROW_TOL["bf16"], off
+
+
+# rows of a multiple of 4 KB: every group begins its walk over K at another place (12 groups: first, last and middle slices),
+# by the tiles with a ring, with a load stream across tiles (grids of few workgroups: the walk wraps in the middle of a tile and
+# at its end), in pieces and streamed; fp32 rows of 4 KB
+@pytest.mark.parametrize("d,F", [(2048, 64), (64, 2048)])
+@pytest.mark.parametrize("dtype,tile,cap", [("bf16", t, c) for t in (16, 22, 26, 28, 33, 34, 35, 40) for c in (-1, 3)] +
+                         [("fp32", 30, -1), ("fp32", 32, 3)])
+def test_walks_that_begin_anywhere(dtype, tile, cap, d, F):
+    if dtype == "fp32":
+        d, F = d // 2, F // 2
+    got, want, mine = _ffn(RAGGED, d, F, dtype, knobs=((0, tile), (1, tile), (4, cap)), seed=tile)
+    _check(got, want, mine, dtype)
+
+
+def test_one_rank_gives_the_bits_of_all():
+    """a rank's launch numbers its groups from the first one it has; the walks are those of the whole launch"""
+    rows, knobs = (30, 64, 17, 40, 9, 33, 128, 50), ((0, 33), (1, 33))
+    every, _, _ = _ffn(rows, 2048, 128, "bf16", D=2, rank=-1, knobs=knobs, seed=5)
+    second, _, mine = _ffn(rows, 2048, 128, "bf16", D=2, rank=1, knobs=knobs, seed=5)
+    assert (every[mine] == second[mine]).all()
