@@ -466,15 +466,20 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //     have a compute unit each from K 2560 (-1 to -3 %; up to 1408 +3 to +6 %).  20 to 39 rows: from K 1408 on, not with a
 //     compute unit each (+1 to +10 %), and up to fewer tiles the more rows it drags along: K 1408 to 2099 20 to 24 rows -3 % up
 //     to 2048 tiles, +1 % beyond, 25 to 29 rows level up to 1024, +1 % beyond, 30 to 39 rows -2 % up to 512, +4 % beyond.
-//   * K 2048 and 4096: the rows of a panel lie a power of two apart, and a slice of the 128 x 64 tile, 128 bytes of each of 192
-//     rows, falls on few memory channels; a streamed step reads 512 consecutive bytes of a row.  64 x 64 is ahead of it
-//     at any number of tiles, 10 to 19 rows K 2048 -4 to -13 %, K 4096 -7 to -20 %, 20 to 39 rows -2 to -13 % (K 1536, 2560,
-//     3072 and 6144 in the same 6649 launches of common widths: as the lines above).
+//   * K 2048 and 4096: rows a power of two apart, where one slice of the 128 x 64 tile, 128 bytes of each of 192 rows, falls on
+//     few memory channels; a streamed step reads 512 consecutive bytes of a row.  With a common start of all walks 64 x 64 was ahead
+//     at any number of tiles (10 to 19 rows 4 to 20 %, 20 to 39 rows 2 to 13 %); with the starts spread over the groups it
+//     still is 3 to 11 % at 10 to 24 rows, level with the lines above from 34 on.
 //   * 256 x 128 tiles need work for every compute unit: 40 to 95 rows, fewer than 96 of them +10 to +20 %, half of the
 //     compute units +1 % at K 1000 and -3 % from K 1400, all of them +6 % below K 384 and 0 to -7 % from 640, two rounds -7 %.
 //     One rank's launch counts the tiles of three times the mean: a loaded rank has that many, and if it has not the loss is
 //     smaller than the gain (5995 random shapes with half to eight times the mean on the rank; 40 to 95 rows expected and 8 times
 //     as many there: 5 % over counting the mean's, even loads: 1 % behind it).
+//     From 20 rows expected on one rank's launch takes them at K 1408 and more where they are half the compute units (a rank that
+//     has as many rows as it expects 0 to 5 % behind 128 x 64, one with two or four times as many up to 18 % ahead; d 4096, F 1536,
+//     32 expected, 64 there: 157 -> 133 us; d 7168, F 2048, 24 and 48: 177 -> 145; below half of the compute units level), a launch
+//     with all experts from 34 rows, K 1024 and all compute units (128 experts of 39 rows, d 2048: 262 -> 240 us, 64 of d 4096, F
+//     1536: 453 -> 438; at 30 rows 4 % behind 64 x 64 streamed, at 32 level).
 //     384 experts and more leave no room in its LDS for their table (512 experts, d 1024, F 512, 300 rows: 776 us as
 //     256 x 256 tiles, 1134 as 128 x 64).
 // Rows that are no whole 128 bytes: neighbouring slices share cache lines, and from about ten rows on the staged tiles
@@ -488,7 +493,7 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 // 33); K below 1024 is three steps a wave or less (d 640, F 384: 11.0 with four waves, 12.4 with eight).  Beyond
 // one tile a compute unit: up to 128 rows four waves on 32 x 32, two workgroups a compute unit; else 128 x 128 pieces as long as
 // they are one round (C, down, 640 rows: 140 tiles of 256 x 128 are 8 % ahead of two rounds of pieces; B, 1024 rows: 128
-// tiles 15 % behind one); 64 x 64 with four waves where the weight rows lie 8 KB or a multiple apart (as K 2048 below; B, gate/up,
+// tiles 15 % behind one); 64 x 64 with four waves where the weight rows lie 8 KB or a multiple apart (one set has no starts to spread; B, gate/up,
 // 640 rows: 63 us with pieces, 53 so).  188 shapes (d, F 256 to 20000, 1 to 2048 rows): 0.83 of the time before.  2000 rows of
 // it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.  256 x 256 tiles are ahead of 256 x 128
 // from three fifths of the compute units on (170 to 190 of them: 2 to 4 %; 130 to 150: 2 % behind); 2514 rows of d 6968,
@@ -516,14 +521,18 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
     if (ring > 2 * cus && a.K < 1536) return a.K >= 640 ? 35 : 26;
     return a.K >= 960 ? 34 : 26;
   }
+  const bool w4_room = W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds());
   if (est < 40) {
+    const long long mid = (long long)a.nq * w_rows / 256;  // 256 x 128 tiles, one per group along the tokens
+    if (whole_slices && w4_room && (all_rows ? est >= 34 && mid >= cus && a.K >= 1024 : est >= 20 && mid * 2 >= cus && a.K >= 1408))
+      return 33;
     if (!whole_slices || (est >= 20 && !all_rows)) return 26;
-    if (a.K >= 2048 && (a.K & (a.K - 1)) == 0) return 35;
+    if (a.K >= 2048 && (a.K & (a.K - 1)) == 0 && est < 34) return 35;
     const bool one_each = ring * 2 > cus && ring <= cus;
     if (est < 20) return a.K >= (ring * 2 <= cus ? 640 : (one_each ? 2560 : 960)) ? 35 : 26;
     return a.K >= 1408 && !one_each && ring <= (est < 25 ? 8 : est < 30 ? 4 : 2) * cus ? 35 : 26;
   }
-  if (whole_slices && est < 384 && W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds())) {
+  if (whole_slices && est < 384 && w4_room) {
     // 256 x 128 tiles, as full ones
     const long long mid = (long long)a.nq * w_rows * cdiv(all_rows ? est : 3 * est, 128) / 256;
     if (est < 192) return mid * 2 >= 3 * cus || (mid >= cus && a.K >= 640) || (mid * 2 >= cus && a.K >= 1408) ? 33 : 26;
