@@ -475,9 +475,10 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //     One rank's launch counts the tiles of three times the mean: a loaded rank has that many, and if it has not the loss is
 //     smaller than the gain (5995 random shapes with half to eight times the mean on the rank; 40 to 95 rows expected and 8 times
 //     as many there: 5 % over counting the mean's, even loads: 1 % behind it).
-//     From 20 rows expected on one rank's launch takes them at K 1408 and more where they are half the compute units (a rank that
-//     has as many rows as it expects 0 to 5 % behind 128 x 64, one with two or four times as many up to 18 % ahead; d 4096, F 1536,
-//     32 expected, 64 there: 157 -> 133 us; d 7168, F 2048, 24 and 48: 177 -> 145; below half of the compute units level), a launch
+//     From 20 rows expected on one rank's launch takes them where, one per group along the tokens, they are one round of five
+//     eighths of the compute units or more, K 2560 and above (K 2880, 180 of them: 0.95 of 128 x 64 with the rows it expects, 0.88
+//     with twice as many, 1.01 at worst; K 4096, 192: 0.98, 0.85 and 1.01).  Half the compute units (K 7168): 4 % behind with the rows
+//     it expects, 17 ahead with twice as many; beyond one round 3 to 12 % behind (K 1408 to 2880, 250 to 360 tiles).  A launch
 //     with all experts from 34 rows, K 1024 and all compute units (128 experts of 39 rows, d 2048: 262 -> 240 us, 64 of d 4096, F
 //     1536: 453 -> 438; at 30 rows 4 % behind 64 x 64 streamed, at 32 level).
 //     384 experts and more leave no room in its LDS for their table (512 experts, d 1024, F 512, 300 rows: 776 us as
@@ -524,7 +525,7 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
   const bool w4_room = W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds());
   if (est < 40) {
     const long long mid = (long long)a.nq * w_rows / 256;  // 256 x 128 tiles, one per group along the tokens
-    if (whole_slices && w4_room && (all_rows ? est >= 34 && mid >= cus && a.K >= 1024 : est >= 20 && mid * 2 >= cus && a.K >= 1408))
+    if (whole_slices && w4_room && (all_rows ? est >= 34 && mid >= cus && a.K >= 1024 : est >= 20 && mid * 8 >= 5 * cus && mid <= cus && a.K >= 2560))
       return 33;
     if (!whole_slices || (est >= 20 && !all_rows)) return 26;
     if (a.K >= 2048 && (a.K & (a.K - 1)) == 0 && est < 34) return 35;
