@@ -427,7 +427,8 @@ int32_t semmoe_dispatch_rows(const semmoe_config* cfg, void* stream, const void*
  *   for every physical expert q of `rank` (rank = -1: all), for slots s in [expert_offsets[q],
  *   expert_offsets[q+1]):  Y[s] = W_down[e] ( silu(W_gate[e] x_s) * (W_up[e] x_s) ),  e = expert_of_phys[q],
  *   W_gate[e] = W_gu[e, 0:F, :], W_up[e] = W_gu[e, F:2F, :].  fp32 accumulate; the hidden activation is
- *   rounded to the act type once.  Rows of other ranks in Y are not written.
+ *   rounded to the act type once.  Rows of other ranks in Y are not written.  The order of a row's sums depends on the
+ *   shape and on e, not on q: an expert that is placed elsewhere gives the same rows bit for bit.
  * dev in : X_perm[P,d] act; expert_offsets[E+1]; expert_of_phys[E]; W_gu[E,2F,d] act; W_down[E,d,F] act
  *          (both indexed by ORIGINAL expert id).   dev out: Y[P,d] act.
  */

@@ -95,7 +95,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
   if (my.count == 0) return;  // the whole workgroup leaves, before any further barrier
 
   struct Tile {
-    int row_lo, n_tok, f0, widx, q;
+    int row_lo, n_tok, f0, widx;
     bool once;  // the group has one token tile: nobody else reads these weights
   };
   auto locate = [&](int t) __attribute__((always_inline)) {
@@ -111,7 +111,6 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     r.f0 = ft * C::FEAT;
     r.widx = __builtin_amdgcn_readfirstlane(gtab[3 * q + 2]);
     r.once = n_tt == 1;
-    r.q = q;
     return r;
   };
 
@@ -139,7 +138,7 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
     l_ntt = (r.n_tok + 15) >> 4;
     l_once = r.once;
     // where K is cut evenly (what a last, partial slice holds is masked by its place in the walk)
-    l_at = KTAIL || nst % NW != 0 ? 0 : first_step(a, r.q, ES, n);
+    l_at = KTAIL || nst % NW != 0 ? 0 : first_step(a, r.widx, ES, n);
     koff = wave * 128 + l_at * (NW * 128);
   };
   u32x4_t wb[2 * TW], xb[2 * TT];

@@ -184,7 +184,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
   // ---- load stream state (runs NSTAGE slices ahead of the MFMAs, across tiles)
   int i_tile = 0;  // round of this workgroup
   int i_slice = 0;
-  int i_k = 0;  // place of that slice in K: a group's walk begins where first_step says and wraps around
+  int i_k = 0;  // place of that slice in K: an expert's walk begins where first_step says and wraps around
   int i_stage = 0;
   bool i_done = false;
   // The loads between the MFMAs are issued unconditionally (a branch per load costs more than the load).  Where the
@@ -224,7 +224,7 @@ __device__ __forceinline__ void gemm_bf16_w4_body(const GemmArgs& a, unsigned ch
       const int c = d_pos ^ (((sr + C::BW) / C::RPB) % C::CPR);
       return uint32_t(min(sr, t.n_tok - 1)) * uint32_t(a.ldx) * 2u + uint32_t(c) * 16u;
     };
-    i_k = first_step(a, t.q, 2, nk);
+    i_k = first_step(a, t.widx, 2, nk);
     i_base = (first_w ? w_panel : x_panel) + i_k * C::RB;
     if constexpr (TJ != 4) i_base2 = (loads_w ? w_panel : x_panel) + i_k * C::RB;
     if (first_w) {
@@ -552,7 +552,7 @@ __device__ __forceinline__ void gemm_bf16_piece_body(const GemmArgs& a, unsigned
       }
     }
     int i_slice = 0, i_stage = 0;
-    int i_k = first_step(a, at.q, 2, nk);  // place of the slice in K
+    int i_k = first_step(a, widx, 2, nk);  // place of the slice in K
     i_base += i_k * C::RB;
     bool i_done = false;
     unsigned i_dst = 0;

@@ -270,3 +270,38 @@ def test_one_rank_gives_the_bits_of_all():
     every, _, _ = _ffn(rows, 2048, 128, "bf16", D=2, rank=-1, knobs=knobs, seed=5)
     second, _, mine = _ffn(rows, 2048, 128, "bf16", D=2, rank=1, knobs=knobs, seed=5)
     assert (every[mine] == second[mine]).all()
+
+
+def _placed(place, rows, X, W_gu, W_dn, F, dtype, knobs):
+    """{expert: its rows of Y} with expert place[q] at physical position q"""
+    d, E, P = W_dn.shape[1], len(rows), int(sum(rows))
+    off = np.concatenate([[0], np.cumsum([rows[e] for e in place])]).astype(np.int32)
+    m = S.SemMoE(S.Config(T=P, d=d, E=E, k=1, F=F, D=1, dtype=dtype, cap=P))
+    Y = torch.empty(P, d, dtype=W_dn.dtype, device=H.DEV)
+    try:
+        for key, value in knobs:
+            m.set_tuning(key, value)
+        m.expert_ffn(-1, torch.cat([X[e] for e in place]), torch.from_numpy(off).to(H.DEV),
+                     torch.tensor(place, dtype=torch.int32, device=H.DEV), W_gu, W_dn, Y)
+        torch.cuda.synchronize()
+    finally:
+        for key, _ in knobs:
+            m.set_tuning(key, -1)
+    return {e: Y[off[q]:off[q + 1]] for q, e in enumerate(place)}
+
+
+# rows of 4 KB, where the experts begin their walks at different columns: an expert's rows have the same bits wherever it
+# is placed, by every kernel that spreads the starts and by the library's own choice
+@pytest.mark.parametrize("d,F", [(2048, 64), (64, 2048)])
+@pytest.mark.parametrize("dtype,tile", [("bf16", t) for t in (-1, 16, 22, 26, 28, 33, 34, 35, 40)] + [("fp32", -1), ("fp32", 32)])
+def test_bits_of_an_expert_wherever_it_is_placed(dtype, tile, d, F):
+    if dtype == "fp32":
+        d, F = d // 2, F // 2
+    g = torch.Generator().manual_seed(tile + d)
+    act, rows = (torch.bfloat16 if dtype == "bf16" else torch.float32), (30, 64, 17, 0, 40, 9, 65, 128, 300, 1)
+    new = lambda std, *shape: torch.empty(shape).normal_(0, std, generator=g).to(act).to(H.DEV)
+    X, W_gu, W_dn = [new(1.0, n, d) for n in rows], new(0.05, len(rows), 2 * F, d), new(0.05, len(rows), d, F)
+    first = _placed(list(range(len(rows))), rows, X, W_gu, W_dn, F, dtype, ((0, tile), (1, tile)))
+    other = _placed([7, 0, 8, 5, 1, 9, 2, 3, 6, 4], rows, X, W_gu, W_dn, F, dtype, ((0, tile), (1, tile)))
+    for e in first:
+        assert torch.equal(first[e], other[e]), "expert %d: %d of %d values" % (e, (first[e] != other[e]).sum(), first[e].numel())
