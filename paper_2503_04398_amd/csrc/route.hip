@@ -1043,12 +1043,14 @@ __global__ __launch_bounds__(256) void select_topk_rows_kernel(semmoe_config cfg
 // The two kernels below in one, for the row forms of the selection and E a multiple of four: a wave adds up the parts
 // of its four tokens (ascending order, then b_g, then the class bias: the same sums as route_reduce_kernel)
 // into LDS with 16-byte loads and selects from there.  The partial sums are read once and never again.
+// paired_bias: b_g + class bias first and their sum to the logit, as the fused kernel with 16-byte bias loads does; for sums
+// that are the fused kernel's own (one part), so that a call gives the same bits by either.
 constexpr int kSumSelectMaxE = 256;
 constexpr int kSumSelectChains = 1;                       // four tokens a wave: twice the waves to hide the latencies
 constexpr int kSumSelectTokens = 4 * kSumSelectChains;
 // PB parts of U chunks of four experts are requested before the first is used.
 template <typename FORM, bool SIG, int PB, int U>
-__global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg, int n_parts,
+__global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg, int n_parts, bool paired_bias,
                                                                const float* __restrict__ partial,
                                                                const float* __restrict__ b_g,
                                                                const int32_t* __restrict__ token_class,
@@ -1100,14 +1102,21 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
 #pragma unroll
     for (int c = 0; c < U; ++c) {
       if (idx0 + c * 64 >= n_idx) break;
+      const float* cb = cls[c] >= 0 && cls[c] < cfg.num_classes && class_bias ? class_bias + size_t(cls[c]) * E : nullptr;
+      f32x4_t add = {0.0f, 0.0f, 0.0f, 0.0f};
       if (b_g) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[c][u] += b_g[e[c] + u];
+        for (int u = 0; u < 4; ++u) add[u] = b_g[e[c] + u];
       }
-      if (cls[c] >= 0 && cls[c] < cfg.num_classes && class_bias) {
+      if (!paired_bias) {
+        v[c] += add;
+        add = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+      if (cb) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[c][u] += class_bias[size_t(cls[c]) * E + e[c] + u];
+        for (int u = 0; u < 4; ++u) add[u] += cb[e[c] + u];
       }
+      v[c] += add;
       *reinterpret_cast<f32x4_t*>(lg + tl[c] * ld + e[c]) = v[c];
       if constexpr (SIG) {
         i32x4_t key;
@@ -1132,7 +1141,7 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
 
 // launches route_sum_select_kernel when the shape has a row form of the selection and E is a multiple of four;
 // false: nothing was launched (the caller runs the two kernels)
-static bool launch_sum_select(const semmoe_config* cfg, hipStream_t s, int n_parts, const float* partial,
+static bool launch_sum_select(const semmoe_config* cfg, hipStream_t s, int n_parts, bool paired_bias, const float* partial,
                               const float* b_g, const int32_t* token_class, const float* class_bias,
                               const float* sel_bias, float* logits_out, int32_t* topk_ids, float* topk_w) {
   const int slots = select_slots(*cfg);
@@ -1147,8 +1156,8 @@ static bool launch_sum_select(const semmoe_config* cfg, hipStream_t s, int n_par
     using FORM = decltype(form);
     constexpr bool SIG = decltype(sig)::value;
     auto kern = waves == 4 ? route_sum_select_kernel<FORM, SIG, 8, 1> : route_sum_select_kernel<FORM, SIG, 16, 2>;
-    hipLaunchKernelGGL(kern, grid, block, 0, s, *cfg, n_parts, partial, b_g, token_class, class_bias, sel_bias, logits_out,
-                       topk_ids, topk_w);
+    hipLaunchKernelGGL(kern, grid, block, 0, s, *cfg, n_parts, paired_bias, partial, b_g, token_class, class_bias, sel_bias,
+                       logits_out, topk_ids, topk_w);
     return SEMMOE_OK;
   };
   if (slots == 16) with_select_form<16>(*cfg, launch);
@@ -1306,7 +1315,7 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       float* lg = c.take<float>(size_t(cfg->T) * cfg->E);
       if (!c.ok) return SEMMOE_EWORKSPACE;
       st = launch_ksplit_gemm(X, W_r, cfg->T, cfg->E, cfg->d, big_parts, part, s);
-      if (st == SEMMOE_OK && launch_sum_select(cfg, s, big_parts, part, b_g, token_class, class_bias, sel_bias,
+      if (st == SEMMOE_OK && launch_sum_select(cfg, s, big_parts, false, part, b_g, token_class, class_bias, sel_bias,
                                                logits_out, topk_ids, topk_w)) {
         SEMMOE_LAUNCH_CHECK();
         return SEMMOE_OK;
@@ -1396,7 +1405,9 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     if (partial) {
       // adding the parts and selecting in one kernel where the shape has a row form (256 tokens, 128 experts, 16 parts:
       // 3.4 + 6.2 us as two kernels and the gap between them)
-      if (launch_sum_select(cfg, s, n_parts, partial, b_g, token_class, class_bias, sel_bias, logits_out, topk_ids,
+      // (one part: the fused kernel's sums, and its order of the bias terms, which its 16-byte loads add to each other first)
+      const bool paired_bias = n_parts == 1 && aligned16(b_g) && aligned16(class_bias) && aligned16(logits_out);
+      if (launch_sum_select(cfg, s, n_parts, paired_bias, partial, b_g, token_class, class_bias, sel_bias, logits_out, topk_ids,
                             topk_w)) {
         SEMMOE_LAUNCH_CHECK();
         return SEMMOE_OK;

@@ -84,3 +84,31 @@ def test_gemm_where_its_form_changes(T, d, E, k):
         assert O.max_rel_err(logits, want) <= 1e-5
         assert (ids == H.oracle_select(w, logits)[0]).all()
         assert (lay.m.ws[lay.m.ws_bytes:] == 0x5a).all()
+
+
+# 129 to 256 experts while two workgroups share a tile: logits, ids and weights have the bits of the fused kernel's, with either bias
+# and both; arrays off a 16-byte boundary take the fused kernel's bias terms one after the other
+@pytest.mark.parametrize("T,d,E", [(7, 136, 160), (300, 136, 256), (513, 1000, 132), (1030, 512, 256), (4096, 136, 252)])
+@pytest.mark.parametrize("biases", ["b_g", "class", "both"])
+@pytest.mark.parametrize("odd", ["", "b_g", "logits"])
+def test_shared_tile_has_the_bits_of_the_fused_kernel(T, d, E, biases, odd):
+    g = torch.Generator().manual_seed(T + E)
+    new = lambda *shape: torch.empty(shape).normal_(0, 1, generator=g)
+    X, W = new(T, d).bfloat16().to(H.DEV), (0.1 * new(E, d)).bfloat16().to(H.DEV)
+    off = lambda name: 1 if odd == name else 0  # floats past a 16-byte boundary
+    b_g = new(E + 1).to(H.DEV)[off("b_g"):][:E] if biases != "class" else None
+    cb, cls = (new(5, E).to(H.DEV), torch.randint(0, 5, (T,), generator=g).int().to(H.DEV)) if biases != "b_g" else (None, None)
+    m = S.SemMoE(S.Config(T=T, d=d, E=E, k=8, F=8, D=1, dtype="bf16", cap=T, num_classes=5, score="sigmoid"), device=H.DEV)
+    got = {}
+    for split in (-1, 0):  # the library's choice, the fused kernel
+        ids, w = torch.empty(T, 8, dtype=torch.int32, device=H.DEV), torch.empty(T, 8, device=H.DEV)
+        logits = torch.empty(T * E + 1, device=H.DEV)[off("logits"):][:T * E].view(T, E)
+        m.set_tuning(7, split)
+        try:
+            m.route(X, W, ids, w, b_g=b_g, token_class=cls, class_bias=cb, logits_out=logits)
+            torch.cuda.synchronize()
+        finally:
+            m.set_tuning(7, -1)
+        got[split] = logits, ids, w
+    for name, a, b in zip(("logits", "ids", "weights"), got[-1], got[0]):
+        assert torch.equal(a, b), "%s: %d of %d differ" % (name, (a != b).sum(), a.numel())
