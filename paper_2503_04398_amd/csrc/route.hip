@@ -1043,8 +1043,8 @@ __global__ __launch_bounds__(256) void select_topk_rows_kernel(semmoe_config cfg
 // The two kernels below in one, for the row forms of the selection and E a multiple of four: a wave adds up the parts
 // of its four tokens (ascending order, then b_g, then the class bias: the same sums as route_reduce_kernel)
 // into LDS with 16-byte loads and selects from there.  The partial sums are read once and never again.
-// paired_bias: b_g + class bias first and their sum to the logit, as the fused kernel with 16-byte bias loads does; for sums
-// that are the fused kernel's own (one part), so that a call gives the same bits by either.
+// paired_bias (with both biases): b_g + class bias first and their sum to the logit, as the fused kernel with 16-byte bias
+// loads does; for sums that are the fused kernel's own (one part), so that a call gives the same bits by either.
 constexpr int kSumSelectMaxE = 256;
 constexpr int kSumSelectChains = 1;                       // four tokens a wave: twice the waves to hide the latencies
 constexpr int kSumSelectTokens = 4 * kSumSelectChains;
@@ -1102,21 +1102,20 @@ __global__ __launch_bounds__(256) void route_sum_select_kernel(semmoe_config cfg
 #pragma unroll
     for (int c = 0; c < U; ++c) {
       if (idx0 + c * 64 >= n_idx) break;
-      const float* cb = cls[c] >= 0 && cls[c] < cfg.num_classes && class_bias ? class_bias + size_t(cls[c]) * E : nullptr;
-      f32x4_t add = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (b_g) {
+      const bool classed = cls[c] >= 0 && cls[c] < cfg.num_classes && class_bias;
+      if (paired_bias && classed) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) add[u] = b_g[e[c] + u];
-      }
-      if (!paired_bias) {
-        v[c] += add;
-        add = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-      }
-      if (cb) {
+        for (int u = 0; u < 4; ++u) v[c][u] += b_g[e[c] + u] + class_bias[size_t(cls[c]) * E + e[c] + u];
+      } else {
+        if (b_g) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) add[u] += cb[e[c] + u];
+          for (int u = 0; u < 4; ++u) v[c][u] += b_g[e[c] + u];
+        }
+        if (classed) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[c][u] += class_bias[size_t(cls[c]) * E + e[c] + u];
+        }
       }
-      v[c] += add;
       *reinterpret_cast<f32x4_t*>(lg + tl[c] * ld + e[c]) = v[c];
       if constexpr (SIG) {
         i32x4_t key;
@@ -1406,7 +1405,7 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
       // adding the parts and selecting in one kernel where the shape has a row form (256 tokens, 128 experts, 16 parts:
       // 3.4 + 6.2 us as two kernels and the gap between them)
       // (one part: the fused kernel's sums, and its order of the bias terms, which its 16-byte loads add to each other first)
-      const bool paired_bias = n_parts == 1 && aligned16(b_g) && aligned16(class_bias) && aligned16(logits_out);
+      const bool paired_bias = n_parts == 1 && b_g && class_bias && aligned16(b_g) && aligned16(class_bias) && aligned16(logits_out);
       if (launch_sum_select(cfg, s, n_parts, paired_bias, partial, b_g, token_class, class_bias, sel_bias, logits_out, topk_ids,
                             topk_w)) {
         SEMMOE_LAUNCH_CHECK();
