@@ -6,28 +6,30 @@
 namespace semmoe {
 
 // Sigmoid as a fixed sequence of individually rounded fp32 operations (no contraction), so that any
-// implementation of the same sequence gives the same bits.
+// implementation of the same sequence gives the same bits.  Plain operators: the pragma does not reach into __fmul_rn and
+// __fadd_rn, inline functions that are compiled with contraction, and a product and a sum of theirs became one FMA (one value
+// in 80 was off by an ulp or two).
 __device__ __forceinline__ float sigmoid_exact_seq(float x) {
 #pragma clang fp contract(off)
   x = fminf(fmaxf(x, -30.0f), 30.0f);
-  const float t = __fmul_rn(-x, 1.4426950408889634f);
+  const float t = -x * 1.4426950408889634f;
   const float n = rintf(t);
-  const float f = __fsub_rn(t, n);
+  const float f = t - n;
   float p = 0.00015403530393381608f;
-  p = __fadd_rn(__fmul_rn(p, f), 0.0013333558146428443f);
-  p = __fadd_rn(__fmul_rn(p, f), 0.009618129107628477f);
-  p = __fadd_rn(__fmul_rn(p, f), 0.05550410866482158f);
-  p = __fadd_rn(__fmul_rn(p, f), 0.2402265069591007f);
-  p = __fadd_rn(__fmul_rn(p, f), 0.6931471805599453f);
-  p = __fadd_rn(__fmul_rn(p, f), 1.0f);
-  const float z = ldexpf(p, static_cast<int>(n));
-  // 1 / q rounded to nearest: the hardware's reciprocal (1 ulp) and two Newton steps with fused residuals.  q lies in
-  // [1, 2^44), where nothing underflows, and the steps scale exactly, so every q of one binade stands for all: equal to the
-  // IEEE division on all 2^23 of them.  Five instructions where the division takes a dozen.
-  const float q = __fadd_rn(1.0f, z);
+  p = p * f + 0.0013333558146428443f;
+  p = p * f + 0.009618129107628477f;
+  p = p * f + 0.05550410866482158f;
+  p = p * f + 0.2402265069591007f;
+  p = p * f + 0.6931471805599453f;
+  p = p * f + 1.0f;
+  const float q = 1.0f + ldexpf(p, static_cast<int>(n));
+  // 1 / q rounded to nearest: the hardware's reciprocal and two Newton steps with fused residuals, five instructions where the
+  // division takes a dozen.  q lies in [1, 2^44), where nothing underflows and the steps scale exactly, so every q of one binade
+  // stands for all.  An error of 1 ulp in the first value would not do (from 0.5 for q = 2 - 2^-23 the steps end at 0.5): it is
+  // gfx950's values for which the result is that of the division, q by q.
   float r = __builtin_amdgcn_rcpf(q);
-  r = __fmaf_rn(__fmaf_rn(-q, r, 1.0f), r, r);
-  return __fmaf_rn(__fmaf_rn(-q, r, 1.0f), r, r);
+  r = __builtin_fmaf(__builtin_fmaf(-q, r, 1.0f), r, r);
+  return __builtin_fmaf(__builtin_fmaf(-q, r, 1.0f), r, r);
 }
 
 // ---- wave-wide reductions through DPP row shifts / broadcasts (no LDS permutes) ---------------------------

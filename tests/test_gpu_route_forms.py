@@ -112,3 +112,33 @@ def test_shared_tile_has_the_bits_of_the_fused_kernel(T, d, E, biases, odd):
         got[split] = logits, ids, w
     for name, a, b in zip(("logits", "ids", "weights"), got[-1], got[0]):
         assert torch.equal(a, b), "%s: %d of %d differ" % (name, (a != b).sum(), a.numel())
+
+
+def test_sigmoid_is_the_oracles_bit_for_bit():
+    """1 / (1 + z) is formed from the hardware's reciprocal and two Newton steps, which give the correctly rounded quotient or
+    not depending on that first value: of 1 / (2 - 2^-23), half way between two results to first order, two steps from 0.5 stay
+    at 0.5.  So: logits for every mantissa that 1 + z takes in [1, 8), the all-ones one among them, those around zero,
+    and the ones clamped.  A weight of one expert, not renormalised, is its sigmoid."""
+    x = [-np.log(np.maximum(np.arange(lo, lo + (1 << 23), dtype=np.uint32).view(np.float32).astype(np.float64) - 1, 1e-14)).astype(np.float32)
+         for lo in (0x3f800000, 0x40000000, 0x40800000)]
+    tiny = np.arange(1 << 16, dtype=np.uint32) << 15 | 1
+    x += [tiny.view(np.float32), (tiny | 0x80000000).view(np.float32),
+          np.array([0.0, -0.0, 30.0, -30.0, 31.0, -31.0, 88.8, -88.8, 104.0, -104.0, np.inf, -np.inf], np.float32)]
+    x = np.concatenate(x)
+    x = x[~np.isnan(x)]
+    t = -np.clip(x, np.float32(-30), np.float32(30)) * O._LOG2E  # the denominators, to see which there are
+    n = np.rint(t)
+    z = np.full_like(t, O._EXP2_COEF[6])
+    for c in O._EXP2_COEF[5::-1]:
+        z = z * (t - n) + c
+    q = np.float32(1) + np.ldexp(z, n.astype(np.int32))
+    s = O.sigmoid_f32(x)
+    assert q.dtype == np.float32 and (np.float32(1) / q == s).all()
+    mantissas = np.unique(q.view(np.uint32) & 0x7fffff)
+    assert mantissas[-1] == 0x7fffff and len(mantissas) > 0.997 * 2 ** 23
+    for at in range(0, len(x), 1 << 23):
+        part = x[at:at + (1 << 23)]
+        ids, w = _select(part[:, None], 1, score="sigmoid", renorm=False)
+        bad = np.flatnonzero(w[:, 0].view(np.uint32) != s[at:at + (1 << 23)].view(np.uint32))
+        assert len(bad) == 0, "%d of %d, the first at %r" % (len(bad), len(part), part[bad[0]])
+        assert (ids == 0).all()
