@@ -1335,9 +1335,13 @@ extern "C" int32_t semmoe_route(const semmoe_config* cfg, void* stream, const vo
     // 129 to 256 experts: two workgroups share a tile of 32 tokens, 128 experts each, while all of them are one round of the
     // chip; the sums stay as they are.  A workgroup then streams 160 rows a slice instead of 288, and the selection's kernel has
     // the whole chip (group-limited sigmoid, d 7168: 16 tokens 16.8 -> 14.1 us, 256 19.8 -> 17.2, 1024 59.5 -> 41.6, 4096 59.7 ->
-    // 44.7).  Not with 64 tokens (5000: 60.0 us fused, 68.9 so) or 128 (10000: 95.7, 98.1).
+    // 44.7).  Not with 64 tokens (5000: 60.0 us fused, 68.9 so) or 128 (10000: 95.7, 98.1).  Where K is not in parts the
+    // selection's launch comes on top, and the walk has to be long enough to repay it (of the fused kernel's time, 513 to 4096 tokens
+    // of 132 to 256 experts: softmax d 512 1.24 to 1.46, d 1536 0.98 to 1.08, d 2048 0.92 to 1.03; sigmoid, whose keys the second kernel
+    // forms on the whole chip, d 1024 0.97 to 1.10, d 1536 0.92 to 1.02).
     bool split_e = tf == 2 && slots == 16 && cfg->E % 4 == 0 && tuning_value(SEMMOE_TUNE_ROUTE_SPLIT) != 0 &&
-                   2 * cdiv(cfg->T, 32) * n_parts <= ncu;
+                   2 * cdiv(cfg->T, 32) * n_parts <= ncu &&
+                   (n_parts > 1 || cdiv(cfg->d, 64) >= (cfg->score == SEMMOE_SIGMOID ? 24 : 32));
     float* partial = nullptr;
     float* logits_ws = nullptr;
     if (n_parts > 1 || split_e) {

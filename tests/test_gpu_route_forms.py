@@ -86,9 +86,10 @@ def test_gemm_where_its_form_changes(T, d, E, k):
         assert (lay.m.ws[lay.m.ws_bytes:] == 0x5a).all()
 
 
-# 129 to 256 experts while two workgroups share a tile: logits, ids and weights have the bits of the fused kernel's, with either bias
-# and both; arrays off a 16-byte boundary take the fused kernel's bias terms one after the other
-@pytest.mark.parametrize("T,d,E", [(7, 136, 160), (300, 136, 256), (513, 1000, 132), (1030, 512, 256), (4096, 136, 252)])
+# 129 to 256 experts while two workgroups share a tile (sigmoid: 513 to 4096 tokens, d from 1473 on), and beside that: logits, ids and
+# weights have the bits of the fused kernel's, with either bias and both; arrays off a 16-byte boundary take the fused kernel's
+# bias terms one after the other
+@pytest.mark.parametrize("T,d,E", [(300, 136, 256), (513, 1480, 132), (1030, 2048, 256), (4096, 1536, 252), (1024, 1472, 160)])
 @pytest.mark.parametrize("biases", ["b_g", "class", "both"])
 @pytest.mark.parametrize("odd", ["", "b_g", "logits"])
 def test_shared_tile_has_the_bits_of_the_fused_kernel(T, d, E, biases, odd):
