@@ -113,9 +113,9 @@ int32_t semmoe_workspace_bytes(const semmoe_config* cfg, size_t* bytes_out /*hos
  *     0 switches it off too
  *   SEMMOE_TUNE_GRID_CAP: most workgroups a grouped GEMM launches (default: compute units x blocks per CU)
  *   SEMMOE_TUNE_INDEX_PATH: which implementation of the index kernels runs (default: a single workgroup for
- *     T <= 512; above, two launches per call in which every workgroup derives its prefixes from the table of
- *     per-workgroup counts, up to T = 131072; beyond, one kernel per phase).  2 asks for the single workgroup where it holds
- *     the batch and is the default elsewhere; all give identical results
+ *     T <= 512, and for T <= 1024 and T*k <= 1536; above, two launches per call in which every workgroup derives its prefixes
+ *     from the table of per-workgroup counts, up to T = 131072; beyond, one kernel per phase).  2 asks for the single workgroup
+ *     where it holds the batch (T <= 512, with k <= 4 T <= 1024) and is the default elsewhere; all give identical results
  */
 #define SEMMOE_TUNE_GATEUP_TILE 0
 #define SEMMOE_TUNE_DOWN_TILE 1

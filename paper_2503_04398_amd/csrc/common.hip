@@ -69,6 +69,19 @@ int32_t validate_config(const semmoe_config* cfg, bool need_T, bool need_rows, b
   return SEMMOE_OK;
 }
 
+// Up to 512 tokens one launch is the faster form (8 experts a token, kernels alone; reshuffle of 32 ranks: 256 tokens 5.2 us
+// against 3.1 + 5.2 as two, 512 tokens 6.3 against 3.4 + 5.6; dispatch index of 256 experts: 6.4 against 4.0 + 7.5 and 9.4
+// against 4.7 + 7.8; as one workgroup of 1024 threads 1024 tokens took 11.1 against 3.6 + 5.7 and 17.6 against 4.7 + 7.9), and
+// beyond with so few pairs that the kernels take no longer and half the launches cost the host less (both, kernels / calls: 16
+// experts, 2 a token, 700 tokens 15.0 / 15.6 us against 15.8 / 20.0, 850 tokens 17.1 / 17.4 against 15.7 / 20.6; 1 a token,
+// 1024 tokens 15.1 / 15.5 against 15.8 / 19.9; 64 experts, 4 a token, 520 tokens 17.1 / 17.8 against 16.2 / 19.9).
+// path (SEMMOE_TUNE_INDEX_PATH): 2 one workgroup wherever there is a kernel for the batch, 1 and 3 never.
+bool index_small(const semmoe_config* cfg, int path) {
+  if (path == 1 || path == 3) return false;
+  if (cfg->T <= 512) return true;
+  return cfg->T <= 1024 && (path == 2 ? cfg->k <= 4 : cfg->T * cfg->k <= 1536);
+}
+
 int route_max_parts(const semmoe_config* cfg) {
   const int tiles = cdiv(cfg->T, 32);  // a workgroup each; a bound that needs no device: no chip has 512 compute units
   if (cfg->T <= 512) return 16;

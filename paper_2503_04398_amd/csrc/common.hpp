@@ -87,6 +87,7 @@ struct Carver {
 
 // Workspace needs per call (bytes), shared by semmoe_workspace_bytes and the calls themselves.
 constexpr int kTokBlock = 256;  // tokens per workgroup in the index kernels
+bool index_small(const semmoe_config* cfg, int path);  // reshuffle, dispatch_index: one workgroup, a thread a token
 int route_max_parts(const semmoe_config* cfg);  // fused bf16 router: parts of K whose sums the workspace holds, at most
 size_t ws_route(const semmoe_config* cfg);
 size_t ws_reshuffle(const semmoe_config* cfg);

@@ -315,7 +315,7 @@ constexpr int kFusedMaxNB = 512;  // beyond, every block reading the whole table
 
 // One workgroup for everything, a thread a token (T <= BLK): one launch, no tables.  A small kernel's time is its chain of
 // dependent loads and barriers: one pass over the tokens, four barriers.  The bits below a token's place: with 8 words a
-// key they are counted in the bitmap, with 16 they come from a prefix over the words.
+// key (and with 32, for up to 4 pairs a token) they are counted in the bitmap, with 16 they come from a prefix over the words.
 template <int KU, int BLK>
 __global__ __launch_bounds__(BLK) void dp_small_kernel(int T, int k, int E, int D, const int32_t* __restrict__ ids,
                                                        const int32_t* __restrict__ token_rank,
@@ -358,10 +358,9 @@ __global__ __launch_bounds__(BLK) void dp_small_kernel(int T, int k, int E, int 
   for (int o = 32; o >= 1; o >>= 1) remote += __shfl_xor(remote, o);
   if ((t & 63) == 0 && remote) atomicAdd(&send[n_send], (uint32_t)remote);
   __syncthreads();
-  if constexpr (W == 8) {
+  if constexpr (W != 16) {
     for (int x = t; x < E; x += BLK) off[x] = bits_of<W>(bm + x * W);
-  } else {
-    static_assert(W == 16, "a key's words are a row of 16 lanes");
+  } else {  // a key's words are a row of 16 lanes
     const int w = t & 15;
     for (int key = t >> 4; key < Ep; key += BLK / 16) {  // four keys a wave: all or none of them below Ep
       const int c = key < E ? __popc(bm[key * W + w]) : 0;
@@ -391,16 +390,12 @@ __global__ __launch_bounds__(BLK) void dp_small_kernel(int T, int k, int E, int 
   for (int j = 0; j < KU; ++j) {
     const int at = max(q[j], 0) & 0xffff;
     int below;
-    if constexpr (W == 8) below = bits_below<W>(bm + at * W, t);
+    if constexpr (W != 16) below = bits_below<W>(bm + at * W, t);
     else below = wpre[at * W + (t >> 5)] + __popc(bm[at * W + (t >> 5)] & ((1u << (t & 31)) - 1u));
     slot[j] = q[j] < 0 ? -1 : off[at] + below;
   }
   store_slots(tok, k, slot, id_quads(slot_of_pair, k), slot_of_pair, pair_of_slot);
 }
-
-// Up to here one launch is the faster form (8 experts a token, 256 experts, kernels alone: 256 tokens 6.4 us against 4.0 +
-// 7.5 as two, 512 tokens 9.4 against 4.7 + 7.8; as one workgroup of 1024 threads 1024 tokens took 17.6 against 4.7 + 7.9).
-constexpr int kSmallMaxT = 512;
 
 static size_t dp_small_lds(int E, int D, int blk) {
   const size_t W = blk / 32, Ep = align_up(E, 4);
@@ -468,14 +463,16 @@ static int32_t dispatch_index_impl(const semmoe_config* cfg, hipStream_t s, cons
   unsigned long long* remote = reinterpret_cast<unsigned long long*>(remote_pairs);
   return with_id_width(k, [&](auto ku) -> int32_t {  // KU: registers for a token's k experts
     constexpr int KU = decltype(ku)::value;
-    if (T <= kSmallMaxT && path != 1 && path != 3) {
-      const bool narrow = T <= 256;
-      auto kern = narrow ? dp_small_kernel<KU, 256> : dp_small_kernel<KU, 512>;
-      const size_t lds = dp_small_lds(E, D, narrow ? 256 : 512);
-      static std::atomic<uint64_t> lds_allowed[2];  // one flag word per kernel, a bit per device
-      const int32_t as = allow_max_dynamic_lds(&lds_allowed[narrow], reinterpret_cast<const void*>(kern));
+    if (index_small(cfg, path)) {
+      const int form = T <= 256 ? 0 : (T <= 512 ? 1 : 2), blk = 256 << form;
+      auto kern = form == 0 ? dp_small_kernel<KU, 256> : dp_small_kernel<KU, 512>;
+      if constexpr (KU == 4)
+        if (form == 2) kern = dp_small_kernel<KU, 1024>;
+      const size_t lds = dp_small_lds(E, D, blk);
+      static std::atomic<uint64_t> lds_allowed[3];  // one flag word per kernel, a bit per device
+      const int32_t as = allow_max_dynamic_lds(&lds_allowed[form], reinterpret_cast<const void*>(kern));
       if (as != SEMMOE_OK) return as;
-      hipLaunchKernelGGL(kern, dim3(1), dim3(narrow ? 256 : 512), lds, s, T, k, E, D, topk_ids, token_rank, shf,
+      hipLaunchKernelGGL(kern, dim3(1), dim3(blk), lds, s, T, k, E, D, topk_ids, token_rank, shf,
                          phys_of_expert, slot_of_pair, pair_of_slot, expert_offsets, rank_offsets, send_matrix, remote);
       SEMMOE_LAUNCH_CHECK();
       return SEMMOE_OK;

@@ -529,10 +529,6 @@ __global__ __launch_bounds__(BLK) void rs_small_kernel(int T, int k, int D, int 
   align_token(L, i < T, i, pref, conf, k, D, token_rank, shf, inv_shf);
 }
 
-// Up to here one launch is the faster form (8 experts a token, 32 ranks, kernels alone: 256 tokens 5.2 us against 3.1 + 5.2 as
-// two, 512 tokens 6.3 against 3.4 + 5.6; as one workgroup of 1024 threads 1024 tokens took 11.1 against 3.6 + 5.7).
-constexpr int kSmallMaxT = 512;
-
 // ------------------------------------------------------------------------------------------------
 // Gain-aware spill rounds (the refinement of `align` towards the objective of Sec. 3.3: the most local pairs
 // under the capacity bound).  Round 0 is the keep phase; in every further round the tokens still unplaced propose
@@ -1174,14 +1170,19 @@ static int32_t reshuffle_with_scratch(const semmoe_config* cfg, void* stream, co
   const int per_home = cdiv(T, D);
   const int nkeys = D * (k + 1);
   const int path = tuning_value(SEMMOE_TUNE_INDEX_PATH);
-  if (T <= kSmallMaxT && path != 1 && path != 3) {
+  if (index_small(cfg, path)) {
     return with_id_width(k, [&](auto ku) -> int32_t {  // KU: registers for a token's k experts
       constexpr int KU = decltype(ku)::value;
-      const bool narrow = T <= 256;
-      auto kern = narrow ? rs_small_kernel<KU, 256> : rs_small_kernel<KU, 512>;
-      const size_t lds = (narrow ? AlignLds<256>::bytes(D, nkeys) : AlignLds<512>::bytes(D, nkeys)) + size_t(cfg->E) * 4;
-      hipLaunchKernelGGL(kern, dim3(1), dim3(narrow ? 256 : 512), lds, s, T, k, D, cfg->E, cfg->cap, per_home, topk_ids,
-                         expert_to_rank, token_rank, shf, inv_shf, rank_count);
+      const int form = T <= 256 ? 0 : (T <= 512 ? 1 : 2);
+      auto kern = form == 0 ? rs_small_kernel<KU, 256> : rs_small_kernel<KU, 512>;
+      size_t lds = form == 0 ? AlignLds<256>::bytes(D, nkeys) : AlignLds<512>::bytes(D, nkeys);
+      if constexpr (KU == 4)
+        if (form == 2) {
+          kern = rs_small_kernel<KU, 1024>;
+          lds = AlignLds<1024>::bytes(D, nkeys);
+        }
+      hipLaunchKernelGGL(kern, dim3(1), dim3(256 << form), lds + size_t(cfg->E) * 4, s, T, k, D, cfg->E, cfg->cap, per_home,
+                         topk_ids, expert_to_rank, token_rank, shf, inv_shf, rank_count);
       SEMMOE_LAUNCH_CHECK();
       return SEMMOE_OK;
     });

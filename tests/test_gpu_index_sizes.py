@@ -1,4 +1,4 @@
-"""reshuffle and dispatch index where their kernels change form: one workgroup of 256 or 512 threads, two launches, one
+"""reshuffle and dispatch index where their kernels change form: one workgroup of 256, 512 or 1024 threads, two launches, one
 kernel per phase; 4, 8 and 16 registers for a token's experts; ids in quads or one by one (k, alignment); the send matrix
 in quads or not.  All outputs bit for bit against the oracle."""
 import numpy as np
@@ -19,10 +19,7 @@ def _odd(a):
     return flat.view(a.shape)
 
 
-@pytest.mark.parametrize("T", [1, 255, 256, 257, 511, 512, 513, 1025, 2047])
-@pytest.mark.parametrize("E,D,k", [(6, 3, 3), (16, 4, 4), (32, 8, 8), (40, 5, 12), (128, 64, 16), (512, 32, 8), (510, 2, 5)])
-@pytest.mark.parametrize("odd", [False, True])
-def test_index_at_the_edges_of_its_forms(T, E, D, k, odd):
+def _check_index(T, E, D, k, odd):
     r = np.random.default_rng(T + E + k)
     ids = np.argsort(r.random((T, E)) - 0.4 * (np.arange(E)[None, :] < E // 2), axis=1)[:, :k].astype(np.int32)
     e2r = r.permutation(np.repeat(np.arange(D), E // D)).astype(np.int32)
@@ -51,3 +48,18 @@ def test_index_at_the_edges_of_its_forms(T, E, D, k, odd):
         for name, g in dp.items():
             assert (H.to_np(g) == wd[name]).all(), name
         assert int(remote.item()) == int(wd["remote_pairs"])
+
+
+@pytest.mark.parametrize("T", [1, 255, 256, 257, 511, 512, 513, 1025, 2047])
+@pytest.mark.parametrize("E,D,k", [(6, 3, 3), (16, 4, 4), (32, 8, 8), (40, 5, 12), (128, 64, 16), (512, 32, 8), (510, 2, 5)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_index_at_the_edges_of_its_forms(T, E, D, k, odd):
+    _check_index(T, E, D, k, odd)
+
+
+# few pairs: one workgroup of 1024 threads up to 1024 tokens (one expert a token) or 768 (two), and where it is asked for (path 2)
+@pytest.mark.parametrize("T", [513, 768, 769, 1000, 1024, 1025])
+@pytest.mark.parametrize("E,D,k", [(8, 2, 1), (510, 2, 1), (512, 64, 2), (6, 3, 2), (12, 4, 4), (512, 64, 4)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_index_of_few_pairs(T, E, D, k, odd):
+    _check_index(T, E, D, k, odd)

@@ -22,9 +22,10 @@ def _say(*a):
     print(*a, flush=True)
 
 
-@pytest.fixture(params=[1, 2, 3], ids=["multi_wg", "single_wg", "two_launch"])
+@pytest.fixture(params=[1, 2, 3], ids=["multi_wg", "single_wg_if_it_holds", "two_launch"])
 def index_path(request):
-    """run the test with each implementation of the index kernels (reshuffle, dispatch index)"""
+    """run the test with each implementation of the index kernels (reshuffle, dispatch index); the single workgroup holds up
+    to 512 tokens (1024 with up to 4 experts each), beyond which its parameter is the library's own choice"""
     m = S.SemMoE(S.Config(T=1, d=8, E=2, k=1, F=8, D=1, cap=1), allocate_workspace=False)
     m.set_tuning(3, request.param)
     yield request.param
