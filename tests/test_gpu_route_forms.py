@@ -61,12 +61,12 @@ def test_best_of_8_groups(E, tg):
         assert O.max_rel_err(w, want_w) <= 1e-5
 
 
-# fused with parts of K (512 | 513 tokens, few and many parts, up to a tile for half of the chip), without (4097), 64 tokens a
-# workgroup (8193), ragged last tiles; more than 128 experts: no parts beyond 512 tokens,
-# two workgroups a tile up to 4096 tokens (and 15 parts of K: 40 tokens), 64 tokens a workgroup from 8193 on
+# up to 512 tokens in parts of K, beyond in one where K is short (what is in parts there: the next test); 32 (4097), 64 (8193) tokens
+# a workgroup, ragged last tiles; more than 128 experts: two workgroups a tile (40 to 500 tokens in parts of K, 1030 and 4095 not), one
+# (4096 and 4100), 64 tokens a workgroup from 8193 on
 @pytest.mark.parametrize("T,d,E,k", [(257, 512, 128, 8), (512, 1000, 64, 4), (513, 1000, 128, 8), (1024, 2048, 128, 8),
                                      (4096, 264, 128, 8), (4097, 264, 128, 8), (8193, 136, 96, 4), (40, 1984, 160, 8), (200, 1024, 252, 8),
-                                     (500, 264, 256, 8), (1030, 1536, 256, 8), (4096, 136, 132, 4), (4100, 136, 132, 4),
+                                     (500, 264, 256, 8), (1030, 2048, 256, 8), (4095, 2056, 132, 4), (4096, 136, 132, 4), (4100, 136, 132, 4),
                                      (8193, 136, 256, 8), (8300, 1024, 160, 6)])
 def test_gemm_where_its_form_changes(T, d, E, k):
     w = WL.small(T=T, d=d, E=E, k=k, D=1, C=4, dtype="bf16")
@@ -77,13 +77,47 @@ def test_gemm_where_its_form_changes(T, d, E, k):
     assert O.max_rel_err(logits, want) <= 1e-5  # exact inputs; the order of fp32 sums
     want_ids, want_w = H.oracle_select(w, logits)
     assert (ids == want_ids).all() and O.max_rel_err(tw, want_w) <= 1e-5
-    if T > 512:  # a workspace for one set of logits, and with more than 128 experts none at all, is enough
-        lay.m.ws_bytes = T * E * 4 + 512 if E <= 128 else 0
-        lay.m.ws[lay.m.ws_bytes:].fill_(0x5a)
+
+
+# Beyond 512 tokens, on 256 compute units: as many parts of K as the 32-token tiles leave units for, at least 6 slices each, at most 8
+# and 512 / tiles (the workspace), and one where the walk gets shorter by less than 20 slices.  513 tokens are 17 tiles (K 2048: 32 / 6 =
+# 5 parts), 1024 32 (8), 1025 33 (7), 1500 47 (5), 2049 65 (3), 4096 128 (2), 4097 129 (none).  More than 128 experts: sums of one
+# part, by two workgroups a tile, up to 4096 tokens from 32 slices on.  100 experts are no whole tile, 90 no whole quads.
+@pytest.mark.parametrize("T,d,E,parts", [(512, 2048, 128, 16), (513, 2048, 128, 5), (1024, 4096, 128, 8), (1025, 4096, 64, 7),
+                                         (1500, 1992, 100, 5), (2049, 4096, 90, 3), (4096, 4096, 128, 2), (4096, 2048, 128, 0),
+                                         (4097, 4096, 128, 0), (1030, 2048, 256, 1), (4096, 2048, 132, 1), (4097, 2048, 132, 0),
+                                         (1030, 1984, 256, 0)])
+def test_parts_of_K(T, d, E, parts):
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256, "the parts above are those of 256 compute units"
+    w = WL.small(T=T, d=d, E=E, k=8, D=1, C=4, F=8, dtype="bf16")
+    inp = H.make_inputs(w)
+    lay = H.Layer(w)
+    need = lay.m.ws_bytes
+    lay.m.ws = torch.full((need + 65536,), 0x5a, dtype=torch.uint8, device=H.DEV)
+    want = O.route_logits(inp.X, inp.W_r, None, inp.token_class, inp.class_bias)
+
+    def routed():
         logits, ids, tw = lay.route(inp)
         assert O.max_rel_err(logits, want) <= 1e-5
-        assert (ids == H.oracle_select(w, logits)[0]).all()
-        assert (lay.m.ws[lay.m.ws_bytes:] == 0x5a).all()
+        want_ids, want_w = H.oracle_select(w, logits)
+        assert (ids == want_ids).all() and O.max_rel_err(tw, want_w) <= 1e-5
+        return logits
+
+    routed()
+    used = lay.m.ws.view(torch.int32) != 0x5a5a5a5a  # which words of the workspace were written: what the sums took
+    sets = parts + (1 if E % 4 != 0 and parts else 0)  # no whole quads: the logits too
+    assert round(used.sum().item() / (T * E)) == sets
+    assert not used[(sets * T * E * 4 + 511) // 4:].any()
+    if T > 512:  # a workspace for one set of logits, and with more than 128 experts none at all, is enough: the fused kernel
+        lay.m.ws_bytes = T * E * 4 + 512 if E <= 128 and parts else (0 if E > 128 else need)
+        lay.m.ws.fill_(0x5a)
+        short = routed()
+        assert (lay.m.ws == 0x5a).all()
+        lay.m.set_tuning(7, 0)
+        try:
+            assert (routed() == short).all()
+        finally:
+            lay.m.set_tuning(7, -1)
 
 
 # 129 to 256 experts while two workgroups share a tile (sigmoid: 513 to 4096 tokens, d from 1473 on), and beside that: logits, ids and
