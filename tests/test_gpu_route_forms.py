@@ -177,3 +177,25 @@ def test_sigmoid_is_the_oracles_bit_for_bit():
         bad = np.flatnonzero(w[:, 0].view(np.uint32) != s[at:at + (1 << 23)].view(np.uint32))
         assert len(bad) == 0, "%d of %d, the first at %r" % (len(bad), len(part), part[bad[0]])
         assert (ids == 0).all()
+
+
+# not a number: with the sign bit clear it is above every number (equal ones: the lower expert first), with it set it is like
+# an expert that is not there, and a row of nothing else has none.  Scores by sigmoid take it for the lowest logit, -30.
+@pytest.mark.parametrize("E", [16, 100, 128, 250, 256])
+@pytest.mark.parametrize("k", [1, 4, 8, 16])
+def test_not_a_number(E, k):
+    r = np.random.default_rng(E + k)
+    L = r.standard_normal((40, E)).astype(np.float32)
+    up, down = np.array([0x7fc00000, 0xffc00000], np.uint32).view(np.float32)
+    for i in range(1, 40):
+        L[i, r.permutation(E)[:i % 5]] = up
+        L[i, r.permutation(E)[:i % 7]] = down
+    L[39] = down
+    ids, _ = _select(L, k, renorm=True)
+    bits = L.view(np.uint32)
+    rank = np.where(bits == 0x7fc00000, np.inf, np.where(bits == 0xffc00000, -np.inf, L))
+    order = np.argsort(-rank, axis=1, kind="stable")[:, :k]
+    assert (ids == np.where(np.take_along_axis(rank, order, 1) > -np.inf, order, NONE)).all()
+    ids, w = _select(L, k, score="sigmoid", renorm=False)
+    want_ids, want_w = O.select_topk(np.where(np.isnan(L), np.float32(-30), L), k, "sigmoid")
+    assert (ids == want_ids).all() and (w == want_w.astype(np.float32)).all()
