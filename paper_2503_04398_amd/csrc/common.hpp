@@ -12,8 +12,6 @@
 
 namespace semmoe {
 
-constexpr int kWave = 64;
-
 // ---- status -------------------------------------------------------------------------------------
 void set_last_hip_error(hipError_t e);
 

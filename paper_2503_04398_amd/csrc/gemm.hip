@@ -494,8 +494,9 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 // 33); K below 1024 is three steps a wave or less (d 640, F 384: 11.0 with four waves, 12.4 with eight).  Beyond
 // one tile a compute unit: up to 128 rows four waves on 32 x 32, two workgroups a compute unit; else 128 x 128 pieces as long as
 // they are one round (C, down, 640 rows: 140 tiles of 256 x 128 are 8 % ahead of two rounds of pieces; B, 1024 rows: 128
-// tiles 15 % behind one); 64 x 64 with four waves where the weight rows lie 8 KB or a multiple apart (one set has no starts to spread; B, gate/up,
-// 640 rows: 63 us with pieces, 53 so).  188 shapes (d, F 256 to 20000, 1 to 2048 rows): 0.83 of the time before.  2000 rows of
+// tiles 15 % behind one); 64 x 64 with four waves where K is 4096 or a larger power of two, whose weight rows all start on the same memory
+// channels (one set has no starts to spread), and there are twice as many weight rows as tokens (B, gate/up, 640 rows: 63 us with pieces,
+// 53 so; K 12288, rows 24 KB apart, was not measured and keeps the pieces).  188 shapes (d, F 256 to 20000, 1 to 2048 rows): 0.83 of the time before.  2000 rows of
 // it: 45 83 179 as 256 x 128 tiles, 66 112 236 as 256 x 256, 37 105 234 as pieces.  256 x 256 tiles are ahead of 256 x 128
 // from three fifths of the compute units on (170 to 190 of them: 2 to 4 %; 130 to 150: 2 % behind); 2514 rows of d 6968,
 // F 1312, gate/up without whole slices: 248 us for the FFN with pieces, 331 with 256 x 256 tiles on less than half of the chip.

@@ -3,10 +3,10 @@
 // What bounds it: with at most 64 token rows per tile a bf16 weight row costs more time in HBM than in the matrix
 // cores, so the kernel is a read stream with MFMAs attached, and its speed is the bytes every compute unit keeps in
 // flight.  Hence:
-//   * a workgroup's four waves share one tile (16*TW weight rows x 16*TT tokens) and cut K between them, 128 bytes of
-//     every row at a time (wave w takes slices w, w+4, ...): the workgroup reads 512 consecutive bytes per row and
-//     step, and no wave needs another's operands, so there is no barrier inside a tile and no wave ever waits for the
-//     slowest line of a slice that four waves share;
+//   * a workgroup's NW waves (four; eight below) share one tile (16*TW weight rows x 16*TT tokens) and cut K between them, 128
+//     bytes of every row at a time (wave w takes slices w, w+NW, ...): the workgroup reads NW * 128 consecutive bytes per row
+//     and step, and no wave needs another's operands, so there is no barrier inside a tile and no wave ever waits for the
+//     slowest line of a slice that all of them share;
 //   * a load instruction covers 8 rows x 128 bytes (four neighbouring lanes in one 64-byte segment; loading MFMA
 //     fragments directly puts them into four rows, and the address unit then passes 16 bytes a cycle instead of 64),
 //     one step ahead into registers; waits are counted by the compiler per register;
@@ -15,7 +15,7 @@
 //   * eight waves (bf16, one set of weights) where the tiles are so few that each compute unit gets one: then the waves of one
 //     workgroup are all that is in flight;
 //   * the load stream does not stop at a tile's end: the steps past it are the first ones of the workgroup's next
-//     tile, so the epilogue (partial sums of the four waves through LDS) runs under loads in flight.
+//     tile, so the epilogue (partial sums of the waves through LDS) runs under loads in flight.
 // fp32 (v_mfma_f32_16x16x4_f32: full fp32 products and sums): a lane's 16 bytes are four k of its row, used by four
 // MFMAs in turn - any order of k will do as long as both operands use the same one.
 #pragma once
@@ -304,7 +304,8 @@ __device__ __forceinline__ void gemm_stream_body(const GemmArgs& a, unsigned cha
 }
 
 template <int MODE, bool F32, int TW, int TT, bool KTAIL, bool WIDE = false, int NW = 4>
-__global__ __launch_bounds__(64 * NW, NW > 8 ? 4 : 2) void gemm_stream_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(64 * NW, 2) void gemm_stream_kernel(const GemmArgs a) {
+  static_assert(NW == 4 || NW == 8, "two workgroups of four waves a compute unit, or one of eight: at least two waves a SIMD");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   gemm_stream_body<MODE, F32, TW, TT, KTAIL, WIDE, false, NW>(a, lds_raw);
 }

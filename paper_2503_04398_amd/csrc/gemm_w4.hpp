@@ -46,14 +46,6 @@ __device__ __forceinline__ const T* scalar_ptr(const T* p) {
   return reinterpret_cast<const T*>(bs);
 }
 
-// Uniform 32-bit load through the scalar cache.  A vector load here would make the compiler wait for every
-// outstanding vector memory operation, that is for the whole ring of tile loads in flight.
-__device__ __forceinline__ int uniform_load(const int32_t* p) {
-  int v;
-  asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(scalar_ptr(p)) : "memory");
-  return v;
-}
-
 // global -> LDS, 16 bytes per lane: address = uniform base + per-lane byte offset; lane L writes LDS[m0 + 16 L]
 __device__ __forceinline__ void lds_dma16_s(const void* sbase, uint32_t voff, unsigned lds_addr_uniform) {
   sbase = scalar_ptr(static_cast<const unsigned char*>(sbase));

@@ -41,16 +41,6 @@ __device__ __forceinline__ float dpp_f32(float old, float v) {
       __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, dpp_f32<0x111, 0xf>(v, v));  // row_shr:1 (lanes without a source keep their own value)
-  v = fmaxf(v, dpp_f32<0x112, 0xf>(v, v));  // row_shr:2
-  v = fmaxf(v, dpp_f32<0x114, 0xf>(v, v));  // row_shr:4
-  v = fmaxf(v, dpp_f32<0x118, 0xf>(v, v));  // row_shr:8
-  v = fmaxf(v, dpp_f32<0x142, 0xf>(v, v));  // row_bcast:15
-  v = fmaxf(v, dpp_f32<0x143, 0xf>(v, v));  // row_bcast:31
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
 // Selection scores are compared as integers: key(x) orders like x (and -0 like +0), integer max needs no NaN
 // canonicalisation, and the row-shift folds into the max instruction.  key is its own inverse.
 __device__ __forceinline__ int to_key(float x) {
