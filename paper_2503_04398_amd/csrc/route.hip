@@ -501,7 +501,7 @@ __device__ __forceinline__ void keep_best_of_8_groups(int (&val)[NCH][NS], int t
 }
 
 // rowp[ch] / idp[ch] / wp[ch]: this lane's token of group ch (the same for the 16 lanes of a row), nullptr = none.
-// Same selection rule as select_rows: the k largest in order, equal values -> lowest expert id.  KEEP >= k: 4, 8 or 16.
+// Same selection rule as select_rows: the k largest in order, equal values -> lowest expert id.  KEEP >= k: 2, 4, 8 or 16.
 // KEYED: the keys of the selection scores have been formed already and lie `key_off` words behind the logits.
 template <int NS, int KEEP, int NCH, bool SIG, bool KEYED>
 __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const float* const (&rowp)[NCH],
@@ -626,19 +626,52 @@ __device__ __forceinline__ void select_rows16(const semmoe_config& cfg, const fl
   // lane j of the row keeps the j-th winner
   int my_id[NCH];
   float my_val[NCH], mx[NCH];
+  if constexpr (KEEP == 2) {
+    // one or two winners: a round each, the row's largest key and the lowest expert that holds it.  The shortest list costs more
+    // than that (8192 tokens of 256 experts, softmax, 1 a token: lists 3.98 us, so 3.41; 128 experts in 4 groups, sigmoid, 2 a
+    // token 8.40 and 7.39)
+    for (int j = 0; j < k; ++j) {
+      int top[NCH], arg[NCH];
 #pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-    double all[NS], top[KEEP];
+      for (int ch = 0; ch < NCH; ++ch) {
+        top[ch] = NEGK;  // keys below -inf's (NaN) are out
 #pragma unroll
-    for (int c = 0; c < NS; ++c) all[c] = pack_entry(max(val[ch][c], NEGK), c * 16 + l16);  // keys below -inf's (NaN): out too
-    largest_of_row(all, top);
-    double mine = top[0];
+        for (int c = 0; c < NS; ++c) top[ch] = max(top[ch], val[ch][c]);
+      }
+      SEMMOE_ROW_REDUCE("v_max_i32_dpp", top);
 #pragma unroll
-    for (int j = 1; j < KEEP; ++j) mine = l16 == j ? top[j] : mine;
-    const int key = entry_key(mine);
-    my_id[ch] = key == NEGK ? kNoExpert : entry_id(mine);
-    my_val[ch] = from_key(key);
-    mx[ch] = from_key(entry_key(top[0]));  // row maximum
+      for (int ch = 0; ch < NCH; ++ch) {
+        arg[ch] = kNoExpert;
+#pragma unroll
+        for (int c = NS - 1; c >= 0; --c) arg[ch] = val[ch][c] == top[ch] ? c * 16 + l16 : arg[ch];
+      }
+      SEMMOE_ROW_REDUCE("v_min_i32_dpp", arg);
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        if (j == 0) mx[ch] = from_key(top[ch]);
+        if (j == 0 || l16 == j) {
+          my_id[ch] = top[ch] == NEGK ? kNoExpert : arg[ch];
+          my_val[ch] = from_key(top[ch]);
+        }
+#pragma unroll
+        for (int c = 0; c < NS; ++c) val[ch][c] = arg[ch] == c * 16 + l16 ? NEGK : val[ch][c];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      double all[NS], top[KEEP];
+#pragma unroll
+      for (int c = 0; c < NS; ++c) all[c] = pack_entry(max(val[ch][c], NEGK), c * 16 + l16);  // keys below -inf's (NaN): out too
+      largest_of_row(all, top);
+      double mine = top[0];
+#pragma unroll
+      for (int j = 1; j < KEEP; ++j) mine = l16 == j ? top[j] : mine;
+      const int key = entry_key(mine);
+      my_id[ch] = key == NEGK ? kNoExpert : entry_id(mine);
+      my_val[ch] = from_key(key);
+      mx[ch] = from_key(entry_key(top[0]));  // row maximum
+    }
   }
   if constexpr (SIG) {
     // the weight is s without the selection bias.  Lane j forms it once more from its winner's logit: carrying s along
@@ -704,7 +737,7 @@ __host__ __device__ inline bool select_by_rows(const semmoe_config& cfg) {
 // count, so that a kernel holds one form instead of all of them (a fused router with every form in it was 150 KB of
 // code: its prologue alone, hoisted set-up of forms it never ran, took 3 us of instruction fetch per workgroup).
 // SLOTS: 0 any E, k and number of groups; else the row form with up to 4, 8 or 16 slots per lane.  KEEP: length of the lists
-// of the row form, 4, 8 or 16 (>= k).
+// of the row form, 4, 8 or 16 (>= k), or 2: no lists, a round per winner.
 template <int SLOTS, int KEEP>
 struct SelForm {
   static constexpr int kSlots = SLOTS, kKeep = KEEP;
@@ -721,6 +754,8 @@ inline int32_t with_select_form(const semmoe_config& cfg, F f) {
   auto with_score = [&](auto form) -> int32_t {
     return cfg.score == SEMMOE_SIGMOID ? f(form, std::true_type{}) : f(form, std::false_type{});
   };
+  // two by softmax: lists of 4 are level with two rounds or 2 % ahead
+  if (cfg.k == 1 || (cfg.k == 2 && cfg.score == SEMMOE_SIGMOID)) return with_score(SelForm<SLOTS, 2>{});
   if (cfg.k <= 4) return with_score(SelForm<SLOTS, 4>{});
   if (cfg.k <= 8) return with_score(SelForm<SLOTS, 8>{});
   return with_score(SelForm<SLOTS, 16>{});

@@ -22,9 +22,9 @@ def _select(L, k, sb=None, **kw):
     return H.to_np(ids), H.to_np(w)
 
 
-# lists of 4, 8 and 16 per lane, 1 to 16 slots a lane, a last slot that is partly there
+# a round per winner (1), lists of 4, 8 and 16 per lane, 1 to 16 slots a lane, a last slot that is partly there
 @pytest.mark.parametrize("E", [1, 7, 16, 33, 64, 100, 128, 130, 250, 256])
-@pytest.mark.parametrize("k", [1, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8, 9, 16])
 def test_ties_and_absent_experts(E, k):
     if k > E:
         pytest.skip("more experts asked for than there are")
@@ -44,11 +44,13 @@ def test_ties_and_absent_experts(E, k):
     assert np.abs(w - e / e.sum(1, keepdims=True)).max() < 1e-6  # a few roundings of numbers up to 1
 
 
+# (1 and 2 a token by sigmoid: a round per winner)
 @pytest.mark.parametrize("E", [128, 256, 64])
 @pytest.mark.parametrize("tg", [1, 3, 4, 7, 8])
-def test_best_of_8_groups(E, tg):
+@pytest.mark.parametrize("k", [1, 2, 8])
+def test_best_of_8_groups(E, tg, k):
     r = np.random.default_rng(E + tg)
-    k = min(8, tg * (E // 8))
+    k = min(k, tg * (E // 8))
     L = np.round(2 * r.standard_normal((70, E))).astype(np.float32)  # equal scores in and across groups
     L[0] = 0.0
     L[1] = np.repeat(np.arange(8)[::-1], E // 8)
@@ -67,7 +69,8 @@ def test_best_of_8_groups(E, tg):
 @pytest.mark.parametrize("T,d,E,k", [(257, 512, 128, 8), (512, 1000, 64, 4), (513, 1000, 128, 8), (1024, 2048, 128, 8),
                                      (4096, 264, 128, 8), (4097, 264, 128, 8), (8193, 136, 96, 4), (40, 1984, 160, 8), (200, 1024, 252, 8),
                                      (500, 264, 256, 8), (1030, 2048, 256, 8), (4095, 2056, 132, 4), (4096, 136, 132, 4), (4100, 136, 132, 4),
-                                     (8193, 136, 256, 8), (8300, 1024, 160, 6)])
+                                     (8193, 136, 256, 8), (8300, 1024, 160, 6), (130, 72, 16, 1), (300, 2048, 128, 1), (700, 264, 64, 1),
+                                     (1030, 2048, 256, 1), (4100, 136, 100, 2)])
 def test_gemm_where_its_form_changes(T, d, E, k):
     w = WL.small(T=T, d=d, E=E, k=k, D=1, C=4, dtype="bf16")
     inp = H.make_inputs(w)
@@ -182,7 +185,7 @@ def test_sigmoid_is_the_oracles_bit_for_bit():
 # not a number: with the sign bit clear it is above every number (equal ones: the lower expert first), with it set it is like
 # an expert that is not there, and a row of nothing else has none.  Scores by sigmoid take it for the lowest logit, -30.
 @pytest.mark.parametrize("E", [16, 100, 128, 250, 256])
-@pytest.mark.parametrize("k", [1, 4, 8, 16])
+@pytest.mark.parametrize("k", [1, 2, 4, 8, 16])
 def test_not_a_number(E, k):
     r = np.random.default_rng(E + k)
     L = r.standard_normal((40, E)).astype(np.float32)
