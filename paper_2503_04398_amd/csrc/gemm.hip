@@ -316,6 +316,9 @@ static int f32_per_cu(int nq) {
 // time with two workgroups a compute unit and tiles that followed the mean alone: 0.975; 48 rows of 16 experts, K 1024: 0.79.
 // Many experts with a mean of a few rows: 64 x 64 too, the mean says nothing about a hot one (512 experts, d = F = 512, mean
 // 11, nearly all rows on one: 212 us on 16 tokens a tile, 140 so; with 64 experts, skewed by 1.0, it would be 10 % behind).
+// A mean of 9 to 48 rows, one tile a group along the tokens: from 8 a compute unit on.  Up to 16 rows, against 16 tokens a tile, 0.96
+// to 0.99 whatever the skew; beyond, against 32 x 32 tiles, 0.91 to 0.96 with even groups (128 experts of 37 rows, d 1000, F 504:
+// 288 -> 259 us), 1.00 to 1.03 and 1.07 skewed by 0.4 and 0.8 with 8 to 10 tiles, 0.98 and 1.01 with 10 to 12.
 // Against plain FMAs on 64 x 64 tiles that share every slice: 0.41 of the time over 834 random shapes; behind by 10 to 36 %
 // only where a row is two slices (K up to 96) and 128 experts or more make the sum over the waves the most of the work
 // (leaving the waves without a slice out of that sum changed nothing).
@@ -337,7 +340,8 @@ static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_
   };
   const long long cus = num_cu();
   int32_t st;
-  if ((est >= 4 && (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64) >= 16 * cus) ||
+  const long long wide = (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64);
+  if ((est >= 4 && wide >= 16 * cus) || (est > 8 && est <= 48 && wide >= 8 * cus) ||
       (est > 32 && items(4, 4) * 2 >= (a.offsets ? 24 : 7) * cus))
     st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
   else if (est > 16 && items(2, 2) >= 2 * cus)

@@ -200,6 +200,17 @@ def test_own_choice_by_depth_and_tiles(rows_per_expert, E, d, F):
     _check(got, want, mine, "bf16")
 
 
+# fp32, both sides of the lines between 16 tokens a tile, 32 x 32 and 64 x 64 tiles: 8 and 16 tiles of 64 weight rows a compute unit
+# (of 256) in gate and up, 8, 9, 16, 17, 48 and 49 rows expected
+@pytest.mark.parametrize("rows_per_expert,E", [(8, 128), (9, 127), (9, 128), (17, 127), (17, 128), (48, 128), (49, 128), (3, 256), (4, 256)])
+def test_own_choice_fp32(rows_per_expert, E):
+    rows = np.full(E, rows_per_expert)
+    rows[0] += int(rows[1]) - 1
+    rows[1] = 1
+    got, want, mine = _ffn(tuple(rows), 16, 512, "fp32", seed=E)
+    _check(got, want, mine, "fp32")
+
+
 # sums are formed in one order: a second call gives the same bits
 @pytest.mark.parametrize("dtype,tile", [("bf16", t) for t in (30, 31, 32, 33, 34, 35)] + [("fp32", t) for t in (30, 31, 32, 36, 37)])
 def test_same_bits_again(dtype, tile):
