@@ -311,7 +311,8 @@ static int f32_per_cu(int nq) {
 
 // fp32: 32 weight rows x 32 tokens with four workgroups a compute unit, 16 tokens where the mean is no more or the tiles are
 // few; 64 x 64 with two a compute unit (half the operand bytes a product) where there are so many tiles that the last
-// round does not matter: from 12 a compute unit on, one set of weights, whose last tile alone is ragged, from 3.5 (d 3064, F
+// round does not matter: from 12 a compute unit on, from 8 where K is 4096
+// or more (16 experts, F 2880, d 4096: 118 rows 1461 against 1345 us, 97 rows 1336 against 1176; K 2880 and 3072: level), one set of weights, whose last tile alone is ragged, from 3.5 (d 3064, F
 // 1504: 1200 tokens 321 against 361 us, 600 tokens 170 each; d 904, F 1792: 600 tokens 91 against 78).  330 FFNs (4 to 256 experts, 4 to 800 rows each, K 256 to 2048), of the
 // time with two workgroups a compute unit and tiles that followed the mean alone: 0.975; 48 rows of 16 experts, K 1024: 0.79.
 // Many experts with a mean of a few rows: 64 x 64 too, the mean says nothing about a hot one (512 experts, d = F = 512, mean
@@ -342,7 +343,7 @@ static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_
   int32_t st;
   const long long wide = (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64);
   if ((est >= 4 && wide >= 16 * cus) || (est > 8 && est <= 48 && wide >= 8 * cus) ||
-      (est > 32 && items(4, 4) * 2 >= (a.offsets ? 24 : 7) * cus))
+      (est > 32 && items(4, 4) * 2 >= (!a.offsets ? 7 : a.K >= 4096 ? 16 : 24) * cus))
     st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
   else if (est > 16 && items(2, 2) >= 2 * cus)
     st = launch_stream<MODE, true, 2, 2>(a, max_rows, f32_per_cu<MODE, 2, 2>(a.nq), stream);
