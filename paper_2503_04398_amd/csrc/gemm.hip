@@ -311,9 +311,10 @@ static int f32_per_cu(int nq) {
 
 // fp32: 32 weight rows x 32 tokens with four workgroups a compute unit, 16 tokens where the mean is no more or the tiles are
 // few; 64 x 64 with two a compute unit (half the operand bytes a product) where there are so many tiles that the last
-// round does not matter: from 12 a compute unit on, from 8 where K is 4096
-// or more (16 experts, F 2880, d 4096: 118 rows 1461 against 1345 us, 97 rows 1336 against 1176; K 2880 and 3072: level), one set of weights, whose last tile alone is ragged, from 3.5 (d 3064, F
-// 1504: 1200 tokens 321 against 361 us, 600 tokens 170 each; d 904, F 1792: 600 tokens 91 against 78).  330 FFNs (4 to 256 experts, 4 to 800 rows each, K 256 to 2048), of the
+// round does not matter: from 12 a compute unit on, from 8 where K is 4096 or more (16 experts, F 2880, d 4096: 118 rows 1461
+// against 1345 us, 97 rows 1336 against 1176; K 2880 and 3072: level), one set of weights, whose last tile alone is ragged, from
+// 3.5 (d 3064, F 1504: 1200 tokens 321 against 361 us, 600 tokens 170 each; d 904, F 1792: 600 tokens 91 against 78).  330 FFNs
+// (4 to 256 experts, 4 to 800 rows each, K 256 to 2048), of the
 // time with two workgroups a compute unit and tiles that followed the mean alone: 0.975; 48 rows of 16 experts, K 1024: 0.79.
 // Many experts with a mean of a few rows: 64 x 64 too, the mean says nothing about a hot one (512 experts, d = F = 512, mean
 // 11, nearly all rows on one: 212 us on 16 tokens a tile, 140 so; with 64 experts, skewed by 1.0, it would be 10 % behind).
@@ -474,7 +475,7 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //   * K 2048 and 4096: rows a power of two apart, where one slice of the 128 x 64 tile, 128 bytes of each of 192 rows, falls on
 //     few memory channels; a streamed step reads 512 consecutive bytes of a row.  With a common start of all walks 64 x 64 was ahead
 //     at any number of tiles (10 to 19 rows 4 to 20 %, 20 to 39 rows 2 to 13 %); with the starts spread over the groups it
-//     still is 3 to 11 % at 10 to 24 rows, level with the lines above from 34 on.
+//     still is 3 to 11 % at 10 to 24 rows; from 34 on, next point.
 //   * 256 x 128 tiles need work for every compute unit: 40 to 95 rows, fewer than 96 of them +10 to +20 %, half of the
 //     compute units +1 % at K 1000 and -3 % from K 1400, all of them +6 % below K 384 and 0 to -7 % from 640, two rounds -7 %.
 //     One rank's launch counts the tiles of three times the mean: a loaded rank has that many, and if it has not the loss is
@@ -484,8 +485,11 @@ static int32_t launch_bf16_tile(int id, const GemmArgs& a, int max_rows, int bpc
 //     eighths of the compute units or more, K 2560 and above (K 2880, 180 of them: 0.95 of 128 x 64 with the rows it expects, 0.88
 //     with twice as many, 1.01 at worst; K 4096, 192: 0.98, 0.85 and 1.01).  Half the compute units (K 7168): 4 % behind with the rows
 //     it expects, 17 ahead with twice as many; beyond one round 3 to 12 % behind (K 1408 to 2880, 250 to 360 tiles).  A launch
-//     with all experts from 34 rows, K 1024 and all compute units (128 experts of 39 rows, d 2048: 262 -> 240 us, 64 of d 4096, F
-//     1536: 453 -> 438; at 30 rows 4 % behind 64 x 64 streamed, at 32 level).
+//     with all experts from 34 rows (128 experts of 39 rows, d 2048: 262 -> 240 us, 64 of d 4096, F 1536: 453 -> 438; at 30 rows 4 %
+//     behind 64 x 64 streamed, at 32 level) and as many tiles as K asks for.  Of the 128 x 64 tiles' time, with one to two a compute
+//     unit, two to four, more: K 1024 to 1407 1.04 to 1.09, 1.00 to 1.06, 0.95 to 0.99; K from 1408 on 1.01 to 1.03, 0.98 to 1.02,
+//     0.98 to 0.99; K 4096 0.95 to 1.01 from one on.  Where it is not taken K 4096, and K 2048 with a tile a compute unit or
+//     more, keep 64 x 64 streamed: 0.94 and 0.96 of the 128 x 64 tiles.
 //     384 experts and more leave no room in its LDS for their table (512 experts, d 1024, F 512, 300 rows: 776 us as
 //     256 x 256 tiles, 1134 as 128 x 64).
 // Rows that are no whole 128 bytes: neighbouring slices share cache lines, and from about ten rows on the staged tiles
@@ -531,10 +535,13 @@ static int default_tile(const GemmArgs& a, int max_rows, int est_rows_per_group,
   const bool w4_room = W4Cfg<kModeStore, 64, 3, 2, 2>::lds_bytes(a.nq) <= size_t(max_lds());
   if (est < 40) {
     const long long mid = (long long)a.nq * w_rows / 256;  // 256 x 128 tiles, one per group along the tokens
-    if (whole_slices && w4_room && (all_rows ? est >= 34 && mid >= cus && a.K >= 1024 : est >= 20 && mid * 8 >= 5 * cus && mid <= cus && a.K >= 2560))
+    const bool pow2 = a.K >= 2048 && (a.K & (a.K - 1)) == 0;
+    const int full = a.K < 1408 ? 4 : (pow2 && a.K >= 4096 ? 1 : 2);  // tiles a compute unit
+    if (whole_slices && w4_room && (all_rows ? est >= 34 && a.K >= 1024 && mid >= full * cus
+                                             : est >= 20 && mid * 8 >= 5 * cus && mid <= cus && a.K >= 2560))
       return 33;
     if (!whole_slices || (est >= 20 && !all_rows)) return 26;
-    if (a.K >= 2048 && (a.K & (a.K - 1)) == 0 && est < 34) return 35;
+    if (pow2 && (est < 34 || a.K >= 4096 || mid >= cus)) return 35;
     const bool one_each = ring * 2 > cus && ring <= cus;
     if (est < 20) return a.K >= (ring * 2 <= cus ? 640 : (one_each ? 2560 : 960)) ? 35 : 26;
     return a.K >= 1408 && !one_each && ring <= (est < 25 ? 8 : est < 30 ? 4 : 2) * cus ? 35 : 26;

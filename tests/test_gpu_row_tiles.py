@@ -189,7 +189,7 @@ def test_own_choice(rows_per_expert, E, D, d, F):
 @pytest.mark.parametrize("rows_per_expert,E,d,F", [
     (1, 8, 184, 192), (1, 8, 192, 384), (1, 64, 384, 376), (1, 96, 64, 960), (1, 128, 640, 632), (1, 128, 1536, 64),
     (12, 4, 640, 576), (12, 64, 320, 960), (12, 128, 960, 128), (25, 16, 1408, 64), (25, 16, 64, 1408), (25, 8, 2048, 64),
-    (35, 4, 64, 4096), (12, 8, 64, 2048),
+    (35, 4, 64, 4096), (12, 8, 64, 2048), (35, 128, 1408, 512), (35, 127, 1408, 512), (34, 32, 2048, 1024),
     (45, 64, 640, 512), (45, 40, 1408, 256), (130, 16, 192, 1408), (200, 32, 640, 512), (100, 382, 192, 192), (100, 384, 192, 64),
     (192, 384, 64, 192)])
 def test_own_choice_by_depth_and_tiles(rows_per_expert, E, d, F):
