@@ -311,16 +311,18 @@ static int f32_per_cu(int nq) {
 
 // fp32: 32 weight rows x 32 tokens with four workgroups a compute unit, 16 tokens where the mean is no more or the tiles are
 // few; 64 x 64 with two a compute unit (half the operand bytes a product) where there are so many tiles that the last
-// round does not matter: from 12 a compute unit on, from 8 where K is 4096 or more (16 experts, F 2880, d 4096: 118 rows 1461
-// against 1345 us, 97 rows 1336 against 1176; K 2880 and 3072: level), one set of weights, whose last tile alone is ragged, from
-// 3.5 (d 3064, F 1504: 1200 tokens 321 against 361 us, 600 tokens 170 each; d 904, F 1792: 600 tokens 91 against 78).  330 FFNs
-// (4 to 256 experts, 4 to 800 rows each, K 256 to 2048), of the
-// time with two workgroups a compute unit and tiles that followed the mean alone: 0.975; 48 rows of 16 experts, K 1024: 0.79.
-// Many experts with a mean of a few rows: 64 x 64 too, the mean says nothing about a hot one (512 experts, d = F = 512, mean
-// 11, nearly all rows on one: 212 us on 16 tokens a tile, 140 so; with 64 experts, skewed by 1.0, it would be 10 % behind).
-// A mean of 9 to 48 rows, one tile a group along the tokens: from 8 a compute unit on.  Up to 16 rows, against 16 tokens a tile, 0.96
-// to 0.99 whatever the skew; beyond, against 32 x 32 tiles, 0.91 to 0.96 with even groups (128 experts of 37 rows, d 1000, F 504:
-// 288 -> 259 us), 1.00 to 1.03 and 1.07 skewed by 0.4 and 0.8 with 8 to 10 tiles, 0.98 and 1.01 with 10 to 12.
+// round does not matter.  From how many a compute unit on, by rows and K (of the time as smaller tiles; 1600 FFNs of 2 to 256 experts,
+// 3 to 400 rows each, skewed by 0 to 1.0):
+//   * more than 32 rows, K of 3600 and more: 4 (4 to 6: gate/up 0.93 to 0.95, down 0.98; 2 to 4: level with single shapes at 1.2)
+//   * more than 8 rows, K of 1024 and more: 6 (6 to 8: 9 to 32 rows 0.97 to 1.00, more rows 0.90 to 0.98; 4 to 6: 0.98 to 1.03)
+//   * more than 48 rows, shorter K: 12 (0.96 from there on, 6 to 12: 0.99 to 1.07); 9 to 48 rows 8, where one tile a group along the
+//     tokens reads the weights once (128 experts of 37 rows, d 1000, F 504: 288 against 259 us; skewed by 0.8, 1.07 with 8 to 10)
+//   * 4 to 8 rows: 8 from K 1024 on (8 to 12: 0.99), 16 below (level; 8 to 16: 1.01 to 1.02).  The mean says nothing about a hot
+//     expert (512 experts, d = F = 512, mean 11, nearly all rows on one: 212 us on 16 tokens a tile, 140 so)
+//   * one set of weights, whose last tile alone is ragged, more than 32 rows: 3.5 (d 3064, F 1504: 1200 tokens 321 against 361 us, 600
+//     tokens 170 each; d 904, F 1792: 600 tokens 91 against 78)
+// With a line at 12 for all of K below 4096 the calls of more than 32 rows were 0.995 of the time with two workgroups a compute unit and
+// tiles that followed the mean alone, a third of them more than 3 % behind.
 // Against plain FMAs on 64 x 64 tiles that share every slice: 0.41 of the time over 834 random shapes; behind by 10 to 36 %
 // only where a row is two slices (K up to 96) and 128 experts or more make the sum over the waves the most of the work
 // (leaving the waves without a slice out of that sum changed nothing).
@@ -342,9 +344,14 @@ static int32_t launch_f32(int id, const GemmArgs& a, int max_rows, int est_rows_
   };
   const long long cus = num_cu();
   int32_t st;
-  const long long wide = (long long)a.nq * cdiv((MODE == kModeSwiglu) ? 2 * a.N : a.N, 64);
-  if ((est >= 4 && wide >= 16 * cus) || (est > 8 && est <= 48 && wide >= 8 * cus) ||
-      (est > 32 && items(4, 4) * 2 >= (!a.offsets ? 7 : a.K >= 4096 ? 16 : 24) * cus))
+  const bool deep = a.K >= 1024;
+  // 64 x 64 tiles from so many half tiles a compute unit on
+  const int line = !a.offsets && est > 32      ? 7
+                   : est > 32 && a.K >= 3600   ? 8
+                   : est > 48                  ? (deep ? 12 : 24)
+                   : est > 8                   ? (deep ? 12 : 16)
+                                               : (deep ? 16 : 32);
+  if (est >= 4 && items(4, 4) * 2 >= line * cus)
     st = launch_stream<MODE, true, 4, 4>(a, max_rows, 2, stream);
   else if (est > 16 && items(2, 2) >= 2 * cus)
     st = launch_stream<MODE, true, 2, 2>(a, max_rows, f32_per_cu<MODE, 2, 2>(a.nq), stream);

@@ -8,7 +8,7 @@ is the row's own norm for weights drawn at random.  bf16 (u = 2^-9, the largest 
 activation and the result are rounded, errors that are independent from entry to entry, so a row is off by sqrt(2) u = 0.28 %
 of its norm at most; fp32 sums of up to 1536 terms and the fast exponential add less than 1e-5.  fp32: a sum of K terms in
 four parts is off by sqrt(K) 2^-24 of its norm where roundings are independent, twice in a row (gate/up, down), 4.7e-6 in
-all at K = 1536; the bounds below are about twice these."""
+all at K = 1536, 5.5e-6 at K = 3600 and then 1024; the bounds below are about twice these."""
 import numpy as np
 import pytest
 import torch
@@ -208,6 +208,17 @@ def test_own_choice_fp32(rows_per_expert, E):
     rows[0] += int(rows[1]) - 1
     rows[1] = 1
     got, want, mine = _ffn(tuple(rows), 16, 512, "fp32", seed=E)
+    _check(got, want, mine, "fp32")
+
+
+# ... and by K: 64 x 64 tiles from 12, 6 and 4 a compute unit on (gate and up, K below 1024, below 3600 and from there), one tile less
+@pytest.mark.parametrize("rows_per_expert,E,d,F", [(1024, 3, 1016, 2048), (1024, 3, 1016, 2016), (1024, 2, 1024, 1536), (1024, 2, 1024, 1504),
+                                                   (1024, 2, 3592, 1024), (1024, 2, 3600, 1024), (1024, 2, 3600, 992)])
+def test_own_choice_fp32_by_depth(rows_per_expert, E, d, F):
+    rows = np.full(E, rows_per_expert)
+    rows[0] += int(rows[1]) - 1
+    rows[1] = 1
+    got, want, mine = _ffn(tuple(rows), d, F, "fp32", seed=d)
     _check(got, want, mine, "fp32")
 
 
