@@ -44,23 +44,36 @@ def test_ties_and_absent_experts(E, k):
     assert np.abs(w - e / e.sum(1, keepdims=True)).max() < 1e-6  # a few roundings of numbers up to 1
 
 
+def _check_groups(E, n, tg, k):
+    r = np.random.default_rng(E + tg)
+    k = min(k, tg * (E // n))
+    L = np.round(2 * r.standard_normal((70, E))).astype(np.float32)  # equal scores in and across groups
+    L[0] = 0.0
+    L[1] = np.repeat(np.arange(n)[::-1], E // n)
+    L[2] = r.standard_normal(E)
+    sb = np.round(4 * r.standard_normal(E)).astype(np.float32) / 4
+    for bias in (None, sb):
+        ids, w = _select(L, k, sb=bias, score="sigmoid", renorm=True, n_group=n, topk_group=tg, routed_scale=2.5)
+        want_ids, want_w = O.select_topk(L, k, "sigmoid", True, n, tg, 2.5, bias)
+        assert (ids == want_ids).all()
+        assert O.max_rel_err(w, want_w) <= 1e-5
+
+
 # (1 and 2 a token by sigmoid: a round per winner)
 @pytest.mark.parametrize("E", [128, 256, 64])
 @pytest.mark.parametrize("tg", [1, 3, 4, 7, 8])
 @pytest.mark.parametrize("k", [1, 2, 8])
 def test_best_of_8_groups(E, tg, k):
-    r = np.random.default_rng(E + tg)
-    k = min(k, tg * (E // 8))
-    L = np.round(2 * r.standard_normal((70, E))).astype(np.float32)  # equal scores in and across groups
-    L[0] = 0.0
-    L[1] = np.repeat(np.arange(8)[::-1], E // 8)
-    L[2] = r.standard_normal(E)
-    sb = np.round(4 * r.standard_normal(E)).astype(np.float32) / 4
-    for bias in (None, sb):
-        ids, w = _select(L, k, sb=bias, score="sigmoid", renorm=True, n_group=8, topk_group=tg, routed_scale=2.5)
-        want_ids, want_w = O.select_topk(L, k, "sigmoid", True, 8, tg, 2.5, bias)
-        assert (ids == want_ids).all()
-        assert O.max_rel_err(w, want_w) <= 1e-5
+    _check_groups(E, 8, tg, k)
+
+
+# other numbers of groups, and 8 of other sizes: whole slots of 16 experts (16, 48, 64, 80 a group), and groups that share one (1 to 12)
+@pytest.mark.parametrize("E,n", [(16, 16), (32, 16), (96, 16), (128, 16), (160, 16), (192, 16), (256, 16), (96, 2), (256, 4), (160, 2),
+                                 (40, 4), (60, 12), (72, 8), (96, 8)])
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+def test_best_of_any_groups(E, n, half, k):
+    _check_groups(E, n, n // 2 if half else 1, k)
 
 
 # up to 512 tokens in parts of K, beyond in one where K is short (what is in parts there: the next test); 32 (4097), 64 (8193) tokens
